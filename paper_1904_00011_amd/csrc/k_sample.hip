@@ -56,9 +56,9 @@ hipError_t launch_entries(const pcmd_grid *g, const double *scale, double *lam, 
 __device__ __forceinline__ void prep_body(const PrepArgs &a, int i) {
   // every lane of the block takes part in the group summary below (no early return)
   const int E = a.E, B = a.B;
-  EntryRec r{{0xFFFFFFFFu, 0u, 0u}, KIND_ZERO, {0.0, 0.0, 0.0, 0.0}};
+  EntryRec r{{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu}, KIND_ZERO, {0.0, 0.0, 0.0, 0.0}};
   bool red_alias = false;  // the entry is thinned and its reddened part is on the alias rule
-  double lam_inv = 0.0;    // lambda of an entry drawn by inversion (the group's density flag)
+  bool dense = false;      // an entry drawn by inversion of which a wave usually has a lane with three stars
   if (i < E) {
     // every load before the first store (the output could alias the inputs for the compiler,
     // which otherwise waits for each load in turn)
@@ -109,11 +109,11 @@ __device__ __forceinline__ void prep_body(const PrepArgs &a, int i) {
       uint32_t first[3] = {0u, 0u, 0u};
       const uint32_t K = inversion_table(l, a.thr + i, (size_t)entries_padded(E), first);
       if (K > 0) {
-        // T_0 >= 1 below ALIAS_MIN, so u >= T_0 is exactly u > T_0 - 1
-        r.T[0] = first[0] - 1u;
-        for (uint32_t k = 1; k < 3 && k < K; ++k) r.T[k] = first[k];
+        // T_0 >= 1 below ALIAS_MIN, so u >= T_k is exactly u > T_k - 1; an absent threshold's
+        // 0xFFFFFFFF is never exceeded
+        for (uint32_t k = 0; k < 3 && k < K; ++k) r.T[k] = first[k] - 1u;
         r.kk = (K << 8) | KIND_INV;
-        lam_inv = l;
+        dense = l >= LAM_DENSE;
       }
     }
   }
@@ -141,20 +141,17 @@ __device__ __forceinline__ void prep_body(const PrepArgs &a, int i) {
 
   // group of entries GRP g .. GRP g + GRP - 1 = neighbouring lanes of one wave (256-thread blocks)
   const uint32_t kind = r.kk & KIND_MASK;
-  const uint32_t t0m1 = r.T[0];  // 0xFFFFFFFF unless drawn by inversion
-  const uint32_t fl = (r.kk & FLAG_THIN) ? GRP_THIN
-                      : kind == KIND_INV ? GRP_INV : kind == KIND_PTRS ? GRP_PTRS : kind == KIND_ALIAS ? GRP_ALIAS : 0u;
+  const uint32_t fl = (r.kk & FLAG_THIN) ? GRP_THIN | (GRP_THIN_ENTRY << (i & (GRP - 1)))
+                      : kind == KIND_INV ? GRP_INV | (dense ? GRP_DENSE_ENTRY << (i & (GRP - 1)) : 0u)
+                      : kind == KIND_PTRS || kind == KIND_ALIAS ? GRP_TABLE | (GRP_TABLE_ENTRY << (i & (GRP - 1))) : 0u;
   const int first = (int)(threadIdx.x & 63u) & ~(GRP - 1);
   GroupRec gr;
   gr.flags = 0u;
-  double gsum = 0.0;
 #pragma unroll
   for (int q = 0; q < GRP; ++q) {
-    gr.t0m1[q] = (uint32_t)__shfl((int)t0m1, first + q, 64);
+    gr.t0m1[q] = (uint32_t)__shfl((int)(dense ? 0xFFFFFFFFu : r.T[0]), first + q, 64);
     gr.flags |= (uint32_t)__shfl((int)fl, first + q, 64);
-    gsum += __shfl(lam_inv, first + q, 64);
   }
-  if (64.0 * gsum >= GRP_DENSE_LAMBDA64) gr.flags |= GRP_DENSE;
 #pragma unroll
   for (int q = 0; q < 7; ++q) gr.pad[q] = 0u;
   if ((i & (GRP - 1)) == 0 && i < EP) a.grp[i / GRP] = gr;
@@ -552,18 +549,136 @@ __device__ __forceinline__ void thin_quad(const SampleArgs &a, uint32_t q0, cons
   }
 }
 
+// Adds f to acc in the lanes of `mask` only.  Called with all 64 lanes of the wave active (a tile's
+// control flow is wave-uniform), which the last instruction restores.  Written out because the
+// compiler turns a short divergent branch into selects, and a branch it does keep into additions
+// to copies of the sums with moves back.
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+
+template <int B>
+__device__ __forceinline__ void masked_add(double (&acc)[B], const double (&f)[B], uint64_t mask) {
+  static_assert(B >= 1 && B <= 4, "bands");
+  if constexpr (B == 1)
+    asm volatile("s_mov_b64 exec, %1\n\tv_add_f64 %0, %0, %2\n\ts_mov_b64 exec, -1" : "+v"(acc[0]) : "s"(mask), "s"(f[0]));
+  else if constexpr (B == 2)
+    asm volatile("s_mov_b64 exec, %2\n\tv_add_f64 %0, %0, %3\n\tv_add_f64 %1, %1, %4\n\ts_mov_b64 exec, -1"
+                 : "+v"(acc[0]), "+v"(acc[1])
+                 : "s"(mask), "s"(f[0]), "s"(f[1]));
+  else if constexpr (B == 3)
+    asm volatile("s_mov_b64 exec, %3\n\tv_add_f64 %0, %0, %4\n\tv_add_f64 %1, %1, %5\n\tv_add_f64 %2, %2, %6\n\t"
+                 "s_mov_b64 exec, -1"
+                 : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2])
+                 : "s"(mask), "s"(f[0]), "s"(f[1]), "s"(f[2]));
+  else
+    asm volatile("s_mov_b64 exec, %4\n\tv_add_f64 %0, %0, %5\n\tv_add_f64 %1, %1, %6\n\tv_add_f64 %2, %2, %7\n\t"
+                 "v_add_f64 %3, %3, %8\n\ts_mov_b64 exec, -1"
+                 : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+                 : "s"(mask), "s"(f[0]), "s"(f[1]), "s"(f[2]), "s"(f[3]));
+}
+
+// acc += n f (f wave-uniform), the sum staying in its register: where paths join, the compiler's own
+// form left six register moves per path.
+__device__ __forceinline__ void fma_in_place(double &acc, double n, double f) {
+  asm volatile("v_fma_f64 %0, %1, %2, %0" : "+v"(acc) : "v"(n), "s"(f));
+}
+
+// The arguments again, for fields read once per group of entries or less: loaded there through the
+// scalar cache.  The compiler cannot see that the pointer is the same, so it does not load them
+// ahead of the loop, where they would push the loop's own values out of the scalar registers into
+// vector lanes (a vector instruction for each word read back).
+template <typename T>
+__device__ __forceinline__ const PCMD_CONST T *rare(const PCMD_CONST T *p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// Values held in scalar registers from here on: the compiler otherwise loads them again, each time
+// behind a wait, where they are used.
+template <typename T>
+__device__ __forceinline__ void keep_scalar(const PCMD_CONST T *&p) {
+  asm volatile("" : "+s"(p));
+}
+
+__device__ __forceinline__ void keep_scalar(uint32_t &a, uint32_t &b) { asm volatile("" : "+s"(a), "+s"(b)); }
+template <int B>
+__device__ __forceinline__ void keep_scalar(double (&f)[B]) {
+#pragma unroll
+  for (int b = 0; b < B; ++b) asm volatile("" : "+s"(f[b]));
+}
+
+// Slice `chunk` of nchunks takes the 16-entry blocks chunk, chunk + nchunks, chunk + 2 nchunks,
+// ...: every slice then spans all isochrones and masses, so slices cost about the same (runs of
+// consecutive entries differ in cost several-fold: high-lambda low-mass stars cluster at the start
+// of each isochrone).  The j-th group of GRP entries of the slice is group slice_group(j) of the
+// table.  Calls body(group, flags) for the slice's groups with a flag of `want`.
+//
+// Lane l reads the flags of the slice's group jb + l: one vector load finds the groups with
+// entries to draw among the next 64, where one dependent scalar load per group kept a wave waiting
+// through runs of groups with nothing to draw (pruned isochrones; the hybrid sampler's block-rule
+// entries).
+template <typename F>
+__device__ __forceinline__ void for_groups(const GroupRec *grp, int E, int nchunks, int chunk, uint32_t want, F &&body) {
+  static_assert(GRP == 8, "two groups per 16-entry block");
+  const int ngrp = entries_padded(E) / GRP;
+  const int stride = nchunks * (16 / GRP);
+  auto slice_group = [&](int j) { return chunk * (16 / GRP) + (j >> 1) * stride + (j & 1); };
+  const int lane = (int)(threadIdx.x & 63u);
+  for (int jb = 0; slice_group(jb) < ngrp; jb += 64) {
+    const int gl = slice_group(jb + lane);
+    const uint32_t fl = gl < ngrp ? grp[gl].flags : 0u;
+    for (uint64_t pend = __ballot((fl & want) != 0u); pend != 0ull; pend &= pend - 1ull) {
+      const int lsel = (int)__builtin_ctzll(pend);  // wave-uniform
+      // slice_group(jb + lsel), read from lane lsel: one vector instruction instead of seven scalar
+      body(__builtin_amdgcn_readlane(gl, lsel), (uint32_t)__builtin_amdgcn_readlane((int)fl, lsel));
+    }
+  }
+}
+
+// Adds the counts n, of them red reddened, of an entry with fluxes f.
+template <int B, int S>
+__device__ __forceinline__ void add_counts(double (&acc_c)[B], double (&acc_r)[B], const double (&f)[B], uint32_t n,
+                                           uint32_t red) {
+  // the unreddened stream has a star whenever the entry has one, nearly always: added without a
+  // test (zero counts add exact zeros); the reddened stream is skipped when no lane has a
+  // reddened star
+  const double dc = (double)(n - red);
+#pragma unroll
+  for (int b = 0; b < B; ++b) fma_in_place(acc_c[b], dc, f[b]);
+  if (S == 2 && wave_any(red != 0u)) {
+    const double dr = (double)red;
+#pragma unroll
+    for (int b = 0; b < B; ++b) fma_in_place(acc_r[b], dr, f[b]);
+  }
+}
+
 // PASS (SamplePass): PASS_ALL draws every entry, the thinned ones (FLAG_THIN: two independent
-// parts, k_prep's choice under a split 0 < F < 1) inline; PASS_MAIN leaves the thinned ones out,
-// and PASS_THIN then draws only those and adds them to the partial sums PASS_MAIN stored, so the
-// thinning code (live state that slows the common path) is not in the main pass.
+// parts, k_prep's choice under a split 0 < F < 1) inline; PASS_MAIN leaves the thinned ones to
+// sample_thin_tile.
+//
+// Bound by vector-instruction issue (90% of cycles), of which two Philox blocks per eight draws (8
+// instructions a draw) are the part that no layout can drop.  What the loop does beyond them is
+// kept small: one compare per entry, whose lane masks also drive the additions; nothing that the
+// loop uses spilled to vector lanes.  256 x 256 pixels, 52,500 entries, 3 bands, 10^3.4 stars per
+// pixel: 675 -> 587 million wave instructions, 1481 -> 1223 us; 512 x 512 at 10^6: 7.18 -> 6.0 ms.
 template <int B, int S, bool DBG, int PASS>
-__device__ __forceinline__ void sample_tile(const SampleArgs &a, uint32_t p, int chunk) {
-  const PCMD_CONST EntryRec *rec = (const PCMD_CONST EntryRec *)a.rec;
-  const PCMD_CONST uint32_t *thr = (const PCMD_CONST uint32_t *)a.thr;
-  const PCMD_CONST PtrsConst *pc = (const PCMD_CONST PtrsConst *)a.pc;
-  const PCMD_CONST uint32_t *rdesc = (const PCMD_CONST uint32_t *)a.rdesc;
-  const bool live = p < (uint32_t)a.npx;
-  const bool dbg = DBG && live && (int64_t)p >= a.px0 && (int64_t)p < a.px1;
+__device__ __forceinline__ void sample_tile(const PCMD_CONST SampleArgs *ap, uint32_t p, int chunk) {
+  const GroupRec *grp = ap->grp;
+  const int E = ap->E, nchunks = ap->nchunks;
+  const uint32_t k0 = ap->k0, k1 = ap->k1;
+  bool live, dbg = false;
+  {
+    const PCMD_CONST SampleArgs *ca = rare(ap);
+    live = p < (uint32_t)ca->npx;
+    if (DBG) dbg = live && (int64_t)p >= ca->px0 && (int64_t)p < ca->px1;
+  }
+  auto write_dbg = [&](uint32_t i, uint32_t n, uint32_t red) {
+    if (DBG && dbg) {
+      const PCMD_CONST SampleArgs *ca = rare(ap);
+      const size_t o = (size_t)((int64_t)p - ca->px0) * (size_t)ca->E + i;
+      ca->dbg_counts[o] = n;
+      if (ca->dbg_red) ca->dbg_red[o] = red;
+    }
+  };
 
   double acc_c[B], acc_r[B];
 #pragma unroll
@@ -571,168 +686,214 @@ __device__ __forceinline__ void sample_tile(const SampleArgs &a, uint32_t p, int
     acc_c[b] = 0.0;
     acc_r[b] = 0.0;
   }
-
-  u4 sw{0u, 0u, 0u, 0u};
-  int split_blk = -1;         // the 16-entry block whose split bits sw holds
   uint32_t ptrs_failed = 0u;  // per lane, kept in a vector register
-  const PCMD_CONST GroupRec *grp = (const PCMD_CONST GroupRec *)a.grp;
-  // Slice `chunk` of nchunks takes the 16-entry blocks chunk, chunk + nchunks, chunk + 2 nchunks,
-  // ...: every slice then spans all isochrones and masses, so slices cost about the same (runs
-  // of consecutive entries differ in cost several-fold: high-lambda low-mass stars cluster at the
-  // start of each isochrone).  The j-th group of GRP entries of the slice is group
-  // slice_group(j) of the table.
-  const int ngrp = entries_padded(a.E) / GRP;
-  const int stride = a.nchunks * (16 / GRP);
-  auto slice_group = [&](int j) { return chunk * (16 / GRP) + (j >> 1) * stride + (j & 1); };
-  static_assert(GRP == 8, "two groups per 16-entry block");
-  const int lane = (int)(threadIdx.x & 63u);
-  for (int jb = 0; slice_group(jb) < ngrp; jb += 64) {
-    // lane l reads the flags of the slice's group jb + l: one vector load finds the groups with
-    // entries to draw among the next 64, where one dependent scalar load per group kept a wave
-    // waiting through runs of groups with nothing to draw (pruned isochrones; the hybrid
-    // sampler's block-rule entries)
-    const int gl = slice_group(jb + lane);
-    const uint32_t fl = gl < ngrp ? grp[gl].flags : 0u;
-    const uint32_t want = PASS == PASS_ALL ? 0xFFu : PASS == PASS_MAIN ? (GRP_INV | GRP_PTRS | GRP_ALIAS) : GRP_THIN;
-    for (uint64_t pend = __ballot((fl & want) != 0u); pend != 0ull; pend &= pend - 1ull) {
-      const int lsel = (int)__builtin_ctzll(pend);  // wave-uniform
-      // slice_group(jb + lsel), read from lane lsel: one vector instruction instead of seven scalar
-      const int gi = __builtin_amdgcn_readlane(gl, lsel);
-      const int g0 = gi * GRP;
-      const PCMD_CONST GroupRec *gr = grp + gi;
-      // at small lambda most groups end after two Philox blocks and eight compares, without
-      // touching the entry records
-      const uint32_t flags = (uint32_t)__builtin_amdgcn_readlane((int)fl, lsel);
-      // inversion words of the group's two quads: counters (p, i / 4, TAG_MAIN, 0)
-      const u4 wa = philox10(p, (uint32_t)(2 * gi), TAG_MAIN, 0u, a.k0, a.k1);
-      const u4 wb = philox10(p, (uint32_t)(2 * gi + 1), TAG_MAIN, 0u, a.k0, a.k1);
+
+  {
+    const int split_mode = S == 2 ? ap->split_mode : SPLIT_NONE;
+    // the split bits of 16-entry block split_blk; where F is not 1/2 (split_blk = NO_SPLIT) all ones
+    // for F = 1, else zero
+    constexpr int NO_SPLIT = -2;
+    int split_blk = split_mode == SPLIT_HALF ? -1 : NO_SPLIT;
+    const uint32_t fixed = split_mode == SPLIT_ALL ? 0xFFFFFFFFu : 0u;
+    u4 sw{fixed, fixed, fixed, fixed};
+    auto split_word = [&](int gi, int h) {  // the word of quad h of group gi
+      const uint32_t lo = h ? sw.y : sw.x, hi = h ? sw.w : sw.z;
+      return gi & 1 ? hi : lo;
+    };
+    // The entries drawn by inversion.
+    for_groups(grp, E, nchunks, chunk, GRP_INV, [&](int gi, uint32_t flags) {
+      const u4 wa = philox10(p, (uint32_t)(2 * gi), TAG_MAIN, 0u, k0, k1);
+      const u4 wb = philox10(p, (uint32_t)(2 * gi + 1), TAG_MAIN, 0u, k0, k1);
       // the first thresholds are loaded only now: held across the Philox rounds they pushed the
       // scalar register file into spilling inside this loop
       __builtin_amdgcn_sched_barrier(0);
-      if (PASS != PASS_THIN && !(flags & (GRP_PTRS | GRP_ALIAS | GRP_DENSE | (PASS == PASS_ALL ? GRP_THIN : 0u))) &&
-          (__ballot(wa.x > gr->t0m1[0]) | __ballot(wa.y > gr->t0m1[1]) | __ballot(wa.z > gr->t0m1[2]) |
-           __ballot(wa.w > gr->t0m1[3]) | __ballot(wb.x > gr->t0m1[4]) | __ballot(wb.y > gr->t0m1[5]) |
-           __ballot(wb.z > gr->t0m1[6]) | __ballot(wb.w > gr->t0m1[7])) == 0ull)
-        continue;
-      if (PASS == PASS_THIN) {
+      // the lanes with a star, per entry (the threshold of a dense entry, which is always counted, or
+      // of one not drawn by inversion is never exceeded): at small lambda most groups end after two Philox blocks and eight compares,
+      // without touching the entry records
+      const PCMD_CONST GroupRec *gr = (const PCMD_CONST GroupRec *)rare(ap)->grp + gi;
+      const u32x8 w = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+      uint64_t hit[GRP], any = 0ull;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) thin_quad<B, DBG>(a, (uint32_t)(g0 + 4 * h), h ? wb : wa, p, dbg, acc_c, acc_r, ptrs_failed);
-        continue;
-      }
-      // the split bits of the group's 16-entry block: a slow group almost always has a star to
+      for (int q = 0; q < GRP; ++q) any |= hit[q] = __ballot(w[q] > gr->t0m1[q]);
+      uint32_t counted = flags / GRP_DENSE_ENTRY;
+      if (any == 0ull && counted == 0u) return;
+      // the split bits of the group's 16-entry block: a group with a star almost always has one to
       // split, and the two groups of a block share them
-      if (S == 2 && PASS != PASS_THIN && a.split_mode == SPLIT_HALF && split_blk != (gi >> 1)) {
-        sw = philox10(p, (uint32_t)(gi >> 1), TAG_SPLIT, 0u, a.k0, a.k1);
+      if (S == 2 && split_blk != NO_SPLIT && split_blk != (gi >> 1)) {
+        sw = philox10(p, (uint32_t)(gi >> 1), TAG_SPLIT, 0u, k0, k1);
+        split_blk = gi >> 1;
+      }
+      const uint32_t sq0 = split_word(gi, 0), sq1 = split_word(gi, 1);
+      const PCMD_CONST EntryRec *rg = (const PCMD_CONST EntryRec *)rare(ap)->rec + gi * GRP;
+      keep_scalar(rg);
+      // Entries of which no lane has three stars first, then the counted ones: as the two branches
+      // of one loop, the compiler moved all sums at the end of either.
+#pragma unroll
+      for (int q = 0; q < GRP; ++q) {
+        if (hit[q] == 0ull) continue;
+        const uint32_t u = w[q];
+        // thresholds and fluxes behind one wait
+        uint32_t t1m1 = rg[q].T[1], t2m1 = rg[q].T[2];
+        double fv[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) fv[b] = rg[q].fl[b];
+        keep_scalar(t1m1, t2m1);
+        keep_scalar(fv);
+        const uint32_t word = q < 4 ? sq0 : sq1;
+        const uint64_t two = __ballot(u > t1m1);
+        if (PASS == PASS_ALL || (two != 0ull && wave_any(u > t2m1))) {
+          counted |= 1u << q;
+          continue;
+        }
+        // No lane has three stars of the entry, which holds for most entries below lambda ~ 0.3.
+        // The lanes with a first and a second star add the flux to one of their two streams under
+        // the execution mask: six additions each, where counts cost two conversions, six
+        // multiply-adds and the integer steps between.  PASS_ALL (one word per star) takes counts.
+        const uint64_t red = S == 2 ? __ballot((word & (1u << (8 * (q & 3)))) != 0u) & hit[q] : 0ull;
+        masked_add<B>(acc_c, fv, hit[q] & ~red);
+        if (S == 2) masked_add<B>(acc_r, fv, red);
+        uint64_t red2 = 0ull;
+        if (two != 0ull) {
+          red2 = S == 2 ? __ballot((word & (2u << (8 * (q & 3)))) != 0u) & two : 0ull;
+          masked_add<B>(acc_c, fv, two & ~red2);
+          if (S == 2) masked_add<B>(acc_r, fv, red2);
+        }
+        if (DBG)
+          write_dbg((uint32_t)(gi * GRP + q),
+                    (__builtin_amdgcn_inverse_ballot_w64(hit[q]) ? 1u : 0u) + (__builtin_amdgcn_inverse_ballot_w64(two) ? 1u : 0u),
+                    (__builtin_amdgcn_inverse_ballot_w64(red) ? 1u : 0u) + (__builtin_amdgcn_inverse_ballot_w64(red2) ? 1u : 0u));
+      }
+      if (counted == 0u) return;
+#pragma unroll
+      for (int q = 0; q < GRP; ++q) {
+        if (!(counted & (1u << q))) continue;
+        const uint32_t i = (uint32_t)(gi * GRP + q);
+        const uint32_t u = w[q];
+        EntryHead rq = ld_const((const PCMD_CONST EntryHead *)(rg + q));
+        double fv[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) fv[b] = rg[q].fl[b];
+        keep_scalar(fv);
+        const uint32_t word = q < 4 ? sq0 : sq1;
+        // n = #{k < K : T_k <= u}, walking up while any lane of the wave is still above
+        uint32_t n = (u > rq.T[0] ? 1u : 0u) + (u > rq.T[1] ? 1u : 0u);
+        uint32_t c = u > rq.T[2] ? 1u : 0u;
+        if (wave_any(c != 0u)) {
+          n += c;
+          const uint32_t K = rq.kk >> 8;
+          const size_t ep = (size_t)entries_padded(E);
+          const PCMD_CONST uint32_t *t = (const PCMD_CONST uint32_t *)rare(ap)->thr + i + 3 * ep;  // threshold k at [k EP]
+          for (uint32_t k = 3; k < K; ++k, t += ep) {
+            c = u >= *t ? 1u : 0u;
+            if (!wave_any(c != 0u)) break;
+            n += c;
+          }
+        }
+        uint32_t red = 0u;
+        if (S == 2) {
+          const uint32_t q_split = PASS == PASS_ALL ? rare(ap)->split_q : 0u;
+          red = split_count(n, word, 8u * (uint32_t)(q & 3), split_mode, q_split, p, i, k0, k1);
+        }
+        add_counts<B, S>(acc_c, acc_r, fv, n, red);
+        write_dbg(i, n, red);
+      }
+    });
+    // The table entries (in a loop of their own, so that their code and operands stay out of the
+    // one above): slot 0 holds the count (or, thinned, the unreddened part), slot 1 the reddened
+    // part, each an alias column read or a rejection draw.
+    constexpr uint32_t want = PASS == PASS_ALL ? GRP_TABLE | GRP_THIN : GRP_TABLE;
+    for_groups(grp, E, nchunks, chunk, want, [&](int gi, uint32_t flags) {
+      const uint32_t tab = flags / GRP_TABLE_ENTRY | (PASS == PASS_ALL ? flags / GRP_THIN_ENTRY : 0u);
+      const PCMD_CONST SampleArgs *ca = rare(ap);
+      const PCMD_CONST EntryRec *rec = (const PCMD_CONST EntryRec *)ca->rec;
+      const PCMD_CONST PtrsConst *pc = (const PCMD_CONST PtrsConst *)ca->pc;
+      const uint32_t *alias = ca->alias;
+      const float *lnfact = ca->lnfact;
+      if (S == 2 && split_blk != NO_SPLIT && split_blk != (gi >> 1)) {
+        sw = philox10(p, (uint32_t)(gi >> 1), TAG_SPLIT, 0u, k0, k1);
         split_blk = gi >> 1;
       }
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int q0 = g0 + 4 * h;  // first entry of the quad
-        const u4 &w = h ? wb : wa;
-        const uint32_t sq = word_of(sw, 2 * (gi & 1) + h);  // the quad's word of the split block
+        if (((tab >> (4 * h)) & 0xFu) == 0u) continue;
+        const u4 w = philox10(p, (uint32_t)(2 * gi + h), TAG_MAIN, 0u, k0, k1);
+        const uint32_t sq = split_word(gi, h);
         u4 wr{0u, 0u, 0u, 0u};  // thinned entries: the quad's reddened-part words
-        bool wr_ok = false;
+        if (S == 2 && PASS == PASS_ALL && ((flags / GRP_THIN_ENTRY >> (4 * h)) & 0xFu) != 0u)
+          wr = philox10(p, (uint32_t)(2 * gi + h), TAG_RED, 0u, k0, k1);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const uint32_t i = (uint32_t)(q0 + q);
-          // one record at a time keeps the scalar registers of the loop below the spill point
-          const EntryHead rq = ld_const((const PCMD_CONST EntryHead *)(rec + i));  // padded to a multiple of GRP
-          uint32_t n = 0, red_thin = 0u;
-          bool thinned = false;
-          // a pass leaves out the entries of the other pass (wave-uniform: the record is)
-          if (PASS == PASS_MAIN && (rq.kk & FLAG_THIN)) continue;
-          if (PASS == PASS_THIN && !(rq.kk & FLAG_THIN)) continue;
-          const uint32_t kind = rq.kk & KIND_MASK;
-          if (kind <= KIND_INV) {  // inversion; a KIND_ZERO entry never passes its first threshold
-            // n = #{k < K : T_k <= u}, walking up while any lane of the wave is still above
-            const uint32_t u = word_of(w, q);
-            const uint32_t K = rq.kk >> 8;
-            n = u > rq.T[0] ? 1u : 0u;
-            if (!wave_any(n != 0u)) continue;
-            if (K > 1) {
-              uint32_t c = u >= rq.T[1] ? 1u : 0u;
-              if (wave_any(c != 0u)) {
-                n += c;
-                if (K > 2) {
-                  c = u >= rq.T[2] ? 1u : 0u;
-                  if (wave_any(c != 0u)) {
-                    n += c;
-                    const PCMD_CONST uint32_t *t = thr + i;  // threshold k at t[k EP]
-                    const size_t ep = (size_t)entries_padded(a.E);
-                    for (uint32_t k = 3; k < K; ++k) {
-                      c = u >= t[k * ep] ? 1u : 0u;
-                      if (!wave_any(c != 0u)) break;
-                      n += c;
-                    }
-                  }
-                }
-              }
-            }
-          } else {
-            // table entry: slot 0 holds the count (or, thinned, the unreddened part), slot 1 the
-            // reddened part, each an alias column read or a rejection draw
-            n = table_draw(rq.kk, word_of(w, q), a.alias + (size_t)i * 2 * ALIAS_COLS, pc + 2 * (size_t)i, p, i,
-                           TAG_PTRS, a.k0, a.k1, a.lnfact, ptrs_failed);
-            if (S == 2 && PASS != PASS_MAIN && (rq.kk & FLAG_THIN)) {
-              if (!wr_ok) {  // the quad's reddened-part words, drawn once
-                wr = philox10(p, i >> 2, TAG_RED, 0u, a.k0, a.k1);
-                wr_ok = true;
-              }
-              const uint32_t d = ld_const(rdesc + i);
-              red_thin = table_draw(d, word_of(wr, q), a.alias + ((size_t)i * 2 + 1) * ALIAS_COLS, pc + 2 * (size_t)i + 1,
-                                    p, i, TAG_PTRS_RED, a.k0, a.k1, a.lnfact, ptrs_failed);
-              n += red_thin;
-              thinned = true;
-            }
+          if (((tab >> (4 * h + q)) & 1u) == 0u) continue;
+          const uint32_t i = (uint32_t)(gi * GRP + 4 * h + q);
+          const uint32_t kk = rec[i].kk;
+          uint32_t n = table_draw(kk, word_of(w, q), alias + (size_t)i * 2 * ALIAS_COLS, pc + 2 * (size_t)i, p, i, TAG_PTRS, k0,
+                                  k1, lnfact, ptrs_failed);
+          uint32_t red = 0u;
+          if (S == 2 && PASS == PASS_ALL && (kk & FLAG_THIN)) {
+            const uint32_t d = ((const PCMD_CONST uint32_t *)ca->rdesc)[i];
+            red = table_draw(d, word_of(wr, q), alias + ((size_t)i * 2 + 1) * ALIAS_COLS, pc + 2 * (size_t)i + 1, p, i,
+                             TAG_PTRS_RED, k0, k1, lnfact, ptrs_failed);
+            n += red;
+          } else if (S == 2 && wave_any(n != 0u)) {
+            red = split_count(n, sq, 8u * (uint32_t)q, ca->split_mode, ca->split_q, p, i, k0, k1);
           }
           if (!wave_any(n != 0u)) continue;
-          uint32_t red = 0u;
-          if (S == 2) {
-            red = PASS != PASS_MAIN && thinned ? red_thin
-                                                : split_count(n, sq, 8u * q, a.split_mode, a.split_q, p, i, a.k0, a.k1);
-          }
-          // the entry's fluxes, loaded once for both streams
           const PCMD_CONST double *f = rec[i].fl;
           double fv[B];
 #pragma unroll
           for (int b = 0; b < B; ++b) fv[b] = f[b];
-          // the unreddened stream has a star whenever the entry has one, nearly always: added
-          // without a test (zero counts add exact zeros); the reddened stream is skipped when no
-          // lane has a reddened star
-          const uint32_t nc = n - red;
-          {
-            const double dc = (double)nc;
-#pragma unroll
-            for (int b = 0; b < B; ++b) acc_c[b] = fma(dc, fv[b], acc_c[b]);
-          }
-          if (S == 2 && wave_any(red != 0u)) {
-            const double dr = (double)red;
-#pragma unroll
-            for (int b = 0; b < B; ++b) acc_r[b] = fma(dr, fv[b], acc_r[b]);
-          }
-          if (DBG && dbg) {
-            const size_t o = (size_t)((int64_t)p - a.px0) * (size_t)a.E + i;
-            a.dbg_counts[o] = n;
-            if (a.dbg_red) a.dbg_red[o] = red;
-          }
+          add_counts<B, S>(acc_c, acc_r, fv, n, red);
+          write_dbg(i, n, red);
         }
       }
-    }
+    });
   }
+  const PCMD_CONST SampleArgs *ca = rare(ap);
+  if (wave_any(ptrs_failed != 0u) && (threadIdx.x & 63) == 0) atomicOr(ca->status, STATUS_PTRS_RETRY);
+  if (!live) return;
+  const size_t plane = (size_t)ca->npx;
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    float *pc = ca->part + ((size_t)(chunk * S + 0) * B + b) * plane + p;
+    float *pr = ca->part + ((size_t)(chunk * S + 1) * B + b) * plane + p;
+    *pc = (float)acc_c[b];
+    if (S == 2) *pr = (float)acc_r[b];
+  }
+}
+
+// The thinned entries of a tile (PASS_THIN), added to the partial sums that PASS_MAIN stored: a pass
+// of its own, so that the thinning code (live state that slows the common path) is not in the main
+// pass.
+template <int B, bool DBG>
+__device__ __forceinline__ void sample_thin_tile(const SampleArgs &a, uint32_t p, int chunk) {
+  const bool live = p < (uint32_t)a.npx;
+  const bool dbg = DBG && live && (int64_t)p >= a.px0 && (int64_t)p < a.px1;
+  double acc_c[B], acc_r[B];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    acc_c[b] = 0.0;
+    acc_r[b] = 0.0;
+  }
+  uint32_t ptrs_failed = 0u;  // per lane, kept in a vector register
+  for_groups(a.grp, a.E, a.nchunks, chunk, GRP_THIN, [&](int gi, uint32_t) {
+    // inversion words of the group's two quads: counters (p, i / 4, TAG_MAIN, 0)
+    const u4 wa = philox10(p, (uint32_t)(2 * gi), TAG_MAIN, 0u, a.k0, a.k1);
+    const u4 wb = philox10(p, (uint32_t)(2 * gi + 1), TAG_MAIN, 0u, a.k0, a.k1);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      thin_quad<B, DBG>(a, (uint32_t)(gi * GRP + 4 * h), h ? wb : wa, p, dbg, acc_c, acc_r, ptrs_failed);
+  });
   if (wave_any(ptrs_failed != 0u) && (threadIdx.x & 63) == 0) atomicOr(a.status, STATUS_PTRS_RETRY);
   if (!live) return;
   const size_t plane = (size_t)a.npx;
 #pragma unroll
   for (int b = 0; b < B; ++b) {
-    float *pc = a.part + ((size_t)(chunk * S + 0) * B + b) * plane + p;
-    float *pr = a.part + ((size_t)(chunk * S + 1) * B + b) * plane + p;
-    if (PASS == PASS_THIN) {  // exact zeros change nothing: a slice without thinned stars skips
-      if (acc_c[b] != 0.0) *pc = (float)((double)*pc + acc_c[b]);
-      if (S == 2 && acc_r[b] != 0.0) *pr = (float)((double)*pr + acc_r[b]);
-    } else {
-      *pc = (float)acc_c[b];
-      if (S == 2) *pr = (float)acc_r[b];
-    }
+    float *pc = a.part + ((size_t)(chunk * 2 + 0) * B + b) * plane + p;
+    float *pr = a.part + ((size_t)(chunk * 2 + 1) * B + b) * plane + p;
+    // exact zeros change nothing: a slice without thinned stars skips
+    if (acc_c[b] != 0.0) *pc = (float)((double)*pc + acc_c[b]);
+    if (acc_r[b] != 0.0) *pr = (float)((double)*pr + acc_r[b]);
   }
 }
 
@@ -746,7 +907,14 @@ k_sample(SampleArgs a) {
   if (PASS == PASS_THIN && a.thin_seen && *(const PCMD_CONST uint32_t *)a.thin_seen != a.gen) return;  // nothing thinned
   const int nblk_px = (a.npx + 255) >> 8;
   const int chunk = blockIdx.x / nblk_px;
-  sample_tile<B, S, DBG, PASS>(a, (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x), chunk);
+  const uint32_t p = (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x);
+  if constexpr (PASS == PASS_THIN) {
+    sample_thin_tile<B, DBG>(a, p, chunk);
+  } else {
+    // the arguments where the launch put them (the kernel's only parameter)
+    const PCMD_CONST SampleArgs *ap = (const PCMD_CONST SampleArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    sample_tile<B, S, DBG, PASS>(ap, p, chunk);
+  }
 }
 
 template <int B, int PASS>
@@ -833,13 +1001,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
     const int pblocks = cj[j].pblocks;  // 64-pixel blocks of the job
     const int chunk = local / pblocks;
     const int pblk = local - chunk * pblocks;
-    const SampleArgs a = ld_const(&cj[j].a);
+    const PCMD_CONST SampleArgs *ap = &cj[j].a;
     // batch jobs always carry two streams; F = 1/2 jobs draw their thinned entries afterwards in
     // a launch of their own (k_sample_thin_job), as pcmd_simulate does
-    if (thin_mode_of_split(a.split_mode) == THIN_TABLE)
-      sample_tile<B, 2, false, PASS_ALL>(a, (uint32_t)(pblk * 64) + lane, chunk);
+    if (thin_mode_of_split(ap->split_mode) == THIN_TABLE)
+      sample_tile<B, 2, false, PASS_ALL>(ap, (uint32_t)(pblk * 64) + lane, chunk);
     else
-      sample_tile<B, 2, false, PASS_MAIN>(a, (uint32_t)(pblk * 64) + lane, chunk);
+      sample_tile<B, 2, false, PASS_MAIN>(ap, (uint32_t)(pblk * 64) + lane, chunk);
   }
 }
 
@@ -855,7 +1023,7 @@ k_sample_thin_job(const BatchSampleJob *__restrict__ jobs, int t) {
   if (a.thin_seen && *(const PCMD_CONST uint32_t *)a.thin_seen != a.gen) return;  // nothing thinned
   const int nblk_px = (a.npx + 255) >> 8;
   const int chunk = blockIdx.x / nblk_px;
-  sample_tile<B, 2, false, PASS_THIN>(a, (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x), chunk);
+  sample_thin_tile<B, false>(a, (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x), chunk);
 }
 
 hipError_t launch_sample_thin_job(const BatchSampleJob *jobs, int t, int B, int npx, int nchunks, hipStream_t s) {

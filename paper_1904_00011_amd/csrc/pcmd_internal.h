@@ -14,11 +14,11 @@
 namespace pcmd {
 
 // One entry's sampler record (48 bytes, read with scalar loads): the first three inversion
-// thresholds inline (the first as T_0 - 1; the rest in the threshold table), K << 8 | kind, and the entry's star flux
+// thresholds inline (each minus one; the rest in the threshold table), K << 8 | kind, and the entry's star flux
 // in each band (FP64; bands past B are zero).  The fluxes sit in the record so that the
 // sampler reads them from the record address it already holds.
 struct EntryHead {
-  uint32_t T[3];  // T_0 - 1, T_1, T_2 (valid below K); T[0] = 0xFFFFFFFF unless drawn by inversion
+  uint32_t T[3];  // T_0 - 1, T_1 - 1, T_2 - 1; 0xFFFFFFFF from K on, and unless drawn by inversion
   uint32_t kk;    // (number of thresholds K, or k_lo of an alias entry) << 8 | kind
 };
 struct EntryRec {
@@ -29,20 +29,22 @@ struct EntryRec {
 static_assert(sizeof(EntryRec) == 48 && sizeof(EntryHead) == 16, "record layout");
 
 // Summary of eight consecutive entries (64 bytes, scalar loads), enough to finish a group in
-// which no pixel of the wave draws a star: T_0 - 1 of each entry drawn by inversion
-// (0xFFFFFFFF otherwise, so u > t0m1 never holds) and the kinds present.  For inversion
+// which no pixel of the wave draws a star: T_0 - 1 of each entry drawn by inversion below
+// LAM_DENSE (0xFFFFFFFF otherwise, so u > t0m1 never holds) and the kinds present.  For inversion
 // entries T_0 >= 1 (lambda < ALIAS_MIN), so u >= T_0 is exactly u > T_0 - 1.
 constexpr int GRP = 8;  // entries per group record (two Philox blocks)
 struct GroupRec {
   uint32_t t0m1[GRP];
-  uint32_t flags;  // GRP_INV | GRP_PTRS | GRP_ALIAS (entries drawn whole) | GRP_THIN (thinned entries)
+  uint32_t flags;  // GRP_INV | GRP_TABLE (entries drawn whole) | GRP_THIN (thinned entries), and which
   uint32_t pad[7];
 };
-constexpr uint32_t GRP_INV = 1u, GRP_PTRS = 2u, GRP_ALIAS = 4u, GRP_THIN = 8u;
-// The group's inversion entries are dense enough (64 sum lambda >= GRP_DENSE_LAMBDA64) that a
-// 64-pixel wave almost surely draws a star from one of them: the sampler skips its no-star test.
-constexpr uint32_t GRP_DENSE = 16u;
-constexpr double GRP_DENSE_LAMBDA64 = 3.0;
+constexpr uint32_t GRP_INV = 1u, GRP_TABLE = 2u, GRP_THIN = 4u;
+// bit 8 + q: entry q is drawn whole from a table; bit 16 + q: entry q is thinned
+// bit 24 + q: entry q is drawn by inversion with lambda >= LAM_DENSE
+constexpr uint32_t GRP_TABLE_ENTRY = 1u << 8, GRP_THIN_ENTRY = 1u << 16, GRP_DENSE_ENTRY = 1u << 24;
+// From here on more than half of all 64-pixel waves have a lane with three stars of the entry (64
+// lambda^3 / 6 = 0.7), and the sampler counts stars without first looking for lanes with one or two.
+constexpr double LAM_DENSE = 0.4;
 // Sampler passes: every entry (thinned ones inline); every entry but the thinned ones; only the
 // thinned ones, added to the partial sums the main pass stored.
 enum SamplePass { PASS_ALL = 0, PASS_MAIN = 1, PASS_THIN = 2 };
