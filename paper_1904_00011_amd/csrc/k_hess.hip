@@ -20,9 +20,18 @@ hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-constexpr int HESS_THREADS = 512;
-constexpr int HESS_MAX_BLOCKS = 1024;  // four 40 KB private histograms per CU
+constexpr int HESS_THREADS = 1024;
+// Two blocks per CU, each with a private histogram (40 KB for 100 x 100 bins): fewer blocks mean
+// fewer merges into the result by device-wide atomics, and HESS_UNROLL pixels in flight per lane
+// cover the memory latency.  Bound by the reads of its bands: 4096 x 4096 pixels, two bands, 67 ->
+// 42 us (3.2 TB/s; 1,024 blocks of 512 threads with a fence per block before).
+constexpr int HESS_MAX_BLOCKS = 512;
 constexpr int HESS_LDS_MAX_BINS = 40000;  // 160,000 bytes of LDS (of 163,840 per workgroup)
+constexpr int HESS_UNROLL = 4;            // pixels per lane whose loads are issued together
+// Up to this many pixels one block bins the whole image, and then stores its histogram and sums
+// instead of merging them: no launch to clear the result, no atomics (64 x 64 pixels: 12.6 + 2.2 ->
+// 7.1 us).  At 201 x 201 the ten blocks and the clearing take 14 us, one block 5 times the work.
+constexpr int64_t HESS_ONE_BLOCK = 8192;
 int hess_max_blocks() { return HESS_MAX_BLOCKS; }
 
 __device__ __forceinline__ int bin_of(double t, int n) {
@@ -32,121 +41,151 @@ __device__ __forceinline__ int bin_of(double t, int n) {
   return (int)t;
 }
 
-// bin_of((d) / dx) without the division where it cannot matter: t = d * (1 / dx) is within
-// 2^-51 |t| of the correctly rounded quotient (two roundings of the product, one of the
-// quotient), so when t - e and t + e (e = 2^-50 |t|) fall in the same bin, that is the bin of the
-// quotient (bin_of is monotone); otherwise, near a bin edge, and for infinite d, the FP64
-// division decides.  NaN takes bin 0 either way.
+// bin_of(d / dx) without the division where it cannot matter: t = d * (1 / dx) is within 2^-51 |t|
+// of the correctly rounded quotient (two roundings of the product, one of the quotient), so for
+// |t| < 2^20 and a fraction of t more than 2^-30 from 0 and 1 the quotient has the same floor.
+// Everything else (near a bin edge, far outside, infinite, NaN) takes the FP64 division.
 __device__ __forceinline__ int bin_fast(double d, double inv_dx, double dx, int n) {
   const double t = d * inv_dx;
-  const double e = 0x1p-50 * fabs(t);
-  const int lo = bin_of(t - e, n);
-  return lo == bin_of(t + e, n) ? lo : bin_of(d / dx, n);
+  const double f = __builtin_amdgcn_fract(t);
+  if (f > 0x1p-30 && f < 1.0 - 0x1p-30 && fabs(t) < 0x1p20) return min(max((int)t, 0), n - 1);
+  return bin_of(d / dx, n);
 }
 
-__device__ __forceinline__ double block_sum(double v, double *red) {
-  // fixed-order tree: within each wave by shuffles, then over the waves in order (deterministic)
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  const int wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[wave] = v;
+// The three sums over the block in v, in a fixed order: shuffles within each wave, then the waves in
+// order (one barrier on each side for all three).
+__device__ __forceinline__ void block_sum3(double (&v)[3], double (*red)[3]) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) v[c] += __shfl_down(v[c], off, 64);
+  if ((threadIdx.x & 63) == 0)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) red[threadIdx.x >> 6][c] = v[c];
   __syncthreads();
-  double r = 0.0;
-  for (int w = 0; w < HESS_THREADS / 64; ++w) r += red[w];
-  __syncthreads();
-  return r;
+#pragma unroll
+  for (int c = 0; c < 3; ++c) v[c] = 0.0;
+  if (threadIdx.x == 0)  // the only thread that uses the sums
+    for (int w = 0; w < HESS_THREADS / 64; ++w)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) v[c] += red[w][c];
 }
 
 int hess_blocks(int64_t npx) {
+  if (npx <= HESS_ONE_BLOCK) return 1;
   // enough pixels per block to amortise clearing and merging the private histogram
   int64_t blocks = (npx + 4095) / 4096;
-  if (blocks < 1) blocks = 1;
   if (blocks > HESS_MAX_BLOCKS) blocks = HESS_MAX_BLOCKS;
   return (int)blocks;
 }
 bool hess_use_lds(int nbins) { return nbins <= HESS_LDS_MAX_BINS; }
+// one block with a private histogram: the result needs no clearing
+static bool hess_stores(int64_t npx, int nbins) { return hess_use_lds(nbins) && hess_blocks(npx) == 1; }
 
 __device__ __forceinline__ void hess_body(const HessArgs &a) {
   extern __shared__ uint32_t lh[];
-  __shared__ double red[HESS_THREADS / 64];
+  __shared__ double red[HESS_THREADS / 64][3];
   __shared__ bool last;
   const int nb = a.nx * a.ny;
   if (a.use_lds) {
     for (int j = threadIdx.x; j < nb; j += HESS_THREADS) lh[j] = 0u;
     __syncthreads();
   }
-  double sx = 0.0, sy = 0.0, cnt = 0.0;
+  double sum[3] = {0.0, 0.0, 0.0};  // x, y, pixels
   const double inv_dx = 1.0 / a.dx, inv_dy = 1.0 / a.dy;
   const float *mb = a.mags + (size_t)a.bb * a.npx;
   const float *mr = a.mags + (size_t)a.br * a.npx;
   const float *mm = a.mags + (size_t)a.bm * a.npx;
-  for (int64_t p = (int64_t)blockIdx.x * HESS_THREADS + threadIdx.x; p < a.npx;
-       p += (int64_t)gridDim.x * HESS_THREADS) {
-    const double vb = (double)mb[p], vr = (double)mr[p], vm = (double)mm[p];
-    const double x = vb - vr, y = vm;
-    const int ix = bin_fast(x - a.x0, inv_dx, a.dx, a.nx);
-    const int iy = bin_fast(y - a.y0, inv_dy, a.dy, a.ny);
-    const int j = iy * a.nx + ix;
-    if (a.use_lds)
-      atomicAdd(&lh[j], 1u);
-    else
-      atomicAdd(&a.hess[j], 1u);
-    if (isfinite(vb) && isfinite(vr) && isfinite(vm)) {
-      sx += x;
-      sy += y;
-      cnt += 1.0;
+  const uint32_t npx = (uint32_t)a.npx, stride = gridDim.x * HESS_THREADS;  // at most 2^31 pixels
+  for (uint32_t p0 = blockIdx.x * HESS_THREADS + threadIdx.x; p0 < npx; p0 += HESS_UNROLL * stride) {
+    float fb[HESS_UNROLL], fr[HESS_UNROLL], fm[HESS_UNROLL];
+#pragma unroll
+    for (int k = 0; k < HESS_UNROLL; ++k) {
+      const uint32_t p = min(p0 + k * stride, npx - 1u);  // past the end: the last pixel again, not counted
+      fb[k] = mb[p];
+      fr[k] = mr[p];
+      fm[k] = a.bm == a.br ? fr[k] : a.bm == a.bb ? fb[k] : mm[p];
+    }
+#pragma unroll
+    for (int k = 0; k < HESS_UNROLL; ++k) {
+      if (p0 + k * stride >= npx) break;
+      const double x = (double)fb[k] - (double)fr[k], y = (double)fm[k];
+      const int ix = bin_fast(x - a.x0, inv_dx, a.dx, a.nx);
+      const int iy = bin_fast(y - a.y0, inv_dy, a.dy, a.ny);
+      const int j = iy * a.nx + ix;
+      if (a.use_lds)
+        atomicAdd(&lh[j], 1u);
+      else
+        atomicAdd(&a.hess[j], 1u);
+      // the difference of two FP32 values is finite in FP64 exactly when both are
+      if (isfinite(x) && isfinite(y)) {
+        sum[0] += x;
+        sum[1] += y;
+        sum[2] += 1.0;
+      }
     }
   }
+  const bool one = gridDim.x == 1;
   if (a.use_lds) {
     __syncthreads();
     for (int j = threadIdx.x; j < nb; j += HESS_THREADS) {
       const uint32_t v = lh[j];
-      if (v) atomicAdd(&a.hess[j], v);
+      if (one)
+        a.hess[j] = v;
+      else if (v)
+        atomicAdd(&a.hess[j], v);
     }
   }
-  sx = block_sum(sx, red);
-  sy = block_sum(sy, red);
-  cnt = block_sum(cnt, red);
+  block_sum3(sum, red);
+  if (one) {
+    if (threadIdx.x == 0)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a.moments[c] = sum[c];
+    return;
+  }
   if (threadIdx.x == 0) {
-    a.mom_part[blockIdx.x * 3 + 0] = sx;
-    a.mom_part[blockIdx.x * 3 + 1] = sy;
-    a.mom_part[blockIdx.x * 3 + 2] = cnt;
-    __threadfence();
+    // The partial goes out by device-scope stores, which reach memory that every XCD reads, and is
+    // complete before the block counts itself.  A __threadfence here would write back the whole L2
+    // of the XCD, once per block.
+#pragma unroll
+    for (int c = 0; c < 3; ++c)
+      __hip_atomic_store(a.mom_part + blockIdx.x * 3 + c, sum[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const uint32_t prev = atomicAdd(a.counter, 1u);
     last = (prev == gridDim.x - 1);
   }
   __syncthreads();
   if (last) {
-    // every block's partial is visible: thread t adds blocks t, t + HESS_THREADS, ... in order,
-    // then the fixed-order block sum (the combination does not depend on which block is last)
-    __threadfence();
-    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-    for (unsigned k = threadIdx.x; k < gridDim.x; k += HESS_THREADS) {
-      s0 += __builtin_nontemporal_load(&a.mom_part[k * 3 + 0]);
-      s1 += __builtin_nontemporal_load(&a.mom_part[k * 3 + 1]);
-      s2 += __builtin_nontemporal_load(&a.mom_part[k * 3 + 2]);
-    }
-    s0 = block_sum(s0, red);
-    s1 = block_sum(s1, red);
-    s2 = block_sum(s2, red);
+    // every block's partial is in memory: thread t adds blocks t, t + HESS_THREADS, ... in order
+    // (device-scope loads), then the fixed-order block sum (the combination does not depend on
+    // which block is last)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sum[c] = 0.0;
+    for (unsigned k = threadIdx.x; k < gridDim.x; k += HESS_THREADS)
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+        sum[c] += __hip_atomic_load(a.mom_part + k * 3 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    block_sum3(sum, red);
     if (threadIdx.x == 0) {
-      a.moments[0] = s0;
-      a.moments[1] = s1;
-      a.moments[2] = s2;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a.moments[c] = sum[c];
       *a.counter = 0u;  // ready for the next call (also under graph replay)
     }
   }
 }
 
-__global__ void __launch_bounds__(HESS_THREADS) k_hess(HessArgs a) { hess_body(a); }
-__global__ void __launch_bounds__(HESS_THREADS) k_hess_job(const HessArgs *__restrict__ t, int j) {
+__global__ void __launch_bounds__(HESS_THREADS, 8) k_hess(HessArgs a) { hess_body(a); }
+__global__ void __launch_bounds__(HESS_THREADS, 8) k_hess_job(const HessArgs *__restrict__ t, int j) {
   const HessArgs a = t[j];
   hess_body(a);
 }
 
 hipError_t launch_hess(const HessArgs &a, hipStream_t s) {
   const int nb = a.nx * a.ny;
-  hipError_t e = launch_fill_u32(a.hess, 0u, nb, s);
-  if (e != hipSuccess) return e;
+  if (!hess_stores(a.npx, nb)) {
+    const hipError_t e = launch_fill_u32(a.hess, 0u, nb, s);
+    if (e != hipSuccess) return e;
+  }
   const size_t lds = a.use_lds ? (size_t)nb * sizeof(uint32_t) : 0;
   hipLaunchKernelGGL(k_hess, dim3((unsigned)hess_blocks(a.npx)), dim3(HESS_THREADS), lds, s, a);
   return hipGetLastError();
@@ -157,13 +196,10 @@ __global__ void __launch_bounds__(256) k_hess_clear_job(const HessArgs *__restri
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nbins; i += gridDim.x * blockDim.x) h[i] = 0u;
 }
 
-hipError_t launch_hess_clear_job(const HessArgs *table, int j, int nbins, hipStream_t s) {
-  hipLaunchKernelGGL(k_hess_clear_job, dim3((nbins + 255) / 256), dim3(256), 0, s, table, j, nbins);
-  return hipGetLastError();
-}
-
-// The job variant expects the histogram already cleared (k_hess_clear_job).
+// Job j's diagram (cleared first where blocks add to it).
 hipError_t launch_hess_job(const HessArgs *table, int j, int64_t npx, int nbins, hipStream_t s) {
+  if (!hess_stores(npx, nbins))
+    hipLaunchKernelGGL(k_hess_clear_job, dim3((nbins + 255) / 256), dim3(256), 0, s, table, j, nbins);
   const size_t lds = hess_use_lds(nbins) ? (size_t)nbins * sizeof(uint32_t) : 0;
   hipLaunchKernelGGL(k_hess_job, dim3((unsigned)hess_blocks(npx)), dim3(HESS_THREADS), lds, s, table, j);
   return hipGetLastError();

@@ -469,10 +469,7 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
     if (e == hipSuccess && ji.K > 1) e = launch_conv_direct_job(ca, j, ji.B, ji.N, ji.K, ji.grid, s);
     if (e == hipSuccess) e = launch_noise_mag_job(na, j, ji.npx, s);
   }
-  for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) {
-    e = launch_hess_clear_job(ha, j, p->nbins, s);
-    if (e == hipSuccess) e = launch_hess_job(ha, j, p->info[j].npx, p->nbins, s);
-  }
+  for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) e = launch_hess_job(ha, j, p->info[j].npx, p->nbins, s);
   if (e == hipSuccess) e = launch_loglike_jobs(la, p->n_jobs, p->nbins, s);
   return e;
 }

@@ -64,3 +64,27 @@ def test_point_sampler_mixed_groups(ctx, E, B, nim, frac):
     plain = pu.gpu_simulate(ctx, lam, f32, obs)  # the kernel without the counts window
     for g in (got, plain):
         assert np.all(np.abs(g["flux_pre"] - ora["F"]) <= 2e-7 * np.abs(ora["F"]))
+
+
+# One block that stores its histogram (up to 8,192 pixels), several that add, remainders of the four
+# pixels a lane loads at once, a diagram too large for the private histogram; magnitudes on bin
+# edges, infinite and NaN.  Moments: at most 2^21 FP64 additions, each 2^-53 of the running sum.
+@pytest.mark.parametrize("npx", [1, 1023, 4097, 8192, 8193, 70001, 2_200_003])
+@pytest.mark.parametrize("nx,ny,bands", [(5, 3, (0, 1, 1)), (100, 100, (0, 1, 0)), (201, 203, (1, 2, 0))])
+def test_hess_pixel_counts(ctx, npx, nx, ny, bands):
+    from tests import parity_utils as pu
+    r = np.random.default_rng(npx + nx)
+    m = r.normal(25.0, 0.4, (3, npx)).astype(np.float32)
+    edge = r.uniform(size=(3, npx)) < 0.3
+    m[edge] = (np.round(m[edge] / 0.05) * 0.05).astype(np.float32)
+    odd = r.uniform(size=(3, npx))
+    m[odd < 0.01], m[odd > 0.995], m[(odd > 0.99) & (odd < 0.992)] = np.inf, np.nan, 1e30
+    m[:, -1] = 25.0
+    grid = dict(x0=-0.05 * (nx // 2), dx=0.05, y0=25.0 - 0.05 * (ny // 2), dy=0.05, nx=nx, ny=ny)
+    h, mom = pu.gpu_hess(ctx, m, grid, bands)
+    with np.errstate(invalid="ignore"):
+        ho, mo = oh.hess(m, grid, *bands)
+    assert np.array_equal(h, ho) and int(h.sum()) == npx
+    assert mom[2] == mo[2]
+    scale = np.array([1e30, 1e30]) * npx if np.any(m == np.float32(1e30)) else np.abs(mo[:2]) + 1.0
+    assert np.all(np.abs(np.asarray(mom[:2]) - np.asarray(mo[:2])) <= 2.0 ** -32 * scale)
