@@ -88,3 +88,19 @@ def test_hess_pixel_counts(ctx, npx, nx, ny, bands):
     assert mom[2] == mo[2]
     scale = np.array([1e30, 1e30]) * npx if np.any(m == np.float32(1e30)) else np.abs(mo[:2]) + 1.0
     assert np.all(np.abs(np.asarray(mom[:2]) - np.asarray(mo[:2])) <= 2.0 ** -32 * scale)
+
+
+# Bins per thread of the one-block kernel (4, 10, 16) and the first size of the two-kernel path.
+# FP64 sums of at most 2^15 terms of one sign: 2^15 2^-53 = 4e-12 relative, the logarithm's and the
+# table's last places beside it.
+@pytest.mark.parametrize("nbins", [1, 1024, 4096, 4097, 10240, 10241, 16384, 16385])
+@pytest.mark.parametrize("mode", [0, 1, 2])
+def test_loglike_bin_counts(ctx, nbins, mode):
+    from tests import parity_utils as pu
+    r = np.random.default_rng(nbins)
+    hm, hd = r.poisson(r.choice([0.0, 0.3, 20.0], nbins)), r.poisson(r.choice([0.0, 0.3, 20.0, 7000.0], nbins))
+    hm[0] += 1
+    hd[-1] += 2
+    mom_m, mom_d = np.array([0.5, 25.0, 1.0]) * hm.sum(), np.array([0.52, 25.1, 1.0]) * hd.sum()
+    got = pu.gpu_loglike(ctx, hm, hd, mom_m, mom_d, mode)
+    assert got == pytest.approx(ol.loglike(hm, hd, mom_m, mom_d, mode), rel=2e-11, abs=1e-11)
