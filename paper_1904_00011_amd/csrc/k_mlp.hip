@@ -149,10 +149,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
   const int r = lane & 31, kh = (lane >> 5) * 8;
-  // split over K: block z of a split product covers [z kchunk, (z + 1) kchunk)
-  const int kb = g.part ? (int)blockIdx.z * g.kchunk : 0;
-  const int ke = g.part ? min(g.K, kb + g.kchunk) : g.K;
-  const int nk = (ke - kb + GBK - 1) / GBK;
+  constexpr int kb = 0;
+  const int ke = g.K;
+  const int nk = (ke + GBK - 1) / GBK;
   TileRegs<RA> ra;
   TileRegs<RB> rb;
   load_regs(ra, g.A, g.lda, g.M, ke, bm, kb, va);
@@ -193,13 +192,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
   // rows into its own LDS slab (row stride GEPI_LD floats: the two half-waves of one store land
   // in different banks), then reads them back four consecutive columns per lane and writes 16
   // bytes per lane (C) or 8 bytes (BF16 outputs).
-  float *part = g.part ? g.part + (size_t)blockIdx.z * g.M * g.N : nullptr;
   float *slab = reinterpret_cast<float *>(smem) + wave * (32 * GEPI_LD);
-  const int ldo = part ? g.N : g.ldc;
-  const bool v4 = part ? (g.N % 4 == 0 && ((uintptr_t)part & 15) == 0)
-                       : (EPI != EPI_GELU_GRAD && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0 &&
-                          (EPI == EPI_STORE || ((uintptr_t)g.bias & 15) == 0) &&
-                          (EPI != EPI_BIAS_GELU || (g.ldcb % 4 == 0 && ((uintptr_t)g.Cb & 7) == 0)));
+  const bool v4 = EPI != EPI_GELU_GRAD && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0 &&
+                  (EPI == EPI_STORE || ((uintptr_t)g.bias & 15) == 0) &&
+                  (EPI != EPI_BIAS_GELU || (g.ldcb % 4 == 0 && ((uintptr_t)g.Cb & 7) == 0));
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
@@ -219,19 +215,12 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
       if (row >= g.M) continue;
       const float4 v = *reinterpret_cast<const float4 *>(&slab[rr * GEPI_LD + c4]);
       if (v4 && col + 4 <= g.N) {
-        if (part) {
-          *reinterpret_cast<float4 *>(&part[(size_t)row * ldo + col]) = v;
-        } else {
-          gemm_epilogue4<EPI>(g, row, col, v);
-        }
+        gemm_epilogue4<EPI>(g, row, col, v);
       } else {
         const float vv[4] = {v.x, v.y, v.z, v.w};
         for (int q = 0; q < 4; ++q) {
           if (col + q >= g.N) break;
-          if (part)
-            part[(size_t)row * ldo + col + q] = vv[q];
-          else
-            gemm_epilogue<EPI>(g, row, col + q, vv[q]);
+          gemm_epilogue<EPI>(g, row, col + q, vv[q]);
         }
       }
     }
@@ -252,6 +241,192 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs g, int spli
   gemm_epilogue<EPI>(g, (int)(idx / g.N), (int)(idx % g.N), v);
 }
 
+// Row index of batch sample k: rows[k] when a row vector is given (one outside [0, n_total) is
+// taken as row 0 and flagged in *status), else k.
+__device__ __forceinline__ int64_t batch_row(const int32_t *__restrict__ rows, int64_t k, int64_t n_total,
+                                             uint32_t *status) {
+  if (!rows) return k;
+  const int32_t r = rows[k];
+  if (r < 0 || (int64_t)r >= n_total) {
+    atomicOr(status, STATUS_BAD_ROW);
+    return 0;
+  }
+  return r;
+}
+
+// ---------------------------------------------------------------------------------------
+// The same product in 64 x 64 tiles, for products whose 128 x 128 tiles would leave most of the chip
+// idle (every hidden layer's).  Such a product is bound by latency: a block of G groups of 256 threads
+// (4 waves of one 32 x 32 MFMA tile each) reads 128 K elements per operand row and stage, the next
+// stage's loads in flight during the products.  Group g takes the K range [g kchunk, (g + 1) kchunk)
+// of a split product and group 0 adds the groups' sums in order, the sums and order of
+// k_gemm + k_gemm_splitk_reduce without their launch and trip through memory.  More ranges than 4 go
+// to blockIdx.z and the workspace, as in k_gemm.  TA / TB: that operand is stored K-major (A(m, k) =
+// A[k][m]) and transposed on its way into LDS: a thread reads an 8 x 8 block in eight 16-byte rows and
+// permutes it in registers, where a transpose launch had copied the operand first.  AF32: A is the
+// FP32 input batch (rows of it by the row vector), rounded on the way.
+// Measured, products and what went with them (split sums, transposes, rounding of the input): one
+// sample through 12-512-512-512-512-10000 65 -> 37 us, 4,096 samples' hidden layers 90 -> 60 us; all
+// results the same bit for bit.
+// ---------------------------------------------------------------------------------------
+constexpr int HB = 64, HK = 128, HLD = HK + 8;  // tile, K stage, LDS row stride (rows 4 banks apart)
+
+union Run8 {
+  bf16x8 v;
+  uint32_t w[4];
+};
+
+// 4 runs of 8 k of a 64 x HK tile (row-major operand): thread t's run i is row (t + 256 i) / 16.
+__device__ __forceinline__ void load_rows64(Run8 (&x)[4], const __bf16 *__restrict__ src, int ld, int rows, int ke, int r0,
+                                            int k0, bool vec, int t) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int idx = t + 256 * i;
+    const int r = r0 + (idx >> 4), k = k0 + (idx & 15) * 8;
+    if (vec && r < rows && k + 8 <= ke) {
+      x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)r * ld + k);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[i].v[j] = (r < rows && k + j < ke) ? src[(size_t)r * ld + k + j] : (__bf16)0.0f;
+    }
+  }
+}
+__device__ __forceinline__ void store_rows64(__bf16 *lds, const Run8 (&x)[4], int t) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int idx = t + 256 * i;
+    *reinterpret_cast<bf16x8 *>(lds + (idx >> 4) * HLD + (idx & 15) * 8) = x[i].v;
+  }
+}
+// One 8 x 8 block of a K-major operand: block b holds k 8 (b / 8) .. + 7 and rows 8 (b % 8) .. + 7.
+__device__ __forceinline__ void load_cols64(Run8 (&x)[8], const __bf16 *__restrict__ src, int ld, int rows, int ke, int r0,
+                                            int k0, bool vec, int b) {
+  const int r = r0 + (b & 7) * 8, k = k0 + (b >> 3) * 8;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if (vec && r + 8 <= rows && k + i < ke) {
+      x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)(k + i) * ld + r);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[i].v[j] = (r + j < rows && k + i < ke) ? src[(size_t)(k + i) * ld + r + j] : (__bf16)0.0f;
+    }
+  }
+}
+__device__ __forceinline__ void store_cols64(__bf16 *lds, const Run8 (&x)[8], int b) {
+#pragma unroll
+  for (int m = 0; m < 8; ++m) {
+    Run8 o;  // row m of the block: its k pairs from the k-th and (k + 1)-th words
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      o.w[j] = __builtin_amdgcn_perm(x[2 * j + 1].w[m >> 1], x[2 * j].w[m >> 1], (m & 1) ? 0x07060302u : 0x05040100u);
+    *reinterpret_cast<bf16x8 *>(lds + ((b & 7) * 8 + m) * HLD + (b >> 3) * 8) = o.v;
+  }
+}
+// FP32 input rows (few columns: one element at a time), rounded.
+__device__ __forceinline__ void load_f32rows64(Run8 (&x)[4], const GemmArgs &g, int ke, int r0, int k0, int t) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int idx = t + 256 * i;
+    const int r = r0 + (idx >> 4), k = k0 + (idx & 15) * 8;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[i].v[j] = (__bf16)0.0f;
+    if (r >= g.M || k >= ke) continue;
+    const float *row = g.A32 + batch_row(g.rows, r, g.n_total, g.status) * g.lda;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (k + j < ke) {
+        x[i].v[j] = (__bf16)row[k + j];
+        if (g.Aout && blockIdx.x == 0) g.Aout[(size_t)r * g.lda + k + j] = x[i].v[j];
+      }
+  }
+}
+
+template <int EPI, int G, bool TA, bool TB, bool AF32>
+__global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) char smem64[];
+  const int grp = threadIdx.x >> 8, t = threadIdx.x & 255;
+  __bf16 *As = reinterpret_cast<__bf16 *>(smem64) + (size_t)grp * 2 * HB * HLD, *Bs = As + HB * HLD;
+  const int bm = blockIdx.y * HB, bn = blockIdx.x * HB;
+  const int wave = t >> 6, lane = t & 63;
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const bool va = (g.lda % 8 == 0) && (((uintptr_t)g.A & 15) == 0);
+  const bool vb = (g.ldb % 8 == 0) && (((uintptr_t)g.B & 15) == 0);
+  const int chunk = G > 1 ? grp : (int)blockIdx.z;
+  const int kb = chunk * g.kchunk, ke = min(g.K, kb + g.kchunk);
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+  const int r = lane & 31, kh = (lane >> 5) * 8;
+  // every group runs the stages of the longest range (group 0's): the barriers are the block's
+  const int stages = (min(g.K, g.kchunk) + HK - 1) / HK;
+  // K-major operands: the first 128 threads hold A's blocks, the others B's, where both are; else
+  // the first 128 threads
+  constexpr bool BOTH = TA && TB;
+  const int cb = BOTH ? t & 127 : t;
+  const bool has_a = TA && (BOTH ? t < 128 : t < 128), has_b = TB && (BOTH ? t >= 128 : t < 128);
+  Run8 ra[4], rb[4], rc[8];
+  auto load = [&](int k0) {
+    if constexpr (AF32)
+      load_f32rows64(ra, g, ke, bm, k0, t);
+    else if constexpr (!TA)
+      load_rows64(ra, g.A, g.lda, g.M, ke, bm, k0, va, t);
+    if constexpr (!TB) load_rows64(rb, g.B, g.ldb, g.N, ke, bn, k0, vb, t);
+    if constexpr (TA)
+      if (has_a) load_cols64(rc, g.A, g.lda, g.M, ke, bm, k0, va, cb);
+    if constexpr (TB)
+      if (has_b) load_cols64(rc, g.B, g.ldb, g.N, ke, bn, k0, vb, cb);
+  };
+  load(kb);
+  for (int st = 0; st < stages; ++st) {
+    const int k0 = kb + st * HK;
+    if (st > 0) __syncthreads();  // the previous stage's reads are over
+    if constexpr (!TA) store_rows64(As, ra, t);
+    if constexpr (!TB) store_rows64(Bs, rb, t);
+    if constexpr (TA)
+      if (has_a) store_cols64(As, rc, cb);
+    if constexpr (TB)
+      if (has_b) store_cols64(Bs, rc, cb);
+    __syncthreads();
+    if (st + 1 < stages) load(k0 + HK);
+    // whole steps of 16 up to the range's end (what lies past it in the stage is zero)
+#pragma unroll
+    for (int ks = 0; ks < HK; ks += 16) {
+      if (k0 + ks >= ke) break;
+      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&As[(wm + r) * HLD + ks + kh]);
+      const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&Bs[(wn + r) * HLD + ks + kh]);
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+    }
+  }
+  if (G > 1) {
+    // the groups' sums in group order: groups 1.. leave theirs in LDS, group 0 adds them
+    __syncthreads();
+    float *sums = reinterpret_cast<float *>(smem64);  // [G - 1][16][256]
+    if (grp > 0) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sums[((grp - 1) * 16 + e) * 256 + t] = acc[e];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+#pragma unroll
+    for (int q = 0; q < G - 1; ++q)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[e] += sums[(q * 16 + e) * 256 + t];
+  }
+  // accumulator element e: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
+  float *part = g.part ? g.part + (size_t)blockIdx.z * g.M * g.N : nullptr;
+  const int col = bn + wn + (lane & 31);
+  if (col >= g.N) return;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    const int row = bm + wm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+    if (row >= g.M) continue;
+    if (part)
+      part[(size_t)row * g.N + col] = acc[e];
+    else
+      gemm_epilogue<EPI>(g, row, col, acc[e]);
+  }
+}
+
 // Split over K when the output tile grid cannot fill the chip and K is long enough: about two
 // blocks per CU, at least 256 K elements per split.
 static int gemm_splits(int M, int N, int K, int &kchunk) {
@@ -264,19 +439,25 @@ static int gemm_splits(int M, int N, int K, int &kchunk) {
   return (K + kchunk - 1) / kchunk;
 }
 
+// Whether a product takes 64 x 64 tiles: its 128 x 128 tiles would not give every CU two blocks.
+static bool gemm_use64(int M, int N) { return (int64_t)((M + GBM - 1) / GBM) * ((N + GBN - 1) / GBN) < 512; }
+
 // Workspace layout: [A transposed: M x ldk bf16][B transposed: N x ldk bf16][split-K partials:
-// splits x M x N FP32], each part 256-byte aligned and present only when needed.
+// splits x M x N FP32], each part 256-byte aligned and present only when needed (the 64 x 64 tiles
+// read K-major operands as they are and add up to four splits inside a block).
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 static int transposed_ld(int K) { return (K + 7) & ~7; }  // keeps the 16-byte loads of k_gemm
+constexpr int G64_SPLITS = 4;
 
 size_t gemm_workspace_bytes(int M, int N, int K, bool at, bool bt) {
   int kchunk;
   const int splits = gemm_splits(M, N, K, kchunk);
+  const bool t64 = gemm_use64(M, N);
   const size_t lk = (size_t)transposed_ld(K);
   size_t b = 0;
-  if (at) b += align256((size_t)M * lk * 2);
-  if (bt) b += align256((size_t)N * lk * 2);
-  if (splits > 1) b += (size_t)splits * M * N * 4;
+  if (at && !t64) b += align256((size_t)M * lk * 2);
+  if (bt && !t64) b += align256((size_t)N * lk * 2);
+  if (splits > (t64 ? G64_SPLITS : 1)) b += (size_t)splits * M * N * 4;
   return b;
 }
 
@@ -286,9 +467,56 @@ static hipError_t launch_transpose(const __bf16 *src, int ld, int rows, int cols
   return hipGetLastError();
 }
 
+template <int EPI, bool TA, bool TB, bool AF32>
+static hipError_t launch_gemm64_t(GemmArgs g, int splits, void *ws, hipStream_t s) {
+  const bool inside = splits <= G64_SPLITS;
+  g.part = inside ? nullptr : (float *)ws;
+  const dim3 grid((unsigned)((g.N + HB - 1) / HB), (unsigned)((g.M + HB - 1) / HB), inside ? 1u : (unsigned)splits);
+  constexpr size_t lds = 2 * HB * HLD * sizeof(__bf16);  // one group's tiles
+  if (inside && splits > 2)  // a third or fourth range may be empty
+    hipLaunchKernelGGL((k_gemm64<EPI, 4, TA, TB, AF32>), grid, dim3(1024), 4 * lds, s, g);
+  else if (inside && splits == 2)
+    hipLaunchKernelGGL((k_gemm64<EPI, 2, TA, TB, AF32>), grid, dim3(512), 2 * lds, s, g);
+  else
+    hipLaunchKernelGGL((k_gemm64<EPI, 1, TA, TB, AF32>), grid, dim3(256), lds, s, g);
+  if (!inside) {
+    const unsigned rblocks = (unsigned)(((int64_t)g.M * g.N + 255) / 256);
+    hipLaunchKernelGGL((k_gemm_splitk_reduce<EPI>), dim3(rblocks), dim3(256), 0, s, g, splits);
+  }
+  return hipGetLastError();
+}
+
+static hipError_t launch_gemm64(const GemmArgs &g, int splits, bool at, bool bt, int epi, void *ws, hipStream_t s) {
+  if (g.A32) {
+    if (at || bt) return hipErrorInvalidValue;
+    if (epi == EPI_BIAS) return launch_gemm64_t<EPI_BIAS, false, false, true>(g, splits, ws, s);
+    if (epi == EPI_BIAS_GELU) return launch_gemm64_t<EPI_BIAS_GELU, false, false, true>(g, splits, ws, s);
+    return hipErrorInvalidValue;
+  }
+  if (epi == EPI_STORE) {
+    if (at && bt) return launch_gemm64_t<EPI_STORE, true, true, false>(g, splits, ws, s);
+    if (at) return launch_gemm64_t<EPI_STORE, true, false, false>(g, splits, ws, s);
+    if (bt) return launch_gemm64_t<EPI_STORE, false, true, false>(g, splits, ws, s);
+    return launch_gemm64_t<EPI_STORE, false, false, false>(g, splits, ws, s);
+  }
+  if (at || bt) return hipErrorInvalidValue;  // the network's other products are row-major
+  if (epi == EPI_BIAS) return launch_gemm64_t<EPI_BIAS, false, false, false>(g, splits, ws, s);
+  if (epi == EPI_BIAS_GELU) return launch_gemm64_t<EPI_BIAS_GELU, false, false, false>(g, splits, ws, s);
+  if (epi == EPI_GELU_GRAD) return launch_gemm64_t<EPI_GELU_GRAD, false, false, false>(g, splits, ws, s);
+  return hipErrorInvalidValue;
+}
+
+bool gemm_reads_f32(int M, int N) { return gemm_use64(M, N); }
+
 hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s) {
   GemmArgs g = g0;
   if (ws_bytes < gemm_workspace_bytes(g.M, g.N, g.K, at, bt)) return hipErrorInvalidValue;
+  int kchunk;
+  const int splits = gemm_splits(g.M, g.N, g.K, kchunk);
+  const bool split = splits > 1;
+  g.kchunk = split ? kchunk : g.K;
+  if (gemm_use64(g.M, g.N)) return launch_gemm64(g, splits, at, bt, epi, ws, s);
+  if (g.A32) return hipErrorInvalidValue;
   char *w = (char *)ws;
   const int lk = transposed_ld(g.K);
   if (at) {  // A(m, k) = A[k][m]: K rows of M
@@ -307,22 +535,17 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
     g.ldb = lk;
     w += align256((size_t)g.N * lk * 2);
   }
-  int kchunk;
-  const int splits = gemm_splits(g.M, g.N, g.K, kchunk);
-  const bool split = splits > 1;
-  g.part = split ? (float *)w : nullptr;
-  g.kchunk = split ? kchunk : g.K;
+  // 512 blocks or more are never split (gemm_splits splits below 128)
+  g.part = nullptr;
   // 256-row block tiles where the product is large enough to keep every CU busy with them
-  const bool tall = !split && g.M >= 4096 && g.N >= 2048;
-  dim3 grid((g.N + GBN - 1) / GBN, (g.M + (tall ? 2 * GBM : GBM) - 1) / (tall ? 2 * GBM : GBM), split ? splits : 1);
-  const unsigned rblocks = (unsigned)(((int64_t)g.M * g.N + 255) / 256);
+  const bool tall = g.M >= 4096 && g.N >= 2048;
+  dim3 grid((g.N + GBN - 1) / GBN, (g.M + (tall ? 2 * GBM : GBM) - 1) / (tall ? 2 * GBM : GBM));
 #define PCMD_GEMM_CASE(E_)                                                                             \
   if (epi == E_) {                                                                                     \
     if (tall)                                                                                          \
       hipLaunchKernelGGL((k_gemm<E_, 4>), grid, dim3(256), 0, s, g);                                   \
     else                                                                                               \
       hipLaunchKernelGGL((k_gemm<E_, 2>), grid, dim3(256), 0, s, g);                                   \
-    if (split) hipLaunchKernelGGL((k_gemm_splitk_reduce<E_>), dim3(rblocks), dim3(256), 0, s, g, splits); \
     return hipGetLastError();                                                                          \
   }
   PCMD_GEMM_CASE(EPI_STORE)
@@ -344,19 +567,6 @@ __global__ void __launch_bounds__(256) k_f32_to_bf16(const float *__restrict__ x
 hipError_t launch_f32_to_bf16(const float *x, void *y, int64_t n, hipStream_t s) {
   hipLaunchKernelGGL(k_f32_to_bf16, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, x, (__bf16 *)y, n);
   return hipGetLastError();
-}
-
-// Row index of batch sample k: rows[k] when a row vector is given (one outside [0, n_total) is
-// taken as row 0 and flagged in *status), else k.
-__device__ __forceinline__ int64_t batch_row(const int32_t *__restrict__ rows, int64_t k, int64_t n_total,
-                                             uint32_t *status) {
-  if (!rows) return k;
-  const int32_t r = rows[k];
-  if (r < 0 || (int64_t)r >= n_total) {
-    atomicOr(status, STATUS_BAD_ROW);
-    return 0;
-  }
-  return r;
 }
 
 // y[k][j] = bf16(x[row k][j]) for a batch of n samples of d inputs.

@@ -59,8 +59,13 @@ hipError_t forward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, int
   __bf16 *act = (__bf16 *)c->mlp_act.p;
   float *pre = (float *)c->mlp_pre.p;
   const __bf16 *w = (const __bf16 *)net->w_bf16;
-  hipError_t e = rows ? launch_gather_f32_to_bf16(x, rows, n_total, lay.d[0], n, act, c->status, s)
-                      : launch_f32_to_bf16(x, act, (int64_t)n * lay.d[0], s);
+  // the first product reads the FP32 batch itself where it can (and keeps the rounded copy for the
+  // backward pass); a large batch is rounded first
+  const bool direct = gemm_reads_f32(n, lay.d[1]);
+  hipError_t e = hipSuccess;
+  if (!direct)
+    e = rows ? launch_gather_f32_to_bf16(x, rows, n_total, lay.d[0], n, act, c->status, s)
+             : launch_f32_to_bf16(x, act, (int64_t)n * lay.d[0], s);
   int64_t aoff = 0, poff = 0;
   for (int l = 0; l < lay.L && e == hipSuccess; ++l) {
     const int din = lay.d[l], dout = lay.d[l + 1];
@@ -70,6 +75,13 @@ hipError_t forward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, int
     g.K = din;
     g.A = act + aoff;
     g.lda = din;
+    if (l == 0 && direct) {
+      g.A32 = x;
+      g.rows = rows;
+      g.n_total = n_total;
+      g.Aout = act;
+      g.status = c->status;
+    }
     g.B = w + lay.woff[l];
     g.ldb = din;
     g.bias = net->master + lay.off[l] + (int64_t)dout * din;

@@ -23,7 +23,15 @@ struct GemmArgs {
   const float *Z;     // FP32 pre-activations for GELU' (EPI_GELU_GRAD)
   int ldz;
   float *part;        // split-K partial products [splits][M][N] (set by launch_gemm)
-  int kchunk;         // K elements per split (a multiple of the K step)
+  int kchunk;         // K elements per split (a multiple of the K step; set by launch_gemm)
+  // A given in FP32 instead (A unused): row m is row rows[m] of A32 (m when rows is NULL; a row outside
+  // [0, n_total) is taken as row 0 and sets STATUS_BAD_ROW), rounded to BF16 and, unless Aout is NULL,
+  // also written there [M][lda].  Only where gemm_reads_f32(M, N).
+  const float *A32;
+  const int32_t *rows;
+  int64_t n_total;
+  __bf16 *Aout;
+  uint32_t *status;
 };
 
 struct AdamArgs {
@@ -36,6 +44,7 @@ struct AdamArgs {
 
 // Workspace (bytes) launch_gemm needs for an M x N x K product: transposed copies of K-major
 // operands (at: A(m, k) = A[k][m]; bt: B(n, k) = B[k][n]) and split-K partials.
+bool gemm_reads_f32(int M, int N);
 size_t gemm_workspace_bytes(int M, int N, int K, bool at, bool bt);
 hipError_t launch_gemm(const GemmArgs &g, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float *x, void *y, int64_t n, hipStream_t s);

@@ -104,3 +104,53 @@ def test_loglike_bin_counts(ctx, nbins, mode):
     mom_m, mom_d = np.array([0.5, 25.0, 1.0]) * hm.sum(), np.array([0.52, 25.1, 1.0]) * hd.sum()
     got = pu.gpu_loglike(ctx, hm, hd, mom_m, mom_d, mode)
     assert got == pytest.approx(ol.loglike(hm, hd, mom_m, mom_d, mode), rel=2e-11, abs=1e-11)
+
+
+# 64 x 64 tiles: edges of tile, K stage (128) and K ranges (1, 2, 3-4 inside a block, more in the
+# workspace), row starts that allow no 16-byte loads, either operand K-major.  Products of BF16 values
+# are exact in FP32; K additions of 2^-24 relative to the running sum's magnitude, at most
+# sum |a||b| (the largest of the three sums below).
+@pytest.mark.parametrize("M,N,K", [(64, 64, 128), (65, 63, 129), (1, 512, 512), (33, 100, 700), (64, 72, 1024), (200, 8, 2100),
+                                   (1024, 512, 12)])
+@pytest.mark.parametrize("at,bt", [(False, False), (True, True), (True, False), (False, True)])
+def test_gemm_small_tiles(ctx, M, N, K, at, bt):
+    r = np.random.default_rng(M + N + K)
+    A = om.bf16_round(r.normal(size=(M, K)).astype(np.float32))
+    B = om.bf16_round(r.normal(size=(N, K)).astype(np.float32))
+    Ad = torch.from_numpy(A.T.copy() if at else A).to(DEV).to(torch.bfloat16)
+    Bd = torch.from_numpy(B.T.copy() if bt else B).to(DEV).to(torch.bfloat16)
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    print(f"[case] gemm64 M={M} N={N} K={K} at={at} bt={bt}", flush=True)
+    ctx.gemm_bf16(Ad, Bd, C, a_trans=at, b_trans=bt)
+    ctx.sync()
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    bound = K * 2.0 ** -24 * (np.abs(A) @ np.abs(B).T)
+    assert np.all(np.abs(C.cpu().numpy() - A @ B.T) <= bound)
+
+
+# The first layer reads the FP32 batch itself (with and without a row vector): the same forward pass
+# as of the gathered batch, bit for bit, and an index outside the set is reported.
+@pytest.mark.parametrize("n", [1, 65, 300])
+def test_first_layer_reads_the_batch(ctx, n):
+    import paper_1904_00011_amd as P
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    dims = (12, 64, 96, 100)
+    net = SurrogateNet(ctx, dims, si.mlp_init(dims, 3), device=DEV)
+    r = np.random.default_rng(n)
+    x = torch.from_numpy(r.uniform(-1, 1, (400, 12)).astype(np.float32)).to(DEV)
+    t = torch.from_numpy(r.normal(-9, 1, (400, 100)).astype(np.float32)).to(DEV)
+    rows = torch.from_numpy(r.integers(0, 400, n).astype(np.int32)).to(DEV)
+    ref = om.forward(net.master.cpu().numpy(), dims, x[rows.long()].cpu().numpy())
+    y = net.forward(x[rows.long()].contiguous())
+    ctx.sync()
+    ref = ref[0] if isinstance(ref, tuple) else ref
+    assert np.max(np.abs(y.cpu().numpy() - ref)) <= 2e-3 * max(1.0, np.max(np.abs(ref)))  # BF16 flips, as the network test
+    a, b = torch.empty(1, dtype=torch.float64, device=DEV), torch.empty(1, dtype=torch.float64, device=DEV)
+    net.loss(x, t, a, rows=rows)
+    net.loss(x[rows.long()].contiguous(), t[rows.long()].contiguous(), b)
+    ctx.sync()
+    assert a.item() == b.item()
+    rows[-1] = 400
+    net.loss(x, t, a, rows=rows)
+    with pytest.raises(P.PcmdError):
+        ctx.sync()
