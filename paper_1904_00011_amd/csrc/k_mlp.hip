@@ -734,34 +734,66 @@ hipError_t launch_colsum(const void *dz, int n, int m, float *db, hipStream_t s)
   return hipGetLastError();
 }
 
-// Adam on one layer's FP32 master weights [out][in] and biases, refreshing the BF16 copies
-// W [out][in] and W^T [in][out].  With update == 0 only the BF16 copies are refreshed.
-__global__ void __launch_bounds__(256) k_adam_layer(AdamArgs a) {
-  const int64_t nw = (int64_t)a.n_out * a.n_in;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nw + a.n_out) return;
-  float w = a.master[i];
-  if (a.update) {
-    const float g = a.grad[i];
-    const float m = a.beta1 * a.m[i] + (1.0f - a.beta1) * g;
-    const float v = a.beta2 * a.v[i] + (1.0f - a.beta2) * g * g;
-    a.m[i] = m;
-    a.v[i] = v;
-    const float mh = m / a.bc1, vh = v / a.bc2;
-    w = w - a.lr * mh / (sqrtf(vh) + a.eps);
-    a.master[i] = w;
+// Adam on the FP32 master weights [out][in] and biases of every layer in one launch, refreshing the
+// BF16 copies W [out][in] and W^T [in][out].  Without an update only the copies are refreshed.  A
+// block takes a 64 x 64 tile of one layer's weights (tiles of layer l are blocks first[l] .. first[l + 1]
+// - 1; the tile's rows' biases go with the first tile of a row), a row of a wave at a time, and writes
+// W^T's rows from an LDS copy of the tile: a column-strided 2-byte store per weight had cost the
+// update half its time.  Bound by the 32 bytes per weight (moments, master, gradient, copies).
+// 5.4 million weights: 67 us in five launches -> 41 us (4.2 TB/s of a copy's 4.7).
+constexpr int AT = 64;
+
+__global__ void __launch_bounds__(256) k_adam(AdamArgs a) {
+  __shared__ __bf16 tile[AT][AT + 2];
+  int l = 0;
+  while (l + 1 < a.n_layers && (int)blockIdx.x >= a.first[l + 1]) ++l;
+  const int n_in = a.dims[l], n_out = a.dims[l + 1];
+  const int tiles_in = (n_in + AT - 1) / AT;
+  const int q = (int)blockIdx.x - a.first[l];
+  const int o0 = (q / tiles_in) * AT, i0 = (q % tiles_in) * AT;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t base = a.off[l];
+  auto step = [&](int64_t i) {
+    float x = a.master[i];
+    if (a.update) {
+      const float g = a.grad[i];
+      const float m = a.beta1 * a.m[i] + (1.0f - a.beta1) * g;
+      const float v = a.beta2 * a.v[i] + (1.0f - a.beta2) * g * g;
+      a.m[i] = m;
+      a.v[i] = v;
+      const float mh = m / a.bc1, vh = v / a.bc2;
+      x = x - a.lr * mh / (sqrtf(vh) + a.eps);
+      a.master[i] = x;
+    }
+    return (__bf16)x;
+  };
+#pragma unroll 4
+  for (int r = w; r < AT; r += 4) {
+    const int o = o0 + r, i = i0 + lane;
+    if (o >= n_out || i >= n_in) continue;
+    const __bf16 wb = step(base + (int64_t)o * n_in + i);
+    ((__bf16 *)a.w_bf16)[a.woff[l] + (int64_t)o * n_in + i] = wb;
+    tile[r][lane] = wb;
   }
-  if (i < nw) {
-    const int o = (int)(i / a.n_in), k = (int)(i - (int64_t)o * a.n_in);
-    const __bf16 wb = (__bf16)w;
-    ((__bf16 *)a.w_bf16)[i] = wb;
-    ((__bf16 *)a.wt_bf16)[(size_t)k * a.n_out + o] = wb;
+  if (i0 == 0 && threadIdx.x < AT && o0 + (int)threadIdx.x < n_out)
+    (void)step(base + (int64_t)n_out * n_in + o0 + threadIdx.x);
+  __syncthreads();
+  for (int r = w; r < AT; r += 4) {
+    const int i = i0 + r, o = o0 + lane;
+    if (i < n_in && o < n_out) ((__bf16 *)a.wt_bf16)[a.woff[l] + (int64_t)i * n_out + o] = tile[lane][r];
   }
 }
 
-hipError_t launch_adam_layer(const AdamArgs &a, hipStream_t s) {
-  const int64_t n = (int64_t)a.n_out * a.n_in + a.n_out;
-  hipLaunchKernelGGL(k_adam_layer, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+hipError_t launch_adam(AdamArgs a, hipStream_t s) {
+  if (a.n_layers < 1 || a.n_layers > PCMD_MLP_MAX_LAYERS) return hipErrorInvalidValue;
+  int64_t blocks = 0;
+  for (int l = 0; l < a.n_layers; ++l) {
+    a.first[l] = (int)blocks;
+    blocks += (int64_t)((a.dims[l] + AT - 1) / AT) * ((a.dims[l + 1] + AT - 1) / AT);
+    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  }
+  a.first[a.n_layers] = (int)blocks;
+  hipLaunchKernelGGL(k_adam, dim3((unsigned)blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -193,31 +193,30 @@ hipError_t backward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, in
   return e;
 }
 
-// One Adam step (beta1 0.9, beta2 0.999, eps 1e-8, bias-corrected for step `step`) per layer,
-// refreshing the BF16 copies of W and W^T.
+// One Adam step (beta1 0.9, beta2 0.999, eps 1e-8, bias-corrected for step `step`) of every layer,
+// refreshing the BF16 copies of W and W^T; without a gradient only the copies.
 hipError_t adam_impl(const pcmd_mlp *net, const Layout &lay, const float *grad, float lr, int step, hipStream_t s) {
-  const double bc1 = 1.0 - pow(0.9, (double)step), bc2 = 1.0 - pow(0.999, (double)step);
-  hipError_t e = hipSuccess;
-  for (int l = 0; l < lay.L && e == hipSuccess; ++l) {
-    AdamArgs a{};
-    a.n_out = lay.d[l + 1];
-    a.n_in = lay.d[l];
-    a.update = 1;
-    a.master = net->master + lay.off[l];
-    a.m = net->adam_m + lay.off[l];
-    a.v = net->adam_v + lay.off[l];
-    a.grad = grad + lay.off[l];
-    a.w_bf16 = net->w_bf16 + lay.woff[l];
-    a.wt_bf16 = net->wt_bf16 + lay.woff[l];
-    a.lr = lr;
-    a.beta1 = 0.9f;
-    a.beta2 = 0.999f;
-    a.eps = 1e-8f;
-    a.bc1 = (float)bc1;
-    a.bc2 = (float)bc2;
-    e = launch_adam_layer(a, s);
+  AdamArgs a{};
+  a.n_layers = lay.L;
+  a.update = grad ? 1 : 0;
+  for (int l = 0; l <= lay.L; ++l) a.dims[l] = lay.d[l];
+  for (int l = 0; l < lay.L; ++l) {
+    a.off[l] = lay.off[l];
+    a.woff[l] = lay.woff[l];
   }
-  return e;
+  a.master = net->master;
+  a.m = net->adam_m;
+  a.v = net->adam_v;
+  a.grad = grad;
+  a.w_bf16 = net->w_bf16;
+  a.wt_bf16 = net->wt_bf16;
+  a.lr = lr;
+  a.beta1 = 0.9f;
+  a.beta2 = 0.999f;
+  a.eps = 1e-8f;
+  a.bc1 = (float)(1.0 - pow(0.9, (double)step));
+  a.bc2 = (float)(1.0 - pow(0.999, (double)step));
+  return launch_adam(a, s);
 }
 
 }  // namespace
@@ -240,17 +239,8 @@ int pcmd_mlp_refresh(pcmd_ctx *c, const pcmd_mlp *net, pcmd_stream stream) {
   int r = check_net(c, net, lay, "pcmd_mlp_refresh");
   if (r) return r;
   DeviceGuard dg(c->device);
-  for (int l = 0; l < lay.L; ++l) {
-    AdamArgs a{};
-    a.n_out = lay.d[l + 1];
-    a.n_in = lay.d[l];
-    a.update = 0;
-    a.master = net->master + lay.off[l];
-    a.w_bf16 = net->w_bf16 + lay.woff[l];
-    a.wt_bf16 = net->wt_bf16 + lay.woff[l];
-    hipError_t e = launch_adam_layer(a, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(c, e, "pcmd_mlp_refresh");
-  }
+  hipError_t e = adam_impl(net, lay, nullptr, 0.0f, 1, (hipStream_t)stream);
+  if (e != hipSuccess) return hip_fail(c, e, "pcmd_mlp_refresh");
   c->err.clear();
   return PCMD_OK;
 }

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "../../include/pcmd.h"
+
 namespace pcmd {
 
 enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3 };
@@ -34,8 +36,13 @@ struct GemmArgs {
   uint32_t *status;
 };
 
+// Every layer's parameters, packed as in pcmd_mlp (off: W_l in master, adam_m, adam_v and grad, b_l
+// after it; woff: in the BF16 copies).
 struct AdamArgs {
-  int n_out, n_in, update;
+  int n_layers, update;
+  int dims[PCMD_MLP_MAX_LAYERS + 1];
+  int first[PCMD_MLP_MAX_LAYERS + 1];  // set by launch_adam
+  int64_t off[PCMD_MLP_MAX_LAYERS], woff[PCMD_MLP_MAX_LAYERS];
   float *master, *m, *v;
   const float *grad;
   void *w_bf16, *wt_bf16;
@@ -63,7 +70,7 @@ hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, dou
 // out[r][j] = ln((h[r][j] + 1/2) / (N_r + nbins / 2)) for n rows of nbins counts.
 hipError_t launch_log_hess_target(const uint32_t *h, int n, int nbins, float *out, hipStream_t s);
 hipError_t launch_colsum(const void *dz, int n, int m, float *db, hipStream_t s);
-hipError_t launch_adam_layer(const AdamArgs &a, hipStream_t s);
+hipError_t launch_adam(AdamArgs a, hipStream_t s);
 // lnfact64[k] = ln k! for k < nlf (lgamma beyond, or everywhere when lnfact64 is NULL)
 hipError_t launch_surrogate_loglike(const float *y, int n, int nbins, const uint32_t *d, double *out,
                                    const double *lnfact64, int nlf, hipStream_t s);

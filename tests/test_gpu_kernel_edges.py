@@ -154,3 +154,29 @@ def test_first_layer_reads_the_batch(ctx, n):
     net.loss(x, t, a, rows=rows)
     with pytest.raises(P.PcmdError):
         ctx.sync()
+
+
+# One Adam launch over layers whose sides are no multiples of the 64 x 64 tile: master weights against
+# the update rule (one step from zero moments moves a weight by at most lr; FP32 steps), the BF16 copies
+# and the transposed ones exactly the rounded master.
+@pytest.mark.parametrize("dims", [(1, 1), (12, 64, 65, 130), (3, 200, 1, 63)])
+def test_adam_ragged_layers(ctx, dims):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    net = SurrogateNet(ctx, dims, si.mlp_init(dims, 1), device=DEV)
+    before = net.master.cpu().numpy().astype(np.float64)
+    r = np.random.default_rng(sum(dims))
+    g = r.normal(size=net.n_params).astype(np.float32)
+    ctx.mlp_adam(net.struct, torch.from_numpy(g).to(DEV), 1e-2, 1)
+    ctx.sync()
+    one, b1, b2 = np.float32(1.0), np.float32(0.9), np.float32(0.999)  # the rule's constants are FP32
+    mh = float(one - b1) * g / float(np.float32(1.0 - 0.9))
+    vh = float(one - b2) * g.astype(np.float64) ** 2 / float(np.float32(1.0 - 0.999))
+    want = before - float(np.float32(1e-2)) * mh / (np.sqrt(vh) + float(np.float32(1e-8)))
+    got = net.master.cpu().numpy()
+    assert np.all(np.abs(got - want) <= 1e-2 * 8 * 2.0 ** -24 + 2.0 ** -24 * np.abs(want))
+    o = ow = 0
+    for a, b in zip(dims[:-1], dims[1:]):
+        w = net.master[o:o + a * b].view(b, a).to(torch.bfloat16)
+        assert torch.equal(net.w[ow:ow + a * b].view(b, a), w)
+        assert torch.equal(net.wt[ow:ow + a * b].view(a, b), w.t())
+        o, ow = o + a * b + b, ow + a * b
