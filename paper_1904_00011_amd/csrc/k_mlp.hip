@@ -85,6 +85,19 @@ __global__ void __launch_bounds__(256) k_transpose_bf16(const __bf16 *__restrict
   }
 }
 
+// Row index of batch sample k: rows[k] when a row vector is given (one outside [0, n_total) is
+// taken as row 0 and flagged in *status), else k.
+__device__ __forceinline__ int64_t batch_row(const int32_t *__restrict__ rows, int64_t k, int64_t n_total,
+                                             uint32_t *status) {
+  if (!rows) return k;
+  const int32_t r = rows[k];
+  if (r < 0 || (int64_t)r >= n_total) {
+    atomicOr(status, STATUS_BAD_ROW);
+    return 0;
+  }
+  return r;
+}
+
 template <int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int row, int col, float v) {
   if (EPI == EPI_STORE) {
@@ -93,7 +106,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int row, int co
     g.C[(size_t)row * g.ldc + col] = v + g.bias[col];
   } else if (EPI == EPI_BIAS_GELU) {
     v += g.bias[col];
-    g.C[(size_t)row * g.ldc + col] = v;
+    if (g.C) g.C[(size_t)row * g.ldc + col] = v;
     g.Cb[(size_t)row * g.ldcb + col] = (__bf16)gelu_f(v);
   } else {  // EPI_GELU_GRAD: dz_prev = bf16(dx * GELU'(z_prev))
     g.Cb[(size_t)row * g.ldcb + col] = (__bf16)(v * gelu_grad_f(g.Z[(size_t)row * g.ldz + col]));
@@ -112,7 +125,7 @@ __device__ __forceinline__ void gemm_epilogue4(const GemmArgs &g, int row, int c
     v.y += b.y;
     v.z += b.z;
     v.w += b.w;
-    *reinterpret_cast<float4 *>(c) = v;
+    if (EPI != EPI_BIAS_GELU || g.C) *reinterpret_cast<float4 *>(c) = v;
     if (EPI == EPI_BIAS_GELU) {
       bf16x4 o;
       o[0] = (__bf16)gelu_f(v.x);
@@ -122,6 +135,35 @@ __device__ __forceinline__ void gemm_epilogue4(const GemmArgs &g, int row, int c
       *reinterpret_cast<bf16x4 *>(g.Cb + (size_t)row * g.ldcb + col) = o;
     }
   }
+}
+
+// EPI_BIAS_MSE: the prediction y = v + bias is compared with the targets at once and never stored: dy
+// = 2 (y - t) scale in BF16 (unless Cb is NULL); returns (y - t)^2 in FP64.
+__device__ __forceinline__ double mse_epilogue(const GemmArgs &g, int row, int col, float v) {
+  const float d = (v + g.bias[col]) - g.T[(size_t)batch_row(g.rows, row, g.n_total, g.status) * g.N + col];
+  if (g.Cb) g.Cb[(size_t)row * g.ldcb + col] = (__bf16)(g.gscale * d);
+  return (double)d * (double)d;
+}
+__device__ __forceinline__ double mse_epilogue4(const GemmArgs &g, int row, int col, float4 v) {
+  const float4 b = *reinterpret_cast<const float4 *>(g.bias + col);
+  const float4 t = *reinterpret_cast<const float4 *>(g.T + (size_t)batch_row(g.rows, row, g.n_total, g.status) * g.N + col);
+  const float d0 = (v.x + b.x) - t.x, d1 = (v.y + b.y) - t.y, d2 = (v.z + b.z) - t.z, d3 = (v.w + b.w) - t.w;
+  if (g.Cb) {
+    bf16x4 o;
+    o[0] = (__bf16)(g.gscale * d0);
+    o[1] = (__bf16)(g.gscale * d1);
+    o[2] = (__bf16)(g.gscale * d2);
+    o[3] = (__bf16)(g.gscale * d3);
+    *reinterpret_cast<bf16x4 *>(g.Cb + (size_t)row * g.ldcb + col) = o;
+  }
+  return ((double)d0 * (double)d0 + (double)d1 * (double)d1) + ((double)d2 * (double)d2 + (double)d3 * (double)d3);
+}
+// A wave's sum of squared errors to its slot of lpart (block-major, LOSS_WAVES slots per block).
+constexpr int LOSS_WAVES = 4;
+__device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int wave) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+  if ((threadIdx.x & 63u) == 0u) g.lpart[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * LOSS_WAVES + wave] = s;
 }
 
 constexpr int GEPI_LD = 72;  // epilogue slab row stride (floats): 32 x 72 x 4 B per wave
@@ -193,9 +235,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
   // in different banks), then reads them back four consecutive columns per lane and writes 16
   // bytes per lane (C) or 8 bytes (BF16 outputs).
   float *slab = reinterpret_cast<float *>(smem) + wave * (32 * GEPI_LD);
-  const bool v4 = EPI != EPI_GELU_GRAD && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0 &&
-                  (EPI == EPI_STORE || ((uintptr_t)g.bias & 15) == 0) &&
-                  (EPI != EPI_BIAS_GELU || (g.ldcb % 4 == 0 && ((uintptr_t)g.Cb & 7) == 0));
+  const bool v4 = EPI == EPI_BIAS_MSE
+                      ? g.N % 4 == 0 && g.ldcb % 4 == 0 && ((((uintptr_t)g.bias) | ((uintptr_t)g.T)) & 15) == 0 &&
+                            ((uintptr_t)g.Cb & 7) == 0
+                      : EPI != EPI_GELU_GRAD && g.ldc % 4 == 0 && ((uintptr_t)g.C & 15) == 0 &&
+                            (EPI == EPI_STORE || ((uintptr_t)g.bias & 15) == 0) &&
+                            (EPI != EPI_BIAS_GELU || (g.ldcb % 4 == 0 && ((uintptr_t)g.Cb & 7) == 0));
+  double loss = 0.0;
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
@@ -215,12 +261,18 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
       if (row >= g.M) continue;
       const float4 v = *reinterpret_cast<const float4 *>(&slab[rr * GEPI_LD + c4]);
       if (v4 && col + 4 <= g.N) {
-        gemm_epilogue4<EPI>(g, row, col, v);
+        if constexpr (EPI == EPI_BIAS_MSE)
+          loss += mse_epilogue4(g, row, col, v);
+        else
+          gemm_epilogue4<EPI>(g, row, col, v);
       } else {
         const float vv[4] = {v.x, v.y, v.z, v.w};
         for (int q = 0; q < 4; ++q) {
           if (col + q >= g.N) break;
-          gemm_epilogue<EPI>(g, row, col + q, vv[q]);
+          if constexpr (EPI == EPI_BIAS_MSE)
+            loss += mse_epilogue(g, row, col + q, vv[q]);
+          else
+            gemm_epilogue<EPI>(g, row, col + q, vv[q]);
         }
       }
     }
@@ -228,6 +280,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, wave);
 }
 
 // Sum of the split-K partial products in split order, then the epilogue.
@@ -239,19 +292,6 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs g, int spli
   float v = 0.0f;
   for (int z = 0; z < splits; ++z) v += g.part[(size_t)z * mn + idx];
   gemm_epilogue<EPI>(g, (int)(idx / g.N), (int)(idx % g.N), v);
-}
-
-// Row index of batch sample k: rows[k] when a row vector is given (one outside [0, n_total) is
-// taken as row 0 and flagged in *status), else k.
-__device__ __forceinline__ int64_t batch_row(const int32_t *__restrict__ rows, int64_t k, int64_t n_total,
-                                             uint32_t *status) {
-  if (!rows) return k;
-  const int32_t r = rows[k];
-  if (r < 0 || (int64_t)r >= n_total) {
-    atomicOr(status, STATUS_BAD_ROW);
-    return 0;
-  }
-  return r;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -415,16 +455,21 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
   // accumulator element e: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
   float *part = g.part ? g.part + (size_t)blockIdx.z * g.M * g.N : nullptr;
   const int col = bn + wn + (lane & 31);
-  if (col >= g.N) return;
+  double loss = 0.0;
 #pragma unroll
   for (int e = 0; e < 16; ++e) {
     const int row = bm + wm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-    if (row >= g.M) continue;
-    if (part)
-      part[(size_t)row * g.N + col] = acc[e];
-    else
-      gemm_epilogue<EPI>(g, row, col, acc[e]);
+    if (row >= g.M || col >= g.N) continue;
+    if constexpr (EPI == EPI_BIAS_MSE) {
+      loss += mse_epilogue(g, row, col, acc[e]);
+    } else {
+      if (part)
+        part[(size_t)row * g.N + col] = acc[e];
+      else
+        gemm_epilogue<EPI>(g, row, col, acc[e]);
+    }
   }
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, wave);
 }
 
 // Split over K when the output tile grid cannot fill the chip and K is long enough: about two
@@ -439,6 +484,8 @@ static int gemm_splits(int M, int N, int K, int &kchunk) {
   return (K + kchunk - 1) / kchunk;
 }
 
+// 256-row block tiles where the product is large enough to keep every CU busy with them.
+static bool gemm_tall(int M, int N) { return M >= 4096 && N >= 2048; }
 // Whether a product takes 64 x 64 tiles: its 128 x 128 tiles would not give every CU two blocks.
 static bool gemm_use64(int M, int N) { return (int64_t)((M + GBM - 1) / GBM) * ((N + GBN - 1) / GBN) < 512; }
 
@@ -479,7 +526,9 @@ static hipError_t launch_gemm64_t(GemmArgs g, int splits, void *ws, hipStream_t 
     hipLaunchKernelGGL((k_gemm64<EPI, 2, TA, TB, AF32>), grid, dim3(512), 2 * lds, s, g);
   else
     hipLaunchKernelGGL((k_gemm64<EPI, 1, TA, TB, AF32>), grid, dim3(256), lds, s, g);
-  if (!inside) {
+  if constexpr (EPI == EPI_BIAS_MSE) {
+    if (!inside) return hipErrorInvalidValue;  // gemm_loss_parts() == 0
+  } else if (!inside) {
     const unsigned rblocks = (unsigned)(((int64_t)g.M * g.N + 255) / 256);
     hipLaunchKernelGGL((k_gemm_splitk_reduce<EPI>), dim3(rblocks), dim3(256), 0, s, g, splits);
   }
@@ -503,7 +552,16 @@ static hipError_t launch_gemm64(const GemmArgs &g, int splits, bool at, bool bt,
   if (epi == EPI_BIAS) return launch_gemm64_t<EPI_BIAS, false, false, false>(g, splits, ws, s);
   if (epi == EPI_BIAS_GELU) return launch_gemm64_t<EPI_BIAS_GELU, false, false, false>(g, splits, ws, s);
   if (epi == EPI_GELU_GRAD) return launch_gemm64_t<EPI_GELU_GRAD, false, false, false>(g, splits, ws, s);
+  if (epi == EPI_BIAS_MSE) return launch_gemm64_t<EPI_BIAS_MSE, false, false, false>(g, splits, ws, s);
   return hipErrorInvalidValue;
+}
+
+int64_t gemm_loss_parts(int M, int N, int K) {
+  int kchunk;
+  if (gemm_use64(M, N))
+    return gemm_splits(M, N, K, kchunk) > G64_SPLITS ? 0 : (int64_t)((M + HB - 1) / HB) * ((N + HB - 1) / HB) * LOSS_WAVES;
+  const int bm = gemm_tall(M, N) ? 2 * GBM : GBM;
+  return (int64_t)((M + bm - 1) / bm) * ((N + GBN - 1) / GBN) * LOSS_WAVES;
 }
 
 bool gemm_reads_f32(int M, int N) { return gemm_use64(M, N); }
@@ -537,8 +595,7 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
   }
   // 512 blocks or more are never split (gemm_splits splits below 128)
   g.part = nullptr;
-  // 256-row block tiles where the product is large enough to keep every CU busy with them
-  const bool tall = g.M >= 4096 && g.N >= 2048;
+  const bool tall = gemm_tall(g.M, g.N);
   dim3 grid((g.N + GBN - 1) / GBN, (g.M + (tall ? 2 * GBM : GBM) - 1) / (tall ? 2 * GBM : GBM));
 #define PCMD_GEMM_CASE(E_)                                                                             \
   if (epi == E_) {                                                                                     \
@@ -552,6 +609,7 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
   PCMD_GEMM_CASE(EPI_BIAS)
   PCMD_GEMM_CASE(EPI_BIAS_GELU)
   PCMD_GEMM_CASE(EPI_GELU_GRAD)
+  PCMD_GEMM_CASE(EPI_BIAS_MSE)
 #undef PCMD_GEMM_CASE
   return hipErrorInvalidValue;
 }
@@ -659,47 +717,37 @@ __global__ void __launch_bounds__(256) k_mse_grad(const float *__restrict__ y, c
   if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// Loss = scale x the sum of the MSE_BLOCKS partials, by a fixed tree over one block.
-__global__ void __launch_bounds__(256) k_loss_final(const double *__restrict__ part, int nb, double scale,
-                                                    float *__restrict__ out) {
-  __shared__ double red[256];
-  red[threadIdx.x] = threadIdx.x < (unsigned)nb ? part[threadIdx.x] : 0.0;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < (unsigned)k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = (float)(red[0] * scale);
-}
-
 hipError_t launch_mse_grad(const float *y, const float *t, int64_t n, int M, const int32_t *rows, int64_t n_total,
-                           double scale, void *dy, double *part, float *loss_out, uint32_t *status, hipStream_t s) {
+                           double scale, void *dy, double *part, uint32_t *status, hipStream_t s) {
   hipLaunchKernelGGL(k_mse_grad, dim3(MSE_BLOCKS), dim3(256), 0, s, y, t, n, M, rows, n_total, scale, (__bf16 *)dy,
                      part, status);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !loss_out) return e;
-  hipLaunchKernelGGL(k_loss_final, dim3(1), dim3(256), 0, s, part, MSE_BLOCKS, scale, loss_out);
   return hipGetLastError();
 }
 
 // out = scale x the sum of nb partials: thread t sums partials t, t + 256, ... in order, then a
 // fixed tree over the block (the order depends on nb alone).
+template <typename T>
 __global__ void __launch_bounds__(256) k_sum_partials(const double *__restrict__ part, int64_t nb, double scale,
-                                                      double *__restrict__ out) {
+                                                      T *__restrict__ out) {
   __shared__ double red[256];
   double s = 0.0;
+#pragma unroll 8
   for (int64_t i = threadIdx.x; i < nb; i += 256) s += part[i];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < (unsigned)k) red[threadIdx.x] += red[threadIdx.x + k];
+    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] = red[0] * scale;
+  if (threadIdx.x == 0) out[0] = (T)(red[0] * scale);
 }
 
 hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, double *out, hipStream_t s) {
-  hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(256), 0, s, part, nb, scale, out);
+  hipLaunchKernelGGL(k_sum_partials<double>, dim3(1), dim3(256), 0, s, part, nb, scale, out);
+  return hipGetLastError();
+}
+hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, float *out, hipStream_t s) {
+  hipLaunchKernelGGL(k_sum_partials<float>, dim3(1), dim3(256), 0, s, part, nb, scale, out);
   return hipGetLastError();
 }
 

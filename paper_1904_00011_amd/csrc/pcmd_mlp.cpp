@@ -52,10 +52,31 @@ int check_net(pcmd_ctx *c, const pcmd_mlp *net, Layout &lay, const char *who) {
   return PCMD_OK;
 }
 
-// forward through all layers; activations kept in the context for a following backward pass.
-// Sample k of the batch reads input row rows[k] of x (row k when rows is NULL).
+// The squared error of a forward pass against target rows: sums to part (n_part of them, the number
+// loss_parts gives) and, unless dz is NULL, the output gradient.
+struct LossArgs {
+  const float *t;
+  double scale;  // 1 / (samples x outputs), for the gradient
+  __bf16 *dz;
+  double *part;
+};
+
+// Partial sums that the squared error of a batch of n takes: the last product's own, or k_mse_grad's
+// where that product cannot form them.
+int64_t loss_parts(const Layout &lay, int n, bool *fused) {
+  const int64_t p = gemm_loss_parts(n, lay.d[lay.L], lay.d[lay.L - 1]);
+  *fused = p > 0 && !(lay.L == 1 && gemm_reads_f32(n, lay.d[1]));
+  return *fused ? p : MSE_BLOCKS;
+}
+
+// forward through all layers; with `keep` the activations and hidden pre-activations stay in the
+// context for a following backward pass.  Sample k of the batch reads input row rows[k] of x (row k
+// when rows is NULL).  The prediction goes to y_out, or is compared with loss->t.
 hipError_t forward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, int n, const float *x,
-                        const int32_t *rows, int64_t n_total, float *y_out, hipStream_t s) {
+                        const int32_t *rows, int64_t n_total, float *y_out, const LossArgs *loss, bool keep,
+                        hipStream_t s) {
+  bool fused = false;
+  if (loss) (void)loss_parts(lay, n, &fused);
   __bf16 *act = (__bf16 *)c->mlp_act.p;
   float *pre = (float *)c->mlp_pre.p;
   const __bf16 *w = (const __bf16 *)net->w_bf16;
@@ -87,15 +108,31 @@ hipError_t forward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, int
     g.bias = net->master + lay.off[l] + (int64_t)dout * din;
     g.ldc = dout;
     const bool last = l == lay.L - 1;
-    g.C = (last && y_out) ? y_out : pre + poff;
+    if (last)
+      g.C = y_out ? y_out : pre + poff;
+    else if (keep)
+      g.C = pre + poff;
     if (!last) {
       g.Cb = act + aoff + (int64_t)n * din;
+      g.ldcb = dout;
+    } else if (fused) {
+      g.T = loss->t;
+      g.rows = rows;
+      g.n_total = n_total;
+      g.status = c->status;
+      g.gscale = (float)(2.0 * loss->scale);
+      g.lpart = loss->part;
+      g.Cb = loss->dz;
       g.ldcb = dout;
     }
     {
       ScopedTimer tm(c, PCMD_TIMER_GEMM, 2.0 * (double)n * (double)din * (double)dout, s);
-      e = launch_gemm(g, false, false, last ? EPI_BIAS : EPI_BIAS_GELU, c->mlp_ws.p, c->mlp_ws.n, s);
+      e = launch_gemm(g, false, false, !last ? EPI_BIAS_GELU : fused ? EPI_BIAS_MSE : EPI_BIAS, c->mlp_ws.p, c->mlp_ws.n,
+                      s);
     }
+    if (e == hipSuccess && last && loss && !fused)
+      e = launch_mse_grad(pre + poff, loss->t, (int64_t)n * dout, dout, rows, n_total, loss->scale, loss->dz, loss->part,
+                          c->status, s);
     aoff += (int64_t)n * din;
     poff += (int64_t)n * dout;
   }
@@ -114,7 +151,8 @@ int ensure_mlp_scratch(pcmd_ctx *c, const Layout &lay, int n) {
   if ((r = ensure(c, c->mlp_dza, (size_t)n * lay.dmax * 2, "network gradients"))) return r;
   if ((r = ensure(c, c->mlp_dzb, (size_t)n * lay.dmax * 2, "network gradients"))) return r;
   if ((r = ensure(c, c->mlp_grad, (size_t)lay.params * 4, "parameter gradients"))) return r;
-  if ((r = ensure(c, c->mlp_part, 256 * 8, "loss partials"))) return r;
+  bool fused;
+  if ((r = ensure(c, c->mlp_part, (size_t)loss_parts(lay, n, &fused) * 8, "loss partials"))) return r;
   // GEMM workspace: the largest over the forward, weight-gradient and input-gradient products
   size_t ws = 0;
   for (int l = 0; l < lay.L; ++l) {
@@ -131,7 +169,14 @@ int ensure_mlp_scratch(pcmd_ctx *c, const Layout &lay, int n) {
 // master parameters).  Targets of sample k are row rows[k] of t (row k when rows is NULL).
 hipError_t backward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, int n, const float *x, const float *t,
                          const int32_t *rows, int64_t n_total, float *loss_out, float *grad, hipStream_t s) {
-  hipError_t e = forward_impl(c, net, lay, n, x, rows, n_total, nullptr, s);
+  __bf16 *dz = (__bf16 *)c->mlp_dza.p, *dz2 = (__bf16 *)c->mlp_dzb.p;
+  const int dL = lay.d[lay.L];
+  const double scale = 1.0 / ((double)n * (double)dL);
+  const LossArgs loss{t, scale, dz, (double *)c->mlp_part.p};
+  hipError_t e = forward_impl(c, net, lay, n, x, rows, n_total, nullptr, &loss, true, s);
+  bool fused;
+  const int64_t n_part = loss_parts(lay, n, &fused);
+  if (e == hipSuccess && loss_out) e = launch_sum_partials(loss.part, n_part, scale, loss_out, s);
   std::vector<int64_t> aoffs(lay.L), poffs(lay.L);
   {
     int64_t ao = 0, po = 0;
@@ -144,13 +189,6 @@ hipError_t backward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, in
   }
   __bf16 *act = (__bf16 *)c->mlp_act.p;
   float *pre = (float *)c->mlp_pre.p;
-  __bf16 *dz = (__bf16 *)c->mlp_dza.p, *dz2 = (__bf16 *)c->mlp_dzb.p;
-  const int dL = lay.d[lay.L];
-  const double scale = 1.0 / ((double)n * (double)dL);
-  // output layer pre-activations are the prediction
-  if (e == hipSuccess)
-    e = launch_mse_grad(pre + poffs[lay.L - 1], t, (int64_t)n * dL, dL, rows, n_total, scale, dz,
-                        (double *)c->mlp_part.p, loss_out, c->status, s);
   for (int l = lay.L - 1; l >= 0 && e == hipSuccess; --l) {
     const int din = lay.d[l], dout = lay.d[l + 1];
     GemmArgs gw{};
@@ -253,7 +291,7 @@ int pcmd_mlp_forward(pcmd_ctx *c, const pcmd_mlp *net, int32_t n, const float *x
   if (n < 1 || !x || !y) return fail(c, PCMD_E_INVAL, "pcmd_mlp_forward: bad batch or null pointer");
   DeviceGuard dg(c->device);
   if ((r = ensure_mlp_scratch(c, lay, n))) return r;
-  hipError_t e = forward_impl(c, net, lay, n, x, nullptr, n, y, (hipStream_t)stream);
+  hipError_t e = forward_impl(c, net, lay, n, x, nullptr, n, y, nullptr, false, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(c, e, "pcmd_mlp_forward");
   c->err.clear();
   return PCMD_OK;
@@ -321,28 +359,25 @@ int pcmd_mlp_loss(pcmd_ctx *c, const pcmd_mlp *net, int32_t n, const float *x, c
   const int n_chunks = (n + chunk - 1) / chunk;
   DeviceGuard dg(c->device);
   if ((r = ensure_mlp_scratch(c, lay, chunk))) return r;
-  if ((r = ensure(c, c->mlp_lpart, (size_t)n_chunks * MSE_BLOCKS * 8, "loss partials"))) return r;
+  // chunk q's partial sums follow those of the chunks before it (the last chunk may be shorter)
+  bool fused;
+  const int64_t full = loss_parts(lay, chunk, &fused), tail = loss_parts(lay, n - (n_chunks - 1) * chunk, &fused);
+  const int64_t n_part = (int64_t)(n_chunks - 1) * full + tail;
+  if ((r = ensure(c, c->mlp_lpart, (size_t)n_part * 8, "loss partials"))) return r;
   hipStream_t s = (hipStream_t)stream;
   const int dL = lay.d[lay.L];
-  float *pre = (float *)c->mlp_pre.p;
   hipError_t e = hipSuccess;
   for (int q = 0; q < n_chunks && e == hipSuccess; ++q) {
     const int k0 = q * chunk, m = std::min(chunk, n - k0);
-    // the output layer's pre-activations follow those of the hidden layers, m rows each
-    int64_t poff_last = 0;
-    for (int l = 0; l < lay.L - 1; ++l) poff_last += (int64_t)m * lay.d[l + 1];
     // without a row vector, chunk q is rows k0 .. k0 + m - 1 of x and t
     const float *xq = rows ? x : x + (int64_t)k0 * lay.d[0];
     const float *tq = rows ? t : t + (int64_t)k0 * dL;
     const int32_t *rq = rows ? rows + k0 : nullptr;
-    e = forward_impl(c, net, lay, m, xq, rq, n_total, nullptr, s);
-    if (e == hipSuccess)
-      e = launch_mse_grad(pre + poff_last, tq, (int64_t)m * dL, dL, rq, n_total, 1.0, nullptr,
-                          (double *)c->mlp_lpart.p + (int64_t)q * MSE_BLOCKS, nullptr, c->status, s);
+    const LossArgs loss{tq, 1.0, nullptr, (double *)c->mlp_lpart.p + (int64_t)q * full};
+    e = forward_impl(c, net, lay, m, xq, rq, n_total, nullptr, &loss, false, s);
   }
   if (e == hipSuccess)
-    e = launch_sum_partials((const double *)c->mlp_lpart.p, (int64_t)n_chunks * MSE_BLOCKS,
-                            1.0 / ((double)n * (double)dL), mse_out, s);
+    e = launch_sum_partials((const double *)c->mlp_lpart.p, n_part, 1.0 / ((double)n * (double)dL), mse_out, s);
   if (e != hipSuccess) return hip_fail(c, e, "pcmd_mlp_loss");
   c->err.clear();
   return PCMD_OK;

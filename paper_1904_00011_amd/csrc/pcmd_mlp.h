@@ -8,7 +8,7 @@
 
 namespace pcmd {
 
-enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3 };
+enum { EPI_STORE = 0, EPI_BIAS = 1, EPI_BIAS_GELU = 2, EPI_GELU_GRAD = 3, EPI_BIAS_MSE = 4 };
 
 // C[M][N] = sum_k A(m, k) B(n, k) with the operand layouts of k_gemm and a fused epilogue.
 struct GemmArgs {
@@ -17,7 +17,7 @@ struct GemmArgs {
   int lda;
   const __bf16 *B;
   int ldb;
-  float *C;           // FP32 output (EPI_STORE, EPI_BIAS, EPI_BIAS_GELU)
+  float *C;           // FP32 output (EPI_STORE, EPI_BIAS; EPI_BIAS_GELU unless NULL)
   int ldc;
   __bf16 *Cb;         // BF16 output (EPI_BIAS_GELU: GELU(z); EPI_GELU_GRAD: dz_prev)
   int ldcb;
@@ -34,6 +34,12 @@ struct GemmArgs {
   int64_t n_total;
   __bf16 *Aout;
   uint32_t *status;
+  // EPI_BIAS_MSE: y = product + bias is compared with the target rows (by the row vector, as A32's) of
+  // T [n_total][N]: 2 (y - T) scale = gscale (y - T) in BF16 to Cb (unless NULL) and the squared errors'
+  // sums to lpart[gemm_loss_parts(M, N, K)]; y itself is not stored
+  const float *T;
+  float gscale;
+  double *lpart;
 };
 
 // Every layer's parameters, packed as in pcmd_mlp (off: W_l in master, adam_m, adam_v and grad, b_l
@@ -51,6 +57,8 @@ struct AdamArgs {
 
 // Workspace (bytes) launch_gemm needs for an M x N x K product: transposed copies of K-major
 // operands (at: A(m, k) = A[k][m]; bt: B(n, k) = B[k][n]) and split-K partials.
+// Partial sums that an EPI_BIAS_MSE product writes (0: this shape cannot take that epilogue).
+int64_t gemm_loss_parts(int M, int N, int K);
 bool gemm_reads_f32(int M, int N);
 size_t gemm_workspace_bytes(int M, int N, int K, bool at, bool bt);
 hipError_t launch_gemm(const GemmArgs &g, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s);
@@ -60,13 +68,13 @@ hipError_t launch_f32_to_bf16(const float *x, void *y, int64_t n, hipStream_t s)
 hipError_t launch_gather_f32_to_bf16(const float *x, const int32_t *rows, int64_t n_total, int d, int64_t n, void *y,
                                      uint32_t *status, hipStream_t s);
 // Per-block partial sums of the squared error of y [n / M][M] against the target rows (as in the
-// gather), the BF16 gradient 2 (y - t) scale into dy (unless NULL) and, if loss_out is given,
-// scale x the sum.  part holds MSE_BLOCKS doubles.
+// gather) and the BF16 gradient 2 (y - t) scale into dy (unless NULL).  part holds MSE_BLOCKS doubles.
 constexpr int MSE_BLOCKS = 256;
 hipError_t launch_mse_grad(const float *y, const float *t, int64_t n, int M, const int32_t *rows, int64_t n_total,
-                           double scale, void *dy, double *part, float *loss_out, uint32_t *status, hipStream_t s);
+                           double scale, void *dy, double *part, uint32_t *status, hipStream_t s);
 // out[0] = scale x the sum of part[0 .. nb) in an order fixed by nb.
 hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, double *out, hipStream_t s);
+hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, float *out, hipStream_t s);
 // out[r][j] = ln((h[r][j] + 1/2) / (N_r + nbins / 2)) for n rows of nbins counts.
 hipError_t launch_log_hess_target(const uint32_t *h, int n, int nbins, float *out, hipStream_t s);
 hipError_t launch_colsum(const void *dz, int n, int m, float *db, hipStream_t s);
