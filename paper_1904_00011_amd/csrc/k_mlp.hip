@@ -113,6 +113,45 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int row, int co
   }
 }
 
+// Tile (x, y, z) of a product's nx x ny tiles and nz K ranges for block `id`.  Blocks go to the eight
+// XCDs in turn, each with an L2 of its own, so the id's low three bits pick what one XCD keeps to
+// itself: the K ranges when there are at least eight (an XCD then reads its ranges' operands once),
+// else every eighth tile row or column, whichever there are more of (an XCD reads its rows of that
+// operand once and shares the other).  The grid is padded to whole turns; a tile outside is left out.
+struct TileId {
+  int x, y, z;
+  bool inside;
+};
+__host__ __device__ inline unsigned xcd_blocks(int nx, int ny, int nz) {
+  if (nz >= 8) return (unsigned)((nz + 7) / 8 * 8 * nx * ny);
+  return (unsigned)((nx > ny ? (nx + 7) / 8 * 8 * ny : (ny + 7) / 8 * 8 * nx) * nz);
+}
+__device__ __forceinline__ TileId xcd_tile(unsigned id, int nx, int ny, int nz) {
+  const int xcd = (int)(id & 7u);
+  int j = (int)(id >> 3);
+  TileId t;
+  if (nz >= 8) {
+    const int xy = j % (nx * ny);
+    t.z = j / (nx * ny) * 8 + xcd;
+    t.x = xy % nx;
+    t.y = xy / nx;
+  } else {
+    const int per = xcd_blocks(nx, ny, 1) / 8;
+    t.z = j / per;
+    j -= t.z * per;
+    if (nx > ny) {
+      const int nxl = (nx + 7) / 8;
+      t.x = j % nxl * 8 + xcd;
+      t.y = j / nxl;
+    } else {
+      t.x = j % nx;
+      t.y = j / nx * 8 + xcd;
+    }
+  }
+  t.inside = t.x < nx && t.y < ny && t.z < nz;
+  return t;
+}
+
 // The same for four consecutive columns (col a multiple of 4, 16-byte aligned rows).
 template <int EPI>
 __device__ __forceinline__ void gemm_epilogue4(const GemmArgs &g, int row, int col, float4 v) {
@@ -158,12 +197,12 @@ __device__ __forceinline__ double mse_epilogue4(const GemmArgs &g, int row, int 
   }
   return ((double)d0 * (double)d0 + (double)d1 * (double)d1) + ((double)d2 * (double)d2 + (double)d3 * (double)d3);
 }
-// A wave's sum of squared errors to its slot of lpart (block-major, LOSS_WAVES slots per block).
+// A wave's sum of squared errors to its slot of lpart (tile-major, LOSS_WAVES slots per tile).
 constexpr int LOSS_WAVES = 4;
-__device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int wave) {
+__device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int tile, int wave) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
-  if ((threadIdx.x & 63u) == 0u) g.lpart[((size_t)blockIdx.y * gridDim.x + blockIdx.x) * LOSS_WAVES + wave] = s;
+  if ((threadIdx.x & 63u) == 0u) g.lpart[(size_t)tile * LOSS_WAVES + wave] = s;
 }
 
 constexpr int GEPI_LD = 72;  // epilogue slab row stride (floats): 32 x 72 x 4 B per wave
@@ -178,7 +217,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
   __shared__ __attribute__((aligned(16))) __bf16 smem[2 * (BM + GBN) * GLDS];
   __bf16 (*As)[BM * GLDS] = reinterpret_cast<__bf16 (*)[BM * GLDS]>(smem);
   __bf16 (*Bs)[GBN * GLDS] = reinterpret_cast<__bf16 (*)[GBN * GLDS]>(smem + 2 * BM * GLDS);
-  const int bm = blockIdx.y * BM, bn = blockIdx.x * GBN;
+  const int nx = (g.N + GBN - 1) / GBN;
+  const TileId tl = xcd_tile(blockIdx.x, nx, (g.M + BM - 1) / BM, 1);
+  if (!tl.inside) return;
+  const int bm = tl.y * BM, bn = tl.x * GBN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int wm = (wave >> 1) * 32 * MI, wn = (wave & 1) * 64;
   const bool va = (g.lda % 8 == 0) && (((uintptr_t)g.A & 15) == 0);
@@ -280,7 +322,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, wave);
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, wave);
 }
 
 // Sum of the split-K partial products in split order, then the epilogue.
@@ -363,7 +405,8 @@ __device__ __forceinline__ void store_cols64(__bf16 *lds, const Run8 (&x)[8], in
   }
 }
 // FP32 input rows (few columns: one element at a time), rounded.
-__device__ __forceinline__ void load_f32rows64(Run8 (&x)[4], const GemmArgs &g, int ke, int r0, int k0, int t) {
+__device__ __forceinline__ void load_f32rows64(Run8 (&x)[4], const GemmArgs &g, int ke, int r0, int k0, int t,
+                                               bool first_column) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int idx = t + 256 * i;
@@ -376,7 +419,7 @@ __device__ __forceinline__ void load_f32rows64(Run8 (&x)[4], const GemmArgs &g, 
     for (int j = 0; j < 8; ++j)
       if (k + j < ke) {
         x[i].v[j] = (__bf16)row[k + j];
-        if (g.Aout && blockIdx.x == 0) g.Aout[(size_t)r * g.lda + k + j] = x[i].v[j];
+        if (g.Aout && first_column) g.Aout[(size_t)r * g.lda + k + j] = x[i].v[j];
       }
   }
 }
@@ -386,12 +429,15 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) char smem64[];
   const int grp = threadIdx.x >> 8, t = threadIdx.x & 255;
   __bf16 *As = reinterpret_cast<__bf16 *>(smem64) + (size_t)grp * 2 * HB * HLD, *Bs = As + HB * HLD;
-  const int bm = blockIdx.y * HB, bn = blockIdx.x * HB;
+  const int nx = (g.N + HB - 1) / HB;
+  const TileId tl = xcd_tile(blockIdx.x, nx, (g.M + HB - 1) / HB, g.nz);
+  if (!tl.inside) return;
+  const int bm = tl.y * HB, bn = tl.x * HB;
   const int wave = t >> 6, lane = t & 63;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const bool va = (g.lda % 8 == 0) && (((uintptr_t)g.A & 15) == 0);
   const bool vb = (g.ldb % 8 == 0) && (((uintptr_t)g.B & 15) == 0);
-  const int chunk = G > 1 ? grp : (int)blockIdx.z;
+  const int chunk = G > 1 ? grp : tl.z;
   const int kb = chunk * g.kchunk, ke = min(g.K, kb + g.kchunk);
   f32x16 acc;
 #pragma unroll
@@ -407,7 +453,7 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
   Run8 ra[4], rb[4], rc[8];
   auto load = [&](int k0) {
     if constexpr (AF32)
-      load_f32rows64(ra, g, ke, bm, k0, t);
+      load_f32rows64(ra, g, ke, bm, k0, t, tl.x == 0);
     else if constexpr (!TA)
       load_rows64(ra, g.A, g.lda, g.M, ke, bm, k0, va, t);
     if constexpr (!TB) load_rows64(rb, g.B, g.ldb, g.N, ke, bn, k0, vb, t);
@@ -453,7 +499,7 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
       for (int e = 0; e < 16; ++e) acc[e] += sums[(q * 16 + e) * 256 + t];
   }
   // accumulator element e: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
-  float *part = g.part ? g.part + (size_t)blockIdx.z * g.M * g.N : nullptr;
+  float *part = g.part ? g.part + (size_t)tl.z * g.M * g.N : nullptr;
   const int col = bn + wn + (lane & 31);
   double loss = 0.0;
 #pragma unroll
@@ -469,7 +515,7 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
         gemm_epilogue<EPI>(g, row, col, acc[e]);
     }
   }
-  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, wave);
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, wave);
 }
 
 // Split over K when the output tile grid cannot fill the chip and K is long enough: about two
@@ -518,7 +564,8 @@ template <int EPI, bool TA, bool TB, bool AF32>
 static hipError_t launch_gemm64_t(GemmArgs g, int splits, void *ws, hipStream_t s) {
   const bool inside = splits <= G64_SPLITS;
   g.part = inside ? nullptr : (float *)ws;
-  const dim3 grid((unsigned)((g.N + HB - 1) / HB), (unsigned)((g.M + HB - 1) / HB), inside ? 1u : (unsigned)splits);
+  g.nz = inside ? 1 : splits;
+  const dim3 grid(xcd_blocks((g.N + HB - 1) / HB, (g.M + HB - 1) / HB, g.nz));
   constexpr size_t lds = 2 * HB * HLD * sizeof(__bf16);  // one group's tiles
   if (inside && splits > 2)  // a third or fourth range may be empty
     hipLaunchKernelGGL((k_gemm64<EPI, 4, TA, TB, AF32>), grid, dim3(1024), 4 * lds, s, g);
@@ -596,7 +643,7 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
   // 512 blocks or more are never split (gemm_splits splits below 128)
   g.part = nullptr;
   const bool tall = gemm_tall(g.M, g.N);
-  dim3 grid((g.N + GBN - 1) / GBN, (g.M + (tall ? 2 * GBM : GBM) - 1) / (tall ? 2 * GBM : GBM));
+  const dim3 grid(xcd_blocks((g.N + GBN - 1) / GBN, (g.M + (tall ? 2 * GBM : GBM) - 1) / (tall ? 2 * GBM : GBM), 1));
 #define PCMD_GEMM_CASE(E_)                                                                             \
   if (epi == E_) {                                                                                     \
     if (tall)                                                                                          \

@@ -26,6 +26,7 @@ struct GemmArgs {
   int ldz;
   float *part;        // split-K partial products [splits][M][N] (set by launch_gemm)
   int kchunk;         // K elements per split (a multiple of the K step; set by launch_gemm)
+  int nz;             // K ranges over blocks (set by launch_gemm)
   // A given in FP32 instead (A unused): row m is row rows[m] of A32 (m when rows is NULL; a row outside
   // [0, n_total) is taken as row 0 and sets STATUS_BAD_ROW), rounded to BF16 and, unless Aout is NULL,
   // also written there [M][lda].  Only where gemm_reads_f32(M, N).
