@@ -37,20 +37,27 @@ struct TileRegs {
   bf16x8 v[RUNS];
 };
 
-// rows x K row-major: run idx takes row idx / (GBK / 8), k run idx mod (GBK / 8)
+// rows x K row-major: run idx takes row idx / (GBK / 8), k run idx mod (GBK / 8).  Whole steps of a
+// 16-byte aligned operand load without a branch (rows past the end read the last row: what they
+// produce is not stored); a branch per run had made each load wait for the one before it.
 template <int RUNS>
 __device__ __forceinline__ void load_regs(TileRegs<RUNS> &t, const __bf16 *__restrict__ src, int ld, int rows, int K,
                                           int r0, int k0, bool vec_ok) {
+  if (vec_ok && k0 + GBK <= K) {
+#pragma unroll
+    for (int it = 0; it < RUNS; ++it) {
+      const int idx = threadIdx.x + 256 * it;
+      const int gr = min(r0 + idx / (GBK / 8), rows - 1), gk = k0 + (idx % (GBK / 8)) * 8;
+      t.v[it] = *reinterpret_cast<const bf16x8 *>(src + (size_t)gr * ld + gk);
+    }
+    return;
+  }
 #pragma unroll
   for (int it = 0; it < RUNS; ++it) {
     const int idx = threadIdx.x + 256 * it;
     const int gr = r0 + idx / (GBK / 8), gk = k0 + (idx % (GBK / 8)) * 8;
-    if (vec_ok && gr < rows && gk + 8 <= K) {
-      t.v[it] = *reinterpret_cast<const bf16x8 *>(src + (size_t)gr * ld + gk);
-    } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) t.v[it][i] = (gr < rows && gk + i < K) ? src[(size_t)gr * ld + gk + i] : (__bf16)0.0f;
-    }
+    for (int i = 0; i < 8; ++i) t.v[it][i] = (gr < rows && gk + i < K) ? src[(size_t)gr * ld + gk + i] : (__bf16)0.0f;
   }
 }
 
@@ -352,47 +359,44 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs g, int spli
 // results the same bit for bit.
 // ---------------------------------------------------------------------------------------
 constexpr int HB = 64, HK = 128, HLD = HK + 8;  // tile, K stage, LDS row stride (rows 4 banks apart)
+// Element (row, 8 unit) of a staged tile.  The units of a row are permuted by its number over 8, so that
+// a transposed 8 x 8 block's stores (eight lanes, rows 8 apart: 32 banks or none) fall in different
+// banks, as the row-wise stores and the fragment reads do.
+__device__ __forceinline__ int lds64(int row, int unit) { return row * HLD + (unit ^ ((row >> 3) & 7)) * 8; }
 
 union Run8 {
   bf16x8 v;
   uint32_t w[4];
 };
 
-// 4 runs of 8 k of a 64 x HK tile (row-major operand): thread t's run i is row (t + 256 i) / 16.
-__device__ __forceinline__ void load_rows64(Run8 (&x)[4], const __bf16 *__restrict__ src, int ld, int rows, int ke, int r0,
-                                            int k0, bool vec, int t) {
+// A whole stage of a 16-byte aligned operand goes through registers.  Rows past the end keep what the
+// registers hold (what they produce is not stored): a value given to them made every load wait for
+// the one before it, and reading the last row instead (64 times, for one sample, by every block)
+// crowded one L2 channel.
+// Row-major: 4 runs of 8 k; thread t's run i is row (t + 256 i) / 16.
+__device__ __forceinline__ void load_rows64(Run8 (&x)[4], const __bf16 *__restrict__ src, int ld, int rows, int r0, int k0,
+                                            int t) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int idx = t + 256 * i;
     const int r = r0 + (idx >> 4), k = k0 + (idx & 15) * 8;
-    if (vec && r < rows && k + 8 <= ke) {
-      x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)r * ld + k);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x[i].v[j] = (r < rows && k + j < ke) ? src[(size_t)r * ld + k + j] : (__bf16)0.0f;
-    }
+    if (r < rows) x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)r * ld + k);
   }
 }
 __device__ __forceinline__ void store_rows64(__bf16 *lds, const Run8 (&x)[4], int t) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int idx = t + 256 * i;
-    *reinterpret_cast<bf16x8 *>(lds + (idx >> 4) * HLD + (idx & 15) * 8) = x[i].v;
+    *reinterpret_cast<bf16x8 *>(lds + lds64(idx >> 4, idx & 15)) = x[i].v;
   }
 }
-// One 8 x 8 block of a K-major operand: block b holds k 8 (b / 8) .. + 7 and rows 8 (b % 8) .. + 7.
-__device__ __forceinline__ void load_cols64(Run8 (&x)[8], const __bf16 *__restrict__ src, int ld, int rows, int ke, int r0,
-                                            int k0, bool vec, int b) {
+// K-major (rows a multiple of 8): block b holds k 8 (b / 8) .. + 7 and rows 8 (b % 8) .. + 7.
+__device__ __forceinline__ void load_cols64(Run8 (&x)[8], const __bf16 *__restrict__ src, int ld, int rows, int r0, int k0,
+                                            int b) {
   const int r = r0 + (b & 7) * 8, k = k0 + (b >> 3) * 8;
+  if (r >= rows) return;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    if (vec && r + 8 <= rows && k + i < ke) {
-      x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)(k + i) * ld + r);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) x[i].v[j] = (r + j < rows && k + i < ke) ? src[(size_t)(k + i) * ld + r + j] : (__bf16)0.0f;
-    }
-  }
+  for (int i = 0; i < 8; ++i) x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)(k + i) * ld + r);
 }
 __device__ __forceinline__ void store_cols64(__bf16 *lds, const Run8 (&x)[8], int b) {
 #pragma unroll
@@ -401,26 +405,32 @@ __device__ __forceinline__ void store_cols64(__bf16 *lds, const Run8 (&x)[8], in
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       o.w[j] = __builtin_amdgcn_perm(x[2 * j + 1].w[m >> 1], x[2 * j].w[m >> 1], (m & 1) ? 0x07060302u : 0x05040100u);
-    *reinterpret_cast<bf16x8 *>(lds + ((b & 7) * 8 + m) * HLD + (b >> 3) * 8) = o.v;
+    *reinterpret_cast<bf16x8 *>(lds + lds64((b & 7) * 8 + m, b >> 3)) = o.v;
   }
 }
-// FP32 input rows (few columns: one element at a time), rounded.
-__device__ __forceinline__ void load_f32rows64(Run8 (&x)[4], const GemmArgs &g, int ke, int r0, int k0, int t,
-                                               bool first_column) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int idx = t + 256 * i;
-    const int r = r0 + (idx >> 4), k = k0 + (idx & 15) * 8;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[i].v[j] = (__bf16)0.0f;
-    if (r >= g.M || k >= ke) continue;
-    const float *row = g.A32 + batch_row(g.rows, r, g.n_total, g.status) * g.lda;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      if (k + j < ke) {
-        x[i].v[j] = (__bf16)row[k + j];
-        if (g.Aout && first_column) g.Aout[(size_t)r * g.lda + k + j] = x[i].v[j];
+// Any other stage, one element at a time straight into LDS: k0 .. ke - 1 (at most HK), zeros up to the
+// next multiple of 16.
+template <bool T, bool F32>
+__device__ __forceinline__ void stage64(__bf16 *lds, const GemmArgs &g, const __bf16 *__restrict__ src, int ld, int rows,
+                                        int ke, int r0, int k0, int t, bool first_column) {
+  const int steps = (max(0, min(HK, ke - k0)) + 15) / 16;
+  const int n = max(1, min(HB, rows - r0));
+  const int lg = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 0;  // 2^lg >= n rows
+  for (int idx = t; idx < steps << (4 + lg); idx += 256) {
+    // neighbouring threads read neighbouring elements
+    const int rr = (T ? idx : idx >> 4) & ((1 << lg) - 1);
+    const int kk = T ? idx >> lg : (idx & 15) + (idx >> (4 + lg)) * 16;
+    const int r = r0 + rr, k = k0 + kk;
+    __bf16 v = (__bf16)0.0f;
+    if (r < rows && k < ke) {
+      if constexpr (F32) {  // the FP32 input batch, rounded
+        v = (__bf16)g.A32[batch_row(g.rows, r, g.n_total, g.status) * ld + k];
+        if (g.Aout && first_column) g.Aout[(size_t)r * ld + k] = v;
+      } else {
+        v = T ? src[(size_t)k * ld + r] : src[(size_t)r * ld + k];
       }
+    }
+    lds[lds64(rr, kk >> 3) + (kk & 7)] = v;
   }
 }
 
@@ -435,8 +445,8 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
   const int bm = tl.y * HB, bn = tl.x * HB;
   const int wave = t >> 6, lane = t & 63;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const bool va = (g.lda % 8 == 0) && (((uintptr_t)g.A & 15) == 0);
-  const bool vb = (g.ldb % 8 == 0) && (((uintptr_t)g.B & 15) == 0);
+  const bool va = !AF32 && g.lda % 8 == 0 && ((uintptr_t)g.A & 15) == 0 && (!TA || g.M % 8 == 0);
+  const bool vb = g.ldb % 8 == 0 && ((uintptr_t)g.B & 15) == 0 && (!TB || g.N % 8 == 0);
   const int chunk = G > 1 ? grp : tl.z;
   const int kb = chunk * g.kchunk, ke = min(g.K, kb + g.kchunk);
   f32x16 acc;
@@ -450,36 +460,47 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
   constexpr bool BOTH = TA && TB;
   const int cb = BOTH ? t & 127 : t;
   const bool has_a = TA && (BOTH ? t < 128 : t < 128), has_b = TB && (BOTH ? t >= 128 : t < 128);
-  Run8 ra[4], rb[4], rc[8];
+  Run8 ra[4] = {}, rb[4] = {}, rc[8] = {};
   auto load = [&](int k0) {
-    if constexpr (AF32)
-      load_f32rows64(ra, g, ke, bm, k0, t, tl.x == 0);
-    else if constexpr (!TA)
-      load_rows64(ra, g.A, g.lda, g.M, ke, bm, k0, va, t);
-    if constexpr (!TB) load_rows64(rb, g.B, g.ldb, g.N, ke, bn, k0, vb, t);
-    if constexpr (TA)
-      if (has_a) load_cols64(rc, g.A, g.lda, g.M, ke, bm, k0, va, cb);
-    if constexpr (TB)
-      if (has_b) load_cols64(rc, g.B, g.ldb, g.N, ke, bn, k0, vb, cb);
+    if (k0 + HK > ke) return;
+    if (va) {
+      if constexpr (!TA) load_rows64(ra, g.A, g.lda, g.M, bm, k0, t);
+      if constexpr (TA)
+        if (has_a) load_cols64(rc, g.A, g.lda, g.M, bm, k0, cb);
+    }
+    if (vb) {
+      if constexpr (!TB) load_rows64(rb, g.B, g.ldb, g.N, bn, k0, t);
+      if constexpr (TB)
+        if (has_b) load_cols64(rc, g.B, g.ldb, g.N, bn, k0, cb);
+    }
   };
   load(kb);
   for (int st = 0; st < stages; ++st) {
     const int k0 = kb + st * HK;
+    const bool whole = k0 + HK <= ke;
     if (st > 0) __syncthreads();  // the previous stage's reads are over
-    if constexpr (!TA) store_rows64(As, ra, t);
-    if constexpr (!TB) store_rows64(Bs, rb, t);
-    if constexpr (TA)
-      if (has_a) store_cols64(As, rc, cb);
-    if constexpr (TB)
-      if (has_b) store_cols64(Bs, rc, cb);
+    if (whole && va) {
+      if constexpr (!TA) store_rows64(As, ra, t);
+      if constexpr (TA)
+        if (has_a) store_cols64(As, rc, cb);
+    } else {
+      stage64<TA, AF32>(As, g, g.A, g.lda, g.M, ke, bm, k0, t, tl.x == 0);
+    }
+    if (whole && vb) {
+      if constexpr (!TB) store_rows64(Bs, rb, t);
+      if constexpr (TB)
+        if (has_b) store_cols64(Bs, rc, cb);
+    } else {
+      stage64<TB, false>(Bs, g, g.B, g.ldb, g.N, ke, bn, k0, t, false);
+    }
     __syncthreads();
     if (st + 1 < stages) load(k0 + HK);
     // whole steps of 16 up to the range's end (what lies past it in the stage is zero)
 #pragma unroll
     for (int ks = 0; ks < HK; ks += 16) {
       if (k0 + ks >= ke) break;
-      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&As[(wm + r) * HLD + ks + kh]);
-      const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&Bs[(wn + r) * HLD + ks + kh]);
+      const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&As[lds64(wm + r, (ks + kh) / 8)]);
+      const bf16x8 b = *reinterpret_cast<const bf16x8 *>(&Bs[lds64(wn + r, (ks + kh) / 8)]);
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
     }
   }
