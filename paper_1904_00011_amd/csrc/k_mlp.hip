@@ -204,12 +204,12 @@ __device__ __forceinline__ double mse_epilogue4(const GemmArgs &g, int row, int 
   }
   return ((double)d0 * (double)d0 + (double)d1 * (double)d1) + ((double)d2 * (double)d2 + (double)d3 * (double)d3);
 }
-// A wave's sum of squared errors to its slot of lpart (tile-major, LOSS_WAVES slots per tile).
+// A wave's sum of squared errors to its slot of lpart (tile-major, `slots` waves per tile).
 constexpr int LOSS_WAVES = 4;
-__device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int tile, int wave) {
+__device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int tile, int slots, int wave) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
-  if ((threadIdx.x & 63u) == 0u) g.lpart[(size_t)tile * LOSS_WAVES + wave] = s;
+  if ((threadIdx.x & 63u) == 0u) g.lpart[(size_t)tile * slots + wave] = s;
 }
 
 constexpr int GEPI_LD = 72;  // epilogue slab row stride (floats): 32 x 72 x 4 B per wave
@@ -329,7 +329,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, wave);
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, LOSS_WAVES, wave);
 }
 
 // Sum of the split-K partial products in split order, then the epilogue.
@@ -504,39 +504,44 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
     }
   }
+  // With groups, every group leaves its sums in LDS and finishes a G-th of the tile's elements: adds
+  // the groups' sums in group order and runs the epilogue (GELU and its derivative are ~100
+  // instructions an element, which one group's four waves alone took 5 us for).
+  constexpr int EN = 16 / G;
+  float *sums = reinterpret_cast<float *>(smem64);  // [G][16][256]
   if (G > 1) {
-    // the groups' sums in group order: groups 1.. leave theirs in LDS, group 0 adds them
     __syncthreads();
-    float *sums = reinterpret_cast<float *>(smem64);  // [G - 1][16][256]
-    if (grp > 0) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sums[((grp - 1) * 16 + e) * 256 + t] = acc[e];
-    }
+    for (int e = 0; e < 16; ++e) sums[(grp * 16 + e) * 256 + t] = acc[e];
     __syncthreads();
-    if (grp > 0) return;
-#pragma unroll
-    for (int q = 0; q < G - 1; ++q)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] += sums[(q * 16 + e) * 256 + t];
   }
   // accumulator element e: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
   float *part = g.part ? g.part + (size_t)tl.z * g.M * g.N : nullptr;
   const int col = bn + wn + (lane & 31);
   double loss = 0.0;
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
+  for (int i = 0; i < EN; ++i) {
+    const int e = G > 1 ? grp * EN + i : i;
+    float v;
+    if constexpr (G > 1) {
+      v = sums[e * 256 + t];
+#pragma unroll
+      for (int q = 1; q < G; ++q) v += sums[(q * 16 + e) * 256 + t];
+    } else {
+      v = acc[i];
+    }
     const int row = bm + wm + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
     if (row >= g.M || col >= g.N) continue;
     if constexpr (EPI == EPI_BIAS_MSE) {
-      loss += mse_epilogue(g, row, col, acc[e]);
+      loss += mse_epilogue(g, row, col, v);
     } else {
       if (part)
-        part[(size_t)row * g.N + col] = acc[e];
+        part[(size_t)row * g.N + col] = v;
       else
-        gemm_epilogue<EPI>(g, row, col, acc[e]);
+        gemm_epilogue<EPI>(g, row, col, v);
     }
   }
-  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, wave);
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, G * LOSS_WAVES, grp * LOSS_WAVES + wave);
 }
 
 // Split over K when the output tile grid cannot fill the chip and K is long enough: about two
@@ -626,8 +631,10 @@ static hipError_t launch_gemm64(const GemmArgs &g, int splits, bool at, bool bt,
 
 int64_t gemm_loss_parts(int M, int N, int K) {
   int kchunk;
-  if (gemm_use64(M, N))
-    return gemm_splits(M, N, K, kchunk) > G64_SPLITS ? 0 : (int64_t)((M + HB - 1) / HB) * ((N + HB - 1) / HB) * LOSS_WAVES;
+  if (gemm_use64(M, N)) {
+    const int splits = gemm_splits(M, N, K, kchunk), groups = splits > 2 ? 4 : splits;
+    return splits > G64_SPLITS ? 0 : (int64_t)((M + HB - 1) / HB) * ((N + HB - 1) / HB) * groups * LOSS_WAVES;
+  }
   const int bm = gemm_tall(M, N) ? 2 * GBM : GBM;
   return (int64_t)((M + bm - 1) / bm) * ((N + GBN - 1) / GBN) * LOSS_WAVES;
 }
