@@ -3,6 +3,8 @@
 // weights, and the surrogate Poisson log-likelihood.
 #include <math.h>
 
+#include <algorithm>
+
 #include "pcmd_device.h"
 #include "pcmd_internal.h"
 #include "pcmd_mlp.h"
@@ -920,80 +922,172 @@ hipError_t launch_adam(AdamArgs a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Surrogate log-likelihood, one block per sample.  With x_j = y_j - max y and se = sum exp(x_j), bin
-// j expects lam_j = N_d exp(x_j) / se, so ln lam_j = x_j + ln(N_d / se) and sum lam_j = N_d:
+// Surrogate log-likelihood.  With x_j = y_j - max y and se = sum exp(x_j), bin j expects lam_j = N_d
+// exp(x_j) / se, so ln lam_j = x_j + ln(N_d / se) and sum lam_j = N_d:
 //   logL = sum_j d_j x_j + N_d ln(N_d / se) - N_d - sum_j ln d_j!
 // needs one exponential per bin, where the term-by-term form took two and a logarithm (FP64, so
-// bound by their ~150 vector instructions per bin).  y is read once: a thread keeps its bins of the
-// first SLL_REG rounds in registers between the maximum and the exponentials.  1,024 threads also
-// for many samples, so that a sample's sum has one order whatever the batch.
-// 10,000 bins: one sample 42 -> 8 us, 4,096 samples 431 -> 153 us.
-constexpr int SLL_THREADS = 1024, SLL_REG = 10;
+// bound by their vector instructions).  A block of 1,024 threads walks samples, its share of the data
+// (N_d, the factorials' sum, each thread's counts of the first SLL_REG rounds) kept from one to the
+// next; a thread also keeps its bins of y between the maximum and the exponentials.  The order of a
+// sample's sums does not depend on the batch.
+// 10,000 bins: one sample 42 -> 9.4 us, 4,096 samples 431 -> 78 us (156 with the library's exponential,
+// a block per sample and the data's sums formed for each); no spills, which had cost half of that.
+constexpr int SLL_THREADS = 1024, SLL_REG = 10, SLL_BLOCKS = 512;
+constexpr int SLL_SAMPLES = 64;  // samples per block, at most
 
-// Sum over the block in a fixed order (shuffles in each wave, then the waves in order).
-__device__ __forceinline__ double sll_sum(double v, double *red) {
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-  __syncthreads();  // the previous use of red is over
-  if ((threadIdx.x & 63u) == 0u) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = 0.0;
-#pragma unroll
-  for (int w = 0; w < SLL_THREADS / 64; ++w) r += red[w];
-  return r;
+// exp(x) for x <= 0 (NaN stays): Cody and Waite's reduction x = k ln 2 + r, |r| <= ln 2 / 2, and
+// the Taylor polynomial of degree 13 (its remainder is below 2^-57); 0 below -745.
+__device__ __forceinline__ double exp_nonpos(double x) {
+  x = x < -800.0 ? -800.0 : x;
+  const double k = rint(x * 1.4426950408889634);
+  double r = fma(k, -0.6931471805599453, x);   // ln 2 rounded to FP64 ...
+  r = fma(k, -2.3190468138462996e-17, r);      // ... and the rest of it
+  // p = p r + c with c in scalar registers (the compiler copies each addend to a vector register first,
+  // and keeps the copies until they spill)
+  double p = 1.0 / 6227020800.0;
+  auto step = [&](double c) { asm("v_fma_f64 %0, %1, %2, %3" : "=v"(p) : "v"(p), "v"(r), "s"(c)); };
+  step(1.0 / 479001600.0);
+  step(1.0 / 39916800.0);
+  step(1.0 / 3628800.0);
+  step(1.0 / 362880.0);
+  step(1.0 / 40320.0);
+  step(1.0 / 5040.0);
+  step(1.0 / 720.0);
+  step(1.0 / 120.0);
+  step(1.0 / 24.0);
+  step(1.0 / 6.0);
+  step(0.5);
+  step(1.0);
+  step(1.0);
+  return ldexp(p, (int)k);
 }
 
-__global__ void __launch_bounds__(SLL_THREADS) k_surrogate_loglike(const float *__restrict__ y, int nbins,
-                                                                   const uint32_t *__restrict__ d,
-                                                                   double *__restrict__ out,
-                                                                   const double *__restrict__ lnfact64, int nlf) {
-  __shared__ double red[SLL_THREADS / 64];
+// ln x of a positive normal x = m 2^e, m in [1/2, 1): one step of Halley's iteration for exp(y) = m, y +
+// 2 (m - exp y) / (m + exp y), from the FP32 logarithm (its error, below 2^-20, comes out cubed).  The
+// library's logarithm holds a dozen constants in vector registers across the kernel's loop.
+__device__ __forceinline__ double ln_pos(double x) {
+  const double m = __builtin_amdgcn_frexp_mant(x);
+  const double e = (double)__builtin_amdgcn_frexp_exp(x);
+  const double y = (double)__builtin_amdgcn_logf((float)m) * 0.6931471805599453;
+  const double E = exp_nonpos(y);
+  const double z = y + 2.0 * (m - E) / (m + E);
+  return fma(e, 0.6931471805599453, fma(e, 2.3190468138462996e-17, z));
+}
+
+// ln k! for k >= 1000 by Stirling's series in x = k + 1 (the first term left out is below 1e-18).
+__device__ __forceinline__ double ln_factorial_large(uint32_t k) {
+  const double x = (double)k + 1.0, r = 1.0 / x;
+  return (x - 0.5) * ln_pos(x) - x + 0.9189385332046727 + r * (1.0 / 12.0) - r * r * r * (1.0 / 360.0);
+}
+
+// The sums of u and v over the block in a fixed order (trees of shuffles in each wave, then over the
+// waves).
+__device__ __forceinline__ void sll_sum2(double &u, double &v, double (*red)[2]) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    u += __shfl_xor(u, d, 64);
+    v += __shfl_xor(v, d, 64);
+  }
+  if ((threadIdx.x & 63u) == 0u) {
+    red[threadIdx.x >> 6][0] = u;
+    red[threadIdx.x >> 6][1] = v;
+  }
+  __syncthreads();
+  static_assert(SLL_THREADS == 1024, "sixteen waves");
+  u = red[threadIdx.x & 15u][0];
+  v = red[threadIdx.x & 15u][1];
+#pragma unroll
+  for (int d = 8; d > 0; d >>= 1) {
+    u += __shfl_xor(u, d, 64);
+    v += __shfl_xor(v, d, 64);
+  }
+}
+
+__global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const float *__restrict__ y, int n, int nbins,
+                                                                      const uint32_t *__restrict__ d,
+                                                                      double *__restrict__ out,
+                                                                      const double *__restrict__ lnfact64, int nlf) {
+  __shared__ double red[2][SLL_THREADS / 64][2];
   __shared__ float redf[SLL_THREADS / 64];
-  const float *ys = y + (size_t)blockIdx.x * nbins;
+  __shared__ double fin[SLL_SAMPLES][2];  // se and sum d x of the block's samples
   const int t = threadIdx.x;
-  float v[SLL_REG];
   uint32_t dv[SLL_REG];
 #pragma unroll
   for (int k = 0; k < SLL_REG; ++k) {
-    const int j = t + k * SLL_THREADS;
-    v[k] = j < nbins ? ys[j] : -INFINITY;
-    dv[k] = j < nbins ? d[j] : 0u;
+    dv[k] = 0u;
+    if ((uint32_t)t + k * SLL_THREADS < (uint32_t)nbins) dv[k] = (d + k * SLL_THREADS)[(uint32_t)t];
   }
-  float m = -INFINITY;
+  double nd = 0.0, lf = 0.0;
+  bool large = false;
 #pragma unroll
-  for (int k = 0; k < SLL_REG; ++k) m = fmaxf(m, v[k]);
-  for (int j = t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) m = fmaxf(m, ys[j]);
+  for (int k = 0; k < SLL_REG; ++k) {  // ln 0! = ln 1! = 0
+    nd += (double)dv[k];
+    if (dv[k] > 1u) lf += lnfact64[min(dv[k], (uint32_t)nlf - 1u)];
+    large = large || dv[k] >= (uint32_t)nlf;
+  }
+  // counts beyond the table (corrected where they are) and bins beyond the registers
+#pragma unroll 1
+  for (int j = large ? t : t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) {
+    const uint32_t dj = d[j];
+    const bool kept = j < SLL_REG * SLL_THREADS;
+    if (!kept) nd += (double)dj;
+    if (dj >= (uint32_t)nlf)
+      lf += ln_factorial_large(dj) - (kept ? lnfact64[nlf - 1] : 0.0);
+    else if (!kept && dj > 1u)
+      lf += lnfact64[dj];
+  }
+  sll_sum2(nd, lf, red[0]);
+  int q0 = 0;
+  for (int s = blockIdx.x; s < n; s += gridDim.x, ++q0) {
+    const float *ys = y + (size_t)s * nbins;
+    float v[SLL_REG];
 #pragma unroll
-  for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s, 64));
-  if ((t & 63) == 0) redf[t >> 6] = m;
+    for (int k = 0; k < SLL_REG; ++k) {
+      v[k] = -INFINITY;
+      if ((uint32_t)t + k * SLL_THREADS < (uint32_t)nbins) v[k] = (ys + k * SLL_THREADS)[(uint32_t)t];
+    }
+    float m = -INFINITY;
+#pragma unroll
+    for (int k = 0; k < SLL_REG; ++k) m = fmaxf(m, v[k]);
+    for (int j = t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) m = fmaxf(m, ys[j]);
+#pragma unroll
+    for (int q = 32; q > 0; q >>= 1) m = fmaxf(m, __shfl_xor(m, q, 64));
+    if ((t & 63) == 0) redf[t >> 6] = m;
+    __syncthreads();
+    m = redf[t & 15];
+#pragma unroll
+    for (int q = 8; q > 0; q >>= 1) m = fmaxf(m, __shfl_xor(m, q, 64));
+    const double mx = (double)m;
+    double se = 0.0, dx = 0.0;
+    auto bin = [&](float yj, uint32_t dj) {
+      const double x = (double)yj - mx;
+      const double e = exp_nonpos(x);
+      se += e;
+      // a bin whose expectation underflows to zero counts as ln 0, also where it holds no data
+      dx += (double)dj * (e == 0.0 ? -INFINITY : x);
+    };
+#pragma unroll
+    for (int k = 0; k < SLL_REG; ++k) {
+      // converted here for each sample: kept in FP64, the counts would spill
+      asm volatile("" : "+v"(dv[k]));
+      if (t + k * SLL_THREADS < nbins) bin(v[k], dv[k]);
+    }
+    for (int j = t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) bin(ys[j], d[j]);
+    sll_sum2(se, dx, red[1]);  // its barrier also parts this sample's redf from the next one's
+    if (t == 0) {
+      fin[q0][0] = se;
+      fin[q0][1] = dx;
+    }
+  }
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < SLL_THREADS / 64; ++w) m = fmaxf(m, redf[w]);
-  const double mx = (double)m;
-  double se = 0.0, dx = 0.0, lf = 0.0, nd = 0.0;
-  auto bin = [&](float yj, uint32_t dj) {
-    const double x = (double)yj - mx;
-    const double e = exp(x);
-    se += e;
-    // a bin whose expectation underflows to zero counts as ln 0, also where it holds no data
-    dx += (double)dj * (e == 0.0 ? -INFINITY : x);
-    nd += (double)dj;
-    if (dj > 1u) lf += (lnfact64 && dj < (uint32_t)nlf) ? lnfact64[dj] : lgamma((double)dj + 1.0);  // ln 0! = ln 1! = 0
-  };
-#pragma unroll
-  for (int k = 0; k < SLL_REG; ++k)
-    if (t + k * SLL_THREADS < nbins) bin(v[k], dv[k]);
-  for (int j = t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) bin(ys[j], d[j]);
-  se = sll_sum(se, red);
-  dx = sll_sum(dx, red);
-  nd = sll_sum(nd, red);
-  lf = sll_sum(lf, red);
-  if (t == 0) out[blockIdx.x] = dx + nd * log(nd / se) - nd - lf;
+  if (t < q0) out[blockIdx.x + t * gridDim.x] = fin[t][1] + nd * ln_pos(nd / fin[t][0]) - nd - lf;
 }
 
 hipError_t launch_surrogate_loglike(const float *y, int n, int nbins, const uint32_t *d, double *out,
                                    const double *lnfact64, int nlf, hipStream_t s) {
-  hipLaunchKernelGGL(k_surrogate_loglike, dim3(n), dim3(SLL_THREADS), 0, s, y, nbins, d, out, lnfact64, nlf);
+  if (!lnfact64 || nlf < 1000) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_surrogate_loglike, dim3((unsigned)std::max(std::min(n, SLL_BLOCKS), (n + SLL_SAMPLES - 1) / SLL_SAMPLES)), dim3(SLL_THREADS), 0, s, y, n, nbins, d,
+                     out, lnfact64, nlf);
   return hipGetLastError();
 }
 

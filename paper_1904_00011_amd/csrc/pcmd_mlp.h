@@ -80,7 +80,7 @@ hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, flo
 hipError_t launch_log_hess_target(const uint32_t *h, int n, int nbins, float *out, hipStream_t s);
 hipError_t launch_colsum(const void *dz, int n, int m, float *db, hipStream_t s);
 hipError_t launch_adam(AdamArgs a, hipStream_t s);
-// lnfact64[k] = ln k! for k < nlf (lgamma beyond, or everywhere when lnfact64 is NULL)
+// lnfact64[k] = ln k! for k < nlf (Stirling's series beyond; nlf >= 1000)
 hipError_t launch_surrogate_loglike(const float *y, int n, int nbins, const uint32_t *d, double *out,
                                    const double *lnfact64, int nlf, hipStream_t s);
 
