@@ -53,28 +53,37 @@ hipError_t launch_copy_f32(const float *src, float *dst, int64_t n, hipStream_t 
 
 // ---------------------------------------------------------------------------------------
 // Direct periodic convolution.  G[y][x] = sum_{u,v} P[u][v] F[(y-u+h) mod N][(x-v+h) mod N].
-// A 64 x 16 output tile per 256-thread block; each thread owns four neighbouring outputs of one
-// row.  The input tile with its K-1 halo (wrapped periodically) and the flipped PSF (rows
-// zero-padded to a multiple of 4) are staged in LDS as FP32 and read 16 bytes at a time: tile
-// values into a sliding register window, PSF values as broadcasts.  For every PSF row the thread
-// forms the four K-term dot products in FP32 (all terms positive, ascending column; the zero
-// padding adds exact zeros) and adds them to FP64 accumulators in ascending row order.
+// Each thread owns NX neighbouring outputs of one row of a 64-column tile.  The input tile with its
+// K-1 halo (wrapped periodically) and the flipped PSF (rows zero-padded to a multiple of 4) are staged
+// in LDS as FP32 and read 16 bytes at a time: tile values into a sliding register window, PSF values
+// as broadcasts.  For every PSF row the thread forms the NX K-term dot products in FP32 (all terms
+// positive, ascending column; the zero padding adds exact zeros) and adds them to FP64 accumulators
+// in ascending row order.
+// Bound by FP32 multiply-adds: eight outputs take 32 of them (128 cycles of a SIMD) per two 16-byte
+// reads, where four outputs' 64 cycles had the four SIMDs wait for the one LDS.  4096 x 4096 x 3,
+// 31 x 31 PSF: 3.07 -> 1.32 ms (2.3 times the FP32 rate, 0.9 of the peak without packed
+// instructions).
+//
+// RS > 1 splits the PSF rows: RS groups of threads share one tile, group g taking rows [g K / RS,
+// (g + 1) K / RS); groups 1.. leave their FP64 sums in LDS and group 0 adds them in group order.  Used
+// when the image is too small for one-group blocks to fill the chip (256 x 256 x 3, 31 x 31: 24.6 -> 16
+// us).
 // ---------------------------------------------------------------------------------------
-constexpr int CT_X = 64, CT_Y = 16;
+constexpr int CT_X = 64, NX = 8;
+constexpr int CT_Y1 = 32, CT_YS = 16;  // tile rows: one group of 256 threads, or RS groups of 128
+constexpr int CONV_RS = 8;
+constexpr int conv_group(int rows) { return rows * (CT_X / NX); }  // threads of a group
 
 __host__ __device__ inline int conv_kp(int K) { return (K + 3) & ~3; }
+// the last thread's window ends at column (CT_X - NX) + Kp + NX - 1 and is read in fours
 __host__ __device__ inline int conv_tile_w(int K) { return CT_X + conv_kp(K) + 4; }
 
-size_t conv_direct_lds_bytes(int K) {
-  return ((size_t)(CT_Y + K - 1) * conv_tile_w(K) + (size_t)K * conv_kp(K)) * sizeof(float);
+static size_t conv_lds_bytes(int K, int RS, int rows) {
+  return ((size_t)(rows + K - 1) * conv_tile_w(K) + (size_t)K * conv_kp(K)) * sizeof(float) +
+         (size_t)(RS - 1) * conv_group(rows) * NX * sizeof(double);
 }
-// Row splits RS > 1: RS groups of 256 threads share one output tile, group g taking PSF rows
-// [g K / RS, (g + 1) K / RS); groups 1.. leave their FP64 sums in LDS and group 0 adds them in
-// group order.  Used when the image is too small for one-group blocks to fill the chip.
-constexpr int CONV_RS = 4;
-static size_t conv_split_lds_bytes(int K) {
-  return conv_direct_lds_bytes(K) + (size_t)(CONV_RS - 1) * 256 * 4 * sizeof(double);
-}
+// The largest PSF that the direct path takes is set by the smaller tile's LDS.
+size_t conv_direct_lds_bytes(int K) { return conv_lds_bytes(K, 1, CT_YS); }
 
 // The PSF check of psf_check_body done by one wave (the direct convolution's first tile of each
 // PSF runs it beside its own work, which saves the check's launch): per-lane FP64 sums, then a
@@ -93,9 +102,10 @@ __device__ __forceinline__ void psf_check_wave(const ConvArgs &a, int b) {
   if (lane == 0 && (__ballot(bad) != 0ull || !(fabs(s - 1.0) <= 1e-3))) atomicOr(a.status, STATUS_BAD_PSF);
 }
 
-template <int RS>
+template <int RS, int CT_Y>
 __device__ __forceinline__ void conv_direct_body(const ConvArgs &ca) {
   extern __shared__ float4 lds4[];
+  constexpr int TG = conv_group(CT_Y), THREADS = TG * RS;
   float *tile = reinterpret_cast<float *>(lds4);
   const float *__restrict__ F = ca.F;
   float *__restrict__ G = ca.G;
@@ -115,111 +125,130 @@ __device__ __forceinline__ void conv_direct_body(const ConvArgs &ca) {
   float *Pf = tile + TW * TH;  // Pf[a][c] = P[K-1-a][K-1-c], 0 for c >= K
   const float *Fb = F + (size_t)b * N * N;
   const float *psf = ca.psf + (size_t)blockIdx.z * K * K;
-  // tile[ty][tx] = F[(oy - h + ty) mod N][(ox - h + tx) mod N]; columns past the halo are padding
-  for (int idx = threadIdx.x; idx < TW * TH; idx += 256 * RS) {
-    const int ty = idx / TW, tx = idx - ty * TW;
-    int gy = (oy - h + ty) % N;
-    if (gy < 0) gy += N;
-    int gx = (ox - h + tx) % N;
-    if (gx < 0) gx += N;
-    tile[idx] = Fb[(size_t)gy * N + gx];
+  // tile[ty][tx] = F[(oy - h + ty) mod N][(ox - h + tx) mod N]; columns past the halo are padding.  A
+  // wave stages whole rows (no division per element); an index is at most a few sides out of range
+  auto wrap = [N](int i) {
+    if (i < 0) i += N;  // i >= -h > -N
+    while (i >= N) i -= N;
+    return i;
+  };
+  for (int ty = threadIdx.x >> 6; ty < TH; ty += THREADS / 64) {
+    const float *row = Fb + (size_t)wrap(oy - h + ty) * N;
+    for (int tx = threadIdx.x & 63; tx < TW; tx += 64) tile[ty * TW + tx] = row[wrap(ox - h + tx)];
   }
-  for (int idx = threadIdx.x; idx < K * Kp; idx += 256 * RS) {
-    const int a = idx / Kp, c = idx - a * Kp;
-    Pf[idx] = c < K ? psf[(size_t)(K - 1 - a) * K + (K - 1 - c)] : 0.0f;
-  }
+  for (int a = threadIdx.x >> 6; a < K; a += THREADS / 64)
+    for (int c = threadIdx.x & 63; c < Kp; c += 64) Pf[a * Kp + c] = c < K ? psf[(size_t)(K - 1 - a) * K + (K - 1 - c)] : 0.0f;
   __syncthreads();
-  const int grp = threadIdx.x >> 8, lt = threadIdx.x & 255;
-  const int tx4 = lt & 15, ty = lt >> 4;
-  // output (oy + ty, ox + 4 tx4 + i) = sum_{a,c} Pf[a][c] tile[ty + a][4 tx4 + i + c]
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  const int grp = RS > 1 ? threadIdx.x / TG : 0, lt = threadIdx.x % TG;
+  const int tx = (lt % (CT_X / NX)) * NX, ty = lt / (CT_X / NX);
+  // output (oy + ty, ox + tx + i) = sum_{a,c} Pf[a][c] tile[ty + a][tx + i + c]
+  double acc[NX];
+#pragma unroll
+  for (int i = 0; i < NX; ++i) acc[i] = 0.0;
   const int a0 = grp * K / RS, a1 = (grp + 1) * K / RS;
   for (int a = a0; a < a1; ++a) {
-    const float *row = tile + (ty + a) * TW + 4 * tx4;
+    const float *row = tile + (ty + a) * TW + tx;
     const float *prow = Pf + a * Kp;
-    float d0 = 0.0f, d1 = 0.0f, d2 = 0.0f, d3 = 0.0f;
-    float4 lo = *reinterpret_cast<const float4 *>(row);
+    float d[NX], w[NX + 4];
+#pragma unroll
+    for (int i = 0; i < NX; ++i) d[i] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < NX; q += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(row + q);
+      w[q] = v.x;
+      w[q + 1] = v.y;
+      w[q + 2] = v.z;
+      w[q + 3] = v.w;
+    }
     for (int c = 0; c < Kp; c += 4) {
-      const float4 hi = *reinterpret_cast<const float4 *>(row + c + 4);
+      const float4 hi = *reinterpret_cast<const float4 *>(row + c + NX);
       const float4 p4 = *reinterpret_cast<const float4 *>(prow + c);
-      const float w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+      w[NX] = hi.x;
+      w[NX + 1] = hi.y;
+      w[NX + 2] = hi.z;
+      w[NX + 3] = hi.w;
       const float pk[4] = {p4.x, p4.y, p4.z, p4.w};
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        d0 = fmaf(pk[k], w[k], d0);
-        d1 = fmaf(pk[k], w[k + 1], d1);
-        d2 = fmaf(pk[k], w[k + 2], d2);
-        d3 = fmaf(pk[k], w[k + 3], d3);
-      }
-      lo = hi;
+      for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int i = 0; i < NX; ++i) d[i] = fmaf(pk[k], w[i + k], d[i]);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) w[i] = w[i + 4];
     }
-    acc[0] += (double)d0;
-    acc[1] += (double)d1;
-    acc[2] += (double)d2;
-    acc[3] += (double)d3;
+#pragma unroll
+    for (int i = 0; i < NX; ++i) acc[i] += (double)d[i];
   }
   if (RS > 1) {
-    double *part = reinterpret_cast<double *>(Pf + K * Kp);  // [RS - 1][256][4]
+    // [RS - 1][NX][TG]; the tile and PSF sizes are multiples of 4 floats, so 16-byte aligned
+    double *part = reinterpret_cast<double *>(Pf + K * Kp);
     if (grp > 0) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) part[((grp - 1) * 256 + lt) * 4 + i] = acc[i];
+      for (int i = 0; i < NX; ++i) part[((grp - 1) * NX + i) * TG + lt] = acc[i];
     }
     __syncthreads();
     if (grp > 0) return;
-#pragma unroll
+#pragma unroll 2
     for (int g = 1; g < RS; ++g)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc[i] += part[((g - 1) * 256 + lt) * 4 + i];
+      for (int i = 0; i < NX; ++i) acc[i] += part[((g - 1) * NX + i) * TG + lt];
   }
   const int y = oy + ty;
   if (y < y1r) {
+    float *out = G + (size_t)b * N * N + (size_t)y * N + ox + tx;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int x = ox + 4 * tx4 + i;
-      if (x < x1r) G[(size_t)b * N * N + (size_t)y * N + x] = (float)acc[i];
-    }
+    for (int i = 0; i < NX; ++i)
+      if (ox + tx + i < x1r) out[i] = (float)acc[i];
   }
 }
 
-template <int RS>
-__global__ void __launch_bounds__(256 * RS) k_conv_direct(ConvArgs a) { conv_direct_body<RS>(a); }
-template <int RS>
-__global__ void __launch_bounds__(256 * RS) k_conv_direct_job(const ConvArgs *__restrict__ t, int j) {
+template <int RS, int CT_Y>
+__global__ void __launch_bounds__(conv_group(CT_Y) * RS) k_conv_direct(ConvArgs a) { conv_direct_body<RS, CT_Y>(a); }
+template <int RS, int CT_Y>
+__global__ void __launch_bounds__(conv_group(CT_Y) * RS) k_conv_direct_job(const ConvArgs *__restrict__ t, int j) {
   const ConvArgs a = t[j];
-  conv_direct_body<RS>(a);
+  conv_direct_body<RS, CT_Y>(a);
 }
 
 // Blocks per region side: the largest region of a grid x grid split is ceil(N / grid) wide.
-static dim3 conv_grid(int B, int N, int grid) {
+static dim3 conv_grid(int B, int N, int grid, int rows) {
   const int side = (N + grid - 1) / grid;
-  return dim3((side + CT_X - 1) / CT_X, (side + CT_Y - 1) / CT_Y, B * grid * grid);
+  return dim3((side + CT_X - 1) / CT_X, (side + rows - 1) / rows, B * grid * grid);
 }
 
-// Row splits when one-group blocks would leave most SIMDs with a single wave (fewer than 2048
-// blocks) and the split's LDS fits.
-static bool conv_use_split(dim3 g, int K) {
-  return (int64_t)g.x * g.y * g.z < 2048 && conv_split_lds_bytes(K) <= 160 * 1024;
+template <int RS_, int ROWS_>
+struct ConvShape {
+  static constexpr int RS = RS_, ROWS = ROWS_;
+};
+// Calls launch(shape, grid, LDS bytes): row splits when one-group blocks would leave SIMDs with a
+// single wave (fewer than 1,024 blocks) and the split's sums fit, else the taller tile, or for the
+// widest PSFs the shorter one.
+template <typename F>
+static hipError_t conv_launch(int B, int N, int K, int grid, F &&launch) {
+  constexpr size_t most = 160 * 1024;
+  const dim3 g1 = conv_grid(B, N, grid, CT_Y1), gs = conv_grid(B, N, grid, CT_YS);
+  const size_t split = conv_lds_bytes(K, CONV_RS, CT_YS), tall = conv_lds_bytes(K, 1, CT_Y1), low = conv_direct_lds_bytes(K);
+  if ((int64_t)g1.x * g1.y * g1.z < 1024 && split <= most)
+    launch(ConvShape<CONV_RS, CT_YS>{}, gs, split);
+  else if (tall <= most)
+    launch(ConvShape<1, CT_Y1>{}, g1, tall);
+  else if (low <= most)
+    launch(ConvShape<1, CT_YS>{}, gs, low);
+  else
+    return hipErrorInvalidValue;
+  return hipGetLastError();
 }
 
 hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t s) {
-  const size_t lds = conv_direct_lds_bytes(a.K);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  const dim3 g = conv_grid(a.B, a.N, a.grid);
-  if (conv_use_split(g, a.K))
-    hipLaunchKernelGGL(k_conv_direct<CONV_RS>, g, dim3(256 * CONV_RS), conv_split_lds_bytes(a.K), s, a);
-  else
-    hipLaunchKernelGGL(k_conv_direct<1>, g, dim3(256), lds, s, a);
-  return hipGetLastError();
+  return conv_launch(a.B, a.N, a.K, a.grid, [&](auto shape, dim3 g, size_t lds) {
+    using S = decltype(shape);
+    hipLaunchKernelGGL((k_conv_direct<S::RS, S::ROWS>), g, dim3(conv_group(S::ROWS) * S::RS), lds, s, a);
+  });
 }
 hipError_t launch_conv_direct_job(const ConvArgs *table, int j, int B, int N, int K, int grid, hipStream_t s) {
-  const size_t lds = conv_direct_lds_bytes(K);
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  const dim3 g = conv_grid(B, N, grid);
-  if (conv_use_split(g, K))
-    hipLaunchKernelGGL(k_conv_direct_job<CONV_RS>, g, dim3(256 * CONV_RS), conv_split_lds_bytes(K), s, table, j);
-  else
-    hipLaunchKernelGGL(k_conv_direct_job<1>, g, dim3(256), lds, s, table, j);
-  return hipGetLastError();
+  return conv_launch(B, N, K, grid, [&](auto shape, dim3 g, size_t lds) {
+    using S = decltype(shape);
+    hipLaunchKernelGGL((k_conv_direct_job<S::RS, S::ROWS>), g, dim3(conv_group(S::ROWS) * S::RS), lds, s, table, j);
+  });
 }
 
 // ---------------------------------------------------------------------------------------

@@ -21,9 +21,9 @@ namespace pcmd {
 
 int psf_grid_of(const pcmd_obs *o) { return o->psf_grid == 4 ? 4 : 1; }
 
-// AUTO: the direct sum costs N^2 K^2 FMAs per band (15.5e12 FMA/s measured), the FFT chain
+// AUTO: the direct sum costs N^2 K^2 FMAs per band (36.8e12 FMA/s measured on large images), the FFT chain
 // ~7 launches and O(N^2 log N) FP64 work; measured on MI355X the direct path wins for K = 31 at
-// every size tried (256^2: ~12 against 52 us; 4096^2: 3.1 against 8.7 ms) and the FFT for K = 63
+// every size tried (256^2: 16 against 38 us; 4096^2: 1.3 against 3.0 ms) and the FFT for K = 63
 // from 512^2 up, so AUTO takes the FFT from K = 48 on.
 bool uses_fft(const pcmd_obs *o) {
   return o->psf_k > 1 && (o->conv_path == PCMD_CONV_FFT ||

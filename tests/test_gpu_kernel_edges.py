@@ -180,3 +180,42 @@ def test_adam_ragged_layers(ctx, dims):
         assert torch.equal(net.w[ow:ow + a * b].view(b, a), w)
         assert torch.equal(net.wt[ow:ow + a * b].view(a, b), w.t())
         o, ow = o + a * b + b, ow + a * b
+
+
+# Direct convolution at its tile edges: eight columns a thread, 64 x 16 tiles of eight row groups (small
+# images), 64 x 32 (more than 1,024 of them), 64 x 16 with one group (the widest PSFs), PSFs of fewer
+# rows than groups, sides far below a tile, the sub-pixel grid's ragged regions.  FP32 products of
+# positive terms: K 2^-24 per row, FP64 over rows, one rounding of the result.
+@pytest.mark.parametrize("N,K,B,grid", [(9, 9, 2, 1), (5, 3, 1, 1), (63, 31, 3, 1), (65, 7, 4, 1), (130, 127, 1, 1), (129, 119, 1, 1),
+                                        (131, 93, 2, 1), (50, 15, 3, 4), (1030, 5, 3, 1), (2060, 3, 1, 1)])
+def test_direct_convolution_tiles(ctx, N, K, B, grid):
+    from oracle import psf as opsf
+    r = np.random.default_rng(N * 131 + K)
+    P_ = r.uniform(0.0, 1.0, (B, 16, K, K) if grid == 4 else (B, K, K))
+    P_ = (P_ / P_.sum(axis=(-2, -1), keepdims=True)).astype(np.float32)
+    lam = np.array([0.7, 0.01])
+    f32 = (10.0 ** r.uniform(-2.0, 0.0, (B, 2))).astype(np.float32)
+    import paper_1904_00011_amd as P
+    obs = si.Obs(nim=N, seed=5, dmod=0.0, dust_model=0, psf=P_, noise_model=0, noise_sigma_mag=(0.0,) * 4, exptime=(1.0,) * 4,
+                 zp=(25.0,) * 4, sky=(0.0,) * 4, dust_R=(1.0,) * 4)
+    from tests import parity_utils as pu
+    print(f"[case] direct convolution N={N} K={K} B={B} grid={grid}", flush=True)
+    if K > 117:  # refused by the direct path as before where the tile does not fit
+        if 4 * ((16 + K - 1) * (64 + K + 5) + K * (K + 1)) > 160 * 1024:
+            with pytest.raises(P.PcmdError):
+                pu.gpu_simulate(ctx, lam, f32, obs, conv_path=P.CONV_DIRECT)
+            return
+    got = pu.gpu_simulate(ctx, lam, f32, obs, conv_path=P.CONV_DIRECT)
+    F = got["flux_pre"].astype(np.float64).reshape(B, N, N)
+    if grid == 4:
+        want = opsf.convolve_periodic_subpixel(F, P_)
+    else:  # the periodic sum by FFT in FP64: its own error is ~1e-15 of the largest value
+        want = np.empty_like(F)
+        h = (K - 1) // 2
+        for b in range(B):
+            w = np.zeros((N, N))
+            for u in range(K):
+                np.add.at(w, ((u - h) % N, (np.arange(K) - h) % N), P_[b, u].astype(np.float64))
+            want[b] = np.fft.irfft2(np.fft.rfft2(F[b]) * np.fft.rfft2(w), s=(N, N))
+    bound = (K + 2) * 2.0 ** -24 * np.abs(want) + 1e-13 * F.max()
+    assert np.all(np.abs(got["flux_psf"].reshape(B, N, N) - want.reshape(B, N, N)) <= bound)
