@@ -935,45 +935,6 @@ hipError_t launch_adam(AdamArgs a, hipStream_t s) {
 constexpr int SLL_THREADS = 1024, SLL_REG = 10, SLL_BLOCKS = 512;
 constexpr int SLL_SAMPLES = 64;  // samples per block, at most
 
-// exp(x) for x <= 0 (NaN stays): Cody and Waite's reduction x = k ln 2 + r, |r| <= ln 2 / 2, and
-// the Taylor polynomial of degree 13 (its remainder is below 2^-57); 0 below -745.
-__device__ __forceinline__ double exp_nonpos(double x) {
-  x = x < -800.0 ? -800.0 : x;
-  const double k = rint(x * 1.4426950408889634);
-  double r = fma(k, -0.6931471805599453, x);   // ln 2 rounded to FP64 ...
-  r = fma(k, -2.3190468138462996e-17, r);      // ... and the rest of it
-  // p = p r + c with c in scalar registers (the compiler copies each addend to a vector register first,
-  // and keeps the copies until they spill)
-  double p = 1.0 / 6227020800.0;
-  auto step = [&](double c) { asm("v_fma_f64 %0, %1, %2, %3" : "=v"(p) : "v"(p), "v"(r), "s"(c)); };
-  step(1.0 / 479001600.0);
-  step(1.0 / 39916800.0);
-  step(1.0 / 3628800.0);
-  step(1.0 / 362880.0);
-  step(1.0 / 40320.0);
-  step(1.0 / 5040.0);
-  step(1.0 / 720.0);
-  step(1.0 / 120.0);
-  step(1.0 / 24.0);
-  step(1.0 / 6.0);
-  step(0.5);
-  step(1.0);
-  step(1.0);
-  return ldexp(p, (int)k);
-}
-
-// ln x of a positive normal x = m 2^e, m in [1/2, 1): one step of Halley's iteration for exp(y) = m, y +
-// 2 (m - exp y) / (m + exp y), from the FP32 logarithm (its error, below 2^-20, comes out cubed).  The
-// library's logarithm holds a dozen constants in vector registers across the kernel's loop.
-__device__ __forceinline__ double ln_pos(double x) {
-  const double m = __builtin_amdgcn_frexp_mant(x);
-  const double e = (double)__builtin_amdgcn_frexp_exp(x);
-  const double y = (double)__builtin_amdgcn_logf((float)m) * 0.6931471805599453;
-  const double E = exp_nonpos(y);
-  const double z = y + 2.0 * (m - E) / (m + E);
-  return fma(e, 0.6931471805599453, fma(e, 2.3190468138462996e-17, z));
-}
-
 // ln k! for k >= 1000 by Stirling's series in x = k + 1 (the first term left out is below 1e-18).
 __device__ __forceinline__ double ln_factorial_large(uint32_t k) {
   const double x = (double)k + 1.0, r = 1.0 / x;

@@ -548,12 +548,7 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
   na.G = Gp;
   na.mags = mags;
   na.noise_model = o->noise_model;
-  for (int b = 0; b < PCMD_MAX_BANDS; ++b) {
-    na.sigma[b] = b < B ? o->noise_sigma_mag[b] : 0.0;
-    na.exptime[b] = b < B ? o->exptime[b] : 1.0;
-    na.zp[b] = b < B ? o->zp[b] : 0.0;
-    na.sky[b] = b < B ? o->sky[b] : 0.0;
-  }
+  noise_bands(&na, o, B);
   na.k0 = k0;
   na.k1 = k1;
   e = launch_noise_mag(na, s);

@@ -359,12 +359,7 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
     nn.G = ji.K > 1 ? G : F;
     nn.mags = mags;
     nn.noise_model = o->noise_model;
-    for (int b = 0; b < PCMD_MAX_BANDS; ++b) {
-      nn.sigma[b] = b < B ? o->noise_sigma_mag[b] : 0.0;
-      nn.exptime[b] = b < B ? o->exptime[b] : 1.0;
-      nn.zp[b] = b < B ? o->zp[b] : 0.0;
-      nn.sky[b] = b < B ? o->sky[b] : 0.0;
-    }
+    noise_bands(&nn, o, B);
     nn.k0 = k0;
     nn.k1 = k1;
     na[j] = nn;
@@ -467,7 +462,7 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
     const JobInfo &ji = p->info[j];
     e = launch_reduce_job(ra, j, ji.npx, ji.B, s);
     if (e == hipSuccess && ji.K > 1) e = launch_conv_direct_job(ca, j, ji.B, ji.N, ji.K, ji.grid, s);
-    if (e == hipSuccess) e = launch_noise_mag_job(na, j, ji.npx, s);
+    if (e == hipSuccess) e = launch_noise_mag_job(na, j, ji.npx, ji.B, s);
   }
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) e = launch_hess_job(ha, j, p->info[j].npx, p->nbins, s);
   if (e == hipSuccess) e = launch_loglike_jobs(la, p->n_jobs, p->nbins, s);

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
 
@@ -164,6 +165,18 @@ inline uint32_t split_q_of(const pcmd_obs *o) {
   if (q > 4294967295.0) q = 4294967295.0;
   if (q < 0.0) q = 0.0;
   return (uint32_t)q;
+}
+
+// Bands' noise parameters (neutral values past B).
+inline void noise_bands(NoiseArgs *n, const pcmd_obs *o, int B) {
+  for (int b = 0; b < PCMD_MAX_BANDS; ++b) {
+    n->sigma[b] = b < B ? o->noise_sigma_mag[b] : 0.0;
+    n->zp[b] = b < B ? o->zp[b] : 0.0;
+    n->sky[b] = b < B ? o->sky[b] : 0.0;
+    const double t = b < B ? o->exptime[b] : 1.0;
+    n->gain[b] = t * pow(10.0, 0.4 * n->zp[b]);
+    n->inv_t[b] = 1.0 / t;
+  }
 }
 
 // Validate one simulation's arguments (shapes, scalars, pointers).  Returns PCMD_OK or an error

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace pcmd {
@@ -103,9 +104,104 @@ __device__ __forceinline__ double u01_f64(uint32_t w) {
   return ((double)w + 0.5) * 2.3283064365386963e-10;  // 2^-32
 }
 
+// ---------------------------------------------------------------------------------------
+// FP64 elementary functions for the ranges used here, with polynomial coefficients in scalar
+// registers: the library's versions keep a dozen constants in vector registers each and handle every
+// argument.  Each is within about 2 units of the last place.
+// ---------------------------------------------------------------------------------------
+
+// p r + c with a wave-uniform c
+__device__ __forceinline__ double fma_uniform(double p, double r, double c) {
+  double o;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(o) : "v"(p), "v"(r), "s"(c));
+  return o;
+}
+
+// exp(r), |r| <= ln 2 / 2: the Taylor polynomial of degree 13 (its remainder is below 2^-57).
+__device__ __forceinline__ double exp_taylor(double r) {
+  double p = 1.0 / 6227020800.0;
+  p = fma_uniform(p, r, 1.0 / 479001600.0);
+  p = fma_uniform(p, r, 1.0 / 39916800.0);
+  p = fma_uniform(p, r, 1.0 / 3628800.0);
+  p = fma_uniform(p, r, 1.0 / 362880.0);
+  p = fma_uniform(p, r, 1.0 / 40320.0);
+  p = fma_uniform(p, r, 1.0 / 5040.0);
+  p = fma_uniform(p, r, 1.0 / 720.0);
+  p = fma_uniform(p, r, 1.0 / 120.0);
+  p = fma_uniform(p, r, 1.0 / 24.0);
+  p = fma_uniform(p, r, 1.0 / 6.0);
+  p = fma_uniform(p, r, 0.5);
+  p = fma_uniform(p, r, 1.0);
+  return fma_uniform(p, r, 1.0);
+}
+
+// exp(x) for x <= 0 (NaN stays): Cody and Waite's reduction x = k ln 2 + r, |r| <= ln 2 / 2; 0 below
+// -745.
+__device__ __forceinline__ double exp_nonpos(double x) {
+  x = x < -800.0 ? -800.0 : x;
+  const double k = rint(x * 1.4426950408889634);
+  double r = fma(k, -0.6931471805599453, x);  // ln 2 rounded to FP64 ...
+  r = fma(k, -2.3190468138462996e-17, r);     // ... and the rest of it
+  return ldexp(exp_taylor(r), (int)k);
+}
+
+// 10^x (infinite above 308, 0 below -324, NaN stays): x = k log10 2 + r, exp(r ln 10).
+__device__ __forceinline__ double exp10_any(double x) {
+  x = x < -400.0 ? -400.0 : x > 400.0 ? 400.0 : x;
+  const double k = rint(x * 3.321928094887362);
+  double r = fma(k, -0.3010299956639812, x);  // log10 2 rounded to FP64 ...
+  r = fma(k, 2.8037281277851704e-18, r);      // ... and the rest of it
+  return ldexp(exp_taylor(r * 2.302585092994046), (int)k);
+}
+
+// ln x of a positive x = m 2^e, m in [1 / sqrt 2, sqrt 2) (infinity and NaN stay): one step of Halley's
+// iteration for exp(y) = m, y + 2 (m - exp y) / (m + exp y), from the FP32 logarithm (its error comes
+// out cubed).  The quotient is near 1e-7, so that a reciprocal with one Newton step (2^-40) leaves 1e-19.
+__device__ __forceinline__ double ln_pos(double x) {
+  double m = __builtin_amdgcn_frexp_mant(x);
+  int e = __builtin_amdgcn_frexp_exp(x);
+  const bool lo = m < 0.7071067811865476;
+  m = lo ? m + m : m;
+  e = lo ? e - 1 : e;
+  const double y = (double)__builtin_amdgcn_logf((float)m) * 0.6931471805599453;
+  const double E = exp_taylor(y), d = m + E;
+  double q = __builtin_amdgcn_rcp(d);
+  q = fma(q, fma(-d, q, 1.0), q);
+  const double z = fma((m - E) + (m - E), q, y);
+  const double l = fma((double)e, 0.6931471805599453, fma((double)e, 2.3190468138462996e-17, z));
+  return x < INFINITY ? l : x;
+}
+
+// cos(2 pi u) for u in (0, 1): 4 u = q + f with |f| <= 1/2 exactly, then the Taylor polynomials of the
+// sine and cosine on |pi f / 2| <= pi / 4 (remainders below 2^-54).
+__device__ __forceinline__ double cos_2pi(double u) {
+  const double v = 4.0 * u, q = rint(v);
+  const double t = (v - q) * 1.5707963267948966, t2 = t * t;
+  double s = 1.0 / 355687428096000.0;  // 1 / 17!
+  s = fma_uniform(s, t2, -1.0 / 1307674368000.0);
+  s = fma_uniform(s, t2, 1.0 / 6227020800.0);
+  s = fma_uniform(s, t2, -1.0 / 39916800.0);
+  s = fma_uniform(s, t2, 1.0 / 362880.0);
+  s = fma_uniform(s, t2, -1.0 / 5040.0);
+  s = fma_uniform(s, t2, 1.0 / 120.0);
+  s = fma_uniform(s, t2, -1.0 / 6.0);
+  s = fma(s * t2, t, t);
+  double c = 1.0 / 20922789888000.0;  // 1 / 16!
+  c = fma_uniform(c, t2, -1.0 / 87178291200.0);
+  c = fma_uniform(c, t2, 1.0 / 479001600.0);
+  c = fma_uniform(c, t2, -1.0 / 3628800.0);
+  c = fma_uniform(c, t2, 1.0 / 40320.0);
+  c = fma_uniform(c, t2, -1.0 / 720.0);
+  c = fma_uniform(c, t2, 1.0 / 24.0);
+  c = fma_uniform(c, t2, -0.5);
+  c = fma_uniform(c, t2, 1.0);
+  const int qi = (int)q & 3;  // cos, -sin, -cos, sin
+  const double r = qi & 1 ? s : c;
+  return qi == 1 || qi == 2 ? -r : r;
+}
+
 __device__ __forceinline__ double box_muller(uint32_t w0, uint32_t w1) {
-  const double u1 = u01_f64(w0), u2 = u01_f64(w1);
-  return sqrt(-2.0 * log(u1)) * cos(6.283185307179586 * u2);
+  return sqrt(-2.0 * ln_pos(u01_f64(w0))) * cos_2pi(u01_f64(w1));
 }
 
 // ---------------------------------------------------------------------------------------

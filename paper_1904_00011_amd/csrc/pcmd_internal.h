@@ -190,7 +190,8 @@ struct NoiseArgs {
   const float *G;  // [B][npx]
   float *mags;     // [B][npx]
   int noise_model;
-  double sigma[PCMD_MAX_BANDS], exptime[PCMD_MAX_BANDS], zp[PCMD_MAX_BANDS], sky[PCMD_MAX_BANDS];
+  double sigma[PCMD_MAX_BANDS], zp[PCMD_MAX_BANDS], sky[PCMD_MAX_BANDS];
+  double gain[PCMD_MAX_BANDS], inv_t[PCMD_MAX_BANDS];  // exposure time 10^(0.4 zp), 1 / exposure time
   uint32_t k0, k1;
 };
 
@@ -254,7 +255,7 @@ size_t conv_direct_lds_bytes(int K);
 hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t s);
 hipError_t launch_conv_direct_job(const ConvArgs *table, int j, int B, int N, int K, int grid, hipStream_t s);
 hipError_t launch_noise_mag(const NoiseArgs &a, hipStream_t s);
-hipError_t launch_noise_mag_job(const NoiseArgs *table, int j, int npx, hipStream_t s);
+hipError_t launch_noise_mag_job(const NoiseArgs *table, int j, int npx, int B, hipStream_t s);
 hipError_t launch_copy_f32(const float *src, float *dst, int64_t n, hipStream_t s);
 
 // k_fft.hip

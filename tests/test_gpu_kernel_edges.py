@@ -219,3 +219,35 @@ def test_direct_convolution_tiles(ctx, N, K, B, grid):
             want[b] = np.fft.irfft2(np.fft.rfft2(F[b]) * np.fft.rfft2(w), s=(N, N))
     bound = (K + 2) * 2.0 ** -24 * np.abs(want) + 1e-13 * F.max()
     assert np.all(np.abs(got["flux_psf"].reshape(B, N, N) - want.reshape(B, N, N)) <= bound)
+
+
+# Reduction over slices on both sides of the size from which a thread takes all bands, and the noise
+# kernel's own logarithm, power and cosine.  Flux: as for the mixed groups.  Magnitudes are FP64 rounded
+# to FP32 (2^-24); a few units of 2^-53 of counts + sky become 2.5 / ln 10 times as much of c2 (the net
+# counts), which is near zero where the noise takes nearly all of them.
+@pytest.mark.parametrize("N", [37, 511, 512])
+@pytest.mark.parametrize("dust,noise,sky", [(0, 0, 0.0), (1, 1, 0.0), (2, 2, 50.0)])
+def test_reduction_and_noise(ctx, N, dust, noise, sky):
+    from oracle import noise as on
+    from tests import parity_utils as pu
+    lam = np.array([0.7, 0.2, 3.0])
+    f32 = (10.0 ** np.array([[-3.0, -9.0, -11.0], [-2.0, -5.0, -9.5], [-4.0, -9.0, -8.0]])).astype(np.float32)
+    obs = si.Obs(nim=N, seed=123 + N, dmod=2.0, dust_model=dust, dust_mu=-1.0, dust_sigma=0.5, dust_frac=0.4,
+                 dust_R=(3.6, 1.9, 1.3, 1.0), psf=None, noise_model=noise, noise_sigma_mag=(0.02, 0.5, 0.0, 0.1),
+                 exptime=(3000.0, 10.0, 1.0, 1.0), zp=(25.0, 24.0, 22.5, 25.0), sky=(sky,) * 4)
+    print(f"[case] reduction and noise N={N} dust={dust} noise={noise}", flush=True)
+    got = pu.gpu_simulate(ctx, lam, f32, obs)
+    F = op.simulate(lam, f32, obs)["F"]
+    assert np.all(np.abs(got["flux_pre"].reshape(F.shape) - F) <= 2e-7 * np.abs(F))
+    want = on.magnitudes(got["flux_pre"].reshape(F.shape).astype(np.float64), obs)
+    m = got["mags"].reshape(F.shape).astype(np.float64)
+    fin = np.isfinite(want)
+    assert np.array_equal(fin, np.isfinite(m)) and np.all(m[~fin] == np.inf)
+    bound = 1.01 * 2.0 ** -24 * np.abs(want) + 1e-13
+    if noise == 2:
+        for b in range(3):
+            t = obs.exptime[b]
+            c2 = t * 10.0 ** (0.4 * (obs.zp[b] - want[b][fin[b]]))
+            c = got["flux_pre"].reshape(F.shape)[b][fin[b]].astype(np.float64) * t * 10.0 ** (0.4 * obs.zp[b]) + 2 * sky
+            bound[b][fin[b]] += 1.1 * 16 * 2.0 ** -53 * (c + 6.0 * np.sqrt(c)) / c2
+    assert np.all(np.abs(m - want)[fin] <= bound[fin])
