@@ -1053,66 +1053,71 @@ hipError_t launch_sample_persistent(const BatchSampleJob *jobs, int n_jobs, int 
 
 // ---------------------------------------------------------------------------------------
 // Slice reduction + epilogue: F_b = 10^(-0.4 mu_d) (F_clr_b + F_red_b 10^(-0.4 R_b E_p)).
-// One thread per (band, pixel); the partials of all slices are loaded in batches of eight
-// before they are added, in ascending slice order (the order fixes the rounding).
+// The partials of all slices are loaded in batches of eight before they are added, in ascending
+// slice order (the order fixes the rounding).  Small images take a thread per (band, pixel), to
+// have enough waves for the memory's latency; from REDUCE_WIDE pixels on (1,024 blocks, four on
+// every CU) a thread takes all the bands of its pixel, so that the pixel's dust screen (a Philox
+// block, Box-Muller and a power) is drawn once.  4096 x 4096 x 3 with a drawn screen, two
+// slices: 510 -> 344 us, 3.0 TB/s; 256 x 256 x 3, 11 slices, a batch job: 35 -> 25 us.
 // ---------------------------------------------------------------------------------------
 constexpr int RED_BATCH = 8;
+constexpr int REDUCE_WIDE = 262144;
 
-__device__ __forceinline__ void reduce_body(const ReduceArgs &a, int idx) {
-  const int npx = a.npx;
-  if (idx >= a.B * npx) return;
-  const int b = idx / npx, p = idx - b * npx;
-  const size_t plane = (size_t)npx;
+__device__ __forceinline__ void reduce_body(const ReduceArgs &a, int p, int b0, int b1) {
+  if (p >= a.npx) return;
+  const size_t plane = (size_t)a.npx;
   const size_t step = (size_t)a.S * a.B * plane;  // from one slice to the next
-  const float *pc = a.part + (size_t)b * plane + p;
-  const float *pr = pc + (size_t)a.B * plane;  // reddened stream (S == 2)
-  double c = 0.0, r = 0.0;
-  int ch = 0;
-  for (; ch + RED_BATCH <= a.nchunks; ch += RED_BATCH) {
-    double xc[RED_BATCH], xr[RED_BATCH];
+  double ebv = 0.0;
+  if (a.dust_model == PCMD_DUST_SCREEN) {
+    ebv = exp10_any(a.dust_mu);
+  } else if (a.dust_model != PCMD_DUST_NONE) {
+    const u4 w = philox10((uint32_t)p, 0u, TAG_DUST, 0u, a.k0, a.k1);
+    ebv = exp10_any(a.dust_mu + a.dust_sigma * box_muller(w.x, w.y));
+  }
+  for (int b = b0; b < b1; ++b) {
+    const float *pc = a.part + (size_t)b * plane + p;
+    const float *pr = pc + (size_t)a.B * plane;  // reddened stream (S == 2)
+    double c = 0.0, r = 0.0;
+    int ch = 0;
+    for (; ch + RED_BATCH <= a.nchunks; ch += RED_BATCH) {
+      float xc[RED_BATCH], xr[RED_BATCH];
 #pragma unroll
-    for (int k = 0; k < RED_BATCH; ++k) {
-      xc[k] = (double)pc[(size_t)(ch + k) * step];
-      xr[k] = a.S == 2 ? (double)pr[(size_t)(ch + k) * step] : 0.0;
-    }
+      for (int k = 0; k < RED_BATCH; ++k) {
+        xc[k] = pc[(size_t)(ch + k) * step];
+        xr[k] = a.S == 2 ? pr[(size_t)(ch + k) * step] : 0.f;
+      }
 #pragma unroll
-    for (int k = 0; k < RED_BATCH; ++k) {
-      c += xc[k];
-      r += xr[k];
+      for (int k = 0; k < RED_BATCH; ++k) {
+        c += (double)xc[k];
+        r += (double)xr[k];
+      }
     }
-  }
-  for (; ch < a.nchunks; ++ch) {
-    c += (double)pc[(size_t)ch * step];
-    if (a.S == 2) r += (double)pr[(size_t)ch * step];
-  }
-  double F;
-  if (a.dust_model == PCMD_DUST_NONE) {
-    F = a.dist * (c + r);
-  } else {
-    double ebv;
-    if (a.dust_model == PCMD_DUST_SCREEN) {
-      ebv = exp10(a.dust_mu);
-    } else {
-      const u4 w = philox10((uint32_t)p, 0u, TAG_DUST, 0u, a.k0, a.k1);
-      ebv = exp10(a.dust_mu + a.dust_sigma * box_muller(w.x, w.y));
+    for (; ch < a.nchunks; ++ch) {
+      c += (double)pc[(size_t)ch * step];
+      if (a.S == 2) r += (double)pr[(size_t)ch * step];
     }
-    F = a.dist * (c + r * exp10(-0.4 * a.dust_R[b] * ebv));
+    const double F = a.dist * (a.dust_model == PCMD_DUST_NONE ? c + r : c + r * exp10_any(-0.4 * a.dust_R[b] * ebv));
+    a.F[(size_t)b * plane + p] = (float)F;
   }
-  a.F[(size_t)b * plane + p] = (float)F;
 }
 
-__global__ void __launch_bounds__(256) k_reduce(ReduceArgs a) { reduce_body(a, blockIdx.x * blockDim.x + threadIdx.x); }
-__global__ void __launch_bounds__(256) k_reduce_job(const ReduceArgs *__restrict__ t, int j) {
-  const ReduceArgs a = t[j];
-  reduce_body(a, blockIdx.x * blockDim.x + threadIdx.x);
+__global__ void __launch_bounds__(256) k_reduce(ReduceArgs a) {
+  reduce_body(a, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, gridDim.y == 1 ? a.B : blockIdx.y + 1);
 }
+// The record stays in memory: its uniform words are scalar loads, and a copy indexed by the band would
+// lie in scratch.
+__global__ void __launch_bounds__(256) k_reduce_job(const ReduceArgs *__restrict__ t, int j) {
+  reduce_body(t[j], blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, gridDim.y == 1 ? t[j].B : blockIdx.y + 1);
+}
+
+static dim3 reduce_grid(int npx, int B) { return dim3((npx + 255) / 256, npx >= REDUCE_WIDE ? 1 : B); }
 
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3((a.B * a.npx + 255) / 256), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_reduce, reduce_grid(a.npx, a.B), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 hipError_t launch_reduce_job(const ReduceArgs *table, int j, int npx, int B, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_job, dim3((B * npx + 255) / 256), dim3(256), 0, s, table, j);
+  hipLaunchKernelGGL(k_reduce_job, reduce_grid(npx, B), dim3(256), 0, s, table, j);
   return hipGetLastError();
 }
 
