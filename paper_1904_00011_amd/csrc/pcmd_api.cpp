@@ -21,10 +21,10 @@ namespace pcmd {
 
 int psf_grid_of(const pcmd_obs *o) { return o->psf_grid == 4 ? 4 : 1; }
 
-// AUTO: the direct sum costs N^2 K^2 FMAs per band (36.8e12 FMA/s measured on large images), the FFT chain
-// ~7 launches and O(N^2 log N) FP64 work; measured on MI355X the direct path wins for K = 31 at
-// every size tried (256^2: 16 against 38 us; 4096^2: 1.3 against 3.0 ms) and the FFT for K = 63
-// from 512^2 up, so AUTO takes the FFT from K = 48 on.
+// AUTO: the direct sum costs N^2 K^2 FMAs per band (36.8e12 FMA/s measured on large images), the
+// Fourier path three passes over the image in FP64.  K = 31 takes 16 against 17 us at 256^2 and 1.3
+// against 0.7 ms at 4096^2, K = 63 is the Fourier path's from 256^2 up.  The two round differently (FP32
+// row sums against FP64), so the line between them is part of a call's result: it stays at K = 48.
 bool uses_fft(const pcmd_obs *o) {
   return o->psf_k > 1 && (o->conv_path == PCMD_CONV_FFT ||
                           (o->conv_path == PCMD_CONV_AUTO && o->psf_k >= 48 && psf_grid_of(o) == 1 &&

@@ -251,3 +251,38 @@ def test_reduction_and_noise(ctx, N, dust, noise, sky):
             c = got["flux_pre"].reshape(F.shape)[b][fin[b]].astype(np.float64) * t * 10.0 ** (0.4 * obs.zp[b]) + 2 * sky
             bound[b][fin[b]] += 1.1 * 16 * 2.0 ** -53 * (c + 6.0 * np.sqrt(c)) / c2
     assert np.all(np.abs(m - want)[fin] <= bound[fin])
+
+
+# Fourier path at every side it takes (all radices of the last pass, blocks of fewer threads than a wave,
+# bands of a region of two rows), odd PSF sizes up to the side, one PSF and the sub-pixel grid.  FP64
+# transforms: log2 N^2 2^-53 of the image's largest value at most (1e-13 leaves room), one FP32
+# rounding of the result.
+@pytest.mark.parametrize("N,K,B,grid", [(8, 7, 3, 1), (8, 5, 2, 4), (16, 15, 2, 1), (16, 3, 1, 4), (32, 31, 4, 1), (32, 5, 3, 4), (64, 9, 2, 1),
+                                        (128, 127, 1, 1), (256, 31, 3, 1), (256, 11, 1, 4), (512, 63, 2, 1), (1024, 47, 1, 1),
+                                        (2048, 5, 2, 1), (4096, 63, 1, 1)])
+def test_fourier_path_sides(ctx, N, K, B, grid):
+    import paper_1904_00011_amd as P
+    from tests import parity_utils as pu
+    r = np.random.default_rng(N * 7 + K)
+    lam = np.array([0.7, 0.01])
+    f32 = (10.0 ** r.uniform(-2.0, 0.0, (B, 2))).astype(np.float32)
+    for rep in range(2):  # a second PSF: kept spectra are rebuilt
+        psf = r.uniform(0.0, 1.0, (B, 16, K, K) if grid == 4 else (B, K, K))
+        psf = (psf / psf.sum(axis=(-2, -1), keepdims=True)).astype(np.float32)
+        obs = si.Obs(nim=N, seed=5, dmod=0.0, dust_model=0, psf=psf, noise_model=0, noise_sigma_mag=(0.0,) * 4,
+                     exptime=(1.0,) * 4, zp=(25.0,) * 4, sky=(0.0,) * 4, dust_R=(1.0,) * 4)
+        print(f"[case] Fourier path N={N} K={K} B={B} grid={grid}", flush=True)
+        got = pu.gpu_simulate(ctx, lam, f32, obs, conv_path=P.CONV_FFT)
+        F = got["flux_pre"].astype(np.float64).reshape(B, N, N)
+        want = np.empty_like(F)
+        h, side = (K - 1) // 2, N // grid
+        for b in range(B):
+            Fh = np.fft.rfft2(F[b])
+            for k in range(grid * grid):
+                w = np.zeros((N, N))
+                p = psf[b, k] if grid == 4 else psf[b]
+                for u in range(K):
+                    np.add.at(w, ((u - h) % N, (np.arange(K) - h) % N), p[u].astype(np.float64))
+                ys, xs = np.s_[k // grid * side:(k // grid + 1) * side], np.s_[k % grid * side:(k % grid + 1) * side]
+                want[b][ys, xs] = np.fft.irfft2(Fh * np.fft.rfft2(w), s=(N, N))[ys, xs]
+        assert np.all(np.abs(got["flux_psf"].reshape(B, N, N) - want) <= 2.0 ** -24 * np.abs(want) + 1e-13 * F.max())
