@@ -471,7 +471,8 @@ __device__ __forceinline__ uint32_t alias_column_of(uint32_t desc, uint32_t u) {
 __device__ __forceinline__ uint32_t alias_count(uint32_t desc, uint32_t u, uint32_t x) {
   const uint32_t b = (desc >> 8) & 0xFu;
   const uint32_t c = u >> (32u - b);
-  return (desc >> 12) + ((u & (0xFFFFFFFFu >> b)) < (x >> b) ? c : (x & ((1u << b) - 1u)));
+  // r < height, both shifted to the top and r's low b bits set: r 2^b + 2^b - 1 < height 2^b + alias (b >= 1)
+  return (desc >> 12) + (__builtin_amdgcn_alignbit(u, 0xFFFFFFFFu, 32u - b) < x ? c : (x & ((1u << b) - 1u)));
 }
 
 __device__ __forceinline__ uint32_t table_draw(uint32_t desc, uint32_t u, const uint32_t *__restrict__ tab,
@@ -481,72 +482,6 @@ __device__ __forceinline__ uint32_t table_draw(uint32_t desc, uint32_t u, const 
   if ((desc & KIND_MASK) == KIND_ALIAS) return alias_count(desc, u, tab[alias_column_of(desc, u)]);
   const PtrsConst cst = ld_const(pcp);
   return ptrs_draw(cst, p, i, tag, k0, k1, lnfact, failed);
-}
-
-// The thinned entries of quad q0 .. q0 + 3 in the thinned-entry pass (F = 1/2), with the quad's
-// inversion words w: the same counts and sums as the entry-by-entry path, but the column reads of
-// every alias part of the quad (up to eight) are issued before the first is used, so that their
-// latencies overlap instead of adding up.
-template <int B, bool DBG>
-__device__ __forceinline__ void thin_quad(const SampleArgs &a, uint32_t q0, const u4 &w, uint32_t p, bool dbg,
-                                          double (&acc_c)[B], double (&acc_r)[B], uint32_t &ptrs_failed) {
-  const PCMD_CONST EntryRec *rec = (const PCMD_CONST EntryRec *)a.rec;
-  const PCMD_CONST PtrsConst *pc = (const PCMD_CONST PtrsConst *)a.pc;
-  const PCMD_CONST uint32_t *rdesc = (const PCMD_CONST uint32_t *)a.rdesc;
-  uint32_t kk[4], d[4];
-  bool any = false;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    kk[q] = rec[q0 + q].kk;  // q0 + 3 < EP: the table is padded to whole groups
-    d[q] = (kk[q] & FLAG_THIN) ? rdesc[q0 + q] : 0u;
-    any = any || (kk[q] & FLAG_THIN);
-  }
-  if (!any) return;
-  // the quad's reddened-part words: counters (p, i / 4, TAG_RED, 0)
-  const u4 wr = philox10(p, q0 >> 2, TAG_RED, 0u, a.k0, a.k1);
-  uint32_t x0[4], x1[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const size_t i = q0 + (uint32_t)q;
-    x0[q] = 0u;
-    x1[q] = 0u;
-    if (!(kk[q] & FLAG_THIN)) continue;
-    if ((kk[q] & KIND_MASK) == KIND_ALIAS) x0[q] = a.alias[i * 2 * ALIAS_COLS + alias_column_of(kk[q], word_of(w, q))];
-    if ((d[q] & KIND_MASK) == KIND_ALIAS)
-      x1[q] = a.alias[(i * 2 + 1) * ALIAS_COLS + alias_column_of(d[q], word_of(wr, q))];
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    if (!(kk[q] & FLAG_THIN)) continue;
-    const uint32_t i = q0 + (uint32_t)q;
-    const uint32_t nc = (kk[q] & KIND_MASK) == KIND_ALIAS
-                            ? alias_count(kk[q], word_of(w, q), x0[q])
-                            : ptrs_draw(ld_const(pc + 2 * (size_t)i), p, i, TAG_PTRS, a.k0, a.k1, a.lnfact, ptrs_failed);
-    const uint32_t red = (d[q] & KIND_MASK) == KIND_ALIAS
-                             ? alias_count(d[q], word_of(wr, q), x1[q])
-                             : ptrs_draw(ld_const(pc + 2 * (size_t)i + 1), p, i, TAG_PTRS_RED, a.k0, a.k1, a.lnfact,
-                                         ptrs_failed);
-    if (DBG && dbg) {
-      const size_t o = (size_t)((int64_t)p - a.px0) * (size_t)a.E + i;
-      a.dbg_counts[o] = nc + red;
-      if (a.dbg_red) a.dbg_red[o] = red;
-    }
-    if (!wave_any(nc + red != 0u)) continue;
-    const PCMD_CONST double *f = rec[i].fl;
-    double fv[B];
-#pragma unroll
-    for (int b = 0; b < B; ++b) fv[b] = f[b];
-    {
-      const double dc = (double)nc;
-#pragma unroll
-      for (int b = 0; b < B; ++b) acc_c[b] = fma(dc, fv[b], acc_c[b]);
-    }
-    if (wave_any(red != 0u)) {
-      const double dr = (double)red;
-#pragma unroll
-      for (int b = 0; b < B; ++b) acc_r[b] = fma(dr, fv[b], acc_r[b]);
-    }
-  }
 }
 
 // Adds f to acc in the lanes of `mask` only.  Called with all 64 lanes of the wave active (a tile's
@@ -861,13 +796,20 @@ __device__ __forceinline__ void sample_tile(const PCMD_CONST SampleArgs *ap, uin
   }
 }
 
-// The thinned entries of a tile (PASS_THIN), added to the partial sums that PASS_MAIN stored: a pass
-// of its own, so that the thinning code (live state that slows the common path) is not in the main
-// pass.
+// The thinned entries of a tile (PASS_THIN: F = 1/2), added to the partial sums that PASS_MAIN stored:
+// a pass of its own, so that the thinning code (live state that slows the common path) is not in the
+// main pass.  The two halves of an entry have one lambda, so one rule and one table serve both.
+//
+// Bound by vector-instruction issue: per entry two words of Philox (17 instructions), two column reads
+// and counts (8 each) and the additions.  The column reads of a quad are issued before the first is used;
+// rejection draws (halves from ALIAS_MAX on) are in one place, where sixteen inlined copies made the code
+// larger than the instruction cache.  4096 x 4096
+// pixels, 55 thinned entries: 1969 -> 1390 us; 512 x 512, about 10,000 of them: 4.50 -> 2.99 ms.
 template <int B, bool DBG>
-__device__ __forceinline__ void sample_thin_tile(const SampleArgs &a, uint32_t p, int chunk) {
-  const bool live = p < (uint32_t)a.npx;
-  const bool dbg = DBG && live && (int64_t)p >= a.px0 && (int64_t)p < a.px1;
+__device__ __forceinline__ void sample_thin_tile(const PCMD_CONST SampleArgs *ap, uint32_t p, int chunk) {
+  const int E = ap->E, nchunks = ap->nchunks;
+  const uint32_t k0 = ap->k0, k1 = ap->k1;
+  const bool live = p < (uint32_t)ap->npx;
   double acc_c[B], acc_r[B];
 #pragma unroll
   for (int b = 0; b < B; ++b) {
@@ -875,22 +817,82 @@ __device__ __forceinline__ void sample_thin_tile(const SampleArgs &a, uint32_t p
     acc_r[b] = 0.0;
   }
   uint32_t ptrs_failed = 0u;  // per lane, kept in a vector register
-  for_groups(a.grp, a.E, a.nchunks, chunk, GRP_THIN, [&](int gi, uint32_t) {
-    // inversion words of the group's two quads: counters (p, i / 4, TAG_MAIN, 0)
-    const u4 wa = philox10(p, (uint32_t)(2 * gi), TAG_MAIN, 0u, a.k0, a.k1);
-    const u4 wb = philox10(p, (uint32_t)(2 * gi + 1), TAG_MAIN, 0u, a.k0, a.k1);
-    __builtin_amdgcn_sched_barrier(0);
+  auto add = [&](const PCMD_CONST EntryRec *r, uint32_t i, uint32_t nc, uint32_t red) {
+    double fv[B];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-      thin_quad<B, DBG>(a, (uint32_t)(gi * GRP + 4 * h), h ? wb : wa, p, dbg, acc_c, acc_r, ptrs_failed);
+    for (int b = 0; b < B; ++b) fv[b] = r->fl[b];
+    const double dc = (double)nc, dr = (double)red;  // a lane without stars adds exact zeros
+#pragma unroll
+    for (int b = 0; b < B; ++b) fma_in_place(acc_c[b], dc, fv[b]);
+#pragma unroll
+    for (int b = 0; b < B; ++b) fma_in_place(acc_r[b], dr, fv[b]);
+    if (DBG) {
+      const PCMD_CONST SampleArgs *ca = rare(ap);
+      if (live && (int64_t)p >= ca->px0 && (int64_t)p < ca->px1) {
+        const size_t o = (size_t)((int64_t)p - ca->px0) * (size_t)ca->E + i;
+        ca->dbg_counts[o] = nc + red;
+        if (ca->dbg_red) ca->dbg_red[o] = red;
+      }
+    }
+  };
+  for_groups(ap->grp, E, nchunks, chunk, GRP_THIN, [&](int gi, uint32_t flags) {
+    const PCMD_CONST EntryRec *rec = (const PCMD_CONST EntryRec *)rare(ap)->rec + gi * GRP;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint32_t thin = (flags / GRP_THIN_ENTRY >> (4 * h)) & 0xFu;
+      if (thin == 0u) continue;
+      uint32_t kk[4], tab = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) kk[q] = rec[4 * h + q].kk;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) tab |= (kk[q] & KIND_MASK) == KIND_ALIAS ? 1u << q : 0u;
+      tab &= thin;
+      if (tab != 0u) {
+        const uint32_t *alias = rare(ap)->alias + (size_t)(gi * GRP + 4 * h) * (2 * ALIAS_COLS);
+        const u4 w = philox10(p, (uint32_t)(2 * gi + h), TAG_MAIN, 0u, k0, k1);
+        const u4 wr = philox10(p, (uint32_t)(2 * gi + h), TAG_RED, 0u, k0, k1);
+        uint32_t x0[4], x1[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          x0[q] = 0u;
+          x1[q] = 0u;
+          if (tab >> q & 1u) {
+            // byte offsets in 32 bits from a scalar base
+            const char *col = (const char *)(alias + q * (2 * ALIAS_COLS));
+            x0[q] = *(const uint32_t *)(col + (alias_column_of(kk[q], word_of(w, q)) << 2));
+            x1[q] = *(const uint32_t *)(col + (alias_column_of(kk[q], word_of(wr, q)) << 2));
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (tab >> q & 1u)
+            add(rec + 4 * h + q, (uint32_t)(gi * GRP + 4 * h + q), alias_count(kk[q], word_of(w, q), x0[q]),
+                alias_count(kk[q], word_of(wr, q), x1[q]));
+      }
+#pragma unroll 1
+      for (uint32_t rej = thin & ~tab; rej != 0u; rej &= rej - 1u) {
+        const int q = 4 * h + (int)__builtin_ctz(rej);
+        const uint32_t i = (uint32_t)(gi * GRP + q);
+        const PCMD_CONST SampleArgs *ca = rare(ap);
+        const PtrsConst c = ld_const((const PCMD_CONST PtrsConst *)ca->pc + 2 * (size_t)i);
+        uint32_t n[2] = {0u, 0u};
+#pragma unroll 1
+        for (int part = 0; part < 2; ++part) {
+          n[1] = n[0];
+          n[0] = ptrs_draw(c, p, i, part ? TAG_PTRS : TAG_PTRS_RED, k0, k1, ca->lnfact, ptrs_failed);
+        }
+        add(rec + q, i, n[0], n[1]);
+      }
+    }
   });
-  if (wave_any(ptrs_failed != 0u) && (threadIdx.x & 63) == 0) atomicOr(a.status, STATUS_PTRS_RETRY);
+  const PCMD_CONST SampleArgs *ca = rare(ap);
+  if (wave_any(ptrs_failed != 0u) && (threadIdx.x & 63) == 0) atomicOr(ca->status, STATUS_PTRS_RETRY);
   if (!live) return;
-  const size_t plane = (size_t)a.npx;
+  const size_t plane = (size_t)ca->npx;
 #pragma unroll
   for (int b = 0; b < B; ++b) {
-    float *pc = a.part + ((size_t)(chunk * 2 + 0) * B + b) * plane + p;
-    float *pr = a.part + ((size_t)(chunk * 2 + 1) * B + b) * plane + p;
+    float *pc = ca->part + ((size_t)(chunk * 2 + 0) * B + b) * plane + p;
+    float *pr = ca->part + ((size_t)(chunk * 2 + 1) * B + b) * plane + p;
     // exact zeros change nothing: a slice without thinned stars skips
     if (acc_c[b] != 0.0) *pc = (float)((double)*pc + acc_c[b]);
     if (acc_r[b] != 0.0) *pr = (float)((double)*pr + acc_r[b]);
@@ -908,13 +910,12 @@ k_sample(SampleArgs a) {
   const int nblk_px = (a.npx + 255) >> 8;
   const int chunk = blockIdx.x / nblk_px;
   const uint32_t p = (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x);
-  if constexpr (PASS == PASS_THIN) {
-    sample_thin_tile<B, DBG>(a, p, chunk);
-  } else {
-    // the arguments where the launch put them (the kernel's only parameter)
-    const PCMD_CONST SampleArgs *ap = (const PCMD_CONST SampleArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  // the arguments where the launch put them (the kernel's only parameter)
+  const PCMD_CONST SampleArgs *ap = (const PCMD_CONST SampleArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  if constexpr (PASS == PASS_THIN)
+    sample_thin_tile<B, DBG>(ap, p, chunk);
+  else
     sample_tile<B, S, DBG, PASS>(ap, p, chunk);
-  }
 }
 
 template <int B, int PASS>
@@ -1019,11 +1020,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
 template <int B>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
 k_sample_thin_job(const BatchSampleJob *__restrict__ jobs, int t) {
-  const SampleArgs a = jobs[t].a;
-  if (a.thin_seen && *(const PCMD_CONST uint32_t *)a.thin_seen != a.gen) return;  // nothing thinned
-  const int nblk_px = (a.npx + 255) >> 8;
+  const PCMD_CONST SampleArgs *ap = &((const PCMD_CONST BatchSampleJob *)jobs)[t].a;
+  if (ap->thin_seen && *(const PCMD_CONST uint32_t *)ap->thin_seen != ap->gen) return;  // nothing thinned
+  const int nblk_px = (ap->npx + 255) >> 8;
   const int chunk = blockIdx.x / nblk_px;
-  sample_thin_tile<B, false>(a, (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x), chunk);
+  sample_thin_tile<B, false>(ap, (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x), chunk);
 }
 
 hipError_t launch_sample_thin_job(const BatchSampleJob *jobs, int t, int B, int npx, int nchunks, hipStream_t s) {
