@@ -14,11 +14,10 @@
 // At low stellar density most blocks draw nothing in every pixel of a wave and cost one Philox
 // block and one compare, instead of the per-entry rule's sixteen Philox blocks.
 //
-// Layout: one lane per pixel as in k_sample; a wave's 64 lanes also hold one block's 64
-// cumulative thresholds and entry fluxes in registers, so each star's binary search and flux
-// gather are cross-lane reads (ds_bpermute) with no LDS allocation.  Slices interleave blocks
-// like k_sample's interleaved 16-entry blocks and write the same partial-sum layout, which
-// k_reduce then sums in the same order.
+// Layout: a wave takes 128 pixels; its 64 lanes also hold one block's 64 cumulative thresholds and
+// entry fluxes in registers, so each star's binary search and flux gather are cross-lane reads
+// (ds_bpermute).  Slices interleave blocks like k_sample's interleaved 16-entry blocks and write the
+// same partial-sum layout, which k_reduce then sums in the same order.
 #include "pcmd_device.h"
 #include "pcmd_internal.h"
 
@@ -100,106 +99,177 @@ hipError_t launch_prep_block_job(const BlockPrepArgs *table, int j, int nb, hipS
   return hipGetLastError();
 }
 
+// Pixels per lane (one packs the queue worse, four leave LDS for three waves per SIMD: 2.07 and 2.72
+// against 1.75 ms), and groups of four stars per pixel queued at a time (two leave LDS for six waves).
+constexpr int BPPL = 2, BQG = 2;
+
+// The stars of one block over a wave's 64 BPPL pixels are queued as tasks (pixel, group of four stars of
+// it, how many), which the lanes then take 64 at a time: a lane per pixel would draw words and search for
+// as many stars as the fullest of 64 pixels has, 18% to 36% of them there.  A task's stars go to
+// any pixel, so the sums are in LDS (FP64 adds; one wave's, in its own order).  Vector issue and LDS are
+// both busy three quarters of the time.  4096 x 4096 x 3 at 10^3 stars per pixel, 12 blocks: 2103 ->
+// 1561 us; 250 x 250, 726 blocks: 260 -> 193 us.
 template <int B, int S, bool DBG>
 __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
-  constexpr int BP = B <= 2 ? 2 : 4;
-  const int nblk_px = (a.npx + 255) >> 8;
+  constexpr int BP = B <= 2 ? 2 : 4, PX = 64 * BPPL;
+  __shared__ double acc_s[4][S * B][PX];
+  __shared__ uint16_t task_s[4][PX * BQG];
+  const int nblk_px = (a.npx + 4 * PX - 1) / (4 * PX);
   const int chunk = blockIdx.x / nblk_px;
-  const uint32_t p = (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x);
+  const int wv = threadIdx.x >> 6;
   const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t p0 = (uint32_t)((blockIdx.x - chunk * nblk_px) * 4 + wv) * PX;  // the wave's first pixel
+  if (p0 >= (uint32_t)a.npx) return;  // whole waves: no barrier below
   const PCMD_CONST BlockRec *brec = (const PCMD_CONST BlockRec *)a.brec;
   const PCMD_CONST uint32_t *thr = (const PCMD_CONST uint32_t *)a.thr;
   const PCMD_CONST PtrsConst *pc = (const PCMD_CONST PtrsConst *)a.pc;
-  const bool live = p < (uint32_t)a.npx;
-  const bool dbg = DBG && live && (int64_t)p >= a.px0 && (int64_t)p < a.px1;
   const bool draw_split = S == 2 && (a.split_mode == SPLIT_HALF || a.split_mode == SPLIT_GENERAL);
-
-  double acc_c[B], acc_r[B];
+  double(*acc)[PX] = acc_s[wv];
+  uint16_t *task = task_s[wv];
 #pragma unroll
-  for (int k = 0; k < B; ++k) {
-    acc_c[k] = 0.0;
-    acc_r[k] = 0.0;
-  }
+  for (int k = 0; k < S * B; ++k)
+#pragma unroll
+    for (int q = 0; q < BPPL; ++q) acc[k][q * 64 + lane] = 0.0;
+
   uint32_t ptrs_failed = 0u;
-  // every lane runs every step below (lanes past the image included), so the cross-lane reads
-  // always find their source lane active; branches on N go through wave-wide votes
+  // every lane runs every step below, so the cross-lane reads always find their source lane active;
+  // branches on the counts go through wave-wide votes
   for (int b = chunk; b < a.nb; b += a.nchunks) {
     const BlockRec r = ld_const(brec + b);
     const uint32_t kind = r.kk & KIND_MASK;
     if (kind == KIND_ZERO) continue;
-    uint32_t n = 0u;
+    uint32_t n[BPPL];
+    bool some = false;
     if (kind == KIND_INV) {
       // N = #{k < K : T_k <= u}, walking up while any lane of the wave is still above
-      const uint32_t u = philox10(p, (uint32_t)b, TAG_BLOCK, 0u, a.k0, a.k1).x;
+      uint32_t u[BPPL];
+#pragma unroll
+      for (int q = 0; q < BPPL; ++q) {
+        u[q] = philox10(p0 + 64u * q + lane, (uint32_t)b, TAG_BLOCK, 0u, a.k0, a.k1).x;
+        n[q] = u[q] >= r.T[0] ? 1u : 0u;
+        some = some || n[q] != 0u;
+      }
+      if (!wave_any(some)) continue;
       const uint32_t K = r.kk >> 8;
-      n = u >= r.T[0] ? 1u : 0u;
-      if (!wave_any(n != 0u)) continue;
       for (uint32_t k = 1; k < K; ++k) {
         const uint32_t t = k < 3 ? r.T[k] : thr[(size_t)b * THR_STRIDE + k];
-        const uint32_t c = u >= t ? 1u : 0u;
-        if (!wave_any(c != 0u)) break;
-        n += c;
+        bool more = false;
+#pragma unroll
+        for (int q = 0; q < BPPL; ++q) {
+          const bool c = u[q] >= t;
+          n[q] += c ? 1u : 0u;
+          more = more || c;
+        }
+        if (!wave_any(more)) break;
       }
     } else {
-      n = ptrs_draw(ld_const(pc + b), p, (uint32_t)b, TAG_BLOCK_PTRS, a.k0, a.k1, a.lnfact, ptrs_failed);
-      if (!wave_any(n != 0u)) continue;
+      const PtrsConst cst = ld_const(pc + b);
+#pragma unroll
+      for (int q = 0; q < BPPL; ++q) {
+        n[q] = ptrs_draw(cst, p0 + 64u * q + lane, (uint32_t)b, TAG_BLOCK_PTRS, a.k0, a.k1, a.lnfact, ptrs_failed);
+        some = some || n[q] != 0u;
+      }
+      if (!wave_any(some)) continue;
     }
-    // the block's thresholds and fluxes, one entry per lane
+    // the block's thresholds and fluxes (FP32 values), one entry per lane
     const int e = b * SBLK + (int)lane;
-    const uint32_t cl = a.cth[(size_t)b * SBLK + lane];
-    double fl[B];
+    const int cl = (int)a.cth[(size_t)b * SBLK + lane];
+    int fl[B];
 #pragma unroll
-    for (int k = 0; k < B; ++k) fl[k] = e < a.E ? a.fl64[(size_t)e * BP + k] : 0.0;
+    for (int k = 0; k < B; ++k) fl[k] = e < a.E ? __float_as_int((float)a.fl64[(size_t)e * BP + k]) : 0;
     const uint32_t istar = r.istar;
-    u4 ws{0u, 0u, 0u, 0u}, wr{0u, 0u, 0u, 0u};
-    for (uint32_t s = 0; wave_any(s < n); ++s) {
-      if ((s & 3u) == 0u) {
-        ws = philox10(p, (uint32_t)b, TAG_STAR, s >> 2, a.k0, a.k1);
-        if (draw_split) wr = philox10(p, (uint32_t)b, TAG_STAR_SPLIT, s >> 2, a.k0, a.k1);
-      }
-      const uint32_t u = word_of(ws, (int)(s & 3u));
-      // number of thresholds <= u among the 64 (sorted; the count stops at 63), then capped at
-      // istar: the first entry whose threshold exceeds u
-      uint32_t pos = 0u;
+    const uint32_t c16 = (uint32_t)__builtin_amdgcn_readlane(cl, 15), c32 = (uint32_t)__builtin_amdgcn_readlane(cl, 31),
+                   c48 = (uint32_t)__builtin_amdgcn_readlane(cl, 47);
 #pragma unroll
-      for (uint32_t st = 32u; st != 0u; st >>= 1) {
-        const uint32_t v = (uint32_t)__shfl((int)cl, (int)(pos + st - 1u), 64);
-        pos += v <= u ? st : 0u;
-      }
-      const uint32_t cat = min(pos, istar);
-      double f[B];
+    for (int q = 0; q < BPPL; ++q)
+      if (p0 + 64u * q + lane >= (uint32_t)a.npx) n[q] = 0u;
+    for (uint32_t g0 = 0;; g0 += BQG) {
+      // task: pixel | (group - g0) << 8 | (stars - 1) << 9
+      uint32_t tasks = 0u;
+      for (uint32_t gg = 0; gg < BQG; ++gg) {
+        const uint32_t before = tasks, first = 4u * (g0 + gg);
 #pragma unroll
-      for (int k = 0; k < B; ++k) f[k] = __shfl(fl[k], (int)cat, 64);
-      const bool red = S == 2 && (a.split_mode == SPLIT_ALL || (draw_split && word_of(wr, (int)(s & 3u)) < a.split_q));
-      if (s < n) {
-        if (red) {
-#pragma unroll
-          for (int k = 0; k < B; ++k) acc_r[k] += f[k];
-        } else {
-#pragma unroll
-          for (int k = 0; k < B; ++k) acc_c[k] += f[k];
+        for (int q = 0; q < BPPL; ++q) {
+          const uint64_t m = __ballot(n[q] > first);
+          if (m == 0ull) continue;
+          const uint32_t at = tasks + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+          if (n[q] > first) task[at] = (uint16_t)(lane + 64u * q + (gg << 8) + ((min(n[q] - first, 4u) - 1u) << 9));
+          tasks += (uint32_t)__popcll(m);
         }
-        if (DBG && dbg && b * SBLK + (int)cat < a.E) {  // always true: cat <= istar, an entry with stars
-          const size_t o = (size_t)((int64_t)p - a.px0) * (size_t)a.E + (size_t)b * SBLK + cat;
-          a.dbg_counts[o] += 1u;
-          if (red && a.dbg_red) a.dbg_red[o] += 1u;
+        if (tasks == before) break;
+      }
+      if (tasks == 0u) break;
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      for (uint32_t t0 = 0; t0 < tasks; t0 += 64u) {
+        const bool mine = t0 + lane < tasks;
+        const uint32_t t = task[mine ? t0 + lane : 0u];
+        const uint32_t c = mine ? (t >> 9) + 1u : 0u, px = t & 255u, g = g0 + ((t >> 8) & 1u);
+        const u4 ws = philox10(p0 + px, (uint32_t)b, TAG_STAR, g, a.k0, a.k1);
+        u4 wr{0u, 0u, 0u, 0u};
+        if (draw_split) wr = philox10(p0 + px, (uint32_t)b, TAG_STAR_SPLIT, g, a.k0, a.k1);
+#pragma unroll
+        for (uint32_t s = 0; s < 4u; s += 2u) {  // two stars at a time: their searches overlap
+          if (s > 0u && !wave_any(s < c)) break;
+          // number of thresholds <= u among the 64 (sorted; the count stops at 63), then capped at
+          // istar: the first entry whose threshold exceeds u.  Byte offsets of lanes.
+          uint32_t pos[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {  // the first two halvings without cross-lane reads
+            const uint32_t u = word_of(ws, (int)s + j);
+            const bool hi = u >= c32;
+            pos[j] = (hi ? 4u * 32u : 0u) + (u >= (hi ? c48 : c16) ? 4u * 16u : 0u);
+          }
+#pragma unroll
+          for (uint32_t st = 8u; st != 0u; st >>= 1)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+              const uint32_t v = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(pos[j] + 4u * (st - 1u)), cl);
+              pos[j] += v <= word_of(ws, (int)s + j) ? 4u * st : 0u;
+            }
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            const uint32_t cat = min(pos[j], 4u * istar);
+            float f[B];
+#pragma unroll
+            for (int k = 0; k < B; ++k) f[k] = __int_as_float(__builtin_amdgcn_ds_bpermute((int)cat, fl[k]));
+            const bool red = S == 2 && (a.split_mode == SPLIT_ALL || (draw_split && word_of(wr, (int)s + j) < a.split_q));
+            if (s + (uint32_t)j < c) {
+              double *o = &acc[red ? B : 0][px];
+#pragma unroll
+              for (int k = 0; k < B; ++k)
+                __hip_atomic_fetch_add(o + k * PX, (double)f[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+              const int i = b * SBLK + (int)(cat >> 2);
+              if (DBG && (int64_t)(p0 + px) >= a.px0 && (int64_t)(p0 + px) < a.px1 && i < a.E) {  // always: cat <= istar, an entry with stars
+                const size_t d = (size_t)((int64_t)(p0 + px) - a.px0) * (size_t)a.E + (size_t)i;
+                atomicAdd(a.dbg_counts + d, 1u);
+                if (red && a.dbg_red) atomicAdd(a.dbg_red + d, 1u);
+              }
+            }
+          }
         }
       }
     }
   }
   if (wave_any(ptrs_failed != 0u) && lane == 0u) atomicOr(a.status, STATUS_PTRS_RETRY);
-  if (!live) return;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const size_t plane = (size_t)a.npx;
 #pragma unroll
-  for (int k = 0; k < B; ++k) {
-    float *pc = a.part + ((size_t)(chunk * S + 0) * B + k) * plane + p;
-    *pc = (float)(a.accumulate ? (double)*pc + acc_c[k] : acc_c[k]);
-    if (S == 2) {
-      float *pr = a.part + ((size_t)(chunk * S + 1) * B + k) * plane + p;
-      *pr = (float)(a.accumulate ? (double)*pr + acc_r[k] : acc_r[k]);
+  for (int k = 0; k < S * B; ++k)
+#pragma unroll
+    for (int q = 0; q < BPPL; ++q) {
+      const uint32_t p = p0 + 64u * q + lane;
+      if (p >= (uint32_t)a.npx) continue;
+      float *o = a.part + ((size_t)chunk * S * B + k) * plane + p;
+      const double v = acc[k][q * 64 + lane];
+      *o = (float)(a.accumulate ? (double)*o + v : v);
     }
-  }
 }
+
+static dim3 sample_block_grid(int npx, int nchunks) { return dim3((unsigned)((npx + 256 * BPPL - 1) / (256 * BPPL) * nchunks)); }
 
 template <int B, int S, bool DBG>
 __global__ void __launch_bounds__(256) k_sample_block(BlockSampleArgs a) {
@@ -214,8 +284,7 @@ __global__ void __launch_bounds__(256) k_sample_block_job(const BlockSampleArgs 
 
 template <int B>
 static hipError_t launch_sample_block_b(const BlockSampleArgs &a, hipStream_t s) {
-  const int nblk_px = (a.npx + 255) / 256;
-  dim3 grid((unsigned)(nblk_px * a.nchunks));
+  const dim3 grid = sample_block_grid(a.npx, a.nchunks);
   const bool dbg = a.dbg_counts != nullptr;
   if (a.S == 2 && dbg)
     hipLaunchKernelGGL((k_sample_block<B, 2, true>), grid, dim3(256), 0, s, a);
@@ -239,7 +308,7 @@ hipError_t launch_sample_block(const BlockSampleArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, hipStream_t s) {
-  const dim3 grid((unsigned)((npx + 255) / 256 * nchunks));
+  const dim3 grid = sample_block_grid(npx, nchunks);
   switch (B) {
     case 1: hipLaunchKernelGGL(k_sample_block_job<1>, grid, dim3(256), 0, s, table, j); break;
     case 2: hipLaunchKernelGGL(k_sample_block_job<2>, grid, dim3(256), 0, s, table, j); break;

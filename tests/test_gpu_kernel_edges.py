@@ -286,3 +286,26 @@ def test_fourier_path_sides(ctx, N, K, B, grid):
                 ys, xs = np.s_[k // grid * side:(k // grid + 1) * side], np.s_[k % grid * side:(k % grid + 1) * side]
                 want[b][ys, xs] = np.fft.irfft2(Fh * np.fft.rfft2(w), s=(N, N))[ys, xs]
         assert np.all(np.abs(got["flux_psf"].reshape(B, N, N) - want) <= 2.0 ** -24 * np.abs(want) + 1e-13 * F.max())
+
+
+# Block-rule stars queued over a wave's 128 pixels: images that end inside a wave's pixels, pixels with no,
+# few and many stars of a block (more groups of four than are queued at once), block totals by inversion
+# and by rejection, every split.  Counts are those of the oracle; flux as for the mixed groups.
+@pytest.mark.parametrize("frac", [None, 0.3, 0.5, 1.0])
+@pytest.mark.parametrize("E,B,nim,scale", [(1, 1, 3, 1.0), (63, 2, 11, 0.01), (65, 3, 12, 3.0), (130, 4, 23, 0.2), (64, 3, 9, 40.0)])
+def test_block_sampler_queue(ctx, E, B, nim, scale, frac):
+    from tests import parity_utils as pu
+    r = np.random.default_rng(E + B)
+    lam = scale * 10.0 ** r.uniform(-3.0, 0.0, E) * (r.uniform(size=E) < 0.8)
+    f32 = (10.0 ** r.uniform(-6.0, 0.0, (B, E))).astype(np.float32)
+    obs = si.Obs(nim=nim, seed=55 + E, dmod=25.0, dust_model=0 if frac is None else 2, dust_frac=frac or 0.0,
+                 dust_R=(3.6, 1.9, 1.3, 1.0), psf=None, noise_model=0, noise_sigma_mag=(0.02,) * 4, exptime=(3000.0,) * 4,
+                 zp=(25.0,) * 4, sky=(0.0,) * 4)
+    for obs.sampler in (1, 2):  # every block, and the sparse ones of the hybrid rule
+        print(f"[case] block queue E={E} B={B} nim={nim} frac={frac} sampler={obs.sampler}", flush=True)
+        ora = op.simulate(lam, f32, obs, want_counts=True)
+        got = pu.gpu_simulate(ctx, lam, f32, obs, window=(0, nim * nim))
+        pu.assert_block_counts_exact(lam, obs.seed, 0, got["counts"], ora["counts"])
+        plain = pu.gpu_simulate(ctx, lam, f32, obs)
+        for g in (got, plain):
+            assert np.all(np.abs(g["flux_pre"] - ora["F"]) <= 2e-7 * np.abs(ora["F"]))
