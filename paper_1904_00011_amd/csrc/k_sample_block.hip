@@ -49,9 +49,14 @@ __device__ __forceinline__ void prep_block_body(const BlockPrepArgs &a) {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  // cum_l: every lane sums the entries 0..l of its block left to right, the order of Lambda_b
+  // cum_l: every lane sums the entries 0..l of its block left to right, the order of Lambda_b (a fixed
+  // count, so that the reads run ahead of the additions; entries past l add exact zeros)
   double cum = 0.0;
-  for (int k = 0; k <= lane; ++k) cum += lam_s[w][k];
+#pragma unroll 16
+  for (int k = 0; k < SBLK; ++k) {
+    const double v = lam_s[w][k];
+    cum += k <= lane ? v : 0.0;
+  }
   const double L = __shfl(cum, SBLK - 1, 64);  // Lambda_b = cum_63
   BlockRec r{{0u, 0u, 0u}, KIND_ZERO, (uint32_t)SBLK - 1u, {0u, 0u, 0u}};
   if (a.hybrid && L >= 10.0) {  // hybrid: this block's entries go to the per-point rule
@@ -74,7 +79,8 @@ __device__ __forceinline__ void prep_block_body(const BlockPrepArgs &a) {
         uint32_t first[3] = {0u, 0u, 0u};
         const uint32_t K = inversion_table(L, a.thr + (size_t)b * THR_STRIDE, 1, first);
         if (K > 0) {
-          for (uint32_t k = 0; k < 3 && k < K; ++k) r.T[k] = first[k];
+#pragma unroll
+          for (uint32_t k = 0; k < 3; ++k) r.T[k] = k < K ? first[k] : r.T[k];
           r.kk = (K << 8) | KIND_INV;
         }
       }

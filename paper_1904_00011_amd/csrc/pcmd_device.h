@@ -323,6 +323,26 @@ __device__ __forceinline__ uint32_t ptrs_draw(const PtrsConst &c, uint32_t p, ui
   return (uint32_t)k;
 }
 
+// 1 / k for k < KRCP, correctly rounded.
+constexpr int KRCP = 1024;
+struct KRcp {
+  double v[KRCP];
+  constexpr KRcp() : v{} {
+    v[0] = 0.0;
+    for (int k = 1; k < KRCP; ++k) v[k] = 1.0 / (double)k;
+  }
+};
+static __device__ const KRcp k_rcp{};
+
+// x / k, correctly rounded, for 1 <= k < KRCP and x k-fold within the normal range, in three dependent
+// operations where the general division has about ten.  q = x (1/k) is within 1.5 units in the last place,
+// so x - k q is exact, and the corrected quotient is x / k to 2^-52 of a unit before its rounding, while no
+// quotient by an integer below 2^11 lies nearer than 2^-12 of a unit to the middle of two numbers.
+__device__ __forceinline__ double div_count(double x, int k, double y) {  // y = k_rcp.v[k]
+  const double q = x * y;
+  return fma(fma(-(double)k, q, x), y, q);
+}
+
 // C1 table of a Poisson(l) count, 0 < l < 10: T_k = floor(2^32 F(k)) for k = 0, 1, ... while
 // T_k < 2^32 - 1 (at most THR_STRIDE - 1 values), the cdf F built in FP64 by the pmf recurrence
 // p_k = p_{k-1} l / k from p_0 = e^-l.  The first threshold that reaches 2^32 - 1 counts as 2^32
@@ -334,16 +354,21 @@ __device__ inline uint32_t inversion_table(double l, uint32_t *t, size_t stride,
   double pk = exp(-l);
   double F = pk;
   uint32_t K = 0;
+  double y = k_rcp.v[1], yn = k_rcp.v[2];  // two steps ahead of their use
   for (int k = 0; k < THR_STRIDE - 1; ++k) {
     if (k > 0) {
-      pk = pk * l / (double)k;
+      pk = div_count(pk * l, k, y);
+      y = yn;
+      yn = k_rcp.v[k + 2];
       F = F + pk;
     }
     const double tk = floor(F * 4294967296.0);
     if (tk >= 4294967295.0) break;
     const uint32_t tv = (uint32_t)tk;
     t[(size_t)k * stride] = tv;
-    if (k < 3) first[k] = tv;
+    first[0] = k == 0 ? tv : first[0];  // no run-time index: the array stays in registers
+    first[1] = k == 1 ? tv : first[1];
+    first[2] = k == 2 ? tv : first[2];
     K = (uint32_t)(k + 1);
   }
   return K;
