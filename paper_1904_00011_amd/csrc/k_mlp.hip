@@ -437,12 +437,11 @@ __device__ __forceinline__ void stage64(__bf16 *lds, const GemmArgs &g, const __
 }
 
 template <int EPI, int G, bool TA, bool TB, bool AF32>
-__global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
-  extern __shared__ __attribute__((aligned(16))) char smem64[];
+__device__ __forceinline__ void gemm64_block(const GemmArgs &g, unsigned block, char *smem64) {
   const int grp = threadIdx.x >> 8, t = threadIdx.x & 255;
   __bf16 *As = reinterpret_cast<__bf16 *>(smem64) + (size_t)grp * 2 * HB * HLD, *Bs = As + HB * HLD;
   const int nx = (g.N + HB - 1) / HB;
-  const TileId tl = xcd_tile(blockIdx.x, nx, (g.M + HB - 1) / HB, g.nz);
+  const TileId tl = xcd_tile(block, nx, (g.M + HB - 1) / HB, g.nz);
   if (!tl.inside) return;
   const int bm = tl.y * HB, bn = tl.x * HB;
   const int wave = t >> 6, lane = t & 63;
@@ -544,6 +543,70 @@ __global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
     }
   }
   if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, G * LOSS_WAVES, grp * LOSS_WAVES + wave);
+}
+
+template <int EPI, int G, bool TA, bool TB, bool AF32>
+__global__ void __launch_bounds__(256 * G) k_gemm64(GemmArgs g) {
+  extern __shared__ __attribute__((aligned(16))) char smem64[];
+  gemm64_block<EPI, G, TA, TB, AF32>(g, blockIdx.x, smem64);
+}
+
+// db[m] = sum_n dz[n][m] in FP32.  A block takes 64 columns (one per lane, so every row read is
+// 128 contiguous bytes) and COLSUM_WAVES waves split the rows: wave w sums rows w, w + COLSUM_WAVES, ...
+// in order, and the partial sums are added in wave order.  The order is fixed by n alone, so results do
+// not depend on the launch: W waves take COLSUM_WAVES / W of those sums each.
+constexpr int COLSUM_WAVES = 16;
+template <int W>
+__device__ __forceinline__ void colsum_block(const ColsumArgs &a, unsigned block, char *smem) {
+  float(*part)[64] = reinterpret_cast<float(*)[64]>(smem);
+  constexpr int PER = COLSUM_WAVES / W;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int c = block * 64 + lane;
+  float s[PER] = {};
+  if (c < a.m) {
+    int r = w;
+#pragma unroll 8
+    for (; r + (PER - 1) * W < a.n; r += COLSUM_WAVES)
+#pragma unroll
+      for (int k = 0; k < PER; ++k) s[k] += (float)a.dz[(size_t)(r + k * W) * a.m + c];
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (r + k * W < a.n) s[k] += (float)a.dz[(size_t)(r + k * W) * a.m + c];
+  }
+#pragma unroll
+  for (int k = 0; k < PER; ++k) part[w + k * W][lane] = s[k];
+  __syncthreads();
+  if (w == 0 && c < a.m) {
+    float t = part[0][lane];
+#pragma unroll
+    for (int k = 1; k < COLSUM_WAVES; ++k) t += part[k][lane];
+    a.db[c] = t;
+  }
+}
+
+__global__ void __launch_bounds__(64 * COLSUM_WAVES) k_colsum(ColsumArgs a) {
+  __shared__ float part[COLSUM_WAVES][64];
+  colsum_block<COLSUM_WAVES>(a, blockIdx.x, reinterpret_cast<char *>(part));
+}
+
+// A layer's backward products in one launch: the bias gradients (blocks [0, nbc)), dx = dz W (the next nbx)
+// and dW = dz^T x.  They read the same dz and nothing of each other, and each alone leaves most of
+// the chip idle (512 wide, 1,024 samples: 128 blocks, 64 and 8: 26 -> 12 us; the
+// 10,000-bin output layer 65 -> 61 us).
+template <int GW, int GX>
+__global__ void __launch_bounds__(256 * (GW > GX ? GW : GX)) k_gemm64_back(GemmArgs w, GemmArgs x, ColsumArgs c, unsigned nbc,
+                                                                           unsigned nbx) {
+  extern __shared__ __attribute__((aligned(16))) char smem64[];
+  const unsigned id = blockIdx.x;
+  // whole waves leave a product with fewer groups (a barrier waits for the waves that are left)
+  const unsigned thread0 = (unsigned)__builtin_amdgcn_readfirstlane((int)threadIdx.x);
+  if (id < nbc) {
+    if (id * 64u < (unsigned)c.m) colsum_block<4 * (GW > GX ? GW : GX)>(c, id, smem64);
+  } else if (id < nbc + nbx) {
+    if (thread0 < 256 * GX) gemm64_block<EPI_GELU_GRAD, GX, false, false, false>(x, id - nbc, smem64);
+  } else {
+    if (thread0 < 256 * GW) gemm64_block<EPI_STORE, GW, true, true, false>(w, id - nbc - nbx, smem64);
+  }
 }
 
 // Split over K when the output tile grid cannot fill the chip and K is long enough: about two
@@ -691,6 +754,63 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
   return hipErrorInvalidValue;
 }
 
+static hipError_t launch_colsum(const ColsumArgs &c, hipStream_t s) {
+  hipLaunchKernelGGL(k_colsum, dim3((c.m + 63) / 64), dim3(64 * COLSUM_WAVES), 0, s, c);
+  return hipGetLastError();
+}
+
+template <int GW, int GX>
+static void launch_back_t(const GemmArgs &w, const GemmArgs &x, const ColsumArgs &c, unsigned nbw, unsigned nbx, hipStream_t s) {
+  constexpr int G = GW > GX ? GW : GX;
+  constexpr size_t lds = 2 * HB * HLD * sizeof(__bf16);  // one group's tiles
+  const unsigned nbc = (unsigned)((c.m + 63) / 64 + 7) / 8 * 8;  // whole turns over the XCDs
+  hipLaunchKernelGGL((k_gemm64_back<GW, GX>), dim3(nbc + nbx + nbw), dim3(256 * G), G * lds, s, w, x, c, nbc, nbx);
+}
+
+hipError_t launch_backward(const GemmArgs &w0, const GemmArgs *x0, const ColsumArgs &c, void *ws, size_t ws_bytes,
+                           hipStream_t s) {
+  GemmArgs w = w0, x = x0 ? *x0 : GemmArgs{};
+  int kw = w.K, kx = x.K;
+  const int sw = gemm_splits(w.M, w.N, w.K, kw), sx = x0 ? gemm_splits(x.M, x.N, x.K, kx) : 1;
+  const bool iw = sw <= G64_SPLITS, ix = sx <= G64_SPLITS;
+  const int gw = !iw ? 1 : sw > 2 ? 4 : sw, gx = !ix ? 1 : sx > 2 ? 4 : sx;
+  w.nz = iw ? 1 : sw;
+  x.nz = ix ? 1 : sx;
+  const unsigned nbw = xcd_blocks((w.N + HB - 1) / HB, (w.M + HB - 1) / HB, w.nz);
+  const unsigned nbx = x0 ? xcd_blocks((x.N + HB - 1) / HB, (x.M + HB - 1) / HB, x.nz) : 0;
+  // One launch where both take 64 x 64 tiles and have the workspace to themselves, and blocks with
+  // different numbers of groups only where they all run at once (the smaller ones hold the larger ones' LDS)
+  const bool one = gemm_use64(w.M, w.N) && (!x0 || gemm_use64(x.M, x.N)) && (iw || ix) &&
+                   (!x0 || gw == gx || nbw + nbx + (c.m + 63) / 64 <= 256);
+  if (!one) {
+    hipError_t e = launch_gemm(w0, true, true, EPI_STORE, ws, ws_bytes, s);
+    if (e == hipSuccess) e = launch_colsum(c, s);
+    if (e == hipSuccess && x0) e = launch_gemm(*x0, false, false, EPI_GELU_GRAD, ws, ws_bytes, s);
+    return e;
+  }
+  if (ws_bytes < gemm_workspace_bytes(w.M, w.N, w.K, true, true) ||
+      (x0 && ws_bytes < gemm_workspace_bytes(x.M, x.N, x.K, false, false)))
+    return hipErrorInvalidValue;
+  w.kchunk = sw > 1 ? kw : w.K;
+  x.kchunk = sx > 1 ? kx : x.K;
+  w.part = iw ? nullptr : (float *)ws;
+  x.part = ix ? nullptr : (float *)ws;
+#define PCMD_BACK(W_, X_) \
+  if (gw == W_ && gx == X_) launch_back_t<W_, X_>(w, x, c, nbw, nbx, s);
+  if (!x0) {  // the first layer: no dx
+    PCMD_BACK(1, 1) PCMD_BACK(2, 1) PCMD_BACK(4, 1)
+  } else {
+    PCMD_BACK(1, 1) PCMD_BACK(1, 2) PCMD_BACK(1, 4) PCMD_BACK(2, 1) PCMD_BACK(2, 2) PCMD_BACK(2, 4) PCMD_BACK(4, 1)
+    PCMD_BACK(4, 2) PCMD_BACK(4, 4)
+  }
+#undef PCMD_BACK
+  if (!iw)
+    hipLaunchKernelGGL((k_gemm_splitk_reduce<EPI_STORE>), dim3((unsigned)(((int64_t)w.M * w.N + 255) / 256)), dim3(256), 0, s, w, sw);
+  if (!ix)
+    hipLaunchKernelGGL((k_gemm_splitk_reduce<EPI_GELU_GRAD>), dim3((unsigned)(((int64_t)x.M * x.N + 255) / 256)), dim3(256), 0, s, x, sx);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------------------
 // Elementwise and reduction kernels.
 // ---------------------------------------------------------------------------------------
@@ -825,37 +945,6 @@ hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, dou
 }
 hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, float *out, hipStream_t s) {
   hipLaunchKernelGGL(k_sum_partials<float>, dim3(1), dim3(256), 0, s, part, nb, scale, out);
-  return hipGetLastError();
-}
-
-// db[m] = sum_n dz[n][m] in FP32.  A block takes 64 columns (one per lane, so every row read is
-// 128 contiguous bytes) and its COLSUM_WAVES waves split the rows: wave w sums rows w,
-// w + COLSUM_WAVES, ... in order, and the partial sums are added in wave order.  The order is
-// fixed by n alone, so results do not depend on the launch.
-constexpr int COLSUM_WAVES = 16;
-
-__global__ void __launch_bounds__(64 * COLSUM_WAVES) k_colsum(const __bf16 *__restrict__ dz, int n, int m,
-                                                              float *__restrict__ db) {
-  __shared__ float part[COLSUM_WAVES][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + lane;
-  float s = 0.0f;
-  if (c < m) {
-#pragma unroll 8
-    for (int r = w; r < n; r += COLSUM_WAVES) s += (float)dz[(size_t)r * m + c];
-  }
-  part[w][lane] = s;
-  __syncthreads();
-  if (w == 0 && c < m) {
-    float t = part[0][lane];
-#pragma unroll
-    for (int k = 1; k < COLSUM_WAVES; ++k) t += part[k][lane];
-    db[c] = t;
-  }
-}
-
-hipError_t launch_colsum(const void *dz, int n, int m, float *db, hipStream_t s) {
-  hipLaunchKernelGGL(k_colsum, dim3((m + 63) / 64), dim3(64 * COLSUM_WAVES), 0, s, (const __bf16 *)dz, n, m, db);
   return hipGetLastError();
 }
 

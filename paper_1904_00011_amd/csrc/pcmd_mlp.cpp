@@ -201,13 +201,8 @@ hipError_t backward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, in
     gw.ldb = din;
     gw.C = grad + lay.off[l];
     gw.ldc = din;
-    {
-      ScopedTimer tm(c, PCMD_TIMER_GEMM, 2.0 * (double)n * (double)din * (double)dout, s);
-      e = launch_gemm(gw, true, true, EPI_STORE, c->mlp_ws.p, c->mlp_ws.n, s);
-    }
-    if (e == hipSuccess) e = launch_colsum(dz, n, dout, grad + lay.off[l] + (int64_t)dout * din, s);
-    if (e == hipSuccess && l > 0) {
-      GemmArgs gx{};
+    GemmArgs gx{};
+    if (l > 0) {
       gx.M = n;
       gx.N = din;
       gx.K = dout;
@@ -219,10 +214,13 @@ hipError_t backward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, in
       gx.ldcb = din;
       gx.Z = pre + poffs[l - 1];
       gx.ldz = din;
-      {
-        ScopedTimer tm(c, PCMD_TIMER_GEMM, 2.0 * (double)n * (double)din * (double)dout, s);
-        e = launch_gemm(gx, false, false, EPI_GELU_GRAD, c->mlp_ws.p, c->mlp_ws.n, s);
-      }
+    }
+    const ColsumArgs cs{dz, n, dout, grad + lay.off[l] + (int64_t)dout * din};
+    {
+      ScopedTimer tm(c, PCMD_TIMER_GEMM, (l > 0 ? 4.0 : 2.0) * (double)n * (double)din * (double)dout, s);
+      e = launch_backward(gw, l > 0 ? &gx : nullptr, cs, c->mlp_ws.p, c->mlp_ws.n, s);
+    }
+    if (l > 0) {
       __bf16 *tmp = dz;
       dz = dz2;
       dz2 = tmp;

@@ -78,7 +78,14 @@ hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, dou
 hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, float *out, hipStream_t s);
 // out[r][j] = ln((h[r][j] + 1/2) / (N_r + nbins / 2)) for n rows of nbins counts.
 hipError_t launch_log_hess_target(const uint32_t *h, int n, int nbins, float *out, hipStream_t s);
-hipError_t launch_colsum(const void *dz, int n, int m, float *db, hipStream_t s);
+// One layer's backward pass: the weight gradient w (EPI_STORE, both operands K-major), the bias gradient c
+// and, unless x is NULL, the layer below's dz (EPI_GELU_GRAD); in one launch where that pays.
+struct ColsumArgs {  // db[m] = sum_n dz[n][m]
+  const __bf16 *dz;
+  int n, m;
+  float *db;
+};
+hipError_t launch_backward(const GemmArgs &w, const GemmArgs *x, const ColsumArgs &c, void *ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_adam(AdamArgs a, hipStream_t s);
 // lnfact64[k] = ln k! for k < nlf (Stirling's series beyond; nlf >= 1000)
 hipError_t launch_surrogate_loglike(const float *y, int n, int nbins, const uint32_t *d, double *out,

@@ -156,6 +156,35 @@ def test_first_layer_reads_the_batch(ctx, n):
         ctx.sync()
 
 
+# Backward products of a layer in one launch or several: every pairing of the groups that dW (K = n) and dx
+# (K = the layer's width) take, one of them or both over blocks with partial products, the first layer
+# without dx, bias gradients over few and many rows.  Tolerance as in the network's gradient test.
+@pytest.mark.parametrize("n", [3, 65, 600, 800, 1300])
+def test_backward_products_of_a_layer(ctx, n):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    dims = (12, 64, 520, 800, 2100, 40)
+    net = SurrogateNet(ctx, dims, si.mlp_init(dims, 5), device=DEV)
+    master = net.master.cpu().numpy().astype(np.float64)
+    r = np.random.default_rng(n)
+    x = r.uniform(-1, 1, (n, 12)).astype(np.float32)
+    t = r.normal(0, 1, (n, 40)).astype(np.float32)
+    print(f"[case] backward products n={n}", flush=True)
+    grads = []
+    for _ in range(2):
+        g = torch.full((net.n_params,), np.nan, dtype=torch.float32, device=DEV)
+        net.train_step(torch.from_numpy(x).to(DEV), torch.from_numpy(t).to(DEV), 0.0, grad_out=g, apply_update=False)
+        ctx.sync()
+        grads.append(g)
+    assert torch.equal(grads[0], grads[1])
+    g = grads[0].cpu().numpy().astype(np.float64)
+    _, go = om.loss_and_grad(master, dims, x, t)
+    o = 0
+    for a, b in zip(dims[:-1], dims[1:]):
+        for k in (a * b, b):
+            assert np.max(np.abs(g[o:o + k] - go[o:o + k])) <= 1e-2 * np.max(np.abs(go[o:o + k]))
+            o += k
+
+
 # One Adam launch over layers whose sides are no multiples of the 64 x 64 tile: master weights against
 # the update rule (one step from zero moments moves a weight by at most lr; FP32 steps), the BF16 copies
 # and the transposed ones exactly the rounded master.
