@@ -40,19 +40,18 @@ class PcmdError(RuntimeError):
 
 class IsoSet(C.Structure):
     _fields_ = [("n_iso", C.c_int32), ("n_age", C.c_int32), ("n_feh", C.c_int32),
-                ("age_edges", C.POINTER(C.c_double)), ("feh_grid", C.POINTER(C.c_double)),
-                ("iso_age", C.POINTER(C.c_int32)), ("iso_feh", C.POINTER(C.c_int32))]
+                ("age_edges", C.c_void_p), ("feh_grid", C.c_void_p), ("iso_age", C.c_void_p), ("iso_feh", C.c_void_p)]
 
 
 class ModelS(C.Structure):
     _fields_ = [("sfh", C.c_int32), ("mdf", C.c_int32), ("ssp_age_index", C.c_int32), ("feh_index", C.c_int32),
                 ("log_npix", C.c_double), ("tau_gyr", C.c_double), ("feh_mu", C.c_double),
-                ("feh_sigma", C.c_double), ("mdf_prune", C.c_double), ("log_sfh", C.POINTER(C.c_double))]
+                ("feh_sigma", C.c_double), ("mdf_prune", C.c_double), ("log_sfh", C.c_void_p)]
 
 
 class GridS(C.Structure):
     _fields_ = [("n_entries", C.c_int32), ("n_iso", C.c_int32), ("iso_of_entry", C.c_void_p),
-                ("imf_w", C.c_void_p), ("iso_imf_sum", C.POINTER(C.c_double))]
+                ("imf_w", C.c_void_p), ("iso_imf_sum", C.c_void_p)]
 
 
 class IsoS(C.Structure):
@@ -150,21 +149,25 @@ def load(path: str = LIB_PATH):
     return lib
 
 
+# Addresses go to ctypes as integers: on a small image a call is bound by what the host does between
+# launches, and the typed pointer and stream objects made before had cost 15 of a 64 x 64 evaluation's 62 us.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
-def _np_ptr(a, ctype):
-    return a.ctypes.data_as(C.POINTER(ctype))
+def _np_ptr(a):
+    return a.ctypes.data
 
 
 def _stream(stream):
     if stream is None:
         import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+        if torch.cuda.is_initialized():  # the current device's current stream, without a Stream object
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        return stream
+    return stream.cuda_stream
 
 
 # ---------------------------------------------------------------------------------------------
@@ -199,7 +202,7 @@ def model_struct(model, keep: list):
     if getattr(model, "sfh", "ssp") == "nonparam":
         arr = np.ascontiguousarray(model.log_sfh, dtype=np.float64)
         keep.append(arr)
-        log_sfh = _np_ptr(arr, C.c_double)
+        log_sfh = _np_ptr(arr)
     return ModelS(SFH[model.sfh], MDF[model.mdf], int(getattr(model, "ssp_age_index", 0)),
                   int(getattr(model, "feh_index", 0)), float(getattr(model, "log_npix", 2.0)),
                   float(getattr(model, "tau_gyr", 1.0)), float(getattr(model, "feh_mu", 0.0)),
@@ -210,8 +213,8 @@ def isoset_struct(grid, keep: list):
     arrs = [np.ascontiguousarray(grid.age_edges, dtype=np.float64), np.ascontiguousarray(grid.feh_grid, dtype=np.float64),
             np.ascontiguousarray(grid.age_index, dtype=np.int32), np.ascontiguousarray(grid.feh_index, dtype=np.int32)]
     keep.extend(arrs)
-    return IsoSet(int(grid.n_iso), len(arrs[0]) - 1, len(arrs[1]), _np_ptr(arrs[0], C.c_double),
-                  _np_ptr(arrs[1], C.c_double), _np_ptr(arrs[2], C.c_int32), _np_ptr(arrs[3], C.c_int32))
+    return IsoSet(int(grid.n_iso), len(arrs[0]) - 1, len(arrs[1]), _np_ptr(arrs[0]), _np_ptr(arrs[1]), _np_ptr(arrs[2]),
+                  _np_ptr(arrs[3]))
 
 
 def iso_weights(model, grid):
@@ -230,9 +233,8 @@ def iso_weights(model, grid):
 
 def obs_struct(obs, B: int, psf_tensor=None, conv_path: int = CONV_AUTO):
     def arr(v, fill):
-        vals = list(v)[:MAX_BANDS] if v is not None else []
-        vals = vals + [fill] * (MAX_BANDS - len(vals))
-        return D4(*[float(x) for x in vals])
+        vals = [] if v is None else [float(x) for x in list(v)[:MAX_BANDS]]
+        return D4(*vals, *[fill] * (MAX_BANDS - len(vals)))
     K = 1 if psf_tensor is None else int(psf_tensor.shape[-1])
     # [B][K][K]: one PSF per band; [B][16][K][K]: the 4 x 4 grid of sub-pixel PSFs
     grid = 4 if psf_tensor is not None and psf_tensor.dim() == 4 else 1
@@ -295,7 +297,7 @@ class Context:
     def entries(self, n_entries: int, iso_of_entry_dev, imf_w_dev, iso_imf_sum, iso_w, npix, lam_out, stream=None):
         iso_imf_sum = np.ascontiguousarray(iso_imf_sum, dtype=np.float64)
         iso_w = np.ascontiguousarray(iso_w, dtype=np.float64)
-        g = GridS(int(n_entries), len(iso_w), _ptr(iso_of_entry_dev), _ptr(imf_w_dev), _np_ptr(iso_imf_sum, C.c_double))
+        g = GridS(int(n_entries), len(iso_w), _ptr(iso_of_entry_dev), _ptr(imf_w_dev), _np_ptr(iso_imf_sum))
         self._check(self.lib.pcmd_entries(self.h, C.byref(g), iso_w.ctypes.data, float(npix), _ptr(lam_out),
                                           _stream(stream)), "pcmd_entries")
 
