@@ -3,6 +3,8 @@
 // shot noise are added and pixel counts become magnitudes.
 #include <math.h>
 
+#include <algorithm>
+
 #include "pcmd_device.h"
 #include "pcmd_internal.h"
 
@@ -52,6 +54,31 @@ hipError_t launch_copy_f32(const float *src, float *dst, int64_t n, hipStream_t 
 }
 
 // ---------------------------------------------------------------------------------------
+// Noise and magnitude of one pixel of band b with flux G (FP64 arithmetic).  Bound by the vector
+// instructions of a Philox block, Box-Muller and a logarithm (4096 x 4096 x 3 as a pass of its own:
+// 566 -> 317 us; with the library's functions, among them a power per pixel, 443 instructions each).
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ float noise_mag(const NoiseArgs &a, int b, int p, float Gf) {
+  constexpr double MAG = -1.0857362047581296;  // -2.5 / ln 10
+  const double G = (double)Gf;
+  double m;
+  if (a.noise_model == PCMD_NOISE_NONE) {
+    m = G > 0.0 ? MAG * ln_pos(G) : INFINITY;
+  } else {
+    const u4 w = philox10((uint32_t)p, (uint32_t)b, TAG_NOISE, 0u, a.k0, a.k1);
+    const double z = box_muller(w.x, w.y);
+    if (a.noise_model == PCMD_NOISE_GAUSS_MAG) {
+      m = G > 0.0 ? MAG * ln_pos(G) + a.sigma[b] * z : INFINITY;
+    } else {
+      const double c = G * a.gain[b] + a.sky[b];
+      const double c2 = c + sqrt(c > 0.0 ? c : 0.0) * z - a.sky[b];
+      m = c2 > 0.0 ? MAG * ln_pos(c2 * a.inv_t[b]) + a.zp[b] : INFINITY;
+    }
+  }
+  return (float)m;
+}
+
+// ---------------------------------------------------------------------------------------
 // Direct periodic convolution.  G[y][x] = sum_{u,v} P[u][v] F[(y-u+h) mod N][(x-v+h) mod N].
 // Each thread owns NX neighbouring outputs of one row of a 64-column tile.  The input tile with its
 // K-1 halo (wrapped periodically) and the flipped PSF (rows zero-padded to a multiple of 4) are staged
@@ -65,9 +92,13 @@ hipError_t launch_copy_f32(const float *src, float *dst, int64_t n, hipStream_t 
 // instructions).
 //
 // RS > 1 splits the PSF rows: RS groups of threads share one tile, group g taking rows [g K / RS,
-// (g + 1) K / RS); groups 1.. leave their FP64 sums in LDS and group 0 adds them in group order.  Used
+// (g + 1) K / RS); the groups leave their FP64 sums in LDS, where they are added in group order.  Used
 // when the image is too small for one-group blocks to fill the chip (256 x 256 x 3, 31 x 31: 24.6 -> 16
 // us).
+//
+// The tile's results go through LDS (the input tile's) to threads of neighbouring pixels, which add the
+// noise and store the magnitudes: a launch and a trip of the image through memory less (64 x 64 x 2:
+// 9.0 -> 7.7 us, 256 x 256 x 3: 20.7 -> 18.2, 4096 x 4096 x 3: 1615 -> 1611, bound by the arithmetic of both).
 // ---------------------------------------------------------------------------------------
 constexpr int CT_X = 64, NX = 8;
 constexpr int CT_Y1 = 32, CT_YS = 16;  // tile rows: one group of 256 threads, or RS groups of 128
@@ -78,12 +109,20 @@ __host__ __device__ inline int conv_kp(int K) { return (K + 3) & ~3; }
 // the last thread's window ends at column (CT_X - NX) + Kp + NX - 1 and is read in fours
 __host__ __device__ inline int conv_tile_w(int K) { return CT_X + conv_kp(K) + 4; }
 
+// Stride of a group's sums [NX][TG]: the 64 pixels of a tile row, (NX indices) x 8 threads, then lie in
+// different banks.
+constexpr int conv_part_ld(int rows) { return conv_group(rows) + 8; }
+
+static size_t conv_tile_bytes(int K, int rows) {
+  return ((size_t)(rows + K - 1) * conv_tile_w(K) + (size_t)K * conv_kp(K)) * sizeof(float);
+}
+// the tile and the PSF, and afterwards in their place the groups' sums or the results
 static size_t conv_lds_bytes(int K, int RS, int rows) {
-  return ((size_t)(rows + K - 1) * conv_tile_w(K) + (size_t)K * conv_kp(K)) * sizeof(float) +
-         (size_t)(RS - 1) * conv_group(rows) * NX * sizeof(double);
+  const size_t out = RS > 1 ? (size_t)RS * NX * conv_part_ld(rows) * sizeof(double) : (size_t)rows * CT_X * sizeof(float);
+  return std::max(conv_tile_bytes(K, rows), out);
 }
 // The largest PSF that the direct path takes is set by the smaller tile's LDS.
-size_t conv_direct_lds_bytes(int K) { return conv_lds_bytes(K, 1, CT_YS); }
+size_t conv_direct_lds_bytes(int K) { return conv_tile_bytes(K, CT_YS); }
 
 // The PSF check of psf_check_body done by one wave (the direct convolution's first tile of each
 // PSF runs it beside its own work, which saves the check's launch): per-lane FP64 sums, then a
@@ -103,12 +142,11 @@ __device__ __forceinline__ void psf_check_wave(const ConvArgs &a, int b) {
 }
 
 template <int RS, int CT_Y>
-__device__ __forceinline__ void conv_direct_body(const ConvArgs &ca) {
+__device__ __forceinline__ void conv_direct_body(const ConvArgs &ca, const NoiseArgs &na) {
   extern __shared__ float4 lds4[];
   constexpr int TG = conv_group(CT_Y), THREADS = TG * RS;
   float *tile = reinterpret_cast<float *>(lds4);
   const float *__restrict__ F = ca.F;
-  float *__restrict__ G = ca.G;
   const int N = ca.N, K = ca.K, Kp = conv_kp(K);
   // blockIdx.z = band * grid^2 + region; region (ry, rx) holds the pixels with
   // floor(grid y / N) = ry and floor(grid x / N) = rx, i.e. y in [ceil(ry N / grid), ceil((ry+1) N / grid))
@@ -178,35 +216,44 @@ __device__ __forceinline__ void conv_direct_body(const ConvArgs &ca) {
 #pragma unroll
     for (int i = 0; i < NX; ++i) acc[i] += (double)d[i];
   }
+  __syncthreads();
+  constexpr int PLD = conv_part_ld(CT_Y);
+  double *part = reinterpret_cast<double *>(lds4);  // [RS][NX][PLD]
   if (RS > 1) {
-    // [RS - 1][NX][TG]; the tile and PSF sizes are multiples of 4 floats, so 16-byte aligned
-    double *part = reinterpret_cast<double *>(Pf + K * Kp);
-    if (grp > 0) {
 #pragma unroll
-      for (int i = 0; i < NX; ++i) part[((grp - 1) * NX + i) * TG + lt] = acc[i];
-    }
-    __syncthreads();
-    if (grp > 0) return;
-#pragma unroll 2
-    for (int g = 1; g < RS; ++g)
+    for (int i = 0; i < NX; ++i) part[(grp * NX + i) * PLD + lt] = acc[i];
+  } else {
 #pragma unroll
-      for (int i = 0; i < NX; ++i) acc[i] += part[((g - 1) * NX + i) * TG + lt];
+    for (int i = 0; i < NX; ++i) tile[ty * CT_X + tx + i] = (float)acc[i];
   }
-  const int y = oy + ty;
-  if (y < y1r) {
-    float *out = G + (size_t)b * N * N + (size_t)y * N + ox + tx;
+  __syncthreads();
+#pragma unroll 1
+  for (int o = threadIdx.x; o < CT_X * CT_Y; o += THREADS) {
+    const int x = ox + (o & (CT_X - 1)), y = oy + o / CT_X;
+    if (x >= x1r || y >= y1r) continue;
+    float g;
+    if (RS > 1) {
+      const double *q = part + (o & (NX - 1)) * PLD + o / NX;  // thread o / NX of a group, its output o % NX
+      double v = q[0];
 #pragma unroll
-    for (int i = 0; i < NX; ++i)
-      if (ox + tx + i < x1r) out[i] = (float)acc[i];
+      for (int k = 1; k < RS; ++k) v += q[k * NX * PLD];
+      g = (float)v;
+    } else {
+      g = tile[o];
+    }
+    const int p = y * N + x;
+    if (ca.G) ca.G[(size_t)b * N * N + p] = g;
+    na.mags[(size_t)b * N * N + p] = noise_mag(na, b, p, g);
   }
 }
 
 template <int RS, int CT_Y>
-__global__ void __launch_bounds__(conv_group(CT_Y) * RS) k_conv_direct(ConvArgs a) { conv_direct_body<RS, CT_Y>(a); }
+__global__ void __launch_bounds__(conv_group(CT_Y) * RS) k_conv_direct(ConvArgs a, NoiseArgs na) { conv_direct_body<RS, CT_Y>(a, na); }
 template <int RS, int CT_Y>
-__global__ void __launch_bounds__(conv_group(CT_Y) * RS) k_conv_direct_job(const ConvArgs *__restrict__ t, int j) {
+__global__ void __launch_bounds__(conv_group(CT_Y) * RS) k_conv_direct_job(const ConvArgs *__restrict__ t,
+                                                                                const NoiseArgs *__restrict__ tn, int j) {
   const ConvArgs a = t[j];
-  conv_direct_body<RS, CT_Y>(a);
+  conv_direct_body<RS, CT_Y>(a, tn[j]);
 }
 
 // Blocks per region side: the largest region of a grid x grid split is ceil(N / grid) wide.
@@ -238,45 +285,26 @@ static hipError_t conv_launch(int B, int N, int K, int grid, F &&launch) {
   return hipGetLastError();
 }
 
-hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t s) {
+hipError_t launch_conv_direct(const ConvArgs &a, const NoiseArgs &na, hipStream_t s) {
   return conv_launch(a.B, a.N, a.K, a.grid, [&](auto shape, dim3 g, size_t lds) {
     using S = decltype(shape);
-    hipLaunchKernelGGL((k_conv_direct<S::RS, S::ROWS>), g, dim3(conv_group(S::ROWS) * S::RS), lds, s, a);
+    hipLaunchKernelGGL((k_conv_direct<S::RS, S::ROWS>), g, dim3(conv_group(S::ROWS) * S::RS), lds, s, a, na);
   });
 }
-hipError_t launch_conv_direct_job(const ConvArgs *table, int j, int B, int N, int K, int grid, hipStream_t s) {
+hipError_t launch_conv_direct_job(const ConvArgs *table, const NoiseArgs *noise, int j, int B, int N, int K, int grid, hipStream_t s) {
   return conv_launch(B, N, K, grid, [&](auto shape, dim3 g, size_t lds) {
     using S = decltype(shape);
-    hipLaunchKernelGGL((k_conv_direct_job<S::RS, S::ROWS>), g, dim3(conv_group(S::ROWS) * S::RS), lds, s, table, j);
+    hipLaunchKernelGGL((k_conv_direct_job<S::RS, S::ROWS>), g, dim3(conv_group(S::ROWS) * S::RS), lds, s, table, noise, j);
   });
 }
 
-// ---------------------------------------------------------------------------------------
-// Noise and magnitudes (FP64 arithmetic, FP32 storage): one thread per pixel and band.  Bound by the
-// vector instructions of a Philox block, Box-Muller and a logarithm (4096 x 4096 x 3: 566 -> 317 us;
-// with the library's functions, among them a power per pixel, 443 instructions each; a job's
-// table kernel 17.5 -> 6.1 us, its record no longer copied to scratch).
-// ---------------------------------------------------------------------------------------
+// Noise and magnitudes of an image that no convolution has produced here (no PSF, or the Fourier path): one
+// thread per pixel and band.
 __device__ __forceinline__ void noise_mag_body(const NoiseArgs &a, int p) {
   const int b = blockIdx.y;
   if (p >= a.npx) return;
-  constexpr double MAG = -1.0857362047581296;  // -2.5 / ln 10
-  const double G = (double)a.G[(size_t)b * a.npx + p];
-  double m;
-  if (a.noise_model == PCMD_NOISE_NONE) {
-    m = G > 0.0 ? MAG * ln_pos(G) : INFINITY;
-  } else {
-    const u4 w = philox10((uint32_t)p, (uint32_t)b, TAG_NOISE, 0u, a.k0, a.k1);
-    const double z = box_muller(w.x, w.y);
-    if (a.noise_model == PCMD_NOISE_GAUSS_MAG) {
-      m = G > 0.0 ? MAG * ln_pos(G) + a.sigma[b] * z : INFINITY;
-    } else {
-      const double c = G * a.gain[b] + a.sky[b];
-      const double c2 = c + sqrt(c > 0.0 ? c : 0.0) * z - a.sky[b];
-      m = c2 > 0.0 ? MAG * ln_pos(c2 * a.inv_t[b]) + a.zp[b] : INFINITY;
-    }
-  }
-  a.mags[(size_t)b * a.npx + p] = (float)m;
+  const size_t o = (size_t)b * a.npx + p;
+  a.mags[o] = noise_mag(a, b, p, a.G[o]);
 }
 
 __global__ void __launch_bounds__(256) k_noise_mag(NoiseArgs a) { noise_mag_body(a, blockIdx.x * blockDim.x + threadIdx.x); }

@@ -515,6 +515,15 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
     e = launch_copy_f32((const float *)c->F.p, dbg->flux_pre, (int64_t)B * npx, s);
     if (e != hipSuccess) return hip_fail(c, e, "copy flux_pre");
   }
+  NoiseArgs na;
+  na.B = B;
+  na.npx = (int)npx;
+  na.G = nullptr;
+  na.mags = mags;
+  na.noise_model = o->noise_model;
+  noise_bands(&na, o, B);
+  na.k0 = k0;
+  na.k1 = k1;
   const float *Gp = (const float *)c->F.p;
   if (K > 1) {
     ConvArgs ca{B, N, K, (const float *)c->F.p, o->psf, (float *)c->G.p, c->status, psf_grid_of(o)};
@@ -533,8 +542,10 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
         c->fft_K = K;
         c->fft_R = R;
       }
-    } else
-      e = launch_conv_direct(ca, s);
+    } else {  // goes on to the magnitudes, and keeps the convolved image only where it is asked for
+      if (!(dbg && dbg->flux_psf)) ca.G = nullptr;
+      e = launch_conv_direct(ca, na, s);
+    }
     if (e != hipSuccess) return hip_fail(c, e, "convolution");
     Gp = (const float *)c->G.p;
   }
@@ -542,17 +553,11 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
     e = launch_copy_f32(Gp, dbg->flux_psf, (int64_t)B * npx, s);
     if (e != hipSuccess) return hip_fail(c, e, "copy flux_psf");
   }
-  NoiseArgs na;
-  na.B = B;
-  na.npx = (int)npx;
-  na.G = Gp;
-  na.mags = mags;
-  na.noise_model = o->noise_model;
-  noise_bands(&na, o, B);
-  na.k0 = k0;
-  na.k1 = k1;
-  e = launch_noise_mag(na, s);
-  if (e != hipSuccess) return hip_fail(c, e, "k_noise_mag");
+  if (K <= 1 || use_fft) {
+    na.G = Gp;
+    e = launch_noise_mag(na, s);
+    if (e != hipSuccess) return hip_fail(c, e, "k_noise_mag");
+  }
   c->err.clear();
   return PCMD_OK;
 }

@@ -44,7 +44,7 @@ struct pcmd_batch_plan {
   int n_jobs = 0, B = 0, nbins = 0, total_items = 0, wg = 0, order_mode = 0;
   std::vector<JobInfo> info;
   std::vector<int> order;  // sampler table position -> job
-  Buf rec, thr, pc, fl, part, F, G, mags, hess, mom, mom_part, ll_part, counters, desc, alias, rdesc, blk;
+  Buf rec, thr, pc, fl, part, F, mags, hess, mom, mom_part, ll_part, counters, desc, alias, rdesc, blk;
   void *desc_host = nullptr;
   size_t desc_bytes = 0;
   size_t o_prep = 0, o_samp = 0, o_red = 0, o_conv = 0, o_noise = 0, o_hess = 0, o_ll = 0, o_bprep = 0, o_bsamp = 0;
@@ -66,7 +66,7 @@ static void plan_free_device(pcmd_batch_plan *p) {
   if (p->graph) (void)hipGraphDestroy(p->graph);
   p->exec = nullptr;
   p->graph = nullptr;
-  Buf *bufs[] = {&p->rec, &p->thr, &p->pc, &p->fl, &p->part, &p->F, &p->G, &p->mags, &p->hess, &p->mom, &p->mom_part, &p->ll_part,
+  Buf *bufs[] = {&p->rec, &p->thr, &p->pc, &p->fl, &p->part, &p->F, &p->mags, &p->hess, &p->mom, &p->mom_part, &p->ll_part,
                  &p->counters, &p->desc, &p->alias, &p->rdesc, &p->blk};
   for (Buf *b : bufs) release(*b);
   if (p->desc_host) (void)hipHostFree(p->desc_host);
@@ -192,7 +192,6 @@ static int plan_build(pcmd_ctx *c, pcmd_batch_plan *p, int n_jobs, const pcmd_jo
   if ((r = ensure(c, p->fl, n_fl * 8, "batch fluxes"))) return r;
   if ((r = ensure(c, p->part, n_part * 4, "batch partial sums"))) return r;
   if ((r = ensure(c, p->F, n_img * 4, "batch images"))) return r;
-  if ((r = ensure(c, p->G, n_img * 4, "batch convolved images"))) return r;
   if ((r = ensure(c, p->mags, n_img * 4, "batch magnitudes"))) return r;
   if ((r = ensure(c, p->hess, (size_t)n_jobs * p->nbins * 4, "batch Hess"))) return r;
   if ((r = ensure(c, p->mom, (size_t)n_jobs * 3 * 8, "batch moments"))) return r;
@@ -268,7 +267,6 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
     double *fl = (double *)p->fl.p + ji.o_fl;
     float *part = (float *)p->part.p + ji.o_part;
     float *F = (float *)p->F.p + ji.o_img;
-    float *G = (float *)p->G.p + ji.o_img;
     float *mags = (float *)p->mags.p + ji.o_img;
     const uint32_t k0 = (uint32_t)(o->seed & 0xFFFFFFFFu), k1 = (uint32_t)(o->seed >> 32);
     GroupRec *grp = (GroupRec *)(rec + entries_padded(ji.E));
@@ -351,12 +349,12 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
     rr.k0 = k0;
     rr.k1 = k1;
     ra[j] = rr;
-    ca[j] = ConvArgs{B, ji.N, ji.K, F, o->psf, G, c->status, psf_grid_of(o)};
+    ca[j] = ConvArgs{B, ji.N, ji.K, F, o->psf, nullptr, c->status, psf_grid_of(o)};
     NoiseArgs nn;
     memset(&nn, 0, sizeof nn);
     nn.B = B;
     nn.npx = ji.npx;
-    nn.G = ji.K > 1 ? G : F;
+    nn.G = F;  // without a PSF; else the convolution makes the magnitudes
     nn.mags = mags;
     nn.noise_model = o->noise_model;
     noise_bands(&nn, o, B);
@@ -461,8 +459,9 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) {
     const JobInfo &ji = p->info[j];
     e = launch_reduce_job(ra, j, ji.npx, ji.B, s);
-    if (e == hipSuccess && ji.K > 1) e = launch_conv_direct_job(ca, j, ji.B, ji.N, ji.K, ji.grid, s);
-    if (e == hipSuccess) e = launch_noise_mag_job(na, j, ji.npx, ji.B, s);
+    if (e == hipSuccess)
+      e = ji.K > 1 ? launch_conv_direct_job(ca, na, j, ji.B, ji.N, ji.K, ji.grid, s)
+                   : launch_noise_mag_job(na, j, ji.npx, ji.B, s);
   }
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) e = launch_hess_job(ha, j, p->info[j].npx, p->nbins, s);
   if (e == hipSuccess) e = launch_loglike_jobs(la, p->n_jobs, p->nbins, s);

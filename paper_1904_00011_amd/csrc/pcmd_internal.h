@@ -252,8 +252,9 @@ hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, i
 // k_image.hip
 hipError_t launch_psf_check(const ConvArgs &a, hipStream_t s);
 size_t conv_direct_lds_bytes(int K);
-hipError_t launch_conv_direct(const ConvArgs &a, hipStream_t s);
-hipError_t launch_conv_direct_job(const ConvArgs *table, int j, int B, int N, int K, int grid, hipStream_t s);
+// The direct convolution goes on to the noise and magnitudes (na.G unused); a.G may be NULL.
+hipError_t launch_conv_direct(const ConvArgs &a, const NoiseArgs &na, hipStream_t s);
+hipError_t launch_conv_direct_job(const ConvArgs *table, const NoiseArgs *noise, int j, int B, int N, int K, int grid, hipStream_t s);
 hipError_t launch_noise_mag(const NoiseArgs &a, hipStream_t s);
 hipError_t launch_noise_mag_job(const NoiseArgs *table, int j, int npx, int B, hipStream_t s);
 hipError_t launch_copy_f32(const float *src, float *dst, int64_t n, hipStream_t s);

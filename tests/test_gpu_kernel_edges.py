@@ -338,3 +338,32 @@ def test_block_sampler_queue(ctx, E, B, nim, scale, frac):
         plain = pu.gpu_simulate(ctx, lam, f32, obs)
         for g in (got, plain):
             assert np.all(np.abs(g["flux_pre"] - ora["F"]) <= 2e-7 * np.abs(ora["F"]))
+
+
+# The direct convolution's magnitudes, with and without the convolved image stored: the noise kernel's test
+# bound on the stored image, for each tile shape, ragged tiles and regions of the sub-pixel grid.
+@pytest.mark.parametrize("N,K,B,grid", [(9, 9, 2, 1), (63, 31, 3, 1), (129, 119, 1, 1), (50, 15, 3, 4), (1030, 5, 3, 1)])
+def test_convolution_goes_on_to_magnitudes(ctx, N, K, B, grid):
+    import paper_1904_00011_amd as P
+    from oracle import noise as on
+    from tests import parity_utils as pu
+    r = np.random.default_rng(N + K)
+    psf = r.uniform(0.0, 1.0, (B, 16, K, K) if grid == 4 else (B, K, K))
+    psf = (psf / psf.sum(axis=(-2, -1), keepdims=True)).astype(np.float32)
+    lam = np.array([0.7, 0.01])
+    f32 = (10.0 ** r.uniform(-8.0, -7.0, (B, 2))).astype(np.float32)
+    obs = si.Obs(nim=N, seed=5 + N, dmod=0.0, dust_model=0, psf=psf, noise_model=2, noise_sigma_mag=(0.0,) * 4,
+                 exptime=(3000.0,) * 4, zp=(25.0, 24.5, 24.0, 25.0), sky=(10.0,) * 4, dust_R=(1.0,) * 4)
+    print(f"[case] convolution to magnitudes N={N} K={K} B={B} grid={grid}", flush=True)
+    a = pu.gpu_simulate(ctx, lam, f32, obs, conv_path=P.CONV_DIRECT)
+    b = pu.gpu_simulate(ctx, lam, f32, obs, conv_path=P.CONV_DIRECT, want_flux=False)
+    assert np.array_equal(a["mags"], b["mags"])
+    G = a["flux_psf"].reshape(B, N * N).astype(np.float64)
+    want, m = on.magnitudes(G, obs), a["mags"].reshape(B, N * N).astype(np.float64)
+    fin = np.isfinite(want)
+    assert np.array_equal(fin, np.isfinite(m))
+    zp = np.array(obs.zp[:B])[:, None]
+    c = G * 3000.0 * 10.0 ** (0.4 * zp) + 20.0
+    c2 = 3000.0 * 10.0 ** (0.4 * (zp - np.where(fin, want, 0.0)))
+    bound = 1.01 * 2.0 ** -24 * np.abs(want) + 1e-13 + 1.1 * 16 * 2.0 ** -53 * (c + 6.0 * np.sqrt(c)) / c2
+    assert np.all(np.abs(m[fin] - want[fin]) <= bound[fin])
