@@ -22,9 +22,11 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 
 // ---------------------------------------------------------------------------------------
 // C[M][N] = sum_k A[m][k] B[n][k] on v_mfma_f32_32x32x16_bf16 (both operands K-contiguous).
-// (64 MI) x 128 block tile, 4 waves of (32 MI) x 64 (MI x 2 MFMA tiles of 32 x 32): MI = 2 for
-// most products, MI = 4 for large ones, where a wave's larger share of A halves the LDS reads per
-// multiply-add of B.  K step 32 staged in
+// (64 WM) x 128 block tile, 2 WM waves of 64 x 64 (2 x 2 MFMA tiles of 32 x 32): WM = 2 for most
+// products, WM = 4 for large ones, whose blocks then read a quarter less from L2 per multiply-add.  Four
+// waves per SIMD either way: the K loop is bound by the latency of its loads (4096 x 10000 x 512: 92 us
+// with 256 x 128 tiles by four waves of 128 x 64, two per SIMD, 80 with eight waves; 32 of them are the
+// output's stores).  K step 32 staged in
 // LDS as [row][k] (row stride 40 halves = 80 bytes, so every 8-element run is 16-byte aligned).
 // Two LDS buffers: the next K step's global loads are issued into registers before the MFMAs of
 // the current one and written to the other buffer after them, one barrier per K step.  An
@@ -42,13 +44,13 @@ struct TileRegs {
 // rows x K row-major: run idx takes row idx / (GBK / 8), k run idx mod (GBK / 8).  Whole steps of a
 // 16-byte aligned operand load without a branch (rows past the end read the last row: what they
 // produce is not stored); a branch per run had made each load wait for the one before it.
-template <int RUNS>
+template <int THREADS, int RUNS>
 __device__ __forceinline__ void load_regs(TileRegs<RUNS> &t, const __bf16 *__restrict__ src, int ld, int rows, int K,
                                           int r0, int k0, bool vec_ok) {
   if (vec_ok && k0 + GBK <= K) {
 #pragma unroll
     for (int it = 0; it < RUNS; ++it) {
-      const int idx = threadIdx.x + 256 * it;
+      const int idx = threadIdx.x + THREADS * it;
       const int gr = min(r0 + idx / (GBK / 8), rows - 1), gk = k0 + (idx % (GBK / 8)) * 8;
       t.v[it] = *reinterpret_cast<const bf16x8 *>(src + (size_t)gr * ld + gk);
     }
@@ -56,18 +58,18 @@ __device__ __forceinline__ void load_regs(TileRegs<RUNS> &t, const __bf16 *__res
   }
 #pragma unroll
   for (int it = 0; it < RUNS; ++it) {
-    const int idx = threadIdx.x + 256 * it;
+    const int idx = threadIdx.x + THREADS * it;
     const int gr = r0 + idx / (GBK / 8), gk = k0 + (idx % (GBK / 8)) * 8;
 #pragma unroll
     for (int i = 0; i < 8; ++i) t.v[it][i] = (gr < rows && gk + i < K) ? src[(size_t)gr * ld + gk + i] : (__bf16)0.0f;
   }
 }
 
-template <int RUNS>
+template <int THREADS, int RUNS>
 __device__ __forceinline__ void store_lds(__bf16 *lds, const TileRegs<RUNS> &t) {
 #pragma unroll
   for (int it = 0; it < RUNS; ++it) {
-    const int idx = threadIdx.x + 256 * it;
+    const int idx = threadIdx.x + THREADS * it;
     *reinterpret_cast<bf16x8 *>(lds + (idx / (GBK / 8)) * GLDS + (idx % (GBK / 8)) * 8) = t.v[it];
   }
 }
@@ -215,15 +217,15 @@ __device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int
 }
 
 constexpr int GEPI_LD = 72;  // epilogue slab row stride (floats): 32 x 72 x 4 B per wave
-static_assert(4 * 32 * GEPI_LD * 4 <= 2 * (GBM + GBN) * GLDS * 2, "epilogue slabs fit in the tile buffers");
 
-// MI = 2: 64 VGPRs of accumulators, compiled for four waves per SIMD; MI = 4: 128, two waves.
-template <int EPI, int MI>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 2 ? 4 : 2, 8))) k_gemm(GemmArgs g) {
-  constexpr int BM = 64 * MI;                          // block tile rows
-  constexpr int RA = BM * GBK / (256 * 8), RB = GBN * GBK / (256 * 8);
+// WM x 2 waves of 64 x 64 (64 VGPRs of accumulators, four waves per SIMD).
+template <int EPI, int WM>
+__global__ void __launch_bounds__(128 * WM) __attribute__((amdgpu_waves_per_eu(4, 8))) k_gemm(GemmArgs g) {
+  constexpr int MI = 2, BM = 64 * WM, TH = 128 * WM;  // block tile rows, threads
+  constexpr int RA = BM * GBK / (TH * 8), RB = GBN * GBK / (TH * 8);
   // the two A and two B tiles, and after the loop the epilogue slabs
-  __shared__ __attribute__((aligned(16))) __bf16 smem[2 * (BM + GBN) * GLDS];
+  constexpr int TILES = 2 * (BM + GBN) * GLDS, SLABS = 2 * WM * 32 * GEPI_LD * 2;
+  __shared__ __attribute__((aligned(16))) __bf16 smem[TILES > SLABS ? TILES : SLABS];
   __bf16 (*As)[BM * GLDS] = reinterpret_cast<__bf16 (*)[BM * GLDS]>(smem);
   __bf16 (*Bs)[GBN * GLDS] = reinterpret_cast<__bf16 (*)[GBN * GLDS]>(smem + 2 * BM * GLDS);
   const int nx = (g.N + GBN - 1) / GBN;
@@ -247,17 +249,17 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
   const int nk = (ke + GBK - 1) / GBK;
   TileRegs<RA> ra;
   TileRegs<RB> rb;
-  load_regs(ra, g.A, g.lda, g.M, ke, bm, kb, va);
-  load_regs(rb, g.B, g.ldb, g.N, ke, bn, kb, vb);
-  store_lds(As[0], ra);
-  store_lds(Bs[0], rb);
+  load_regs<TH>(ra, g.A, g.lda, g.M, ke, bm, kb, va);
+  load_regs<TH>(rb, g.B, g.ldb, g.N, ke, bn, kb, vb);
+  store_lds<TH>(As[0], ra);
+  store_lds<TH>(Bs[0], rb);
   __syncthreads();
   for (int kt = 0; kt < nk; ++kt) {
     const int cur = kt & 1;
     const bool more = kt + 1 < nk;
     if (more) {
-      load_regs(ra, g.A, g.lda, g.M, ke, bm, kb + (kt + 1) * GBK, va);
-      load_regs(rb, g.B, g.ldb, g.N, ke, bn, kb + (kt + 1) * GBK, vb);
+      load_regs<TH>(ra, g.A, g.lda, g.M, ke, bm, kb + (kt + 1) * GBK, va);
+      load_regs<TH>(rb, g.B, g.ldb, g.N, ke, bn, kb + (kt + 1) * GBK, vb);
     }
     const __bf16 *as = As[cur];
     const __bf16 *bs = Bs[cur];
@@ -274,14 +276,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
         for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
     }
     if (more) {
-      store_lds(As[cur ^ 1], ra);
-      store_lds(Bs[cur ^ 1], rb);
+      store_lds<TH>(As[cur ^ 1], ra);
+      store_lds<TH>(Bs[cur ^ 1], rb);
     }
     __syncthreads();
   }
   // Epilogue through LDS (the A/B buffers are free after the last barrier): accumulator element e
   // of a 32 x 32 tile sits at row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32, so a lane
-  // holds no two neighbours of a row.  Each wave writes its (32 MI) x 64 sub-tile in MI parts of 32
+  // holds no two neighbours of a row.  Each wave writes its 64 x 64 sub-tile in two parts of 32
   // rows into its own LDS slab (row stride GEPI_LD floats: the two half-waves of one store land
   // in different banks), then reads them back four consecutive columns per lane and writes 16
   // bytes per lane (C) or 8 bytes (BF16 outputs).
@@ -331,7 +333,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MI == 
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, LOSS_WAVES, wave);
+  if constexpr (EPI == EPI_BIAS_MSE) store_loss_part(g, loss, tl.y * nx + tl.x, 2 * WM, wave);
 }
 
 // Sum of the split-K partial products in split order, then the epilogue.
@@ -357,7 +359,7 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs g, int spli
 // permutes it in registers, where a transpose launch had copied the operand first.  AF32: A is the
 // FP32 input batch (rows of it by the row vector), rounded on the way.
 // Measured, products and what went with them (split sums, transposes, rounding of the input): one
-// sample through 12-512-512-512-512-10000 65 -> 37 us, 4,096 samples' hidden layers 90 -> 60 us; all
+// sample through 12-512-512-512-512-10000 65 -> 30 us, 4,096 samples' hidden layers 90 -> 50 us; all
 // results the same bit for bit.
 // ---------------------------------------------------------------------------------------
 constexpr int HB = 64, HK = 128, HLD = HK + 8;  // tile, K stage, LDS row stride (rows 4 banks apart)
@@ -700,8 +702,8 @@ int64_t gemm_loss_parts(int M, int N, int K) {
     const int splits = gemm_splits(M, N, K, kchunk), groups = splits > 2 ? 4 : splits;
     return splits > G64_SPLITS ? 0 : (int64_t)((M + HB - 1) / HB) * ((N + HB - 1) / HB) * groups * LOSS_WAVES;
   }
-  const int bm = gemm_tall(M, N) ? 2 * GBM : GBM;
-  return (int64_t)((M + bm - 1) / bm) * ((N + GBN - 1) / GBN) * LOSS_WAVES;
+  const int wm = gemm_tall(M, N) ? 4 : 2;  // wave rows of k_gemm
+  return (int64_t)((M + 64 * wm - 1) / (64 * wm)) * ((N + GBN - 1) / GBN) * 2 * wm;
 }
 
 bool gemm_reads_f32(int M, int N) { return gemm_use64(M, N); }
@@ -740,7 +742,7 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
 #define PCMD_GEMM_CASE(E_)                                                                             \
   if (epi == E_) {                                                                                     \
     if (tall)                                                                                          \
-      hipLaunchKernelGGL((k_gemm<E_, 4>), grid, dim3(256), 0, s, g);                                   \
+      hipLaunchKernelGGL((k_gemm<E_, 4>), grid, dim3(512), 0, s, g);                                   \
     else                                                                                               \
       hipLaunchKernelGGL((k_gemm<E_, 2>), grid, dim3(256), 0, s, g);                                   \
     return hipGetLastError();                                                                          \

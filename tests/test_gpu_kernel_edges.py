@@ -185,6 +185,22 @@ def test_backward_products_of_a_layer(ctx, n):
             o += k
 
 
+# The fused loss in the 256-row tiles of eight waves (4,096 samples and 2,048 bins or more, both ragged):
+# FP64 sums of BF16-rounded activations' errors, as in the network's loss test.
+def test_loss_of_a_large_batch(ctx):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    dims = (12, 64, 2100)
+    net = SurrogateNet(ctx, dims, si.mlp_init(dims, 9), device=DEV)
+    r = np.random.default_rng(9)
+    x = r.uniform(-1, 1, (4100, 12)).astype(np.float32)
+    t = r.normal(0, 1, (4100, 2100)).astype(np.float32)
+    loss = torch.empty(1, dtype=torch.float32, device=DEV)
+    net.train_step(torch.from_numpy(x).to(DEV), torch.from_numpy(t).to(DEV), 0.0, loss_out=loss, apply_update=False)
+    ctx.sync()
+    lo, _ = om.loss_and_grad(net.master.cpu().numpy().astype(np.float64), dims, x, t)
+    assert float(loss.item()) == pytest.approx(lo, rel=1e-4)
+
+
 # One Adam launch over layers whose sides are no multiples of the 64 x 64 tile: master weights against
 # the update rule (one step from zero moments moves a weight by at most lr; FP32 steps), the BF16 copies
 # and the transposed ones exactly the rounded master.
