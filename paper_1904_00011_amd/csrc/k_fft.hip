@@ -14,7 +14,7 @@
 // rows 43 us (full complex transforms, radix-2 stages in LDS and two transposes took 720 us);
 // 4096 x 4096 x 3: 200, 280 and 232 us (3.0 ms).
 //
-// The PSF spectra and twiddles are kept between calls: a one-workgroup kernel compares the
+// The PSF spectra and twiddles are kept between calls: a workgroup compares the
 // caller's PSF with the copy the spectra were built from (and takes the new one), and the
 // spectrum kernels return at once unless something changed, so repeated evaluations with one
 // PSF transform only the image.  With the 4 x 4 sub-pixel grid (Sec. 2.2) each of the 16 regions
@@ -61,18 +61,54 @@ size_t fft_scratch_bytes(int B, int N, int K, int R) {
   return fft_psf_copy_offset(B, N, R) + sizeof(float) * (size_t)R * B * K * K + 256;
 }
 
-// flag = force or (any element of psf differs from copy); copy = psf.  One workgroup: each
-// thread compares its elements with their old copies before overwriting them.
-__global__ void __launch_bounds__(1024) k_psf_update(const float *__restrict__ psf, float *__restrict__ copy, int64_t n,
-                                                      int force, uint32_t *__restrict__ flag) {
+// Block 0: flag = force or (any element of psf differs from copy); copy = psf (each thread compares its
+// elements with their old copies before overwriting them).  The other blocks check one PSF each: finite,
+// non-negative and summing to one within 1e-3 (a failure sets a status bit reported by pcmd_sync).
+// Latency of a few dependent loads: eight at a time.
+__global__ void __launch_bounds__(1024) k_psf_update(const float *__restrict__ psf, float *copy, int64_t n, int KK, int force,
+                                                      uint32_t *__restrict__ flag, uint32_t *status) {
   __shared__ int any;
+  __shared__ double red[16];
+  if (blockIdx.x > 0) {
+    const float *P = psf + (size_t)(blockIdx.x - 1) * KK;
+    double s = 0.0;
+    bool bad = false;
+#pragma unroll 8
+    for (int i = threadIdx.x; i < KK; i += 1024) {
+      const float v = P[i];
+      bad = bad || !(v >= 0.0f) || !isfinite(v);
+      s += (double)v;
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+    if (__any(bad)) s = NAN;
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < 16; ++w) s += red[w];
+      if (!(fabs(s - 1.0) <= 1e-3)) atomicOr(status, STATUS_BAD_PSF);
+    }
+    return;
+  }
   if (threadIdx.x == 0) any = force;
   __syncthreads();
   int d = 0;
-  for (int64_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const float v = psf[i];
-    if (__float_as_uint(v) != __float_as_uint(copy[i])) d = 1;
-    copy[i] = v;
+  for (int64_t i0 = threadIdx.x; i0 < n; i0 += 8192) {
+    float v[8], c[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t i = i0 + 1024 * k;
+      v[k] = i < n ? psf[i] : 0.0f;
+      c[k] = i < n ? copy[i] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const int64_t i = i0 + 1024 * k;
+      if (__float_as_uint(v[k]) != __float_as_uint(c[k])) {
+        d = 1;
+        copy[i] = v[k];
+      }
+    }
   }
   if (d) any = 1;
   __syncthreads();
@@ -366,7 +402,7 @@ static int row_pairs_log(int rows) {
 
 template <int LOGN>
 static hipError_t conv_fft(const float *F, const float *psf, int B, int K, int grid, float *G, void *scratch, bool fresh,
-                           hipStream_t s) {
+                           uint32_t *status, hipStream_t s) {
   using D = FftDim<LOGN>;
   constexpr int N = D::N;
   const int R = grid * grid, pitch = (int)fft_pitch(N);
@@ -386,7 +422,8 @@ static hipError_t conv_fft(const float *F, const float *psf, int B, int K, int g
   if (fresh) hipLaunchKernelGGL(k_twiddles, dim3((N / 2 + 255) / 256), dim3(256), 0, s, tw, N);
   // PSF spectra, rebuilt only when the PSF (or the layout: fresh) changed.  psf is
   // [B][K][K] (grid 1) or [B][16][K][K]: region r of band b at psf + (b R + r) K K.
-  hipLaunchKernelGGL(k_psf_update, dim3(1), dim3(1024), 0, s, psf, copy, (int64_t)R * B * K * K, fresh ? 1 : 0, flag);
+  hipLaunchKernelGGL(k_psf_update, dim3(1 + R * B), dim3(1024), 0, s, psf, copy, (int64_t)R * B * K * K, K * K, fresh ? 1 : 0,
+                     flag, status);
   for (int r = 0; r < R; ++r) {
     cplx *Sr = Sp + (size_t)r * B * band;
     hipLaunchKernelGGL(k_fft_rows_fwd<LOGN>, rgrid, rblk, rlds, s, nullptr, psf + (size_t)r * K * K, K, (int64_t)R * K * K,
@@ -413,11 +450,11 @@ static hipError_t conv_fft(const float *F, const float *psf, int B, int K, int g
 }
 
 hipError_t launch_conv_fft(const float *F, const float *psf, int B, int N, int K, int grid, float *G, void *scratch,
-                           bool fresh, hipStream_t s) {
+                           bool fresh, uint32_t *status, hipStream_t s) {
   if (!fft_supported(N) || (grid != 1 && grid != 4)) return hipErrorInvalidValue;
   switch (ilog2(N)) {
 #define PCMD_FFT(L) \
-  case L: return conv_fft<L>(F, psf, B, K, grid, G, scratch, fresh, s);
+  case L: return conv_fft<L>(F, psf, B, K, grid, G, scratch, fresh, status, s);
     PCMD_FFT(3) PCMD_FFT(4) PCMD_FFT(5) PCMD_FFT(6) PCMD_FFT(7) PCMD_FFT(8) PCMD_FFT(9) PCMD_FFT(10) PCMD_FFT(11) PCMD_FFT(12)
 #undef PCMD_FFT
   }

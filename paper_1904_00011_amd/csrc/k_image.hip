@@ -10,39 +10,6 @@
 
 namespace pcmd {
 
-// One block per PSF (band, and region of the sub-pixel grid): check that it is finite,
-// non-negative and sums to one within 1e-3 (a failure sets a status bit reported by pcmd_sync).
-// The FFT path runs this kernel; the direct convolution makes the same check in its first tile of
-// each PSF (psf_check_wave).
-__device__ __forceinline__ void psf_check_body(const ConvArgs &a) {
-  __shared__ double red[256];
-  __shared__ int bad;
-  const int b = blockIdx.x;  // PSF index b_band * grid^2 + region
-  const int KK = a.K * a.K;
-  if (threadIdx.x == 0) bad = 0;
-  __syncthreads();
-  double s = 0.0;
-  for (int i = threadIdx.x; i < KK; i += 256) {
-    const float v = a.psf[(size_t)b * KK + i];
-    if (!(v >= 0.0f) || !isfinite(v)) bad = 1;
-    s += (double)v;
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0 && (bad || !(fabs(red[0] - 1.0) <= 1e-3))) atomicOr(a.status, STATUS_BAD_PSF);
-}
-
-__global__ void __launch_bounds__(256) k_psf_check(ConvArgs a) { psf_check_body(a); }
-
-hipError_t launch_psf_check(const ConvArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_psf_check, dim3(a.B * a.grid * a.grid), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 __global__ void __launch_bounds__(256) k_copy_f32(const float *__restrict__ src, float *__restrict__ dst, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) dst[i] = src[i];
@@ -124,9 +91,9 @@ static size_t conv_lds_bytes(int K, int RS, int rows) {
 // The largest PSF that the direct path takes is set by the smaller tile's LDS.
 size_t conv_direct_lds_bytes(int K) { return conv_tile_bytes(K, CT_YS); }
 
-// The PSF check of psf_check_body done by one wave (the direct convolution's first tile of each
-// PSF runs it beside its own work, which saves the check's launch): per-lane FP64 sums, then a
-// shuffle reduction.
+// One PSF (band, and region of the sub-pixel grid) checked by one wave, beside the convolution's first tile
+// of it: finite, non-negative and summing to one within 1e-3 (a failure sets a status bit reported by
+// pcmd_sync).  Per-lane FP64 sums, then a shuffle reduction.
 __device__ __forceinline__ void psf_check_wave(const ConvArgs &a, int b) {
   const int KK = a.K * a.K, lane = (int)(threadIdx.x & 63u);
   double s = 0.0;

@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(256) k_gemm_splitk_reduce(GemmArgs g, int spli
 // stage's loads in flight during the products.  Group g takes the K range [g kchunk, (g + 1) kchunk)
 // of a split product and group 0 adds the groups' sums in order, the sums and order of
 // k_gemm + k_gemm_splitk_reduce without their launch and trip through memory.  More ranges than 4 go
-// to blockIdx.z and the workspace, as in k_gemm.  TA / TB: that operand is stored K-major (A(m, k) =
+// to further blocks and the workspace.  TA / TB: that operand is stored K-major (A(m, k) =
 // A[k][m]) and transposed on its way into LDS: a thread reads an 8 x 8 block in eight 16-byte rows and
 // permutes it in registers, where a transpose launch had copied the operand first.  AF32: A is the
 // FP32 input batch (rows of it by the row vector), rounded on the way.

@@ -527,14 +527,11 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
   const float *Gp = (const float *)c->F.p;
   if (K > 1) {
     ConvArgs ca{B, N, K, (const float *)c->F.p, o->psf, (float *)c->G.p, c->status, psf_grid_of(o)};
-    if (use_fft) {  // the direct convolution checks the PSF itself
-      e = launch_psf_check(ca, s);
-      if (e != hipSuccess) return hip_fail(c, e, "psf check");
-    }
     ScopedTimer tm(c, PCMD_TIMER_CONV, 2.0 * (double)B * (double)npx, s);
     if (use_fft) {
       const bool fresh = c->fft_buf != c->fft.p || c->fft_B != B || c->fft_N != N || c->fft_K != K || c->fft_R != R;
-      e = launch_conv_fft((const float *)c->F.p, o->psf, B, N, K, psf_grid_of(o), (float *)c->G.p, c->fft.p, fresh, s);
+      e = launch_conv_fft((const float *)c->F.p, o->psf, B, N, K, psf_grid_of(o), (float *)c->G.p, c->fft.p, fresh,
+                          c->status, s);
       if (e == hipSuccess) {
         c->fft_buf = c->fft.p;
         c->fft_B = B;

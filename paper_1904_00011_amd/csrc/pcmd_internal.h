@@ -174,7 +174,7 @@ struct ReduceArgs {
   uint32_t k0, k1;
 };
 
-// PSF check (k_psf_check) and direct periodic convolution (k_conv_direct).
+// Direct periodic convolution (k_conv_direct).
 struct ConvArgs {
   int B, N, K;
   const float *F;    // [B][N][N]
@@ -250,7 +250,6 @@ hipError_t launch_prep_block_job(const BlockPrepArgs *table, int j, int nb, hipS
 hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, hipStream_t s);
 
 // k_image.hip
-hipError_t launch_psf_check(const ConvArgs &a, hipStream_t s);
 size_t conv_direct_lds_bytes(int K);
 // The direct convolution goes on to the noise and magnitudes (na.G unused); a.G may be NULL.
 hipError_t launch_conv_direct(const ConvArgs &a, const NoiseArgs &na, hipStream_t s);
@@ -264,7 +263,7 @@ int fft_supported(int N);
 size_t fft_scratch_bytes(int B, int N, int K, int R);
 // fresh: the scratch's twiddles, PSF copy and spectra are not those of this (B, N, K, grid)
 hipError_t launch_conv_fft(const float *F, const float *psf, int B, int N, int K, int grid, float *G, void *scratch,
-                           bool fresh, hipStream_t s);
+                           bool fresh, uint32_t *status, hipStream_t s);
 
 // k_hess.hip
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);

@@ -383,3 +383,26 @@ def test_convolution_goes_on_to_magnitudes(ctx, N, K, B, grid):
     c2 = 3000.0 * 10.0 ** (0.4 * (zp - np.where(fin, want, 0.0)))
     bound = 1.01 * 2.0 ** -24 * np.abs(want) + 1e-13 + 1.1 * 16 * 2.0 ** -53 * (c + 6.0 * np.sqrt(c)) / c2
     assert np.all(np.abs(m[fin] - want[fin]) <= bound[fin])
+
+
+# The Fourier path's PSF check (a block per PSF beside the comparison with the kept copy): a good PSF passes,
+# a sum off by more than 1e-3 or a negative value in the last PSF alone is reported.
+@pytest.mark.parametrize("K,grid", [(5, 1), (63, 1), (5, 4)])
+def test_fourier_path_checks_every_psf(ctx, K, grid):
+    import paper_1904_00011_amd as P
+    from tests import parity_utils as pu
+    r = np.random.default_rng(K)
+    good = r.uniform(0.1, 1.0, (2, 16, K, K) if grid == 4 else (2, K, K))
+    good = (good / good.sum(axis=(-2, -1), keepdims=True)).astype(np.float32)
+    high, negative = good.copy(), good.copy()
+    high.reshape(-1, K, K)[-1] *= np.float32(1.002)
+    negative.reshape(-1, K, K)[-1][0, 0] *= -1e-3
+    for psf, ok in ((good, True), (high, False), (negative, False), (good, True)):
+        obs = si.Obs(nim=64, seed=5, dmod=0.0, dust_model=0, psf=psf, noise_model=0, noise_sigma_mag=(0.0,) * 4,
+                     exptime=(1.0,) * 4, zp=(25.0,) * 4, sky=(0.0,) * 4, dust_R=(1.0,) * 4)
+        args = (ctx, np.array([0.7]), np.ones((2, 1), dtype=np.float32), obs)
+        if ok:
+            pu.gpu_simulate(*args, conv_path=P.CONV_FFT)
+        else:
+            with pytest.raises(P.PcmdError):
+                pu.gpu_simulate(*args, conv_path=P.CONV_FFT)
