@@ -14,10 +14,12 @@
 // At low stellar density most blocks draw nothing in every pixel of a wave and cost one Philox
 // block and one compare, instead of the per-entry rule's sixteen Philox blocks.
 //
-// Layout: a wave takes 128 pixels; its 64 lanes also hold one block's 64 cumulative thresholds and
+// Layout: a wave takes 64 or 128 pixels; its 64 lanes also hold one block's 64 cumulative thresholds and
 // entry fluxes in registers, so each star's binary search and flux gather are cross-lane reads
 // (ds_bpermute).  Slices interleave blocks like k_sample's interleaved 16-entry blocks and write the
 // same partial-sum layout, which k_reduce then sums in the same order.
+#include <algorithm>
+
 #include "pcmd_device.h"
 #include "pcmd_internal.h"
 
@@ -105,19 +107,26 @@ hipError_t launch_prep_block_job(const BlockPrepArgs *table, int j, int nb, hipS
   return hipGetLastError();
 }
 
-// Pixels per lane (one packs the queue worse, four leave LDS for three waves per SIMD: 2.07 and 2.72
-// against 1.75 ms), and groups of four stars per pixel queued at a time (two leave LDS for six waves).
-constexpr int BPPL = 2, BQG = 2;
+// Groups of four stars per pixel queued at a time (two leave LDS for six waves per SIMD).
+constexpr int BQG = 2;
 
-// The stars of one block over a wave's 64 BPPL pixels are queued as tasks (pixel, group of four stars of
+// Pixels per lane: two pack the queue better (4096 x 4096 above: 2.07 ms with one, 1.75 with two; four leave
+// LDS for three waves per SIMD: 2.72), one gives twice the waves where an image has few.  The line lies
+// at three two-pixel workgroups per CU: 128 x 128 with 26 slices (832 workgroups) 27 us with one and 24
+// with two, 180 x 180 with 11 (704) 145 and 191, 67 x 67 with 11 blocks of 380 stars each (99) 543 and 1071.
+static int block_ppl(int npx, int nchunks, int nb) {
+  return (int64_t)((npx + 511) / 512) * std::min(nchunks, nb) < 768 ? 1 : 2;
+}
+
+// The stars of one block over a wave's 64 PPL pixels are queued as tasks (pixel, group of four stars of
 // it, how many), which the lanes then take 64 at a time: a lane per pixel would draw words and search for
 // as many stars as the fullest of 64 pixels has, 18% to 36% of them there.  A task's stars go to
 // any pixel, so the sums are in LDS (FP64 adds; one wave's, in its own order).  Vector issue and LDS are
 // both busy three quarters of the time.  4096 x 4096 x 3 at 10^3 stars per pixel, 12 blocks: 2103 ->
 // 1561 us; 250 x 250, 726 blocks: 260 -> 193 us.
-template <int B, int S, bool DBG>
+template <int B, int S, bool DBG, int PPL>
 __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
-  constexpr int BP = B <= 2 ? 2 : 4, PX = 64 * BPPL;
+  constexpr int BP = B <= 2 ? 2 : 4, PX = 64 * PPL;
   __shared__ double acc_s[4][S * B][PX];
   __shared__ uint16_t task_s[4][PX * BQG];
   const int nblk_px = (a.npx + 4 * PX - 1) / (4 * PX);
@@ -135,7 +144,7 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
 #pragma unroll
   for (int k = 0; k < S * B; ++k)
 #pragma unroll
-    for (int q = 0; q < BPPL; ++q) acc[k][q * 64 + lane] = 0.0;
+    for (int q = 0; q < PPL; ++q) acc[k][q * 64 + lane] = 0.0;
 
   uint32_t ptrs_failed = 0u;
   // every lane runs every step below, so the cross-lane reads always find their source lane active;
@@ -144,13 +153,13 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
     const BlockRec r = ld_const(brec + b);
     const uint32_t kind = r.kk & KIND_MASK;
     if (kind == KIND_ZERO) continue;
-    uint32_t n[BPPL];
+    uint32_t n[PPL];
     bool some = false;
     if (kind == KIND_INV) {
       // N = #{k < K : T_k <= u}, walking up while any lane of the wave is still above
-      uint32_t u[BPPL];
+      uint32_t u[PPL];
 #pragma unroll
-      for (int q = 0; q < BPPL; ++q) {
+      for (int q = 0; q < PPL; ++q) {
         u[q] = philox10(p0 + 64u * q + lane, (uint32_t)b, TAG_BLOCK, 0u, a.k0, a.k1).x;
         n[q] = u[q] >= r.T[0] ? 1u : 0u;
         some = some || n[q] != 0u;
@@ -161,7 +170,7 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
         const uint32_t t = k < 3 ? r.T[k] : thr[(size_t)b * THR_STRIDE + k];
         bool more = false;
 #pragma unroll
-        for (int q = 0; q < BPPL; ++q) {
+        for (int q = 0; q < PPL; ++q) {
           const bool c = u[q] >= t;
           n[q] += c ? 1u : 0u;
           more = more || c;
@@ -171,7 +180,7 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
     } else {
       const PtrsConst cst = ld_const(pc + b);
 #pragma unroll
-      for (int q = 0; q < BPPL; ++q) {
+      for (int q = 0; q < PPL; ++q) {
         n[q] = ptrs_draw(cst, p0 + 64u * q + lane, (uint32_t)b, TAG_BLOCK_PTRS, a.k0, a.k1, a.lnfact, ptrs_failed);
         some = some || n[q] != 0u;
       }
@@ -187,7 +196,7 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
     const uint32_t c16 = (uint32_t)__builtin_amdgcn_readlane(cl, 15), c32 = (uint32_t)__builtin_amdgcn_readlane(cl, 31),
                    c48 = (uint32_t)__builtin_amdgcn_readlane(cl, 47);
 #pragma unroll
-    for (int q = 0; q < BPPL; ++q)
+    for (int q = 0; q < PPL; ++q)
       if (p0 + 64u * q + lane >= (uint32_t)a.npx) n[q] = 0u;
     for (uint32_t g0 = 0;; g0 += BQG) {
       // task: pixel | (group - g0) << 8 | (stars - 1) << 9
@@ -195,7 +204,7 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
       for (uint32_t gg = 0; gg < BQG; ++gg) {
         const uint32_t before = tasks, first = 4u * (g0 + gg);
 #pragma unroll
-        for (int q = 0; q < BPPL; ++q) {
+        for (int q = 0; q < PPL; ++q) {
           const uint64_t m = __ballot(n[q] > first);
           if (m == 0ull) continue;
           const uint32_t at = tasks + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -266,7 +275,7 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
 #pragma unroll
   for (int k = 0; k < S * B; ++k)
 #pragma unroll
-    for (int q = 0; q < BPPL; ++q) {
+    for (int q = 0; q < PPL; ++q) {
       const uint32_t p = p0 + 64u * q + lane;
       if (p >= (uint32_t)a.npx) continue;
       float *o = a.part + ((size_t)chunk * S * B + k) * plane + p;
@@ -275,54 +284,63 @@ __device__ __forceinline__ void sample_block_body(const BlockSampleArgs &a) {
     }
 }
 
-static dim3 sample_block_grid(int npx, int nchunks) { return dim3((unsigned)((npx + 256 * BPPL - 1) / (256 * BPPL) * nchunks)); }
+static dim3 sample_block_grid(int npx, int nchunks, int ppl) {
+  return dim3((unsigned)((npx + 256 * ppl - 1) / (256 * ppl) * nchunks));
+}
 
-template <int B, int S, bool DBG>
+template <int B, int S, bool DBG, int PPL>
 __global__ void __launch_bounds__(256) k_sample_block(BlockSampleArgs a) {
-  sample_block_body<B, S, DBG>(a);
+  sample_block_body<B, S, DBG, PPL>(a);
 }
 // batched: job j of a descriptor table, both partial streams (as every batch job)
-template <int B>
+template <int B, int PPL>
 __global__ void __launch_bounds__(256) k_sample_block_job(const BlockSampleArgs *__restrict__ t, int j) {
   const BlockSampleArgs a = t[j];
-  sample_block_body<B, 2, false>(a);
+  sample_block_body<B, 2, false, PPL>(a);
 }
 
-template <int B>
+template <int B, int PPL>
 static hipError_t launch_sample_block_b(const BlockSampleArgs &a, hipStream_t s) {
-  const dim3 grid = sample_block_grid(a.npx, a.nchunks);
+  const dim3 grid = sample_block_grid(a.npx, a.nchunks, PPL);
   const bool dbg = a.dbg_counts != nullptr;
   if (a.S == 2 && dbg)
-    hipLaunchKernelGGL((k_sample_block<B, 2, true>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_sample_block<B, 2, true, PPL>), grid, dim3(256), 0, s, a);
   else if (a.S == 2)
-    hipLaunchKernelGGL((k_sample_block<B, 2, false>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_sample_block<B, 2, false, PPL>), grid, dim3(256), 0, s, a);
   else if (dbg)
-    hipLaunchKernelGGL((k_sample_block<B, 1, true>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_sample_block<B, 1, true, PPL>), grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((k_sample_block<B, 1, false>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_sample_block<B, 1, false, PPL>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 hipError_t launch_sample_block(const BlockSampleArgs &a, hipStream_t s) {
+  const bool two = block_ppl(a.npx, a.nchunks, a.nb) == 2;
   switch (a.B) {
-    case 1: return launch_sample_block_b<1>(a, s);
-    case 2: return launch_sample_block_b<2>(a, s);
-    case 3: return launch_sample_block_b<3>(a, s);
-    case 4: return launch_sample_block_b<4>(a, s);
+    case 1: return two ? launch_sample_block_b<1, 2>(a, s) : launch_sample_block_b<1, 1>(a, s);
+    case 2: return two ? launch_sample_block_b<2, 2>(a, s) : launch_sample_block_b<2, 1>(a, s);
+    case 3: return two ? launch_sample_block_b<3, 2>(a, s) : launch_sample_block_b<3, 1>(a, s);
+    case 4: return two ? launch_sample_block_b<4, 2>(a, s) : launch_sample_block_b<4, 1>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
-hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, hipStream_t s) {
-  const dim3 grid = sample_block_grid(npx, nchunks);
+template <int PPL>
+static hipError_t launch_sample_block_job_p(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, hipStream_t s) {
+  const dim3 grid = sample_block_grid(npx, nchunks, PPL);
   switch (B) {
-    case 1: hipLaunchKernelGGL(k_sample_block_job<1>, grid, dim3(256), 0, s, table, j); break;
-    case 2: hipLaunchKernelGGL(k_sample_block_job<2>, grid, dim3(256), 0, s, table, j); break;
-    case 3: hipLaunchKernelGGL(k_sample_block_job<3>, grid, dim3(256), 0, s, table, j); break;
-    case 4: hipLaunchKernelGGL(k_sample_block_job<4>, grid, dim3(256), 0, s, table, j); break;
+    case 1: hipLaunchKernelGGL((k_sample_block_job<1, PPL>), grid, dim3(256), 0, s, table, j); break;
+    case 2: hipLaunchKernelGGL((k_sample_block_job<2, PPL>), grid, dim3(256), 0, s, table, j); break;
+    case 3: hipLaunchKernelGGL((k_sample_block_job<3, PPL>), grid, dim3(256), 0, s, table, j); break;
+    case 4: hipLaunchKernelGGL((k_sample_block_job<4, PPL>), grid, dim3(256), 0, s, table, j); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, int nb, hipStream_t s) {
+  return block_ppl(npx, nchunks, nb) == 2 ? launch_sample_block_job_p<2>(table, j, B, npx, nchunks, s)
+                                          : launch_sample_block_job_p<1>(table, j, B, npx, nchunks, s);
 }
 
 }  // namespace pcmd

@@ -247,7 +247,7 @@ hipError_t launch_sample_block(const BlockSampleArgs &a, hipStream_t s);
 hipError_t launch_sample_thin_job(const BatchSampleJob *jobs, int t, int B, int npx, int nchunks, hipStream_t s);
 // batched: job j of a descriptor table (nb blocks; the sampler's grid covers npx pixels x nchunks)
 hipError_t launch_prep_block_job(const BlockPrepArgs *table, int j, int nb, hipStream_t s);
-hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, hipStream_t s);
+hipError_t launch_sample_block_job(const BlockSampleArgs *table, int j, int B, int npx, int nchunks, int nb, hipStream_t s);
 
 // k_image.hip
 size_t conv_direct_lds_bytes(int K);

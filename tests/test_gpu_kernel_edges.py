@@ -333,11 +333,11 @@ def test_fourier_path_sides(ctx, N, K, B, grid):
         assert np.all(np.abs(got["flux_psf"].reshape(B, N, N) - want) <= 2.0 ** -24 * np.abs(want) + 1e-13 * F.max())
 
 
-# Block-rule stars queued over a wave's 128 pixels: images that end inside a wave's pixels, pixels with no,
+# Block-rule stars queued over a wave's 64 pixels (small images) or 128 (the last size): images that end inside a wave's pixels, pixels with no,
 # few and many stars of a block (more groups of four than are queued at once), block totals by inversion
 # and by rejection, every split.  Counts are those of the oracle; flux as for the mixed groups.
 @pytest.mark.parametrize("frac", [None, 0.3, 0.5, 1.0])
-@pytest.mark.parametrize("E,B,nim,scale", [(1, 1, 3, 1.0), (63, 2, 11, 0.01), (65, 3, 12, 3.0), (130, 4, 23, 0.2), (64, 3, 9, 40.0)])
+@pytest.mark.parametrize("E,B,nim,scale", [(1, 1, 3, 1.0), (63, 2, 11, 0.01), (65, 3, 12, 3.0), (130, 4, 23, 0.2), (64, 3, 9, 40.0), (3, 2, 630, 1.0)])
 def test_block_sampler_queue(ctx, E, B, nim, scale, frac):
     from tests import parity_utils as pu
     r = np.random.default_rng(E + B)
