@@ -377,13 +377,16 @@ union Run8 {
 // registers hold (what they produce is not stored): a value given to them made every load wait for
 // the one before it, and reading the last row instead (64 times, for one sample, by every block)
 // crowded one L2 channel.
+// So does a last stage of whole steps of 16 (a layer of 64 or 96: one element at a time its staging took
+// 2 us a product): in place of a run from ke on the last one is loaded, and nothing reads it in LDS.
+__device__ __forceinline__ bool whole_steps64(int k0, int ke) { return k0 < ke && (k0 + HK <= ke || (ke - k0) % 16 == 0); }
 // Row-major: 4 runs of 8 k; thread t's run i is row (t + 256 i) / 16.
 __device__ __forceinline__ void load_rows64(Run8 (&x)[4], const __bf16 *__restrict__ src, int ld, int rows, int r0, int k0,
-                                            int t) {
+                                            int ke, int t) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int idx = t + 256 * i;
-    const int r = r0 + (idx >> 4), k = k0 + (idx & 15) * 8;
+    const int r = r0 + (idx >> 4), k = min(k0 + (t & 15) * 8, ke - 8);
     if (r < rows) x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)r * ld + k);
   }
 }
@@ -396,8 +399,8 @@ __device__ __forceinline__ void store_rows64(__bf16 *lds, const Run8 (&x)[4], in
 }
 // K-major (rows a multiple of 8): block b holds k 8 (b / 8) .. + 7 and rows 8 (b % 8) .. + 7.
 __device__ __forceinline__ void load_cols64(Run8 (&x)[8], const __bf16 *__restrict__ src, int ld, int rows, int r0, int k0,
-                                            int b) {
-  const int r = r0 + (b & 7) * 8, k = k0 + (b >> 3) * 8;
+                                            int ke, int b) {
+  const int r = r0 + (b & 7) * 8, k = min(k0 + (b >> 3) * 8, ke - 8);
   if (r >= rows) return;
 #pragma unroll
   for (int i = 0; i < 8; ++i) x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)(k + i) * ld + r);
@@ -465,22 +468,22 @@ __device__ __forceinline__ void gemm64_block(const GemmArgs &g, unsigned block, 
   const bool has_a = TA && (BOTH ? t < 128 : t < 128), has_b = TB && (BOTH ? t >= 128 : t < 128);
   Run8 ra[4] = {}, rb[4] = {}, rc[8] = {};
   auto load = [&](int k0) {
-    if (k0 + HK > ke) return;
+    if (!whole_steps64(k0, ke)) return;
     if (va) {
-      if constexpr (!TA) load_rows64(ra, g.A, g.lda, g.M, bm, k0, t);
+      if constexpr (!TA) load_rows64(ra, g.A, g.lda, g.M, bm, k0, ke, t);
       if constexpr (TA)
-        if (has_a) load_cols64(rc, g.A, g.lda, g.M, bm, k0, cb);
+        if (has_a) load_cols64(rc, g.A, g.lda, g.M, bm, k0, ke, cb);
     }
     if (vb) {
-      if constexpr (!TB) load_rows64(rb, g.B, g.ldb, g.N, bn, k0, t);
+      if constexpr (!TB) load_rows64(rb, g.B, g.ldb, g.N, bn, k0, ke, t);
       if constexpr (TB)
-        if (has_b) load_cols64(rc, g.B, g.ldb, g.N, bn, k0, cb);
+        if (has_b) load_cols64(rc, g.B, g.ldb, g.N, bn, k0, ke, cb);
     }
   };
   load(kb);
   for (int st = 0; st < stages; ++st) {
     const int k0 = kb + st * HK;
-    const bool whole = k0 + HK <= ke;
+    const bool whole = whole_steps64(k0, ke);
     if (st > 0) __syncthreads();  // the previous stage's reads are over
     if (whole && va) {
       if constexpr (!TA) store_rows64(As, ra, t);
@@ -596,8 +599,8 @@ __global__ void __launch_bounds__(64 * COLSUM_WAVES) k_colsum(ColsumArgs a) {
 // the chip idle (512 wide, 1,024 samples: 128 blocks, 64 and 8: 26 -> 12 us; the
 // 10,000-bin output layer 65 -> 61 us).
 template <int GW, int GX>
-__global__ void __launch_bounds__(256 * (GW > GX ? GW : GX)) k_gemm64_back(GemmArgs w, GemmArgs x, ColsumArgs c, unsigned nbc,
-                                                                           unsigned nbx) {
+__global__ void __launch_bounds__(256 * (GW > GX ? GW : GX))
+k_gemm64_back(GemmArgs w, GemmArgs x, ColsumArgs c, unsigned nbc, unsigned nbx) {
   extern __shared__ __attribute__((aligned(16))) char smem64[];
   const unsigned id = blockIdx.x;
   // whole waves leave a product with fewer groups (a barrier waits for the waves that are left)

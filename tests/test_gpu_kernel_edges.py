@@ -111,7 +111,7 @@ def test_loglike_bin_counts(ctx, nbins, mode):
 # are exact in FP32; K additions of 2^-24 relative to the running sum's magnitude, at most
 # sum |a||b| (the largest of the three sums below).
 @pytest.mark.parametrize("M,N,K", [(64, 64, 128), (65, 63, 129), (1, 512, 512), (33, 100, 700), (64, 72, 1024), (200, 8, 2100),
-                                   (1024, 512, 12)])
+                                   (1024, 512, 12), (72, 104, 64), (64, 72, 144), (130, 40, 96), (40, 64, 24), (8, 16, 16)])
 @pytest.mark.parametrize("at,bt", [(False, False), (True, True), (True, False), (False, True)])
 def test_gemm_small_tiles(ctx, M, N, K, at, bt):
     r = np.random.default_rng(M + N + K)
