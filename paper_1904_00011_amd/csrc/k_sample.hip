@@ -158,8 +158,11 @@ __device__ __forceinline__ void prep_body(const PrepArgs &a, int i) {
 }
 
 __global__ void __launch_bounds__(256) k_prep(PrepArgs a) { prep_body(a, blockIdx.x * blockDim.x + threadIdx.x); }
+// batched: the jobs j + blockIdx.z of a descriptor table, the grid sized for the largest of them (a launch
+// per job left most of the chip idle in each: 24 uneven jobs' tables 24 x 18 us, sums 24 x 25)
 __global__ void __launch_bounds__(256) k_prep_job(const PrepArgs *__restrict__ t, int j) {
-  const PrepArgs a = t[j];
+  const PrepArgs a = t[j + blockIdx.z];
+  if (blockIdx.x * blockDim.x >= (unsigned)entries_padded(a.E)) return;
   prep_body(a, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
@@ -387,7 +390,7 @@ __device__ __forceinline__ void prep_alias_walk(const PrepArgs &a) {
 }
 __global__ void __launch_bounds__(64 * ALIAS_WAVES) k_prep_alias(PrepArgs a) { prep_alias_walk(a); }
 __global__ void __launch_bounds__(64 * ALIAS_WAVES) k_prep_alias_job(const PrepArgs *__restrict__ t, int j) {
-  const PrepArgs a = t[j];
+  const PrepArgs a = t[j + blockIdx.z];
   prep_alias_walk(a);
 }
 
@@ -401,9 +404,11 @@ hipError_t launch_prep_alias(const PrepArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_prep_alias, prep_alias_grid(a.E, a.thin == THIN_TABLE ? 2 : 1), dim3(64 * ALIAS_WAVES), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_prep_alias_job(const PrepArgs *table, int j, int E, int parts, hipStream_t s) {
+hipError_t launch_prep_alias_job(const PrepArgs *table, int j, int n, int E, int parts, hipStream_t s) {
   if (parts != 1 && parts != 2) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_prep_alias_job, prep_alias_grid(E, parts), dim3(64 * ALIAS_WAVES), 0, s, table, j);
+  dim3 grid = prep_alias_grid(E, parts);
+  grid.z = (unsigned)n;
+  hipLaunchKernelGGL(k_prep_alias_job, grid, dim3(64 * ALIAS_WAVES), 0, s, table, j);
   return hipGetLastError();
 }
 
@@ -411,8 +416,8 @@ hipError_t launch_prep(const PrepArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_prep, dim3((a.E + 255) / 256), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_prep_job(const PrepArgs *table, int j, int E, hipStream_t s) {
-  hipLaunchKernelGGL(k_prep_job, dim3((E + 255) / 256), dim3(256), 0, s, table, j);
+hipError_t launch_prep_job(const PrepArgs *table, int j, int n, int E, hipStream_t s) {
+  hipLaunchKernelGGL(k_prep_job, dim3((E + 255) / 256, 1, n), dim3(256), 0, s, table, j);
   return hipGetLastError();
 }
 
@@ -1063,8 +1068,10 @@ hipError_t launch_sample_persistent(const BatchSampleJob *jobs, int n_jobs, int 
 constexpr int RED_BATCH = 8;
 constexpr int REDUCE_WIDE = 262144;
 
-__device__ __forceinline__ void reduce_body(const ReduceArgs &a, int p, int b0, int b1) {
-  if (p >= a.npx) return;
+__device__ __forceinline__ void reduce_body(const ReduceArgs &a, int p) {
+  const bool wide = a.npx >= REDUCE_WIDE;
+  const int b0 = wide ? 0 : blockIdx.y, b1 = wide ? a.B : b0 + 1;
+  if (p >= a.npx || b0 >= a.B || (wide && blockIdx.y > 0)) return;
   const size_t plane = (size_t)a.npx;
   const size_t step = (size_t)a.S * a.B * plane;  // from one slice to the next
   double ebv = 0.0;
@@ -1101,23 +1108,20 @@ __device__ __forceinline__ void reduce_body(const ReduceArgs &a, int p, int b0, 
   }
 }
 
-__global__ void __launch_bounds__(256) k_reduce(ReduceArgs a) {
-  reduce_body(a, blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, gridDim.y == 1 ? a.B : blockIdx.y + 1);
-}
-// The record stays in memory: its uniform words are scalar loads, and a copy indexed by the band would
-// lie in scratch.
+__global__ void __launch_bounds__(256) k_reduce(ReduceArgs a) { reduce_body(a, blockIdx.x * blockDim.x + threadIdx.x); }
+// The jobs j + blockIdx.z, as in k_prep_job.  The record stays in memory: its uniform words are scalar loads,
+// and a copy indexed by the band would lie in scratch.
 __global__ void __launch_bounds__(256) k_reduce_job(const ReduceArgs *__restrict__ t, int j) {
-  reduce_body(t[j], blockIdx.x * blockDim.x + threadIdx.x, blockIdx.y, gridDim.y == 1 ? t[j].B : blockIdx.y + 1);
+  reduce_body(t[j + blockIdx.z], blockIdx.x * blockDim.x + threadIdx.x);
 }
-
-static dim3 reduce_grid(int npx, int B) { return dim3((npx + 255) / 256, npx >= REDUCE_WIDE ? 1 : B); }
 
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, reduce_grid(a.npx, a.B), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_reduce, dim3((a.npx + 255) / 256, a.npx >= REDUCE_WIDE ? 1 : a.B), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-hipError_t launch_reduce_job(const ReduceArgs *table, int j, int npx, int B, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_job, reduce_grid(npx, B), dim3(256), 0, s, table, j);
+// npx_min, npx_max: of the n jobs
+hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_min, int npx_max, int B, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_job, dim3((npx_max + 255) / 256, npx_min >= REDUCE_WIDE ? 1 : B, n), dim3(256), 0, s, table, j);
   return hipGetLastError();
 }
 

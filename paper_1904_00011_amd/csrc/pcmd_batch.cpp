@@ -419,6 +419,9 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
 }
 
 // Queue the whole batch on stream s (eagerly, or into a graph under capture).
+// Jobs of one launch at most (a grid's third dimension goes to 65,535).
+constexpr int MAX_JOBS_Z = 32768;
+
 static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
   char *d = (char *)p->desc.p;
   const PrepArgs *pa = (const PrepArgs *)(d + p->o_prep);
@@ -432,14 +435,21 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
   const BlockSampleArgs *bsa = (const BlockSampleArgs *)(d + p->o_bsamp);
   uint32_t *persist = (uint32_t *)p->counters.p + p->n_jobs;
   hipError_t e = hipSuccess;
+  // block tables first: the hybrid's per-point tables leave out the blocks the block rule draws
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) {
     const JobInfo &ji = p->info[j];
-    // block tables first: the hybrid's per-point tables leave out the blocks the block rule draws
     if (ji.sampler != PCMD_SAMPLER_POINT) e = launch_prep_block_job(bpa, j, ji.nb, s);
-    if (e == hipSuccess && ji.sampler != PCMD_SAMPLER_BLOCK) {
-      e = launch_prep_job(pa, j, ji.E, s);
-      if (e == hipSuccess) e = launch_prep_alias_job(pa, j, ji.E, ji.alias_parts, s);
+  }
+  // runs of consecutive jobs with per-point tables (all of them, unless some take the block rule alone)
+  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess;) {
+    int j1 = j0, E = 0, parts = 1;
+    for (; j1 < p->n_jobs && j1 - j0 < MAX_JOBS_Z && p->info[j1].sampler != PCMD_SAMPLER_BLOCK; ++j1) {
+      E = std::max(E, p->info[j1].E);
+      parts = std::max(parts, p->info[j1].alias_parts);
     }
+    if (j1 > j0) e = launch_prep_job(pa, j0, j1 - j0, E, s);
+    if (j1 > j0 && e == hipSuccess) e = launch_prep_alias_job(pa, j0, j1 - j0, E, parts, s);
+    j0 = j1 > j0 ? j1 : j0 + 1;
   }
   if (e == hipSuccess) e = launch_reset_counter(persist, s);
   if (e == hipSuccess)
@@ -456,12 +466,19 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
     const JobInfo &ji = p->info[j];
     if (ji.sampler != PCMD_SAMPLER_POINT) e = launch_sample_block_job(bsa, j, ji.B, ji.npx, ji.nchunks, superblocks(ji.E), s);
   }
+  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess; j0 += MAX_JOBS_Z) {
+    const int n = std::min(p->n_jobs - j0, MAX_JOBS_Z);
+    int lo = p->info[j0].npx, hi = lo;
+    for (int j = j0; j < j0 + n; ++j) {
+      lo = std::min(lo, p->info[j].npx);
+      hi = std::max(hi, p->info[j].npx);
+    }
+    e = launch_reduce_job(ra, j0, n, lo, hi, p->B, s);
+  }
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) {
     const JobInfo &ji = p->info[j];
-    e = launch_reduce_job(ra, j, ji.npx, ji.B, s);
-    if (e == hipSuccess)
-      e = ji.K > 1 ? launch_conv_direct_job(ca, na, j, ji.B, ji.N, ji.K, ji.grid, s)
-                   : launch_noise_mag_job(na, j, ji.npx, ji.B, s);
+    e = ji.K > 1 ? launch_conv_direct_job(ca, na, j, ji.B, ji.N, ji.K, ji.grid, s)
+                 : launch_noise_mag_job(na, j, ji.npx, ji.B, s);
   }
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) e = launch_hess_job(ha, j, p->info[j].npx, p->nbins, s);
   if (e == hipSuccess) e = launch_loglike_jobs(la, p->n_jobs, p->nbins, s);

@@ -230,15 +230,15 @@ struct BatchSampleJob {
 // k_sample.hip
 hipError_t launch_entries(const pcmd_grid *g, const double *scale, double *lam, uint32_t *status, hipStream_t s);
 hipError_t launch_prep(const PrepArgs &a, hipStream_t s);
-hipError_t launch_prep_job(const PrepArgs *table, int j, int E, hipStream_t s);
+hipError_t launch_prep_job(const PrepArgs *table, int j, int n, int E, hipStream_t s);
 hipError_t launch_prep_alias(const PrepArgs &a, hipStream_t s);
-hipError_t launch_prep_alias_job(const PrepArgs *table, int j, int E, int parts, hipStream_t s);
+hipError_t launch_prep_alias_job(const PrepArgs *table, int j, int n, int E, int parts, hipStream_t s);
 hipError_t launch_sample(const SampleArgs &a, hipStream_t s);
 hipError_t launch_sample_persistent(const BatchSampleJob *jobs, int n_jobs, int total_items, int B, uint32_t *counter,
                                     int n_workgroups, hipStream_t s);
 hipError_t launch_reset_counter(uint32_t *counter, hipStream_t s);
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t s);
-hipError_t launch_reduce_job(const ReduceArgs *table, int j, int npx, int B, hipStream_t s);
+hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_min, int npx_max, int B, hipStream_t s);
 
 // k_sample_block.hip
 hipError_t launch_prep_block(const BlockPrepArgs &a, hipStream_t s);
