@@ -979,6 +979,19 @@ hipError_t launch_reset_counter(uint32_t *counter, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The job owning an item: the last one with item0 <= item (binary search over the table).
+__device__ __forceinline__ int job_of_item(const PCMD_CONST BatchSampleJob *cj, int n_jobs, int item) {
+  int lo = 0, hi = n_jobs - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (cj[mid].item0 <= item)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
+
 // Persistent batched sampler: every wave takes (job, 64-pixel block, slice) items from one
 // atomic counter until none is left, so no wave waits for another (items of one job are
 // consecutive; jobs come in the host's order).
@@ -992,23 +1005,14 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
     if (lane == 0) got = atomicAdd(counter, 1u);
     const int item = (int)__builtin_amdgcn_readfirstlane(got);
     if (item >= total_items) break;
-    // job owning the item: last job with item0 <= item (binary search over the table)
-    int lo = 0, hi = n_jobs - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (cj[mid].item0 <= item)
-        lo = mid;
-      else
-        hi = mid - 1;
-    }
-    const int j = __builtin_amdgcn_readfirstlane(lo);
+    const int j = job_of_item(cj, n_jobs, item);
     const int local = item - cj[j].item0;
     const int pblocks = cj[j].pblocks;  // 64-pixel blocks of the job
     const int chunk = local / pblocks;
     const int pblk = local - chunk * pblocks;
     const PCMD_CONST SampleArgs *ap = &cj[j].a;
     // batch jobs always carry two streams; F = 1/2 jobs draw their thinned entries afterwards in
-    // a launch of their own (k_sample_thin_job), as pcmd_simulate does
+    // a launch of their own (k_sample_thin_jobs), as pcmd_simulate does
     if (thin_mode_of_split(ap->split_mode) == THIN_TABLE)
       sample_tile<B, 2, false, PASS_ALL>(ap, (uint32_t)(pblk * 64) + lane, chunk);
     else
@@ -1016,28 +1020,31 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
   }
 }
 
-// The thinned entries' pass of one batch job (position t of the persistent sampler's table); a
-// job whose k_prep thinned nothing returns on one scalar load.  Held to 8 waves per SIMD like the
-// other sampler kernels (the compiler's own choice, 7 with 106 scalar registers, ran the uneven
-// batch 2.5% slower).  One persistent launch over the items of all listed jobs, as for the main
-// pass, measured 8% slower than these launches.
+// The thinned entries' pass of a batch: a wave takes one (job, 64-pixel block, slice) item of the persistent
+// sampler's table; items of jobs that are not at F = 1/2, or whose k_prep thinned nothing, return on a few
+// scalar loads.  (A launch per job left the chip idle at each one's end: 24 uneven jobs 2.85 -> 2.61 ms.)
+// Held to 8 waves per SIMD like the other sampler kernels.
 template <int B>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_sample_thin_job(const BatchSampleJob *__restrict__ jobs, int t) {
-  const PCMD_CONST SampleArgs *ap = &((const PCMD_CONST BatchSampleJob *)jobs)[t].a;
+k_sample_thin_jobs(const BatchSampleJob *__restrict__ jobs, int n_jobs, int total_items) {
+  const PCMD_CONST BatchSampleJob *cj = (const PCMD_CONST BatchSampleJob *)jobs;
+  const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (item >= total_items) return;
+  const int j = job_of_item(cj, n_jobs, item);
+  const PCMD_CONST SampleArgs *ap = &cj[j].a;
+  if (thin_mode_of_split(ap->split_mode) != THIN_HALF_HIGH) return;
   if (ap->thin_seen && *(const PCMD_CONST uint32_t *)ap->thin_seen != ap->gen) return;  // nothing thinned
-  const int nblk_px = (ap->npx + 255) >> 8;
-  const int chunk = blockIdx.x / nblk_px;
-  sample_thin_tile<B, false>(ap, (uint32_t)((blockIdx.x - chunk * nblk_px) * 256 + threadIdx.x), chunk);
+  const int local = item - cj[j].item0, pblocks = cj[j].pblocks, chunk = local / pblocks;
+  sample_thin_tile<B, false>(ap, (uint32_t)((local - chunk * pblocks) * 64) + (threadIdx.x & 63u), chunk);
 }
 
-hipError_t launch_sample_thin_job(const BatchSampleJob *jobs, int t, int B, int npx, int nchunks, hipStream_t s) {
-  const dim3 grid((unsigned)((npx + 255) / 256 * nchunks));
+hipError_t launch_sample_thin_jobs(const BatchSampleJob *jobs, int n_jobs, int total_items, int B, hipStream_t s) {
+  const dim3 grid((unsigned)((total_items + 3) / 4));
   switch (B) {
-    case 1: hipLaunchKernelGGL(k_sample_thin_job<1>, grid, dim3(256), 0, s, jobs, t); break;
-    case 2: hipLaunchKernelGGL(k_sample_thin_job<2>, grid, dim3(256), 0, s, jobs, t); break;
-    case 3: hipLaunchKernelGGL(k_sample_thin_job<3>, grid, dim3(256), 0, s, jobs, t); break;
-    case 4: hipLaunchKernelGGL(k_sample_thin_job<4>, grid, dim3(256), 0, s, jobs, t); break;
+    case 1: hipLaunchKernelGGL(k_sample_thin_jobs<1>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
+    case 2: hipLaunchKernelGGL(k_sample_thin_jobs<2>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
+    case 3: hipLaunchKernelGGL(k_sample_thin_jobs<3>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
+    case 4: hipLaunchKernelGGL(k_sample_thin_jobs<4>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

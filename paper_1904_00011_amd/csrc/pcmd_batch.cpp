@@ -455,13 +455,11 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
   if (e == hipSuccess)
     e = launch_sample_persistent(sa, p->n_jobs, p->total_items, p->B, persist, c->n_cu * p->wg, s);
   // then, in the order pcmd_simulate takes: the thinned entries of F = 1/2 jobs, added to the
-  // per-point partials (a launch per job; a job whose k_prep thinned nothing returns at once),
+  // per-point partials (a job whose k_prep thinned nothing returns at once),
   // and the block-rule draws, stored (block sampler) or added (hybrid)
-  for (int t = 0; t < p->n_jobs && e == hipSuccess; ++t) {
-    const int j = p->order[t];
-    const JobInfo &ji = p->info[j];
-    if (ji.items > 0 && ji.thin_mode == THIN_HALF_HIGH) e = launch_sample_thin_job(sa, t, ji.B, ji.npx, ji.nchunks, s);
-  }
+  bool thin = false;
+  for (int j = 0; j < p->n_jobs; ++j) thin = thin || (p->info[j].items > 0 && p->info[j].thin_mode == THIN_HALF_HIGH);
+  if (e == hipSuccess && thin) e = launch_sample_thin_jobs(sa, p->n_jobs, p->total_items, p->B, s);
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) {
     const JobInfo &ji = p->info[j];
     if (ji.sampler != PCMD_SAMPLER_POINT) e = launch_sample_block_job(bsa, j, ji.B, ji.npx, ji.nchunks, superblocks(ji.E), s);
