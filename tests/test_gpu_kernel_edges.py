@@ -406,3 +406,44 @@ def test_fourier_path_checks_every_psf(ctx, K, grid):
         else:
             with pytest.raises(P.PcmdError):
                 pu.gpu_simulate(*args, conv_path=P.CONV_FFT)
+
+
+# Launches over all jobs of a batch, sized for the largest: images on both sides of the size from which a
+# thread sums all bands, jobs of one entry and of many, without a PSF, dust splits with no, one and two tables
+# per entry, a block-rule job between the others.  Bit for bit the sequential calls, twice (graph replay).
+def test_batch_of_unlike_jobs(ctx):
+    r = np.random.default_rng(4)
+    psf = np.stack([np.outer(k, k) / np.sum(k) ** 2 for k in (np.array([1.0, 2.0, 1.0]), np.array([1.0, 3.0, 1.0]))])
+    hgrid = dict(x0=-2.0, dx=0.1, y0=-5.0, dy=0.3, nx=40, ny=40)
+    jobs = []
+    for k, (nim, E, dust, sampler, with_psf) in enumerate([(512, 40, 0.5, 0, True), (20, 1, 0.3, 0, True), (64, 700, None, 1, False),
+                                                          (33, 300, 0.5, 2, False), (520, 9, 0.3, 0, False)]):
+        obs = si.Obs(nim=nim, seed=31 + k, dmod=0.0, dust_model=0 if dust is None else 2, dust_frac=dust or 0.0,
+                     dust_R=(3.6, 1.9, 1.3, 1.0), psf=None, noise_model=2, noise_sigma_mag=(0.02,) * 4, exptime=(100.0,) * 4,
+                     zp=(25.0,) * 4, sky=(1.0,) * 4)
+        obs.sampler = sampler
+        lam = np.where(r.uniform(size=E) < 0.2, 10.0 ** r.uniform(0.0, 2.0, E), 10.0 ** r.uniform(-3.0, 0.0, E))
+        f32 = (10.0 ** r.uniform(-3.0, 0.0, (2, E))).astype(np.float32)
+        jobs.append(dict(lam=torch.from_numpy(lam).to(DEV), flux=torch.from_numpy(f32).to(DEV), obs=obs, conv_path=1,
+                         psf=torch.from_numpy(psf.astype(np.float32)).to(DEV) if with_psf else None))
+    data = torch.ones(1600, dtype=torch.int32, device=DEV)
+    mom_d = torch.tensor([1.0, 2.0, 3.0], dtype=torch.float64, device=DEV)
+    for rep in range(2):
+        want_h, want_l = [], []
+        for j in jobs:
+            j["obs"].seed += 1000
+            n = j["obs"].nim ** 2
+            mags = torch.empty((2, n), dtype=torch.float32, device=DEV)
+            h, mom = torch.empty(1600, dtype=torch.int32, device=DEV), torch.empty(3, dtype=torch.float64, device=DEV)
+            ll = torch.empty(1, dtype=torch.float64, device=DEV)
+            ctx.simulate(j["lam"], j["flux"], j["obs"], mags, psf=j["psf"], conv_path=1)
+            ctx.hess(mags, 2, n, hgrid, h, mom, (0, 1, 1))
+            ctx.loglike(h, data, mom, mom_d, ll)
+            want_h.append(h)
+            want_l.append(ll)
+        got_l = torch.empty(len(jobs), dtype=torch.float64, device=DEV)
+        got_h = torch.empty((len(jobs), 1600), dtype=torch.int32, device=DEV)
+        print(f"[case] batch of unlike jobs rep={rep}", flush=True)
+        ctx.batch_run(jobs, hgrid, data, mom_d, got_l, hess_out=got_h, use_graph=True, bands=(0, 1, 1))
+        ctx.sync()
+        assert torch.equal(got_h, torch.stack(want_h)) and torch.equal(got_l, torch.cat(want_l))
