@@ -191,15 +191,20 @@ hipError_t launch_hess(const HessArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-__global__ void __launch_bounds__(256) k_hess_clear_job(const HessArgs *__restrict__ t, int j, int nbins) {
-  uint32_t *h = t[j].hess;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nbins; i += gridDim.x * blockDim.x) h[i] = 0u;
+__global__ void __launch_bounds__(256) k_hess_clear_jobs(const HessArgs *__restrict__ t, int nbins) {
+  uint32_t *h = t[blockIdx.y].hess;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < nbins) h[i] = 0u;
 }
 
-// Job j's diagram (cleared first where blocks add to it).
+// The diagrams of n jobs cleared, for the blocks that add to them (a small image's one block stores).
+hipError_t launch_hess_clear_jobs(const HessArgs *table, int n, int nbins, hipStream_t s) {
+  hipLaunchKernelGGL(k_hess_clear_jobs, dim3((nbins + 255) / 256, n), dim3(256), 0, s, table, nbins);
+  return hipGetLastError();
+}
+
+// Job j's diagram, cleared before.
 hipError_t launch_hess_job(const HessArgs *table, int j, int64_t npx, int nbins, hipStream_t s) {
-  if (!hess_stores(npx, nbins))
-    hipLaunchKernelGGL(k_hess_clear_job, dim3((nbins + 255) / 256), dim3(256), 0, s, table, j, nbins);
   const size_t lds = hess_use_lds(nbins) ? (size_t)nbins * sizeof(uint32_t) : 0;
   hipLaunchKernelGGL(k_hess_job, dim3((unsigned)hess_blocks(npx)), dim3(HESS_THREADS), lds, s, table, j);
   return hipGetLastError();
