@@ -71,18 +71,20 @@ __device__ __forceinline__ void block_sum3(double (&v)[3], double (*red)[3]) {
       for (int c = 0; c < 3; ++c) v[c] += red[w][c];
 }
 
-int hess_blocks(int64_t npx) {
+__host__ __device__ static inline int hess_blocks_of(int64_t npx) {
   if (npx <= HESS_ONE_BLOCK) return 1;
   // enough pixels per block to amortise clearing and merging the private histogram
   int64_t blocks = (npx + 4095) / 4096;
   if (blocks > HESS_MAX_BLOCKS) blocks = HESS_MAX_BLOCKS;
   return (int)blocks;
 }
+int hess_blocks(int64_t npx) { return hess_blocks_of(npx); }
 bool hess_use_lds(int nbins) { return nbins <= HESS_LDS_MAX_BINS; }
 // one block with a private histogram: the result needs no clearing
 static bool hess_stores(int64_t npx, int nbins) { return hess_use_lds(nbins) && hess_blocks(npx) == 1; }
 
-__device__ __forceinline__ void hess_body(const HessArgs &a) {
+// by nblk blocks
+__device__ __forceinline__ void hess_body(const HessArgs &a, unsigned nblk) {
   extern __shared__ uint32_t lh[];
   __shared__ double red[HESS_THREADS / 64][3];
   __shared__ bool last;
@@ -96,7 +98,7 @@ __device__ __forceinline__ void hess_body(const HessArgs &a) {
   const float *mb = a.mags + (size_t)a.bb * a.npx;
   const float *mr = a.mags + (size_t)a.br * a.npx;
   const float *mm = a.mags + (size_t)a.bm * a.npx;
-  const uint32_t npx = (uint32_t)a.npx, stride = gridDim.x * HESS_THREADS;  // at most 2^31 pixels
+  const uint32_t npx = (uint32_t)a.npx, stride = nblk * HESS_THREADS;  // at most 2^31 pixels
   for (uint32_t p0 = blockIdx.x * HESS_THREADS + threadIdx.x; p0 < npx; p0 += HESS_UNROLL * stride) {
     float fb[HESS_UNROLL], fr[HESS_UNROLL], fm[HESS_UNROLL];
 #pragma unroll
@@ -125,7 +127,7 @@ __device__ __forceinline__ void hess_body(const HessArgs &a) {
       }
     }
   }
-  const bool one = gridDim.x == 1;
+  const bool one = nblk == 1;
   if (a.use_lds) {
     __syncthreads();
     for (int j = threadIdx.x; j < nb; j += HESS_THREADS) {
@@ -152,7 +154,7 @@ __device__ __forceinline__ void hess_body(const HessArgs &a) {
       __hip_atomic_store(a.mom_part + blockIdx.x * 3 + c, sum[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     const uint32_t prev = atomicAdd(a.counter, 1u);
-    last = (prev == gridDim.x - 1);
+    last = (prev == nblk - 1);
   }
   __syncthreads();
   if (last) {
@@ -161,7 +163,7 @@ __device__ __forceinline__ void hess_body(const HessArgs &a) {
     // which block is last)
 #pragma unroll
     for (int c = 0; c < 3; ++c) sum[c] = 0.0;
-    for (unsigned k = threadIdx.x; k < gridDim.x; k += HESS_THREADS)
+    for (unsigned k = threadIdx.x; k < nblk; k += HESS_THREADS)
 #pragma unroll
       for (int c = 0; c < 3; ++c)
         sum[c] += __hip_atomic_load(a.mom_part + k * 3 + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -174,10 +176,11 @@ __device__ __forceinline__ void hess_body(const HessArgs &a) {
   }
 }
 
-__global__ void __launch_bounds__(HESS_THREADS, 8) k_hess(HessArgs a) { hess_body(a); }
-__global__ void __launch_bounds__(HESS_THREADS, 8) k_hess_job(const HessArgs *__restrict__ t, int j) {
-  const HessArgs a = t[j];
-  hess_body(a);
+__global__ void __launch_bounds__(HESS_THREADS, 8) k_hess(HessArgs a) { hess_body(a, gridDim.x); }
+__global__ void __launch_bounds__(HESS_THREADS, 8) k_hess_jobs(const HessArgs *__restrict__ t) {
+  const HessArgs a = t[blockIdx.y];
+  const unsigned nblk = (unsigned)hess_blocks_of(a.npx);  // those of the same single call
+  if (blockIdx.x < nblk) hess_body(a, nblk);
 }
 
 hipError_t launch_hess(const HessArgs &a, hipStream_t s) {
@@ -203,10 +206,11 @@ hipError_t launch_hess_clear_jobs(const HessArgs *table, int n, int nbins, hipSt
   return hipGetLastError();
 }
 
-// Job j's diagram, cleared before.
-hipError_t launch_hess_job(const HessArgs *table, int j, int64_t npx, int nbins, hipStream_t s) {
+// The diagrams of n jobs, cleared before, of at most npx_max pixels.  (24 uneven jobs 24 x 11 us one by one,
+// 26 together.)
+hipError_t launch_hess_jobs(const HessArgs *table, int n, int64_t npx_max, int nbins, hipStream_t s) {
   const size_t lds = hess_use_lds(nbins) ? (size_t)nbins * sizeof(uint32_t) : 0;
-  hipLaunchKernelGGL(k_hess_job, dim3((unsigned)hess_blocks(npx)), dim3(HESS_THREADS), lds, s, table, j);
+  hipLaunchKernelGGL(k_hess_jobs, dim3((unsigned)hess_blocks(npx_max), n), dim3(HESS_THREADS), lds, s, table);
   return hipGetLastError();
 }
 

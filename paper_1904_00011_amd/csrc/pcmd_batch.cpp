@@ -478,9 +478,13 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
     e = ji.K > 1 ? launch_conv_direct_job(ca, na, j, ji.B, ji.N, ji.K, ji.grid, s)
                  : launch_noise_mag_job(na, j, ji.npx, ji.B, s);
   }
-  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess; j0 += MAX_JOBS_Z)
-    e = launch_hess_clear_jobs(ha + j0, std::min(p->n_jobs - j0, MAX_JOBS_Z), p->nbins, s);
-  for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) e = launch_hess_job(ha, j, p->info[j].npx, p->nbins, s);
+  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess; j0 += MAX_JOBS_Z) {
+    const int n = std::min(p->n_jobs - j0, MAX_JOBS_Z);
+    int hi = 0;
+    for (int j = j0; j < j0 + n; ++j) hi = std::max(hi, p->info[j].npx);
+    e = launch_hess_clear_jobs(ha + j0, n, p->nbins, s);
+    if (e == hipSuccess) e = launch_hess_jobs(ha + j0, n, hi, p->nbins, s);
+  }
   if (e == hipSuccess) e = launch_loglike_jobs(la, p->n_jobs, p->nbins, s);
   return e;
 }

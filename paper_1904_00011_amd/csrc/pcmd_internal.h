@@ -272,7 +272,7 @@ int hess_blocks(int64_t npx);
 bool hess_use_lds(int nbins);
 hipError_t launch_hess(const HessArgs &a, hipStream_t s);
 hipError_t launch_hess_clear_jobs(const HessArgs *table, int n, int nbins, hipStream_t s);
-hipError_t launch_hess_job(const HessArgs *table, int j, int64_t npx, int nbins, hipStream_t s);
+hipError_t launch_hess_jobs(const HessArgs *table, int n, int64_t npx_max, int nbins, hipStream_t s);
 constexpr int LL_THREADS = 256;  // bins per likelihood block
 __host__ __device__ inline int loglike_blocks(int nbins) { return (nbins + LL_THREADS - 1) / LL_THREADS; }
 hipError_t launch_loglike(const LoglikeArgs &a, hipStream_t s);
