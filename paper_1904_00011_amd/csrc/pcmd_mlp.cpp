@@ -355,11 +355,13 @@ int pcmd_mlp_loss(pcmd_ctx *c, const pcmd_mlp *net, int32_t n, const float *x, c
   if (rows && n_total < 1) return fail(c, PCMD_E_INVAL, "pcmd_mlp_loss: n_total must be >= 1 with a row vector");
   const int chunk = std::min<int>(n, MLP_LOSS_CHUNK);
   const int n_chunks = (n + chunk - 1) / chunk;
+  const int last = n - (n_chunks - 1) * chunk;
   DeviceGuard dg(c->device);
-  if ((r = ensure_mlp_scratch(c, lay, chunk))) return r;
-  // chunk q's partial sums follow those of the chunks before it (the last chunk may be shorter)
+  // the last chunk may be shorter, and its products then take more K ranges and workspace
+  if ((r = ensure_mlp_scratch(c, lay, chunk)) || (r = ensure_mlp_scratch(c, lay, last))) return r;
+  // chunk q's partial sums follow those of the chunks before it
   bool fused;
-  const int64_t full = loss_parts(lay, chunk, &fused), tail = loss_parts(lay, n - (n_chunks - 1) * chunk, &fused);
+  const int64_t full = loss_parts(lay, chunk, &fused), tail = loss_parts(lay, last, &fused);
   const int64_t n_part = (int64_t)(n_chunks - 1) * full + tail;
   if ((r = ensure(c, c->mlp_lpart, (size_t)n_part * 8, "loss partials"))) return r;
   hipStream_t s = (hipStream_t)stream;

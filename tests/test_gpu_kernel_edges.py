@@ -447,3 +447,25 @@ def test_batch_of_unlike_jobs(ctx):
         ctx.batch_run(jobs, hgrid, data, mom_d, got_l, hess_out=got_h, use_graph=True, bands=(0, 1, 1))
         ctx.sync()
         assert torch.equal(got_h, torch.stack(want_h)) and torch.equal(got_l, torch.cat(want_l))
+
+
+# A set's last chunk of fewer samples than the others takes more K ranges and more workspace than they do
+# (over 4 in the output layer at 100 rows), with nothing that an earlier call left: a fresh context per set.
+# Tolerance as in the network's set-loss test.
+@pytest.mark.parametrize("n", [1025, 1124, 1500, 3])
+@pytest.mark.parametrize("dims", [(12, 2048, 2601), (2100, 2048, 300)])
+def test_set_loss_with_a_short_last_chunk(n, dims):
+    import paper_1904_00011_amd as P
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    c = P.Context(0)
+    net = SurrogateNet(c, dims, si.mlp_init(dims, 11), device=DEV)
+    r = np.random.default_rng(n)
+    x = r.uniform(-1, 1, (n, dims[0])).astype(np.float32)
+    t = r.normal(0, 1, (n, dims[-1])).astype(np.float32)
+    out = torch.empty(1, dtype=torch.float64, device=DEV)
+    print(f"[case] set loss with a short last chunk n={n} dims={dims}", flush=True)
+    net.loss(torch.from_numpy(x).to(DEV), torch.from_numpy(t).to(DEV), out)
+    c.sync()
+    c.close()
+    y, _ = om.forward(net.master.cpu().numpy().astype(np.float64), dims, x)
+    assert out.item() == pytest.approx(om.mse(y, t), rel=1e-4)
