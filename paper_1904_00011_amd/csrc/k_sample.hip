@@ -1026,9 +1026,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))
 // Held to 8 waves per SIMD like the other sampler kernels.
 template <int B>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_sample_thin_jobs(const BatchSampleJob *__restrict__ jobs, int n_jobs, int total_items) {
+k_sample_thin_jobs(const BatchSampleJob *__restrict__ jobs, int n_jobs, int first_item, int total_items) {
   const PCMD_CONST BatchSampleJob *cj = (const PCMD_CONST BatchSampleJob *)jobs;
-  const int item = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  const int item = first_item + __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
   if (item >= total_items) return;
   const int j = job_of_item(cj, n_jobs, item);
   const PCMD_CONST SampleArgs *ap = &cj[j].a;
@@ -1038,16 +1038,27 @@ k_sample_thin_jobs(const BatchSampleJob *__restrict__ jobs, int n_jobs, int tota
   sample_thin_tile<B, false>(ap, (uint32_t)((local - chunk * pblocks) * 64) + (threadIdx.x & 63u), chunk);
 }
 
-hipError_t launch_sample_thin_jobs(const BatchSampleJob *jobs, int n_jobs, int total_items, int B, hipStream_t s) {
-  const dim3 grid((unsigned)((total_items + 3) / 4));
-  switch (B) {
-    case 1: hipLaunchKernelGGL(k_sample_thin_jobs<1>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
-    case 2: hipLaunchKernelGGL(k_sample_thin_jobs<2>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
-    case 3: hipLaunchKernelGGL(k_sample_thin_jobs<3>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
-    case 4: hipLaunchKernelGGL(k_sample_thin_jobs<4>, grid, dim3(256), 0, s, jobs, n_jobs, total_items); break;
-    default: return hipErrorInvalidValue;
+// A grid dimension holds fewer than 2^32 threads, 64 to an item: five 4096 x 4096 jobs of 52,500 entries
+// have more items than that.
+constexpr int THIN_LAUNCH_ITEMS = 1 << 25;
+
+template <int B>
+static hipError_t launch_sample_thin_jobs_b(const BatchSampleJob *jobs, int n_jobs, int total_items, hipStream_t s) {
+  for (int64_t first = 0; first < total_items; first += THIN_LAUNCH_ITEMS) {
+    const int64_t n = std::min<int64_t>(total_items - first, THIN_LAUNCH_ITEMS);
+    hipLaunchKernelGGL(k_sample_thin_jobs<B>, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, jobs, n_jobs, (int)first,
+                       (int)(first + n));
   }
   return hipGetLastError();
+}
+hipError_t launch_sample_thin_jobs(const BatchSampleJob *jobs, int n_jobs, int total_items, int B, hipStream_t s) {
+  switch (B) {
+    case 1: return launch_sample_thin_jobs_b<1>(jobs, n_jobs, total_items, s);
+    case 2: return launch_sample_thin_jobs_b<2>(jobs, n_jobs, total_items, s);
+    case 3: return launch_sample_thin_jobs_b<3>(jobs, n_jobs, total_items, s);
+    case 4: return launch_sample_thin_jobs_b<4>(jobs, n_jobs, total_items, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_sample_persistent(const BatchSampleJob *jobs, int n_jobs, int total_items, int B, uint32_t *counter,

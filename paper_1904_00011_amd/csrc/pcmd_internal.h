@@ -243,7 +243,7 @@ hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_min,
 // k_sample_block.hip
 hipError_t launch_prep_block(const BlockPrepArgs &a, hipStream_t s);
 hipError_t launch_sample_block(const BlockSampleArgs &a, hipStream_t s);
-// batched: the thinned entries' pass (F = 1/2) of the job at position t of the persistent table
+// batched: the thinned entries' pass of the persistent table's jobs at F = 1/2
 hipError_t launch_sample_thin_jobs(const BatchSampleJob *jobs, int n_jobs, int total_items, int B, hipStream_t s);
 // batched: job j of a descriptor table (nb blocks; the sampler's grid covers npx pixels x nchunks)
 hipError_t launch_prep_block_job(const BlockPrepArgs *table, int j, int nb, hipStream_t s);

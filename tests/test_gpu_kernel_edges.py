@@ -469,3 +469,42 @@ def test_set_loss_with_a_short_last_chunk(n, dims):
     c.close()
     y, _ = om.forward(net.master.cpu().numpy().astype(np.float64), dims, x)
     assert out.item() == pytest.approx(om.mse(y, t), rel=1e-4)
+
+
+# A batch whose thinned pass has more items than one launch takes (2^25; past 2^26 a grid dimension ends): five
+# large images, whose last job in the sampler's order lies past both, against sequential calls bit for bit.
+def test_batch_of_more_items_than_a_launch():
+    import paper_1904_00011_amd as P
+    E, nim = 52 * 1024, 4096  # 52 slices x 262,144 blocks of 64 pixels: 13.6 million items a job
+    assert 5 * 52 * (nim * nim // 64) > 1 << 26
+    r = np.random.default_rng(12)
+    hgrid = dict(x0=-1.0, dx=0.1, y0=-6.0, dy=0.05, nx=20, ny=200)
+    jobs = []
+    for k in range(5):
+        lam = np.zeros(E)
+        lam[r.choice(E, 40, replace=False)] = 10.0 ** r.uniform(-2.0, 0.0, 40)
+        lam[r.choice(E, 30, replace=False)] = r.uniform(5.0, 30.0, 30)  # thinned
+        obs = si.Obs(nim=nim, seed=91 + k, dmod=0.0, dust_model=2, dust_frac=0.5, dust_R=(3.6,) * 4, psf=None, noise_model=0,
+                     noise_sigma_mag=(0.0,) * 4, exptime=(1.0,) * 4, zp=(25.0,) * 4, sky=(0.0,) * 4)
+        jobs.append(dict(lam=torch.from_numpy(lam).to(DEV), obs=obs, conv_path=1, psf=None,
+                         flux=torch.from_numpy((10.0 ** r.uniform(-2.0, 0.0, (1, E))).astype(np.float32)).to(DEV)))
+    data = torch.ones(4000, dtype=torch.int32, device=DEV)
+    mom_d = torch.tensor([1.0, 2.0, 3.0], dtype=torch.float64, device=DEV)
+    got_l = torch.empty(5, dtype=torch.float64, device=DEV)
+    got_h = torch.empty((5, 4000), dtype=torch.int32, device=DEV)
+    c = P.Context(0)
+    print("[case] batch of 68 million sampler items", flush=True)
+    c.batch_run(jobs, hgrid, data, mom_d, got_l, hess_out=got_h, use_graph=False, bands=(0, 0, 0))
+    c.sync()
+    c.close()
+    c = P.Context(0)
+    for k, j in enumerate(jobs):
+        mags = torch.empty((1, nim * nim), dtype=torch.float32, device=DEV)
+        h, mom = torch.empty(4000, dtype=torch.int32, device=DEV), torch.empty(3, dtype=torch.float64, device=DEV)
+        ll = torch.empty(1, dtype=torch.float64, device=DEV)
+        c.simulate(j["lam"], j["flux"], j["obs"], mags, conv_path=1)
+        c.hess(mags, 1, nim * nim, hgrid, h, mom, (0, 0, 0))
+        c.loglike(h, data, mom, mom_d, ll)
+        c.sync()
+        assert int((h > 0).sum()) > 20 and torch.equal(got_h[k], h) and torch.equal(got_l[k:k + 1], ll)
+    c.close()
