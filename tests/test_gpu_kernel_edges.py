@@ -508,3 +508,36 @@ def test_batch_of_more_items_than_a_launch():
         c.sync()
         assert int((h > 0).sum()) > 20 and torch.equal(got_h[k], h) and torch.equal(got_l[k:k + 1], ll)
     c.close()
+
+
+# Box-Muller where its logarithm nears zero (u1 near 1), made visible in FP32: a count c = z^2 (1 + eps) and a
+# negative deviate z leave c + sqrt(c) z = c eps / 2, so a relative error a of z becomes 2 a / eps = 2e8 a
+# of the result.  Ten roundings of 2^-53 and the magnitude's own 2^-24; the reference is in 80 bits.
+def test_noise_deviate_near_zero(ctx):
+    from oracle import rng as orng
+    from tests import parity_utils as pu
+    nim, eps = 128, 1e-8
+    px = np.arange(nim * nim, dtype=np.int64)
+    found = []
+    for seed in range(40):
+        w0, w1 = orng.philox4x32_10(px, 0, orng.TAG_NOISE, 0, seed)[:2]
+        c = np.cos(2.0 * np.pi * orng.u01_open_f64(w1))
+        gap = np.where(c < -0.3, 1.0 - orng.u01_open_f64(w0), 1.0)
+        k = int(np.argmin(gap))
+        found.append((gap[k], seed, k, int(w0[k]), int(w1[k])))
+    ld = np.longdouble
+    for gap, seed, k, w0, w1 in sorted(found)[:6]:
+        u1, u2 = (ld(w0) + ld(0.5)) / ld(2.0) ** 32, (ld(w1) + ld(0.5)) / ld(2.0) ** 32
+        z = np.sqrt(ld(-2.0) * np.log(u1)) * np.cos(ld(8.0) * np.arctan(ld(1.0)) * u2)
+        obs = si.Obs(nim=nim, seed=seed, dmod=0.0, dust_model=0, psf=None, noise_model=2, noise_sigma_mag=(0.0,) * 4,
+                     exptime=(1.0,) * 4, zp=(0.0,) * 4, sky=(0.0,) * 4, dust_R=(1.0,) * 4)
+        lam, f32 = np.array([9.0]), np.ones((1, 1), dtype=np.float32)
+        G = float(pu.gpu_simulate(ctx, lam, f32, obs)["flux_pre"][0, k])
+        assert G > 0.0 and z < 0.0
+        t = float(z * z * (1 + ld(eps)) / ld(G))
+        obs.exptime = (t,) * 4
+        got = float(pu.gpu_simulate(ctx, lam, f32, obs)["mags"][0, k])
+        cnt = ld(G) * ld(t)
+        want = float(ld(-2.5) * np.log10((cnt + np.sqrt(cnt) * z) / ld(t)))
+        print(f"[case] deviate near zero 1 - u1 = {gap:.2e}: {got - want:.2e} mag", flush=True)
+        assert abs(got - want) <= 1.0857 * 10 * 2.0 ** -53 * 2 / eps + 1.01 * 2.0 ** -24 * abs(want)
