@@ -37,9 +37,10 @@ __device__ __forceinline__ float noise_mag(const NoiseArgs &a, int b, int p, flo
     if (a.noise_model == PCMD_NOISE_GAUSS_MAG) {
       m = G > 0.0 ? MAG * ln_pos(G) + a.sigma[b] * z : INFINITY;
     } else {
-      const double c = G * a.gain[b] + a.sky[b];
+      // in this order, and divided: neither t 10^(0.4 zp) nor 1 / t need be finite
+      const double t = a.exptime[b], c = G * t * a.zp_flux[b] + a.sky[b];
       const double c2 = c + sqrt(c > 0.0 ? c : 0.0) * z - a.sky[b];
-      m = c2 > 0.0 ? MAG * ln_pos(c2 * a.inv_t[b]) + a.zp[b] : INFINITY;
+      m = c2 > 0.0 ? MAG * ln_pos(c2 / t) + a.zp[b] : INFINITY;
     }
   }
   return (float)m;

@@ -173,9 +173,8 @@ inline void noise_bands(NoiseArgs *n, const pcmd_obs *o, int B) {
     n->sigma[b] = b < B ? o->noise_sigma_mag[b] : 0.0;
     n->zp[b] = b < B ? o->zp[b] : 0.0;
     n->sky[b] = b < B ? o->sky[b] : 0.0;
-    const double t = b < B ? o->exptime[b] : 1.0;
-    n->gain[b] = t * pow(10.0, 0.4 * n->zp[b]);
-    n->inv_t[b] = 1.0 / t;
+    n->exptime[b] = b < B ? o->exptime[b] : 1.0;
+    n->zp_flux[b] = pow(10.0, 0.4 * n->zp[b]);
   }
 }
 

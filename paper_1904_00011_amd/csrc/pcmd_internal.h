@@ -191,7 +191,7 @@ struct NoiseArgs {
   float *mags;     // [B][npx]
   int noise_model;
   double sigma[PCMD_MAX_BANDS], zp[PCMD_MAX_BANDS], sky[PCMD_MAX_BANDS];
-  double gain[PCMD_MAX_BANDS], inv_t[PCMD_MAX_BANDS];  // exposure time 10^(0.4 zp), 1 / exposure time
+  double exptime[PCMD_MAX_BANDS], zp_flux[PCMD_MAX_BANDS];  // 10^(0.4 zp)
   uint32_t k0, k1;
 };
 

@@ -541,3 +541,23 @@ def test_noise_deviate_near_zero(ctx):
         want = float(ld(-2.5) * np.log10((cnt + np.sqrt(cnt) * z) / ld(t)))
         print(f"[case] deviate near zero 1 - u1 = {gap:.2e}: {got - want:.2e} mag", flush=True)
         assert abs(got - want) <= 1.0857 * 10 * 2.0 ** -53 * 2 / eps + 1.01 * 2.0 ** -24 * abs(want)
+
+
+# Exposure times and zero points whose product or reciprocal is not finite while the counts are: the count
+# and its division by the time keep the order of the oracle.  The magnitude's FP32 rounding, and a few units
+# of 2^-53 of a count of which the noise leaves a share of at least 1e-6.
+@pytest.mark.parametrize("t,zp,flux", [(1e-310, 25.0, 1e-3), (1e300, 25.0, 1e-6), (1.5e308, 2.0, 1e-3), (100.0, 768.0, 1e-20), (3000.0, 25.0, 1e-6)])
+@pytest.mark.parametrize("psf", [False, True])
+def test_noise_at_extreme_exposures(ctx, t, zp, flux, psf):
+    import paper_1904_00011_amd as P
+    from oracle import noise as on
+    from tests import parity_utils as pu
+    obs = si.Obs(nim=16, seed=9, dmod=0.0, dust_model=0, psf=np.full((1, 3, 3), 1.0 / 9.0, np.float32) if psf else None, noise_model=2,
+                 noise_sigma_mag=(0.0,) * 4, exptime=(t,) * 4, zp=(zp,) * 4, sky=(0.0,) * 4, dust_R=(1.0,) * 4)
+    print(f"[case] extreme exposure t={t} zp={zp} psf={psf}", flush=True)
+    got = pu.gpu_simulate(ctx, np.array([2.0]), np.full((1, 1), flux, np.float32), obs, conv_path=P.CONV_DIRECT)
+    G = got["flux_psf"].astype(np.float64)
+    want = on.magnitudes(G, obs)
+    fin = np.isfinite(want)
+    assert np.array_equal(fin, np.isfinite(got["mags"])) and fin.any()
+    assert np.all(np.abs(got["mags"] - np.where(fin, want, 0.0))[fin] <= 2.0 ** -24 * 1.01 * np.abs(want[fin]) + 1e-8)
