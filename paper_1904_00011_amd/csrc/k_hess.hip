@@ -230,16 +230,26 @@ hipError_t launch_hess_jobs(const HessArgs *table, int n, int64_t npx_max, int n
 // (0 ln lam = 0; with no data at all lam = 0 and the term is 0 ln 0, not a number).
 struct BinTerm {
   int mode;
-  double eps, Nm, Nd, scale;  // scale: N_d / (N_m + eps n_bins) or N_d / N_m
+  double eps, Nm, Nd, den, inv;  // den: N_m + eps n_bins or N_m
+  bool near;                     // inv = 1 / den is a normal number (eps near either end of the range: it may not be)
   const double *lnfact64;
   __device__ __forceinline__ BinTerm(const LoglikeArgs &a, double nm, double nd)
       : mode(a.mode), eps(a.eps), Nm(nm), Nd(nd), lnfact64(a.lnfact64) {
-    scale = mode == PCMD_LL_POISSON ? nd / (nm + a.eps * (double)a.nbins) : nd / nm;
+    den = mode == PCMD_LL_POISSON ? nm + a.eps * (double)a.nbins : nm;
+    inv = 1.0 / den;
+    near = inv >= 0x1p-1022 && inv < INFINITY;
+  }
+  // x / den: with the rounded reciprocal, and the quotient corrected by its exact remainder, the rounded
+  // quotient (Markstein) in three operations
+  __device__ __forceinline__ double over_den(double x) const {
+    if (!near) return x / den;
+    const double q = x * inv;
+    return fma(fma(-den, q, x), inv, q);
   }
   __device__ __forceinline__ double operator()(uint32_t hm, uint32_t hd) const {
     const double m = (double)hm, d = (double)hd;
     if (mode == PCMD_LL_POISSON) {
-      const double lam = scale * (m + eps);
+      const double lam = over_den(Nd * (m + eps));
       if (hd == 0u && Nd != 0.0) return -lam;
       const double lf = (lnfact64 && hd < (uint32_t)LNFACT64_N) ? lnfact64[hd] : lgamma(d + 1.0);
       return d * log(lam) - lam - lf;
@@ -247,7 +257,7 @@ struct BinTerm {
     // Gaussian: sigma^2 = max(variance, 2^2)
     double df, var;
     if (mode == PCMD_LL_GAUSS_PAPER) {
-      const double mh = m * scale;
+      const double mh = over_den(m * Nd);
       df = d - mh;
       var = d + mh;
     } else {

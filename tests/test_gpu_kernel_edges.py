@@ -561,3 +561,19 @@ def test_noise_at_extreme_exposures(ctx, t, zp, flux, psf):
     fin = np.isfinite(want)
     assert np.array_equal(fin, np.isfinite(got["mags"])) and fin.any()
     assert np.all(np.abs(got["mags"] - np.where(fin, want, 0.0))[fin] <= 2.0 ** -24 * 1.01 * np.abs(want[fin]) + 1e-8)
+
+
+# Scaled counts of the likelihoods.  A model of 49 times the data (1 / 49 times 49 is not 1) scales back to
+# the data exactly: m N_d is exact and its quotient an integer.  A pseudo-count whose reciprocal overflows, under
+# an empty model, spreads the data's total evenly; tolerance of the bin-count test.
+@pytest.mark.parametrize("nbins", [50, 17000])  # one block, and several
+def test_likelihood_scaled_counts(ctx, nbins):
+    from tests import parity_utils as pu
+    r = np.random.default_rng(nbins)
+    hd = r.poisson(3.0, nbins)
+    hd[0] += 1
+    mom = np.array([0.5, 25.0, 1.0])
+    assert pu.gpu_loglike(ctx, 49 * hd, hd, mom * 49.0, mom, 1) == 0.0
+    for eps in (1e-310, 1e-6, 1e303):
+        got = pu.gpu_loglike(ctx, np.zeros_like(hd), hd, mom, mom, 0, eps)
+        assert got == pytest.approx(ol.loglike(np.zeros_like(hd), hd, mom, mom, 0, eps), rel=2e-11)
