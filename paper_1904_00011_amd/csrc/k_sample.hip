@@ -1089,7 +1089,7 @@ constexpr int REDUCE_WIDE = 262144;
 __device__ __forceinline__ void reduce_body(const ReduceArgs &a, int p) {
   const bool wide = a.npx >= REDUCE_WIDE;
   const int b0 = wide ? 0 : blockIdx.y, b1 = wide ? a.B : b0 + 1;
-  if (p >= a.npx || b0 >= a.B || (wide && blockIdx.y > 0)) return;
+  if (p >= a.npx) return;
   const size_t plane = (size_t)a.npx;
   const size_t step = (size_t)a.S * a.B * plane;  // from one slice to the next
   double ebv = 0.0;
@@ -1133,13 +1133,15 @@ __global__ void __launch_bounds__(256) k_reduce_job(const ReduceArgs *__restrict
   reduce_body(t[j + blockIdx.z], blockIdx.x * blockDim.x + threadIdx.x);
 }
 
+bool reduce_wide(int npx) { return npx >= REDUCE_WIDE; }
+
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce, dim3((a.npx + 255) / 256, a.npx >= REDUCE_WIDE ? 1 : a.B), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_reduce, dim3((a.npx + 255) / 256, reduce_wide(a.npx) ? 1 : a.B), dim3(256), 0, s, a);
   return hipGetLastError();
 }
-// npx_min, npx_max: of the n jobs
-hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_min, int npx_max, int B, hipStream_t s) {
-  hipLaunchKernelGGL(k_reduce_job, dim3((npx_max + 255) / 256, npx_min >= REDUCE_WIDE ? 1 : B, n), dim3(256), 0, s, table, j);
+// n jobs on one side of REDUCE_WIDE, the largest of npx_max pixels
+hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_max, int B, hipStream_t s) {
+  hipLaunchKernelGGL(k_reduce_job, dim3((npx_max + 255) / 256, reduce_wide(npx_max) ? 1 : B, n), dim3(256), 0, s, table, j);
   return hipGetLastError();
 }
 

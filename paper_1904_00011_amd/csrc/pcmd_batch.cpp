@@ -44,6 +44,9 @@ struct pcmd_batch_plan {
   int n_jobs = 0, B = 0, nbins = 0, total_items = 0, wg = 0, order_mode = 0;
   std::vector<JobInfo> info;
   std::vector<int> order;  // sampler table position -> job
+  // positions of a job in the entry tables' descriptors (most entries first, jobs under the block rule
+  // alone last) and in the images' (most pixels first), and the jobs in those orders
+  std::vector<int> pos_e, pos_n, by_e, by_n;
   Buf rec, thr, pc, fl, part, F, mags, hess, mom, mom_part, ll_part, counters, desc, alias, rdesc, blk;
   void *desc_host = nullptr;
   size_t desc_bytes = 0;
@@ -180,6 +183,15 @@ static int plan_build(pcmd_ctx *c, pcmd_batch_plan *p, int n_jobs, const pcmd_jo
   if (p->order_mode == 0)
     std::stable_sort(p->order.begin(), p->order.end(),
                      [&](int a, int b) { return p->info[a].cost > p->info[b].cost; });
+  auto sorted = [n_jobs](std::vector<int> &by, std::vector<int> &pos, auto &&size) {
+    by.resize(n_jobs);
+    pos.resize(n_jobs);
+    std::iota(by.begin(), by.end(), 0);
+    std::stable_sort(by.begin(), by.end(), [&](int a, int b) { return size(a) > size(b); });
+    for (int k = 0; k < n_jobs; ++k) pos[by[k]] = k;
+  };
+  sorted(p->by_e, p->pos_e, [&](int j) { return p->info[j].items > 0 ? p->info[j].E : 0; });
+  sorted(p->by_n, p->pos_n, [&](int j) { return p->info[j].npx; });
   p->total_items = 0;
   for (int j = 0; j < n_jobs; ++j) p->total_items += p->info[p->order[j]].items;
   int r;
@@ -315,24 +327,24 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
     }
     bpa[j] = bp;
     bsa[j] = bs;
-    pa[j] = PrepArgs{ji.E,
-                     B,
-                     BP,
-                     jobs[j].iso.lam,
-                     jobs[j].iso.flux,
-                     rec,
-                     grp,
-                     thr,
-                     pc,
-                     fl,
-                     c->status,
-                     (uint32_t *)p->alias.p + ji.o_alias,
-                     ji.sampler == PCMD_SAMPLER_HYBRID ? bp.brec : nullptr,
-                     thin_mode_of_split(sm),
-                     jobs[j].obs.dust_frac,
-                     (uint32_t *)p->rdesc.p + ji.o_rdesc,
-                     thin_word(p, j),
-                     p->thin_gen};
+    pa[p->pos_e[j]] = PrepArgs{ji.E,
+                               B,
+                               BP,
+                               jobs[j].iso.lam,
+                               jobs[j].iso.flux,
+                               rec,
+                               grp,
+                               thr,
+                               pc,
+                               fl,
+                               c->status,
+                               (uint32_t *)p->alias.p + ji.o_alias,
+                               ji.sampler == PCMD_SAMPLER_HYBRID ? bp.brec : nullptr,
+                               thin_mode_of_split(sm),
+                               jobs[j].obs.dust_frac,
+                               (uint32_t *)p->rdesc.p + ji.o_rdesc,
+                               thin_word(p, j),
+                               p->thin_gen};
     ReduceArgs rr;
     memset(&rr, 0, sizeof rr);
     rr.B = B;
@@ -348,7 +360,7 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
     for (int b = 0; b < PCMD_MAX_BANDS; ++b) rr.dust_R[b] = b < B ? o->dust_R[b] : 0.0;
     rr.k0 = k0;
     rr.k1 = k1;
-    ra[j] = rr;
+    ra[p->pos_n[j]] = rr;
     ca[j] = ConvArgs{B, ji.N, ji.K, F, o->psf, nullptr, c->status, psf_grid_of(o)};
     NoiseArgs nn;
     memset(&nn, 0, sizeof nn);
@@ -379,7 +391,7 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
     hh.counter = (uint32_t *)p->counters.p + j;
     hh.moments = (double *)p->mom.p + (size_t)j * 3;
     hh.use_lds = hess_use_lds(p->nbins);
-    ha[j] = hh;
+    ha[p->pos_n[j]] = hh;
     la[j] = LoglikeArgs{hh.hess, hess_data,    p->nbins,    mode, hh.moments, mom_data, eps, logl_out + j,
                         (double *)p->ll_part.p + (size_t)j * loglike_blocks(p->nbins), 0, c->lnfact64};
   }
@@ -418,10 +430,26 @@ static void fill_descriptors(pcmd_ctx *c, pcmd_batch_plan *p, const pcmd_job *jo
   }
 }
 
-// Queue the whole batch on stream s (eagerly, or into a graph under capture).
 // Jobs of one launch at most (a grid's third dimension goes to 65,535).
 constexpr int MAX_JOBS_Z = 32768;
 
+// End of the run of jobs, from position k0 of a table sorted by size on, that one launch takes.  Its grid is sized
+// for the first, the largest: the run goes on while that is at most twice the blocks that the jobs need
+// themselves, or a block per CU more.  (One 4096 x 4096 image among 1,000 of 64 x 64 in one launch: 200
+// million blocks without work, 54 ms where the two parts take 3.8 and 9.6.)
+template <typename F>
+static int run_end(int k0, int n, F &&blocks) {
+  const int64_t most = blocks(k0);
+  int64_t sum = most;
+  int k = k0 + 1;
+  for (; k < n && k - k0 < MAX_JOBS_Z; ++k) {
+    sum += blocks(k);
+    if (most * (k - k0 + 1) > 2 * sum + 256) break;
+  }
+  return k;
+}
+
+// Queue the whole batch on stream s (eagerly, or into a graph under capture).
 static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
   char *d = (char *)p->desc.p;
   const PrepArgs *pa = (const PrepArgs *)(d + p->o_prep);
@@ -440,16 +468,15 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
     const JobInfo &ji = p->info[j];
     if (ji.sampler != PCMD_SAMPLER_POINT) e = launch_prep_block_job(bpa, j, ji.nb, s);
   }
-  // runs of consecutive jobs with per-point tables (all of them, unless some take the block rule alone)
-  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess;) {
-    int j1 = j0, E = 0, parts = 1;
-    for (; j1 < p->n_jobs && j1 - j0 < MAX_JOBS_Z && p->info[j1].sampler != PCMD_SAMPLER_BLOCK; ++j1) {
-      E = std::max(E, p->info[j1].E);
-      parts = std::max(parts, p->info[j1].alias_parts);
-    }
-    if (j1 > j0) e = launch_prep_job(pa, j0, j1 - j0, E, s);
-    if (j1 > j0 && e == hipSuccess) e = launch_prep_alias_job(pa, j0, j1 - j0, E, parts, s);
-    j0 = j1 > j0 ? j1 : j0 + 1;
+  int n_point = 0;  // jobs with per-point tables
+  for (const JobInfo &ji : p->info) n_point += ji.items > 0 ? 1 : 0;
+  for (int k0 = 0, k1; k0 < n_point && e == hipSuccess; k0 = k1) {
+    k1 = run_end(k0, n_point, [&](int k) { return (p->info[p->by_e[k]].E + 255) / 256; });
+    const int E = p->info[p->by_e[k0]].E;
+    int parts = 1;
+    for (int k = k0; k < k1; ++k) parts = std::max(parts, p->info[p->by_e[k]].alias_parts);
+    e = launch_prep_job(pa, k0, k1 - k0, E, s);
+    if (e == hipSuccess) e = launch_prep_alias_job(pa, k0, k1 - k0, E, parts, s);
   }
   if (e == hipSuccess) e = launch_reset_counter(persist, s);
   if (e == hipSuccess)
@@ -464,26 +491,22 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
     const JobInfo &ji = p->info[j];
     if (ji.sampler != PCMD_SAMPLER_POINT) e = launch_sample_block_job(bsa, j, ji.B, ji.npx, ji.nchunks, superblocks(ji.E), s);
   }
-  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess; j0 += MAX_JOBS_Z) {
-    const int n = std::min(p->n_jobs - j0, MAX_JOBS_Z);
-    int lo = p->info[j0].npx, hi = lo;
-    for (int j = j0; j < j0 + n; ++j) {
-      lo = std::min(lo, p->info[j].npx);
-      hi = std::max(hi, p->info[j].npx);
-    }
-    e = launch_reduce_job(ra, j0, n, lo, hi, p->B, s);
+  auto npx = [&](int k) { return p->info[p->by_n[k]].npx; };
+  for (int k0 = 0, k1; k0 < p->n_jobs && e == hipSuccess; k0 = k1) {
+    int n = k0 + 1;  // images of one kind of split
+    while (n < p->n_jobs && reduce_wide(npx(n)) == reduce_wide(npx(k0))) ++n;
+    k1 = run_end(k0, n, [&](int k) { return (npx(k) + 255) / 256 * (reduce_wide(npx(k)) ? 1 : p->B); });
+    e = launch_reduce_job(ra, k0, k1 - k0, npx(k0), p->B, s);
   }
   for (int j = 0; j < p->n_jobs && e == hipSuccess; ++j) {
     const JobInfo &ji = p->info[j];
     e = ji.K > 1 ? launch_conv_direct_job(ca, na, j, ji.B, ji.N, ji.K, ji.grid, s)
                  : launch_noise_mag_job(na, j, ji.npx, ji.B, s);
   }
-  for (int j0 = 0; j0 < p->n_jobs && e == hipSuccess; j0 += MAX_JOBS_Z) {
-    const int n = std::min(p->n_jobs - j0, MAX_JOBS_Z);
-    int hi = 0;
-    for (int j = j0; j < j0 + n; ++j) hi = std::max(hi, p->info[j].npx);
-    e = launch_hess_clear_jobs(ha + j0, n, p->nbins, s);
-    if (e == hipSuccess) e = launch_hess_jobs(ha + j0, n, hi, p->nbins, s);
+  for (int k0 = 0, k1; k0 < p->n_jobs && e == hipSuccess; k0 = k1) {
+    k1 = run_end(k0, p->n_jobs, [&](int k) { return hess_blocks(npx(k)); });
+    e = launch_hess_clear_jobs(ha + k0, k1 - k0, p->nbins, s);
+    if (e == hipSuccess) e = launch_hess_jobs(ha + k0, k1 - k0, npx(k0), p->nbins, s);
   }
   if (e == hipSuccess) e = launch_loglike_jobs(la, p->n_jobs, p->nbins, s);
   return e;

@@ -238,7 +238,8 @@ hipError_t launch_sample_persistent(const BatchSampleJob *jobs, int n_jobs, int 
                                     int n_workgroups, hipStream_t s);
 hipError_t launch_reset_counter(uint32_t *counter, hipStream_t s);
 hipError_t launch_reduce(const ReduceArgs &a, hipStream_t s);
-hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_min, int npx_max, int B, hipStream_t s);
+bool reduce_wide(int npx);  // the reduction takes a thread per pixel, not per pixel and band
+hipError_t launch_reduce_job(const ReduceArgs *table, int j, int n, int npx_max, int B, hipStream_t s);
 
 // k_sample_block.hip
 hipError_t launch_prep_block(const BlockPrepArgs &a, hipStream_t s);

@@ -577,3 +577,40 @@ def test_likelihood_scaled_counts(ctx, nbins):
     for eps in (1e-310, 1e-6, 1e303):
         got = pu.gpu_loglike(ctx, np.zeros_like(hd), hd, mom, mom, 0, eps)
         assert got == pytest.approx(ol.loglike(np.zeros_like(hd), hd, mom, mom, 0, eps), rel=2e-11)
+
+
+# One large image among many small ones costs about what the two parts cost (1.0 measured; a launch sized for
+# the largest job, times the jobs, took 3.5 times that), and scores each job as its part does.
+def test_batch_of_one_large_job_and_many_small():
+    import paper_1904_00011_amd as P
+    r = np.random.default_rng(14)
+    hgrid = dict(x0=-2.0, dx=0.1, y0=-5.0, dy=0.3, nx=40, ny=40)
+    jobs = []
+    for k, (nim, E) in enumerate([(64, 40)] * 300 + [(4096, 30)] + [(64, 40)] * 300):
+        obs = si.Obs(nim=nim, seed=31 + k, dmod=0.0, dust_model=2, dust_frac=0.5, dust_R=(3.6, 1.9, 1.3, 1.0), psf=None, noise_model=0,
+                     noise_sigma_mag=(0.02,) * 4, exptime=(100.0,) * 4, zp=(25.0,) * 4, sky=(1.0,) * 4)
+        jobs.append(dict(lam=torch.from_numpy(10.0 ** r.uniform(-3.0, 0.0, E)).to(DEV), obs=obs, conv_path=1, psf=None,
+                         flux=torch.from_numpy((10.0 ** r.uniform(-3.0, 0.0, (3, E))).astype(np.float32)).to(DEV)))
+    data = torch.ones(1600, dtype=torch.int32, device=DEV)
+    mom_d = torch.tensor([1.0, 2.0, 3.0], dtype=torch.float64, device=DEV)
+    ctx = P.Context(0)
+
+    def run(js):
+        out = torch.empty(len(js), dtype=torch.float64, device=DEV)
+        best = np.inf
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            ctx.batch_run(js, hgrid, data, mom_d, out, use_graph=True, bands=(0, 1, 1))
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        ctx.sync()
+        return out, best
+
+    small, large = jobs[:300] + jobs[301:], jobs[300:301]
+    (s, ts), (l, tl), (both, t) = run(small), run(large), run(jobs)
+    ctx.close()
+    print(f"[case] one large job {tl:.2f} ms, 600 small {ts:.2f}, together {t:.2f}", flush=True)
+    assert torch.equal(both, torch.cat([s[:300], l, s[300:]]))
+    assert t <= 1.5 * (ts + tl)
