@@ -709,7 +709,13 @@ int64_t gemm_loss_parts(int M, int N, int K) {
   return (int64_t)((M + 64 * wm - 1) / (64 * wm)) * ((N + GBN - 1) / GBN) * 2 * wm;
 }
 
-bool gemm_reads_f32(int M, int N) { return gemm_use64(M, N); }
+// Every 64-column tile rounds the FP32 rows again, an element at a time, where a pass of its own costs a launch: 64
+// rows or more (of each tile) cross between 32 and 48 inputs, 16 rows between 128 and 192, a single
+// row not up to 8,192.  Into 512-512: 1,024 rows of 12 inputs 16.6 us against 18.4 rounded first, of 64 18.7
+// against 17.0, of 2,048 52 against 36; 16 rows of 128 13.8 against 13.9; one of 2,048 13.9 against 15.2.
+bool gemm_reads_f32(int M, int N, int K) {
+  return gemm_use64(M, N) && (M == 1 || (int64_t)std::min(M, HB) * K <= 2048);
+}
 
 hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s) {
   GemmArgs g = g0;

@@ -65,7 +65,7 @@ struct LossArgs {
 // where that product cannot form them.
 int64_t loss_parts(const Layout &lay, int n, bool *fused) {
   const int64_t p = gemm_loss_parts(n, lay.d[lay.L], lay.d[lay.L - 1]);
-  *fused = p > 0 && !(lay.L == 1 && gemm_reads_f32(n, lay.d[1]));
+  *fused = p > 0 && !(lay.L == 1 && gemm_reads_f32(n, lay.d[1], lay.d[0]));
   return *fused ? p : MSE_BLOCKS;
 }
 
@@ -82,7 +82,7 @@ hipError_t forward_impl(pcmd_ctx *c, const pcmd_mlp *net, const Layout &lay, int
   const __bf16 *w = (const __bf16 *)net->w_bf16;
   // the first product reads the FP32 batch itself where it can (and keeps the rounded copy for the
   // backward pass); a large batch is rounded first
-  const bool direct = gemm_reads_f32(n, lay.d[1]);
+  const bool direct = gemm_reads_f32(n, lay.d[1], lay.d[0]);
   hipError_t e = hipSuccess;
   if (!direct)
     e = rows ? launch_gather_f32_to_bf16(x, rows, n_total, lay.d[0], n, act, c->status, s)

@@ -29,7 +29,7 @@ struct GemmArgs {
   int nz;             // K ranges over blocks (set by launch_gemm)
   // A given in FP32 instead (A unused): row m is row rows[m] of A32 (m when rows is NULL; a row outside
   // [0, n_total) is taken as row 0 and sets STATUS_BAD_ROW), rounded to BF16 and, unless Aout is NULL,
-  // also written there [M][lda].  Only where gemm_reads_f32(M, N).
+  // also written there [M][lda].  Only where gemm_reads_f32(M, N, K).
   const float *A32;
   const int32_t *rows;
   int64_t n_total;
@@ -60,7 +60,8 @@ struct AdamArgs {
 // operands (at: A(m, k) = A[k][m]; bt: B(n, k) = B[k][n]) and split-K partials.
 // Partial sums that an EPI_BIAS_MSE product writes (0: this shape cannot take that epilogue).
 int64_t gemm_loss_parts(int M, int N, int K);
-bool gemm_reads_f32(int M, int N);
+// Whether a product of these sizes takes A in FP32 (A32): where that is faster than rounding it first.
+bool gemm_reads_f32(int M, int N, int K);
 size_t gemm_workspace_bytes(int M, int N, int K, bool at, bool bt);
 hipError_t launch_gemm(const GemmArgs &g, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float *x, void *y, int64_t n, hipStream_t s);

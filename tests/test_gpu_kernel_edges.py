@@ -614,3 +614,57 @@ def test_batch_of_one_large_job_and_many_small():
     print(f"[case] one large job {tl:.2f} ms, 600 small {ts:.2f}, together {t:.2f}", flush=True)
     assert torch.equal(both, torch.cat([s[:300], l, s[300:]]))
     assert t <= 1.5 * (ts + tl)
+
+
+# First layers on both sides of the line between reading the FP32 batch in the product (up to 2,048 inputs over
+# at most 64 rows, or one row) and rounding it first, with and without a row vector: against the oracle, and
+# the gathered batch gives the same bits.
+@pytest.mark.parametrize("n,K", [(1, 32), (1, 3000), (16, 128), (16, 129), (64, 32), (64, 33), (300, 32), (300, 33), (70, 300)])
+def test_first_layer_widths(ctx, n, K):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    dims = (K, 64, 100)
+    net = SurrogateNet(ctx, dims, si.mlp_init(dims, 3), device=DEV)
+    r = np.random.default_rng(n + K)
+    x = torch.from_numpy(r.uniform(-1, 1, (400, K)).astype(np.float32)).to(DEV)
+    t = torch.from_numpy(r.normal(-9, 1, (400, 100)).astype(np.float32)).to(DEV)
+    rows = torch.from_numpy(r.integers(0, 400, n).astype(np.int32)).to(DEV)
+    xg, tg = x[rows.long()].contiguous(), t[rows.long()].contiguous()
+    master = net.master.cpu().numpy().astype(np.float64)
+    y = net.forward(xg)
+    ctx.sync()
+    ref, _ = om.forward(master, dims, xg.cpu().numpy())
+    assert np.max(np.abs(y.cpu().numpy() - ref)) <= 2e-3 * max(1.0, np.max(np.abs(ref)))  # BF16 flips, as the network test
+    ga, gb = (torch.full((net.n_params,), np.nan, dtype=torch.float32, device=DEV) for _ in range(2))
+    ctx.mlp_backward(net.struct, x, t, ga, rows=rows)
+    ctx.mlp_backward(net.struct, xg, tg, gb)
+    ctx.sync()
+    assert torch.equal(ga, gb)
+    _, go = om.loss_and_grad(master, dims, xg.cpu().numpy(), tg.cpu().numpy())
+    assert np.max(np.abs(ga.cpu().numpy() - go)[:K * 64]) <= 1e-2 * np.max(np.abs(go[:K * 64]))
+
+
+# A wide first layer takes about the time of its product and of rounding its input (rounded
+# again for each column tile it took 5.7 times that).
+def test_wide_first_layer_time(ctx):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+    n, dims = 4096, (2048, 512)
+    net = SurrogateNet(ctx, dims, si.mlp_init(dims, 3), device=DEV)
+    x = torch.rand((n, 2048), device=DEV)
+    y, w = torch.empty((n, 512), device=DEV), net.w.view(512, 2048)
+
+    def time(f):
+        best = np.inf
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(20):
+                f()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) / 20)
+        return best
+
+    layer, parts = time(lambda: net.forward(x, y)), time(lambda: ctx.gemm_bf16(x.to(torch.bfloat16), w, y))
+    ctx.sync()
+    print(f"[case] wide first layer {1e3 * layer:.1f} us, rounding and product {1e3 * parts:.1f}", flush=True)
+    assert layer <= 2.0 * parts
