@@ -519,7 +519,7 @@ def run_counters(args):
 
 
 def image_plane_at_scale(ctx, P, si, hgrid, N: int = 4096, reps: int = 3) -> dict:
-    """PSF convolution (both paths) and Hess binning of a 4096x4096x3 image: at the benchmark's
+    """PSF convolution to magnitudes (both paths) and Hess binning of a 4096x4096x3 image: at the benchmark's
     256x256 the image-plane kernels are bound by launch latency, here by the memory system.  The
     stars come from the headline grid thinned to 1,050 entries so that sampling stays short."""
     import torch
@@ -529,7 +529,8 @@ def image_plane_at_scale(ctx, P, si, hgrid, N: int = 4096, reps: int = 3) -> dic
     obs.nim = N
     ev = P.Evaluator(ctx, G, N, obs.psf, hgrid)
     out = {"image": f"{N}x{N}x3, 31x31 PSF, {hgrid['nx']}x{hgrid['ny']} Hess"}
-    for path, name in ((P.CONV_FFT, "conv_fft"), (P.CONV_DIRECT, "conv_direct")):
+    for path, name, kernel in ((P.CONV_FFT, "conv_fft", "PSF convolution (FFT chain), noise, magnitudes"),
+                               (P.CONV_DIRECT, "conv_direct", "PSF convolution (direct), noise, magnitudes")):
         ev.simulate(model, obs, path)
         ctx.sync()
         ctx.timer_enable(True)
@@ -538,7 +539,7 @@ def image_plane_at_scale(ctx, P, si, hgrid, N: int = 4096, reps: int = 3) -> dic
         ctx.sync()
         c_ms, c_n, _ = ctx.timer_read(P._lib.TIMER_CONV)
         ctx.timer_enable(False)
-        out[name] = hbm_roofline(8.0 * 3 * N * N, c_ms / max(c_n, 1), name)
+        out[name] = hbm_roofline(8.0 * 3 * N * N, c_ms / max(c_n, 1), kernel)
     h = torch.empty(hgrid["nx"] * hgrid["ny"], dtype=torch.int32, device=ev.mags.device)
     mom = torch.empty(3, dtype=torch.float64, device=ev.mags.device)
     ev.hess_of(ev.mags, h, mom)
@@ -852,11 +853,12 @@ def main():
         "poisson_draws_per_s": s_units / (s_ms / 1e3) if s_ms > 0 else None,
         "draws_per_eval": draws_per_launch,
         "kernel_ms_per_eval": {"sample": s_ms / max(s_n, 1), "conv": c_ms / max(c_n, 1), "hess": h_ms / max(h_n, 1)},
-        # HBM view of the image-plane steps: algorithmic bytes (convolution: read F, write G, 4 B
-        # each per pixel and band; Hess: read the two magnitude planes it bins, 4 B each per
+        # HBM view of the image-plane steps: algorithmic bytes (convolution, noise and magnitudes: read
+        # F, write the magnitudes, 4 B each per pixel and band; Hess: read the two magnitude planes it bins, 4 B each per
         # pixel, write the bins) over the timed launches' average duration, against 8 TB/s
         "conv_roofline": hbm_roofline(8.0 * 3 * obs_d.nim ** 2, c_ms / max(c_n, 1),
-                                      "PSF convolution (FFT chain)" if obs_d.psf.shape[-1] >= 48 else "PSF convolution (direct)"),
+                                      ("PSF convolution (FFT chain)" if obs_d.psf.shape[-1] >= 48 else "PSF convolution (direct)")
+                                      + ", noise, magnitudes"),
         "hess_roofline": hbm_roofline(8.0 * obs_d.nim ** 2 + 4.0 * nh * nh, h_ms / max(h_n, 1), "k_hess"),
         "roofline": {"bound": "alu", "kernel": "k_sample", "achieved": achieved / 1e12,
                      "peak": VALU_LANE_OPS_PEAK / 1e12, "unit": "T lane-instr/s (VALU)",

@@ -405,9 +405,12 @@ enum { PCMD_TIMER_SAMPLE = 0, PCMD_TIMER_CONV = 1, PCMD_TIMER_HESS = 2, PCMD_TIM
 int pcmd_timer_enable(pcmd_ctx *ctx, int on);
 /* Wait for the recorded launches of kernel `which` and return their summed duration (ms),
  * their number and the algorithmic units they processed (SAMPLE: pixel x entry draws;
- * CONV: image values read and written; HESS: pixels binned; BATCH: a whole pcmd_batch_run,
- * pixel x entry draws of all its jobs; GEMM: each BF16 matrix product of the surrogate,
- * 2 M N K floating-point operations).  Consumes those records. */
+ * CONV: the PSF convolution of a pcmd_simulate and the noise and magnitudes that follow it, on
+ * either path, flux values read and magnitudes written; HESS: pixels binned; BATCH: a whole
+ * pcmd_batch_run, pixel x entry draws of all its jobs; GEMM: the surrogate's BF16 matrix products,
+ * 2 M N K floating-point operations each, with what their launches do beside them: the squared
+ * error of the last layer, and in a backward pass one record per layer for both products and the
+ * bias gradient).  Consumes those records. */
 int pcmd_timer_read(pcmd_ctx *ctx, int which, double *total_ms, int64_t *launches, double *units);
 
 #ifdef __cplusplus

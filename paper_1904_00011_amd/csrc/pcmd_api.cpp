@@ -538,22 +538,23 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
         c->fft_N = N;
         c->fft_K = K;
         c->fft_R = R;
+        na.G = (const float *)c->G.p;
+        e = launch_noise_mag(na, s);
       }
     } else {  // goes on to the magnitudes, and keeps the convolved image only where it is asked for
       if (!(dbg && dbg->flux_psf)) ca.G = nullptr;
       e = launch_conv_direct(ca, na, s);
     }
-    if (e != hipSuccess) return hip_fail(c, e, "convolution");
+    if (e != hipSuccess) return hip_fail(c, e, "convolution, noise and magnitudes");
     Gp = (const float *)c->G.p;
+  } else {
+    na.G = Gp;
+    e = launch_noise_mag(na, s);
+    if (e != hipSuccess) return hip_fail(c, e, "k_noise_mag");
   }
   if (dbg && dbg->flux_psf) {
     e = launch_copy_f32(Gp, dbg->flux_psf, (int64_t)B * npx, s);
     if (e != hipSuccess) return hip_fail(c, e, "copy flux_psf");
-  }
-  if (K <= 1 || use_fft) {
-    na.G = Gp;
-    e = launch_noise_mag(na, s);
-    if (e != hipSuccess) return hip_fail(c, e, "k_noise_mag");
   }
   c->err.clear();
   return PCMD_OK;

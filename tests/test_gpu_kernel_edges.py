@@ -668,3 +668,29 @@ def test_wide_first_layer_time(ctx):
     ctx.sync()
     print(f"[case] wide first layer {1e3 * layer:.1f} us, rounding and product {1e3 * parts:.1f}", flush=True)
     assert layer <= 2.0 * parts
+
+
+# The convolution's timer covers the same work on both paths: one record per call, and the noise in it.
+def test_convolution_timer_on_both_paths(ctx):
+    import paper_1904_00011_amd as P
+    nim, flux = 2048, torch.full((3, 1), 1e-3, device=DEV)
+    lam = torch.full((1,), 1.0, dtype=torch.float64, device=DEV)
+    psf = torch.full((3, 5, 5), 0.04, device=DEV)
+    mags = torch.empty((3, nim * nim), device=DEV)
+    for path in (P.CONV_DIRECT, P.CONV_FFT):
+        ms = {}
+        for noise in (0, 2):
+            obs = si.Obs(nim=nim, seed=5, dmod=0.0, dust_model=0, psf=None, noise_model=noise, noise_sigma_mag=(0.0,) * 4,
+                         exptime=(3000.0,) * 4, zp=(25.0,) * 4, sky=(1.0,) * 4, dust_R=(1.0,) * 4)
+            best = np.inf
+            for _ in range(8):
+                ctx.timer_enable(True)
+                ctx.simulate(lam, flux, obs, mags, psf=psf, conv_path=path)
+                ctx.sync()
+                t, launches, units = ctx.timer_read(P._lib.TIMER_CONV)
+                assert launches == 1 and units == 2.0 * 3 * nim * nim
+                best = min(best, t)
+            ms[noise] = best
+        ctx.timer_enable(False)
+        print(f"[case] convolution timer path={path}: {ms[0]:.3f} ms without noise, {ms[2]:.3f} with", flush=True)
+        assert ms[2] >= 1.05 * ms[0]
