@@ -378,7 +378,8 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
   if ((r = ensure(c, c->fl64, (size_t)E * BP * 8, "fluxes"))) return r;
   if ((r = ensure(c, c->part, (size_t)nchunks * S * B * npx * 4, "partial sums"))) return r;
   if ((r = ensure(c, c->F, (size_t)B * npx * 4, "image"))) return r;
-  if ((r = ensure(c, c->G, (size_t)B * npx * 4, "convolved image"))) return r;
+  const bool store_G = K > 1 && (use_fft || (dbg && dbg->flux_psf));  // else the convolution goes on to the magnitudes
+  if (store_G && (r = ensure(c, c->G, (size_t)B * npx * 4, "convolved image"))) return r;
   const int R = psf_grid_of(o) * psf_grid_of(o);
   if (K > 1 && use_fft && (r = ensure(c, c->fft, fft_scratch_bytes(B, N, K, R), "fft"))) return r;
 
@@ -526,7 +527,7 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
   na.k1 = k1;
   const float *Gp = (const float *)c->F.p;
   if (K > 1) {
-    ConvArgs ca{B, N, K, (const float *)c->F.p, o->psf, (float *)c->G.p, c->status, psf_grid_of(o)};
+    const ConvArgs ca{B, N, K, (const float *)c->F.p, o->psf, store_G ? (float *)c->G.p : nullptr, c->status, psf_grid_of(o)};
     ScopedTimer tm(c, PCMD_TIMER_CONV, 2.0 * (double)B * (double)npx, s);
     if (use_fft) {
       const bool fresh = c->fft_buf != c->fft.p || c->fft_B != B || c->fft_N != N || c->fft_K != K || c->fft_R != R;
@@ -541,12 +542,11 @@ int pcmd_simulate(pcmd_ctx *c, const pcmd_iso *iso, const pcmd_obs *o, float *ma
         na.G = (const float *)c->G.p;
         e = launch_noise_mag(na, s);
       }
-    } else {  // goes on to the magnitudes, and keeps the convolved image only where it is asked for
-      if (!(dbg && dbg->flux_psf)) ca.G = nullptr;
+    } else {
       e = launch_conv_direct(ca, na, s);
     }
     if (e != hipSuccess) return hip_fail(c, e, "convolution, noise and magnitudes");
-    Gp = (const float *)c->G.p;
+    Gp = ca.G;
   } else {
     na.G = Gp;
     e = launch_noise_mag(na, s);

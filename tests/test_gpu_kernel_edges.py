@@ -694,3 +694,33 @@ def test_convolution_timer_on_both_paths(ctx):
         ctx.timer_enable(False)
         print(f"[case] convolution timer path={path}: {ms[0]:.3f} ms without noise, {ms[2]:.3f} with", flush=True)
         assert ms[2] >= 1.05 * ms[0]
+
+
+# Scratch for the convolved image only where something reads it: three bands of 4096 x 4096 are 201 MB
+# (226 as allocated), asked for by the Fourier path and by a caller, in any order of calls.
+def test_convolved_image_scratch():
+    import paper_1904_00011_amd as P
+    nim = 4096
+    lam = torch.full((1,), 1.0, dtype=torch.float64, device=DEV)
+    flux, psf = torch.full((3, 1), 1e-3, device=DEV), torch.full((3, 3, 3), 1.0 / 9.0, device=DEV)
+    G, *mags = torch.empty((5, 3, nim * nim), device=DEV)  # no allocation of the test's own between the calls
+    obs = si.Obs(nim=nim, seed=5, dmod=0.0, dust_model=0, psf=None, noise_model=0, noise_sigma_mag=(0.0,) * 4, exptime=(1.0,) * 4,
+                 zp=(25.0,) * 4, sky=(0.0,) * 4, dust_R=(1.0,) * 4)
+    torch.cuda.synchronize()
+    c = P.Context(0)
+
+    def call(with_psf, path, want=None):
+        m = mags.pop()
+        c.simulate(lam, flux, obs, m, psf=psf if with_psf else None, conv_path=path, flux_psf=want)
+        c.sync()
+        return torch.cuda.mem_get_info(0)[0], m
+
+    image = 3 * nim * nim * 4
+    f0, _ = call(False, P.CONV_DIRECT)
+    f1, m1 = call(True, P.CONV_DIRECT)
+    f2, m2 = call(True, P.CONV_DIRECT, G)
+    f3, m3 = call(True, P.CONV_DIRECT)
+    c.close()
+    assert f1 == f0 and f1 - f2 >= image and f3 == f2
+    assert torch.equal(m1, m2) and torch.equal(m1, m3)
+    assert torch.all((-2.5 * torch.log10(G.double()) - m2).nan_to_num(0.0).abs() <= 1e-5 * 25)
