@@ -724,3 +724,78 @@ def test_convolved_image_scratch():
     assert f1 == f0 and f1 - f2 >= image and f3 == f2
     assert torch.equal(m1, m2) and torch.equal(m1, m3)
     assert torch.all((-2.5 * torch.log10(G.double()) - m2).nan_to_num(0.0).abs() <= 1e-5 * 25)
+
+
+# Blocks that walk several samples: the last grid of one sample a block (512), uneven shares, and the size from
+# which a block's share is bounded (64 x 512 + 1).  Every sample as the oracle gives it, and as alone, bit for bit.
+@pytest.mark.parametrize("n", [512, 513, 1300, 32769])
+@pytest.mark.parametrize("nbins", [7, 1025])
+def test_surrogate_loglike_many_samples(ctx, n, nbins):
+    r = np.random.default_rng(n + nbins)
+    y = r.normal(-9.0, 2.0, (n, nbins)).astype(np.float32)
+    d = r.poisson(r.choice([0.0, 0.5, 40.0, 6000.0], nbins)).astype(np.int32)
+    d[0] = 3
+    yd, dd = torch.from_numpy(y).to(DEV), torch.from_numpy(d).to(DEV)
+    out = torch.full((n,), float("nan"), dtype=torch.float64, device=DEV)
+    ctx.surrogate_loglike(yd, dd, out)
+    ctx.sync()
+    got = out.cpu().numpy()
+    for k in [*range(min(n, 700)), *range(max(0, n - 700), n)]:
+        assert got[k] == pytest.approx(om.surrogate_loglike(y[k], d), rel=4e-10, abs=1e-9)
+    alone = torch.empty(1, dtype=torch.float64, device=DEV)
+    for k in (0, 1, 511, n // 2, n - 1):
+        ctx.surrogate_loglike(yd[k:k + 1], dd, alone)
+        ctx.sync()
+        assert alone.item() == got[k]
+    ctx.surrogate_loglike(yd[n // 3:], dd, out[n // 3:])  # other shares, the same bits
+    ctx.sync()
+    assert np.array_equal(out.cpu().numpy(), got)
+
+
+# Predictions of -infinity, +infinity, NaN and so far below the largest that their expectation underflows, bins with
+# and without data there, a diagram without data: infinite or not a number as the oracle's sum is, and the
+# ordinary samples between them untouched.  The same for the likelihood of counts without data.
+@pytest.mark.parametrize("nbins", [40, 11000])  # bins in registers, and beyond
+def test_likelihood_edge_values(ctx, nbins):
+    from tests import parity_utils as pu
+    r = np.random.default_rng(nbins)
+    d = r.poisson(3.0, nbins).astype(np.int32)
+    d[[1, -2]], d[[2, -3]] = 0, 5
+    y = np.repeat(r.normal(-9.0, 2.0, (1, nbins)).astype(np.float32), 16, axis=0)
+    values = [(v, j) for v in (-np.inf, np.inf, np.nan, -2000.0) for j in (1, 2, nbins - 2)]  # bins without, with and without data
+    for k, (v, j) in enumerate(values):
+        y[k, j] = v
+    y[14] = -np.inf
+    y[15] = 3e38
+    for data in (d, np.zeros_like(d)):
+        out = torch.empty(16, dtype=torch.float64, device=DEV)
+        ctx.surrogate_loglike(torch.from_numpy(y).to(DEV), torch.from_numpy(data).to(DEV), out)
+        ctx.sync()
+        with np.errstate(all="ignore"):
+            want = np.array([om.surrogate_loglike(y[k], data) for k in range(16)])
+        assert out.cpu().numpy() == pytest.approx(want, rel=4e-10, abs=1e-9, nan_ok=True)
+    hm, mom = r.poisson(2.0, nbins) + 1, np.array([0.5, 25.0, 1.0])
+    for mode in (0, 1, 2):  # no data: 0 ln 0, scaled model of nothing, 0 / 0
+        with np.errstate(all="ignore"):
+            want = ol.loglike(hm, np.zeros_like(hm), mom, mom, mode)
+        assert pu.gpu_loglike(ctx, hm, np.zeros_like(hm), mom, mom, mode) == pytest.approx(want, rel=2e-11, nan_ok=True)
+
+
+# The moments where every ordinary pixel shows in them (the pixel-count test's 1e30 pixels hide the rest): at most
+# 2^21 FP64 additions, each 2^-53 of the running sum, and nothing from pixels that are not finite.
+@pytest.mark.parametrize("npx", [1, 1023, 8192, 8193, 70001, 2_200_003])
+@pytest.mark.parametrize("bands", [(0, 1, 1), (1, 2, 0)])
+def test_hess_moments_of_ordinary_pixels(ctx, npx, bands):
+    from tests import parity_utils as pu
+    r = np.random.default_rng(npx)
+    m = r.normal(25.0, 0.4, (3, npx)).astype(np.float32)
+    odd = r.uniform(size=(3, npx))
+    m[odd < 0.01], m[odd > 0.995] = np.inf, np.nan
+    m[:, -1] = 25.0
+    h, mom = pu.gpu_hess(ctx, m, dict(x0=-2.0, dx=0.05, y0=23.0, dy=0.05, nx=80, ny=80), bands)
+    with np.errstate(invalid="ignore"):
+        x = m[bands[0]].astype(np.float64) - m[bands[1]]
+    ok = np.isfinite(m[list(bands)]).all(axis=0)
+    assert int(h.sum()) == npx and mom[2] == ok.sum()
+    for got, v in zip(mom[:2], (x[ok], m[bands[2]][ok].astype(np.float64))):
+        assert abs(got - np.sum(v)) <= 2.0 ** -32 * np.sum(np.abs(v))
