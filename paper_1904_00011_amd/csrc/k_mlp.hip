@@ -35,6 +35,22 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 // ---------------------------------------------------------------------------------------
 constexpr int GBM = 128, GBN = 128, GBK = 32, GLDS = GBK + 8;
 
+// Eight elements from any address: a 16-byte load needs no alignment here.  (Operands whose rows are no multiple
+// of 16 bytes were staged an element at a time: the backward pass of 12-500-500-2500 with 1,024 samples 432 ->
+// 138 us, of 12-512-512-2512 108.)
+__device__ __forceinline__ bf16x8 load8(const __bf16 *p) {
+  typedef bf16x8 any_address __attribute__((aligned(2)));
+  return *reinterpret_cast<const any_address *>(p);
+}
+// The first n of them (all from 8 on, none up to 0), zeros after.
+__device__ __forceinline__ bf16x8 load8_part(const __bf16 *p, int n) {
+  if (n >= 8) return load8(p);
+  bf16x8 v;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = i < n ? p[i] : (__bf16)0.0f;
+  return v;
+}
+
 // One thread's share of a (rows) x GBK operand tile: RUNS = rows GBK / (256 8) runs of 8 elements.
 template <int RUNS>
 struct TileRegs {
@@ -59,9 +75,8 @@ __device__ __forceinline__ void load_regs(TileRegs<RUNS> &t, const __bf16 *__res
 #pragma unroll
   for (int it = 0; it < RUNS; ++it) {
     const int idx = threadIdx.x + THREADS * it;
-    const int gr = r0 + idx / (GBK / 8), gk = k0 + (idx % (GBK / 8)) * 8;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) t.v[it][i] = (gr < rows && gk + i < K) ? src[(size_t)gr * ld + gk + i] : (__bf16)0.0f;
+    const int gr = min(r0 + idx / (GBK / 8), rows - 1), gk = k0 + (idx % (GBK / 8)) * 8;
+    t.v[it] = load8_part(src + (size_t)gr * ld + gk, K - gk);
   }
 }
 
@@ -373,7 +388,7 @@ union Run8 {
   uint32_t w[4];
 };
 
-// A whole stage of a 16-byte aligned operand goes through registers.  Rows past the end keep what the
+// A whole stage of an operand goes through registers.  Rows past the end keep what the
 // registers hold (what they produce is not stored): a value given to them made every load wait for
 // the one before it, and reading the last row instead (64 times, for one sample, by every block)
 // crowded one L2 channel.
@@ -387,7 +402,7 @@ __device__ __forceinline__ void load_rows64(Run8 (&x)[4], const __bf16 *__restri
   for (int i = 0; i < 4; ++i) {
     const int idx = t + 256 * i;
     const int r = r0 + (idx >> 4), k = min(k0 + (t & 15) * 8, ke - 8);
-    if (r < rows) x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)r * ld + k);
+    if (r < rows) x[i].v = load8(src + (size_t)r * ld + k);
   }
 }
 __device__ __forceinline__ void store_rows64(__bf16 *lds, const Run8 (&x)[4], int t) {
@@ -397,45 +412,60 @@ __device__ __forceinline__ void store_rows64(__bf16 *lds, const Run8 (&x)[4], in
     *reinterpret_cast<bf16x8 *>(lds + lds64(idx >> 4, idx & 15)) = x[i].v;
   }
 }
-// K-major (rows a multiple of 8): block b holds k 8 (b / 8) .. + 7 and rows 8 (b % 8) .. + 7.
+// Any other last stage, zeros from ke on.
+__device__ __forceinline__ void stage_rows64(__bf16 *lds, const __bf16 *__restrict__ src, int ld, int rows, int r0, int k0,
+                                             int ke, int t) {
+#pragma unroll 1
+  for (int idx = t; idx < 64 * 16; idx += 256) {
+    const int r = r0 + (idx >> 4), k = k0 + (idx & 15) * 8;
+    if (r >= rows || k >= ke + 8) continue;
+    *reinterpret_cast<bf16x8 *>(lds + lds64(idx >> 4, idx & 15)) = load8_part(src + (size_t)r * ld + k, ke - k);
+  }
+}
+// K-major: block b holds k 8 (b / 8) .. + 7 and rows 8 (b % 8) .. + 7 of the tile's, the last rows again where
+// there are not as many (cols64_row: the first of them; a tile has eight or more).
+__device__ __forceinline__ int cols64_row(int rows, int r0, int b) { return min((b & 7) * 8, rows - r0 - 8); }
 __device__ __forceinline__ void load_cols64(Run8 (&x)[8], const __bf16 *__restrict__ src, int ld, int rows, int r0, int k0,
                                             int ke, int b) {
-  const int r = r0 + (b & 7) * 8, k = min(k0 + (b >> 3) * 8, ke - 8);
-  if (r >= rows) return;
+  const int k = min(k0 + (b >> 3) * 8, ke - 8);
+  const __bf16 *p = src + (size_t)k * ld + r0 + cols64_row(rows, r0, b);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) x[i].v = *reinterpret_cast<const bf16x8 *>(src + (size_t)(k + i) * ld + r);
+  for (int i = 0; i < 8; ++i) x[i].v = load8(p + (size_t)i * ld);
 }
-__device__ __forceinline__ void store_cols64(__bf16 *lds, const Run8 (&x)[8], int b) {
+__device__ __forceinline__ void store_cols64(__bf16 *lds, const Run8 (&x)[8], int row, int unit) {
 #pragma unroll
   for (int m = 0; m < 8; ++m) {
     Run8 o;  // row m of the block: its k pairs from the k-th and (k + 1)-th words
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       o.w[j] = __builtin_amdgcn_perm(x[2 * j + 1].w[m >> 1], x[2 * j].w[m >> 1], (m & 1) ? 0x07060302u : 0x05040100u);
-    *reinterpret_cast<bf16x8 *>(lds + lds64((b & 7) * 8 + m, b >> 3)) = o.v;
+    *reinterpret_cast<bf16x8 *>(lds + lds64(row + m, unit)) = o.v;
   }
 }
-// Any other stage, one element at a time straight into LDS: k0 .. ke - 1 (at most HK), zeros up to the
-// next multiple of 16.
-template <bool T, bool F32>
-__device__ __forceinline__ void stage64(__bf16 *lds, const GemmArgs &g, const __bf16 *__restrict__ src, int ld, int rows,
-                                        int ke, int r0, int k0, int t, bool first_column) {
+// Any other stage: the last, or of a tile of fewer than eight rows; zeros from ke on.
+__device__ __forceinline__ void stage_cols64(__bf16 *lds, Run8 (&x)[8], const __bf16 *__restrict__ src, int ld, int rows,
+                                             int r0, int k0, int ke, int b) {
+  const int k = k0 + (b >> 3) * 8;
+  if (k >= ke + 8) return;
+  const int row = max(cols64_row(rows, r0, b), 0);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) x[i].v = load8_part(src + (size_t)min(k + i, ke - 1) * ld + r0 + row, k + i < ke ? rows - r0 - row : 0);
+  store_cols64(lds, x, row, b >> 3);
+}
+// The FP32 input batch, rounded, one element at a time straight into LDS: k0 .. ke - 1 (at most HK), zeros up to
+// the next multiple of 16.
+__device__ __forceinline__ void stage_f32_64(__bf16 *lds, const GemmArgs &g, int ke, int r0, int k0, int t, bool first_column) {
   const int steps = (max(0, min(HK, ke - k0)) + 15) / 16;
-  const int n = max(1, min(HB, rows - r0));
+  const int n = max(1, min(HB, g.M - r0));
   const int lg = n > 1 ? 32 - __builtin_clz((unsigned)(n - 1)) : 0;  // 2^lg >= n rows
   for (int idx = t; idx < steps << (4 + lg); idx += 256) {
     // neighbouring threads read neighbouring elements
-    const int rr = (T ? idx : idx >> 4) & ((1 << lg) - 1);
-    const int kk = T ? idx >> lg : (idx & 15) + (idx >> (4 + lg)) * 16;
+    const int rr = (idx >> 4) & ((1 << lg) - 1), kk = (idx & 15) + (idx >> (4 + lg)) * 16;
     const int r = r0 + rr, k = k0 + kk;
     __bf16 v = (__bf16)0.0f;
-    if (r < rows && k < ke) {
-      if constexpr (F32) {  // the FP32 input batch, rounded
-        v = (__bf16)g.A32[batch_row(g.rows, r, g.n_total, g.status) * ld + k];
-        if (g.Aout && first_column) g.Aout[(size_t)r * ld + k] = v;
-      } else {
-        v = T ? src[(size_t)k * ld + r] : src[(size_t)r * ld + k];
-      }
+    if (r < g.M && k < ke) {
+      v = (__bf16)g.A32[batch_row(g.rows, r, g.n_total, g.status) * g.lda + k];
+      if (g.Aout && first_column) g.Aout[(size_t)r * g.lda + k] = v;
     }
     lds[lds64(rr, kk >> 3) + (kk & 7)] = v;
   }
@@ -451,8 +481,8 @@ __device__ __forceinline__ void gemm64_block(const GemmArgs &g, unsigned block, 
   const int bm = tl.y * HB, bn = tl.x * HB;
   const int wave = t >> 6, lane = t & 63;
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  const bool va = !AF32 && g.lda % 8 == 0 && ((uintptr_t)g.A & 15) == 0 && (!TA || g.M % 8 == 0);
-  const bool vb = g.ldb % 8 == 0 && ((uintptr_t)g.B & 15) == 0 && (!TB || g.N % 8 == 0);
+  // operands whose whole stages go through registers
+  const bool va = !AF32 && (!TA || g.M - bm >= 8), vb = !TB || g.N - bn >= 8;
   const int chunk = G > 1 ? grp : tl.z;
   const int kb = chunk * g.kchunk, ke = min(g.K, kb + g.kchunk);
   f32x16 acc;
@@ -485,19 +515,29 @@ __device__ __forceinline__ void gemm64_block(const GemmArgs &g, unsigned block, 
     const int k0 = kb + st * HK;
     const bool whole = whole_steps64(k0, ke);
     if (st > 0) __syncthreads();  // the previous stage's reads are over
-    if (whole && va) {
-      if constexpr (!TA) store_rows64(As, ra, t);
-      if constexpr (TA)
-        if (has_a) store_cols64(As, rc, cb);
+    if constexpr (AF32) {
+      stage_f32_64(As, g, ke, bm, k0, t, tl.x == 0);
+    } else if constexpr (TA) {
+      if (has_a && whole && va)
+        store_cols64(As, rc, cols64_row(g.M, bm, cb), cb >> 3);
+      else if (has_a)
+        stage_cols64(As, rc, g.A, g.lda, g.M, bm, k0, ke, cb);
     } else {
-      stage64<TA, AF32>(As, g, g.A, g.lda, g.M, ke, bm, k0, t, tl.x == 0);
+      if (whole)
+        store_rows64(As, ra, t);
+      else
+        stage_rows64(As, g.A, g.lda, g.M, bm, k0, ke, t);
     }
-    if (whole && vb) {
-      if constexpr (!TB) store_rows64(Bs, rb, t);
-      if constexpr (TB)
-        if (has_b) store_cols64(Bs, rc, cb);
+    if constexpr (TB) {
+      if (has_b && whole && vb)
+        store_cols64(Bs, rc, cols64_row(g.N, bn, cb), cb >> 3);
+      else if (has_b)
+        stage_cols64(Bs, rc, g.B, g.ldb, g.N, bn, k0, ke, cb);
     } else {
-      stage64<TB, false>(Bs, g, g.B, g.ldb, g.N, ke, bn, k0, t, false);
+      if (whole)
+        store_rows64(Bs, rb, t);
+      else
+        stage_rows64(Bs, g.B, g.ldb, g.N, bn, k0, ke, t);
     }
     __syncthreads();
     if (st + 1 < stages) load(k0 + HK);

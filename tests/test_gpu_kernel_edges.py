@@ -799,3 +799,56 @@ def test_hess_moments_of_ordinary_pixels(ctx, npx, bands):
     assert int(h.sum()) == npx and mom[2] == ok.sum()
     for got, v in zip(mom[:2], (x[ok], m[bands[2]][ok].astype(np.float64))):
         assert abs(got - np.sum(v)) <= 2.0 ** -32 * np.sum(np.abs(v))
+
+
+# Operands that start at an odd address and whose rows allow no aligned 16-byte load, at the edges of an 8 x 8
+# block of a K-major operand (tiles of fewer than eight rows, a last block that overlaps the one before), of a
+# run of 8 and of a last stage, in 64 x 64 tiles and in both of the larger ones.  Bound as for the small tiles.
+@pytest.mark.parametrize("M,N,K", [(1, 7, 9), (7, 8, 500), (9, 63, 131), (65, 71, 137), (135, 66, 505), (71, 300, 1031), (130, 9, 2503),
+                                   (2049, 4100, 43), (4097, 2049, 33)])
+@pytest.mark.parametrize("at,bt", [(False, False), (True, True), (True, False), (False, True)])
+def test_gemm_unaligned_operands(ctx, M, N, K, at, bt):
+    r = np.random.default_rng(M + N + K)
+    A = om.bf16_round(r.normal(size=(M, K)).astype(np.float32))
+    B = om.bf16_round(r.normal(size=(N, K)).astype(np.float32))
+
+    def odd(X):  # guarded by NaN on both sides
+        buf = torch.full((X.size + 16,), float("nan"), dtype=torch.bfloat16, device=DEV)
+        v = buf[1:1 + X.size].view(*X.shape)
+        v.copy_(torch.from_numpy(X).to(DEV))
+        return v
+
+    Ad, Bd = odd(A.T.copy() if at else A), odd(B.T.copy() if bt else B)
+    C = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+    print(f"[case] unaligned operands M={M} N={N} K={K} at={at} bt={bt}", flush=True)
+    ctx.gemm_bf16(Ad, Bd, C, a_trans=at, b_trans=bt)
+    ctx.sync()
+    Af, Bf = (torch.from_numpy(x).to(DEV).double() for x in (A, B))
+    bound = K * 2.0 ** -24 * (Af.abs() @ Bf.abs().T)
+    assert torch.all((C.double() - Af @ Bf.T).abs() <= bound)
+
+
+# A network of widths that are no multiple of 8 takes about the time of the next larger ones (1.3 times; staged an
+# element at a time it took 4 times as long).
+def test_odd_network_widths_time(ctx):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+
+    def time(dims, n=1024):
+        net = SurrogateNet(ctx, dims, si.mlp_init(dims, 3), device=DEV)
+        x, t = torch.rand((n, dims[0]), device=DEV), torch.rand((n, dims[-1]), device=DEV)
+        grad = torch.empty(net.n_params, device=DEV)
+        best = np.inf
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                ctx.mlp_backward(net.struct, x, t, grad)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) / 10)
+        return best
+
+    odd, even = time((12, 500, 500, 2500)), time((12, 512, 512, 2512))
+    ctx.sync()
+    print(f"[case] odd widths {1e3 * odd:.1f} us, even {1e3 * even:.1f}", flush=True)
+    assert odd <= 2.0 * even
