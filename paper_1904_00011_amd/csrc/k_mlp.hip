@@ -141,15 +141,19 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs &g, int row, int co
 
 // Tile (x, y, z) of a product's nx x ny tiles and nz K ranges for block `id`.  Blocks go to the eight
 // XCDs in turn, each with an L2 of its own, so the id's low three bits pick what one XCD keeps to
-// itself: the K ranges when there are at least eight (an XCD then reads its ranges' operands once),
+// itself: every eighth K range when there are at least eight (an XCD then reads its ranges' operands once),
 // else every eighth tile row or column, whichever there are more of (an XCD reads its rows of that
 // operand once and shares the other).  The grid is padded to whole turns; a tile outside is left out.
+// The ranges past the last eight are shared out by tiles, from three blocks per CU on: of nine ranges one
+// XCD had twice the others' work (64 x 8000 x 2304 20.9 -> 17.2 us, x 10000 51 -> 39), while fewer blocks all
+// run at once either way (512 x 512 x 2304 14.1 us, shared out 14.9).
 struct TileId {
   int x, y, z;
   bool inside;
 };
+__host__ __device__ inline bool xcd_share_rest(int tiles) { return tiles >= 768; }
 __host__ __device__ inline unsigned xcd_blocks(int nx, int ny, int nz) {
-  if (nz >= 8) return (unsigned)((nz + 7) / 8 * 8 * nx * ny);
+  if (nz >= 8) return (unsigned)(xcd_share_rest(nx * ny * nz) ? nz / 8 * 8 * nx * ny + (nz % 8 * nx * ny + 7) / 8 * 8 : (nz + 7) / 8 * 8 * nx * ny);
   return (unsigned)((nx > ny ? (nx + 7) / 8 * 8 * ny : (ny + 7) / 8 * 8 * nx) * nz);
 }
 __device__ __forceinline__ TileId xcd_tile(unsigned id, int nx, int ny, int nz) {
@@ -157,10 +161,15 @@ __device__ __forceinline__ TileId xcd_tile(unsigned id, int nx, int ny, int nz) 
   int j = (int)(id >> 3);
   TileId t;
   if (nz >= 8) {
-    const int xy = j % (nx * ny);
-    t.z = j / (nx * ny) * 8 + xcd;
-    t.x = xy % nx;
-    t.y = xy / nx;
+    const int n = nx * ny, whole = nz / 8 * n, rest = nz % 8 * n;
+    int i = j;
+    t.z = j / n * 8 + xcd;
+    if (j >= whole && xcd_share_rest(n * nz)) {
+      i = rest / 8 * xcd + min(xcd, rest % 8) + j - whole;
+      t.z = j - whole < rest / 8 + (xcd < rest % 8 ? 1 : 0) ? nz / 8 * 8 + i / n : nz;
+    }
+    t.x = i % n % nx;
+    t.y = i % n / nx;
   } else {
     const int per = xcd_blocks(nx, ny, 1) / 8;
     t.z = j / per;
