@@ -4,6 +4,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "pcmd_device.h"
 #include "pcmd_internal.h"
@@ -77,6 +78,19 @@ __device__ __forceinline__ void load_regs(TileRegs<RUNS> &t, const __bf16 *__res
     const int idx = threadIdx.x + THREADS * it;
     const int gr = min(r0 + idx / (GBK / 8), rows - 1), gk = k0 + (idx % (GBK / 8)) * 8;
     t.v[it] = load8_part(src + (size_t)gr * ld + gk, K - gk);
+  }
+}
+
+// A whole step, or (PART) the last, from any address.
+template <int THREADS, bool PART, int RUNS>
+__device__ __forceinline__ void load_step(TileRegs<RUNS> &t, const __bf16 *__restrict__ src, int ld, int rows, int K,
+                                          int r0, int k0) {
+#pragma unroll
+  for (int it = 0; it < RUNS; ++it) {
+    const int idx = threadIdx.x + THREADS * it;
+    const int gr = min(r0 + idx / (GBK / 8), rows - 1), gk = k0 + (idx % (GBK / 8)) * 8;
+    const __bf16 *p = src + (size_t)gr * ld + gk;
+    t.v[it] = PART ? load8_part(p, K - gk) : load8(p);
   }
 }
 
@@ -243,7 +257,11 @@ __device__ __forceinline__ void store_loss_part(const GemmArgs &g, double s, int
 constexpr int GEPI_LD = 72;  // epilogue slab row stride (floats): 32 x 72 x 4 B per wave
 
 // WM x 2 waves of 64 x 64 (64 VGPRs of accumulators, four waves per SIMD).
-template <int EPI, int WM>
+//
+// STEPS: the K loop has whole steps alone, and the last one's partial loads follow it.  As a branch in the
+// loop they make the compiler wait for A's loads before it issues B's (1024 x 8192 x 4096: 114 us, 94
+// without).
+template <int EPI, int WM, bool STEPS>
 __global__ void __launch_bounds__(128 * WM) __attribute__((amdgpu_waves_per_eu(4, 8))) k_gemm(GemmArgs g) {
   constexpr int MI = 2, BM = 64 * WM, TH = 128 * WM;  // block tile rows, threads
   constexpr int RA = BM * GBK / (TH * 8), RB = GBN * GBK / (TH * 8);
@@ -252,8 +270,19 @@ __global__ void __launch_bounds__(128 * WM) __attribute__((amdgpu_waves_per_eu(4
   __shared__ __attribute__((aligned(16))) __bf16 smem[TILES > SLABS ? TILES : SLABS];
   __bf16 (*As)[BM * GLDS] = reinterpret_cast<__bf16 (*)[BM * GLDS]>(smem);
   __bf16 (*Bs)[GBN * GLDS] = reinterpret_cast<__bf16 (*)[GBN * GLDS]>(smem + 2 * BM * GLDS);
-  const int nx = (g.N + GBN - 1) / GBN;
-  const TileId tl = xcd_tile(blockIdx.x, nx, (g.M + BM - 1) / BM, 1);
+  const int nx = (g.N + GBN - 1) / GBN, ny = (g.M + BM - 1) / BM;
+  TileId tl;
+  if (g.nz > 1) {  // K ranges over blocks, each into its part of the workspace (EPI_STORE)
+    const int xy = (int)blockIdx.x % (nx * ny), z = (int)blockIdx.x / (nx * ny), kb = z * g.kchunk;
+    tl = TileId{xy % nx, xy / nx, z, true};
+    g.A += kb;
+    g.B += kb;
+    g.K = min(g.K - kb, g.kchunk);
+    g.C = g.part + (size_t)z * g.M * g.N;
+    g.ldc = g.N;
+  } else {
+    tl = xcd_tile(blockIdx.x, nx, ny, 1);
+  }
   if (!tl.inside) return;
   const int bm = tl.y * BM, bn = tl.x * GBN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -268,25 +297,23 @@ __global__ void __launch_bounds__(128 * WM) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
   const int r = lane & 31, kh = (lane >> 5) * 8;
-  constexpr int kb = 0;
-  const int ke = g.K;
-  const int nk = (ke + GBK - 1) / GBK;
   TileRegs<RA> ra;
   TileRegs<RB> rb;
-  load_regs<TH>(ra, g.A, g.lda, g.M, ke, bm, kb, va);
-  load_regs<TH>(rb, g.B, g.ldb, g.N, ke, bn, kb, vb);
-  store_lds<TH>(As[0], ra);
-  store_lds<TH>(Bs[0], rb);
-  __syncthreads();
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) {
-      load_regs<TH>(ra, g.A, g.lda, g.M, ke, bm, kb + (kt + 1) * GBK, va);
-      load_regs<TH>(rb, g.B, g.ldb, g.N, ke, bn, kb + (kt + 1) * GBK, vb);
-    }
-    const __bf16 *as = As[cur];
-    const __bf16 *bs = Bs[cur];
+  auto load = [&](int k0) {
+    load_regs<TH>(ra, g.A, g.lda, g.M, g.K, bm, k0, va);
+    load_regs<TH>(rb, g.B, g.ldb, g.N, g.K, bn, k0, vb);
+  };
+  auto load_one = [&](int k0, auto part) {
+    load_step<TH, decltype(part)::value>(ra, g.A, g.lda, g.M, g.K, bm, k0);
+    load_step<TH, decltype(part)::value>(rb, g.B, g.ldb, g.N, g.K, bn, k0);
+  };
+  auto store = [&](int buf) {
+    store_lds<TH>(As[buf], ra);
+    store_lds<TH>(Bs[buf], rb);
+  };
+  auto multiply = [&](int buf) {
+    const __bf16 *as = As[buf];
+    const __bf16 *bs = Bs[buf];
 #pragma unroll
     for (int ks = 0; ks < GBK; ks += 16) {
       bf16x8 a[MI], b[2];
@@ -299,11 +326,46 @@ __global__ void __launch_bounds__(128 * WM) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni) acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[mi], b[ni], acc[mi][ni], 0, 0, 0);
     }
-    if (more) {
-      store_lds<TH>(As[cur ^ 1], ra);
-      store_lds<TH>(Bs[cur ^ 1], rb);
-    }
+  };
+  if constexpr (STEPS) {
+    constexpr std::integral_constant<bool, false> whole{};
+    constexpr std::integral_constant<bool, true> part{};
+    const int steps = g.K / GBK;
+    if (steps > 0)
+      load_one(0, whole);
+    else
+      load_one(0, part);
+    store(0);
     __syncthreads();
+    int cur = 0;
+    for (int kt = 1; kt < steps; ++kt, cur ^= 1) {
+      load_one(kt * GBK, whole);
+      __builtin_amdgcn_sched_barrier(0);  // issued before the products, not among them
+      multiply(cur);
+      store(cur ^ 1);
+      __syncthreads();
+    }
+    if (steps > 0 && g.K % GBK != 0) {
+      load_one(steps * GBK, part);
+      multiply(cur);
+      cur ^= 1;
+      store(cur);
+      __syncthreads();
+    }
+    multiply(cur);
+    __syncthreads();
+  } else {
+    const int nk = (g.K + GBK - 1) / GBK;
+    load(0);
+    store(0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+      const bool more = kt + 1 < nk;
+      if (more) load((kt + 1) * GBK);
+      multiply(kt & 1);
+      if (more) store((kt & 1) ^ 1);
+      __syncthreads();
+    }
   }
   // Epilogue through LDS (the A/B buffers are free after the last barrier): accumulator element e
   // of a 32 x 32 tile sits at row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32, so a lane
@@ -766,6 +828,48 @@ bool gemm_reads_f32(int M, int N, int K) {
   return gemm_use64(M, N) && (M == 1 || (int64_t)std::min(M, HB) * K <= 2048);
 }
 
+// Row starts that fall on 64 bytes: a step's loads of a row (32 elements) then take one cache line.
+static bool gemm_aligned64(const GemmArgs &g) {
+  return g.lda % 32 == 0 && g.ldb % 32 == 0 && (((uintptr_t)g.A | (uintptr_t)g.B) & 63) == 0;
+}
+// Whether an unsplit product takes the loop of whole steps: with two blocks per CU (1024 x 8192 x 4096: 114 -> 94 us);
+// of many more, those that run ahead find less in L2 (4096 x 10000 x 512: 72 -> 96 us).
+static bool gemm_steps(int M, int N) {
+  return !gemm_tall(M, N) && (int64_t)((M + GBM - 1) / GBM) * ((N + GBN - 1) / GBN) <= 512;
+}
+// Whether a product over K ranges of row-major operands takes 128 x 128 tiles after all: its 64 x 64 tiles
+// would not all run at once (four blocks per CU), the larger tiles waste no more of their rows and columns, and
+// the ranges are short, so that the larger tiles' fewer operand reads show (1024 x 512 x 2048: 22.5 -> 20 us, x
+// 3000 26 -> 21; 512 x 512 x 2048, 512 blocks, 13 and 15; 900 x 1100 x 4096 33 and 36), or long ones and the
+// blocks whole turns over the CUs (1024 x 1024 x 16384: 77 -> 63 us, 640 x 640 x 10000, 525 blocks, 32 and 38).
+static bool gemm_split128(const GemmArgs &g, int splits, bool at, bool bt) {
+  if (splits <= G64_SPLITS || at || bt || g.A32) return false;
+  const int64_t b128 = (int64_t)((g.M + GBM - 1) / GBM) * ((g.N + GBN - 1) / GBN) * splits;
+  const int64_t b64 = (int64_t)((g.M + HB - 1) / HB) * ((g.N + HB - 1) / HB) * splits;
+  const bool turns = (b128 + 255) / 256 * 256 * 100 <= b128 * 106;
+  return b64 >= 1024 && 4 * b128 * 100 <= b64 * 106 && (g.K <= 4096 || (turns && gemm_aligned64(g)));
+}
+
+static hipError_t launch_split128(GemmArgs g, int splits, int epi, void *ws, hipStream_t s) {
+  g.part = (float *)ws;
+  g.nz = splits;
+  const unsigned blocks = (unsigned)((g.M + GBM - 1) / GBM * ((g.N + GBN - 1) / GBN) * splits);
+  const unsigned rblocks = (unsigned)(((int64_t)g.M * g.N + 255) / 256);
+  // the loop of whole steps where rows fall on cache lines (1024 x 512 x 3000, which do not: 25.5 us, 21.5 without)
+  if (gemm_aligned64(g))
+    hipLaunchKernelGGL((k_gemm<EPI_STORE, 2, true>), dim3(blocks), dim3(256), 0, s, g);
+  else
+    hipLaunchKernelGGL((k_gemm<EPI_STORE, 2, false>), dim3(blocks), dim3(256), 0, s, g);
+#define PCMD_REDUCE_CASE(E_) \
+  if (epi == E_) hipLaunchKernelGGL((k_gemm_splitk_reduce<E_>), dim3(rblocks), dim3(256), 0, s, g, splits);
+  PCMD_REDUCE_CASE(EPI_STORE)
+  PCMD_REDUCE_CASE(EPI_BIAS)
+  PCMD_REDUCE_CASE(EPI_BIAS_GELU)
+  PCMD_REDUCE_CASE(EPI_GELU_GRAD)
+#undef PCMD_REDUCE_CASE
+  return epi == EPI_BIAS_MSE ? hipErrorInvalidValue : hipGetLastError();  // gemm_loss_parts() == 0
+}
+
 hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s) {
   GemmArgs g = g0;
   if (ws_bytes < gemm_workspace_bytes(g.M, g.N, g.K, at, bt)) return hipErrorInvalidValue;
@@ -773,6 +877,7 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
   const int splits = gemm_splits(g.M, g.N, g.K, kchunk);
   const bool split = splits > 1;
   g.kchunk = split ? kchunk : g.K;
+  if (gemm_split128(g, splits, at, bt)) return launch_split128(g, splits, epi, ws, s);
   if (gemm_use64(g.M, g.N)) return launch_gemm64(g, splits, at, bt, epi, ws, s);
   if (g.A32) return hipErrorInvalidValue;
   char *w = (char *)ws;
@@ -795,14 +900,17 @@ hipError_t launch_gemm(const GemmArgs &g0, bool at, bool bt, int epi, void *ws, 
   }
   // 512 blocks or more are never split (gemm_splits splits below 128)
   g.part = nullptr;
-  const bool tall = gemm_tall(g.M, g.N);
+  g.nz = 1;
+  const bool tall = gemm_tall(g.M, g.N), steps = gemm_steps(g.M, g.N);
   const dim3 grid(xcd_blocks((g.N + GBN - 1) / GBN, (g.M + (tall ? 2 * GBM : GBM) - 1) / (tall ? 2 * GBM : GBM), 1));
 #define PCMD_GEMM_CASE(E_)                                                                             \
   if (epi == E_) {                                                                                     \
     if (tall)                                                                                          \
-      hipLaunchKernelGGL((k_gemm<E_, 4>), grid, dim3(512), 0, s, g);                                   \
+      hipLaunchKernelGGL((k_gemm<E_, 4, false>), grid, dim3(512), 0, s, g);                            \
+    else if (steps)                                                                                    \
+      hipLaunchKernelGGL((k_gemm<E_, 2, true>), grid, dim3(256), 0, s, g);                             \
     else                                                                                               \
-      hipLaunchKernelGGL((k_gemm<E_, 2>), grid, dim3(256), 0, s, g);                                   \
+      hipLaunchKernelGGL((k_gemm<E_, 2, false>), grid, dim3(256), 0, s, g);                            \
     return hipGetLastError();                                                                          \
   }
   PCMD_GEMM_CASE(EPI_STORE)
