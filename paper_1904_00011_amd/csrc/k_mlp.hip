@@ -1118,21 +1118,26 @@ hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, flo
 
 // Adam on the FP32 master weights [out][in] and biases of every layer in one launch, refreshing the
 // BF16 copies W [out][in] and W^T [in][out].  Without an update only the copies are refreshed.  A
-// block takes a 64 x 64 tile of one layer's weights (tiles of layer l are blocks first[l] .. first[l + 1]
-// - 1; the tile's rows' biases go with the first tile of a row), a row of a wave at a time, and writes
+// block takes a tile of ROWS rows and 64 columns of one layer's weights (tiles of layer l are blocks first[l] ..
+// first[l + 1] - 1; the tile's rows' biases go with the first tile of a row), a row of a wave at a time, and writes
 // W^T's rows from an LDS copy of the tile: a column-strided 2-byte store per weight had cost the
 // update half its time.  Bound by the 32 bytes per weight (moments, master, gradient, copies).
 // 5.4 million weights: 67 us in five launches -> 41 us (4.2 TB/s of a copy's 4.7).
-constexpr int AT = 64;
+// Networks of few 64-row tiles are bound by the latency of a wave's rows one after another, and take 16 rows
+// (four to a wave): 512 x 512 11.0 -> 5.0 us, 3 -> 580 13.8 -> 5.9 us, 2048 x 1024 (512 tiles) 18.8 -> 11.4 us; at
+// 1,504 tiles 39 us with either, at 4,096 tiles 110 with 16 rows and 96 with 64 (W^T in pieces of 128 bytes, not 32).
+constexpr int AT = 64, ADAM_SHORT = 16;
+constexpr int64_t ADAM_SHORT_BLOCKS = 1536;
 
+template <int ROWS>
 __global__ void __launch_bounds__(256) k_adam(AdamArgs a) {
-  __shared__ __bf16 tile[AT][AT + 2];
+  __shared__ __bf16 tile[ROWS][AT + 2];
   int l = 0;
   while (l + 1 < a.n_layers && (int)blockIdx.x >= a.first[l + 1]) ++l;
   const int n_in = a.dims[l], n_out = a.dims[l + 1];
   const int tiles_in = (n_in + AT - 1) / AT;
   const int q = (int)blockIdx.x - a.first[l];
-  const int o0 = (q / tiles_in) * AT, i0 = (q % tiles_in) * AT;
+  const int o0 = (q / tiles_in) * ROWS, i0 = (q % tiles_in) * AT;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t base = a.off[l];
   auto step = [&](int64_t i) {
@@ -1150,32 +1155,41 @@ __global__ void __launch_bounds__(256) k_adam(AdamArgs a) {
     return (__bf16)x;
   };
 #pragma unroll 4
-  for (int r = w; r < AT; r += 4) {
+  for (int r = w; r < ROWS; r += 4) {
     const int o = o0 + r, i = i0 + lane;
     if (o >= n_out || i >= n_in) continue;
     const __bf16 wb = step(base + (int64_t)o * n_in + i);
     ((__bf16 *)a.w_bf16)[a.woff[l] + (int64_t)o * n_in + i] = wb;
     tile[r][lane] = wb;
   }
-  if (i0 == 0 && threadIdx.x < AT && o0 + (int)threadIdx.x < n_out)
+  if (i0 == 0 && threadIdx.x < ROWS && o0 + (int)threadIdx.x < n_out)
     (void)step(base + (int64_t)n_out * n_in + o0 + threadIdx.x);
   __syncthreads();
-  for (int r = w; r < AT; r += 4) {
-    const int i = i0 + r, o = o0 + lane;
-    if (i < n_in && o < n_out) ((__bf16 *)a.wt_bf16)[a.woff[l] + (int64_t)i * n_out + o] = tile[lane][r];
+  for (int t = threadIdx.x; t < AT * ROWS; t += 256) {
+    const int i = i0 + t / ROWS, o = o0 + t % ROWS;
+    if (i < n_in && o < n_out) ((__bf16 *)a.wt_bf16)[a.woff[l] + (int64_t)i * n_out + o] = tile[t % ROWS][t / ROWS];
   }
 }
 
 hipError_t launch_adam(AdamArgs a, hipStream_t s) {
   if (a.n_layers < 1 || a.n_layers > PCMD_MLP_MAX_LAYERS) return hipErrorInvalidValue;
-  int64_t blocks = 0;
-  for (int l = 0; l < a.n_layers; ++l) {
-    a.first[l] = (int)blocks;
-    blocks += (int64_t)((a.dims[l] + AT - 1) / AT) * ((a.dims[l + 1] + AT - 1) / AT);
-    if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  auto lay_out = [&](int rows) {
+    int64_t blocks = 0;
+    for (int l = 0; l < a.n_layers && blocks <= 0x7FFFFFFF; ++l) {
+      a.first[l] = (int)blocks;
+      blocks += (int64_t)((a.dims[l] + AT - 1) / AT) * ((a.dims[l + 1] + rows - 1) / rows);
+    }
+    a.first[a.n_layers] = (int)blocks;
+    return blocks;
+  };
+  int64_t blocks = lay_out(AT);
+  if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
+  if (blocks < ADAM_SHORT_BLOCKS) {
+    blocks = lay_out(ADAM_SHORT);
+    hipLaunchKernelGGL(k_adam<ADAM_SHORT>, dim3((unsigned)blocks), dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_adam<AT>, dim3((unsigned)blocks), dim3(256), 0, s, a);
   }
-  a.first[a.n_layers] = (int)blocks;
-  hipLaunchKernelGGL(k_adam, dim3((unsigned)blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

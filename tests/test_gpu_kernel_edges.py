@@ -917,3 +917,33 @@ def test_gemm_relative_times(ctx, small, large, share):
     s, l = time(*small), time(*large)
     print(f"[case] product {small} {1e3 * s:.1f} us, {large} {1e3 * l:.1f}", flush=True)
     assert s <= share * l
+
+
+# Adam's short and tall tiles, on either side of the line between them, with sides that are no multiples of
+# either: the BF16 copies and the transposed ones are exactly the rounded master, biases and weights follow
+# the update rule (bound as in test_adam_ragged_layers).
+@pytest.mark.parametrize("dims", [(7, 15, 17, 64), (65, 16, 1), (3000, 1985), (3000, 2113)])
+def test_adam_tile_heights(ctx, dims):
+    test_adam_ragged_layers(ctx, dims)
+
+
+# A small network's update is one pass of a few loads per thread: 512 x 512 weights (9 MB) take less than 1.8
+# times a one-weight call's (1.2 measured).  Tiles of 64 rows, sixteen to a wave, had made it 2.6 times.
+def test_adam_small_network_time(ctx):
+    from paper_1904_00011_amd.surrogate import SurrogateNet
+
+    def best(dims):
+        net = SurrogateNet(ctx, dims, si.mlp_init(dims, 1), device=DEV)
+        g = torch.ones(net.n_params, device=DEV)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t = []
+        for _ in range(8):
+            a.record()
+            for _ in range(30):
+                ctx.mlp_adam(net.struct, g, 1e-4, 1)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) / 30)
+        return min(t)
+
+    assert best((512, 512)) < 1.8 * best((1, 1))
