@@ -1206,12 +1206,6 @@ hipError_t launch_adam(AdamArgs a, hipStream_t s) {
 constexpr int SLL_THREADS = 1024, SLL_REG = 10, SLL_BLOCKS = 512;
 constexpr int SLL_SAMPLES = 64;  // samples per block, at most
 
-// ln k! for k >= 1000 by Stirling's series in x = k + 1 (the first term left out is below 1e-18).
-__device__ __forceinline__ double ln_factorial_large(uint32_t k) {
-  const double x = (double)k + 1.0, r = 1.0 / x;
-  return (x - 0.5) * ln_pos(x) - x + 0.9189385332046727 + r * (1.0 / 12.0) - r * r * r * (1.0 / 360.0);
-}
-
 // The sums of u and v over the block in a fixed order (trees of shuffles in each wave, then over the
 // waves).
 __device__ __forceinline__ void sll_sum2(double &u, double &v, double (*red)[2]) {
@@ -1254,17 +1248,17 @@ __global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const floa
 #pragma unroll
   for (int k = 0; k < SLL_REG; ++k) {  // ln 0! = ln 1! = 0
     nd += (double)dv[k];
-    if (dv[k] > 1u) lf += lnfact64[min(dv[k], (uint32_t)nlf - 1u)];
+    if (dv[k] > 1u) lf += lnfact64[dv[k] < (uint32_t)nlf ? dv[k] : 0u];
     large = large || dv[k] >= (uint32_t)nlf;
   }
-  // counts beyond the table (corrected where they are) and bins beyond the registers
+  // counts beyond the table and bins beyond the registers
 #pragma unroll 1
   for (int j = large ? t : t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) {
     const uint32_t dj = d[j];
     const bool kept = j < SLL_REG * SLL_THREADS;
     if (!kept) nd += (double)dj;
     if (dj >= (uint32_t)nlf)
-      lf += ln_factorial_large(dj) - (kept ? lnfact64[nlf - 1] : 0.0);
+      lf += ln_factorial_large(dj);
     else if (!kept && dj > 1u)
       lf += lnfact64[dj];
   }

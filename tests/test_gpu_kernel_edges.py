@@ -947,3 +947,24 @@ def test_adam_small_network_time(ctx):
         return min(t)
 
     assert best((512, 512)) < 1.8 * best((1, 1))
+
+
+# ln k! beyond the table, seen through diagrams of k equal bins that hold k counts, all in one: every expectation is
+# 1, so logL = -k - ln k!.  Rounded once, and ln k! within 0.75 of its last place (0.71 measured): 1.25 units.  A
+# series that rounds its logarithm, its product and every sum is off by up to 2.2 before the last rounding.
+def test_large_counts_precision(ctx):
+    r = np.random.default_rng(19)
+    k = np.unique(np.round(np.exp(r.uniform(np.log(4096.0), np.log(65536.0), 400)))).astype(np.int64)
+    y = torch.zeros((1, 65536), dtype=torch.float32, device=DEV)
+    data = torch.zeros(65536, dtype=torch.int32, device=DEV)
+    out = torch.empty(k.size, dtype=torch.float64, device=DEV)
+    for j in range(k.size):
+        data[0] = int(k[j])
+        ctx.surrogate_loglike(y[:, :k[j]].contiguous(), data[:k[j]], out[j:j + 1])
+    ctx.sync()
+    kl, x = k.astype(np.longdouble), k.astype(np.longdouble) + 1
+    half_ln_2pi = np.log(2 * np.longdouble("3.14159265358979323846264")) / 2
+    lf = (x - np.longdouble(0.5)) * np.log(x) - x + half_ln_2pi + 1 / (12 * x) - 1 / (360 * x ** 3)
+    want = -kl - lf
+    err = np.abs(out.cpu().numpy() - want).astype(np.float64)
+    assert np.max(err / np.spacing(np.abs(want.astype(np.float64)))) <= 1.25
