@@ -217,12 +217,14 @@ hipError_t launch_hess_jobs(const HessArgs *table, int n, int64_t npx_max, int n
 // ---------------------------------------------------------------------------------------
 // Log-likelihood.  A diagram of up to LL_ONE_BINS bins is scored by one block of LL_ONE_THREADS
 // threads, which loads all its bins before it uses the first, so that the totals N_m, N_d, the bins'
-// terms and the mean-colour / mean-magnitude term take one launch and no scratch: bound by the
-// latency of two loads, a division and a logarithm (10,000 bins: 7.7 + 2.5 us in two
-// launches before, 7.8 us in one; a whole small likelihood call 66.1 -> 63.3 us).  Larger diagrams take ceil(nbins / LL_THREADS) blocks, each of which
-// recomputes the totals (integer sums are exact, so they agree) and writes its sum to part[block]; a
-// second one-block kernel adds the sums in block order.  (40,000 bins: 21.5 + 4.6 us; one block has four
-// times the work of 10,000 bins and 1/256 of the chip.)
+// terms and the mean-colour / mean-magnitude term take one launch and no scratch: bound by a launch (1,000
+// bins: 9.5 us in two launches, 4.7 us in one), and from some thousand bins by one CU's FP64 rate, which the
+// logarithms of the bins with data take (4,096 bins 5.9 us, 10,000 bins 9.5 us, 7.8 us where most waves' bins
+// hold none, 14.1 us if every bin's count is beyond the table of factorials).  Larger diagrams take
+// ceil(nbins / LL_THREADS) blocks, each of which recomputes the totals (integer sums are exact, so they agree) and
+// writes its sum to part[block]; a second one-block kernel adds the sums in block order (10,000 bins 9.5 us, 16,384
+// bins 10.8 us, where one block takes 15; 40,000 bins: 21.5 + 4.6 us, and one block has four
+// times the work of 10,000 bins and 1/256 of the chip).
 // The order of every sum depends on nbins alone.
 // ---------------------------------------------------------------------------------------
 
@@ -251,8 +253,16 @@ struct BinTerm {
     if (mode == PCMD_LL_POISSON) {
       const double lam = over_den(Nd * (m + eps));
       if (hd == 0u && Nd != 0.0) return -lam;
-      const double lf = (lnfact64 && hd < (uint32_t)LNFACT64_N) ? lnfact64[hd] : lgamma(d + 1.0);
-      return d * log(lam) - lam - lf;
+      const double lf = hd < (uint32_t)LNFACT64_N ? lnfact64[hd] : ln_factorial_large(hd);
+      // d ln lam with ln lam = hi + lo: two roundings less than product and sums one by one, and half the
+      // instructions of the library's logarithm (10,000 bins 12.0 -> 9.8 us, of large counts 21.9 -> 14.1)
+      double lo;
+      double hi = ln_split(lam, lo);
+      if (!(lam > 0.0 && lam < INFINITY)) {
+        hi = lam == 0.0 ? -INFINITY : lam;
+        lo = 0.0;
+      }
+      return fma(d, hi, fma(d, lo, -lam - lf));
     }
     // Gaussian: sigma^2 = max(variance, 2^2)
     double df, var;
@@ -277,7 +287,7 @@ __device__ __forceinline__ double mean_term(const LoglikeArgs &a) {
 }
 
 constexpr int LL_ONE_THREADS = 1024;
-constexpr int LL_ONE_BINS = 16 * LL_ONE_THREADS;
+constexpr int LL_ONE_BINS = 10 * LL_ONE_THREADS;
 
 // Sum over the block's waves in order, of values already summed within each wave.
 template <typename T>
@@ -425,10 +435,8 @@ hipError_t launch_loglike(const LoglikeArgs &a, hipStream_t s) {
   const dim3 one(LL_ONE_THREADS);
   if (a.nbins <= 4 * LL_ONE_THREADS) {
     hipLaunchKernelGGL(k_loglike_one<4>, dim3(1), one, 0, s, a);
-  } else if (a.nbins <= 10 * LL_ONE_THREADS) {
-    hipLaunchKernelGGL(k_loglike_one<10>, dim3(1), one, 0, s, a);
   } else if (a.nbins <= LL_ONE_BINS) {
-    hipLaunchKernelGGL(k_loglike_one<16>, dim3(1), one, 0, s, a);
+    hipLaunchKernelGGL(k_loglike_one<10>, dim3(1), one, 0, s, a);
   } else {
     hipLaunchKernelGGL(k_loglike_bins, dim3((unsigned)loglike_blocks(a.nbins)), dim3(LL_THREADS), 0, s, a);
     hipLaunchKernelGGL(k_loglike_final, dim3(1), dim3(64), 0, s, a);
@@ -439,10 +447,8 @@ hipError_t launch_loglike_jobs(const LoglikeArgs *table, int n_jobs, int nbins, 
   const dim3 one(LL_ONE_THREADS), jobs((unsigned)n_jobs);
   if (nbins <= 4 * LL_ONE_THREADS) {
     hipLaunchKernelGGL(k_loglike_one_jobs<4>, jobs, one, 0, s, table);
-  } else if (nbins <= 10 * LL_ONE_THREADS) {
-    hipLaunchKernelGGL(k_loglike_one_jobs<10>, jobs, one, 0, s, table);
   } else if (nbins <= LL_ONE_BINS) {
-    hipLaunchKernelGGL(k_loglike_one_jobs<16>, jobs, one, 0, s, table);
+    hipLaunchKernelGGL(k_loglike_one_jobs<10>, jobs, one, 0, s, table);
   } else {
     hipLaunchKernelGGL(k_loglike_bins_jobs, dim3((unsigned)loglike_blocks(nbins), (unsigned)n_jobs), dim3(LL_THREADS), 0,
                        s, table);

@@ -201,7 +201,9 @@ __device__ __forceinline__ double ln_pos(double x) {
 // for those of the lesser terms: the largest error met over four million k from 4,096 up is 0.71 units of the last
 // place, 2.2 with the logarithm rounded and the terms added one by one, the library's lgamma 1.5.
 __device__ __forceinline__ double ln_factorial_large(uint32_t k) {
-  const double x = (double)k + 1.0, r = 1.0 / x, h = x - 0.5;
+  const double x = (double)k + 1.0, h = x - 0.5;
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);  // within a few units of 1 / x, which has a share of 2^-18 in the result
   double lo;
   const double hi = ln_split(x, lo);
   const double rest = (0.9189385332046727 + (r * (1.0 / 12.0) - r * r * r * (1.0 / 360.0))) - x;

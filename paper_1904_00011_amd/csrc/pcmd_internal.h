@@ -217,7 +217,7 @@ struct LoglikeArgs {
   double *out;
   double *part;  // [loglike_blocks(nbins)] block sums
   int accumulate;  // add to *out instead of storing
-  const double *lnfact64;  // ln k! for k < LNFACT64_N (host lgamma), or NULL
+  const double *lnfact64;  // ln k! for k < LNFACT64_N (host lgamma)
 };
 constexpr int LNFACT64_N = 4096;
 

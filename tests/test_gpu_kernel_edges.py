@@ -968,3 +968,27 @@ def test_large_counts_precision(ctx):
     want = -kl - lf
     err = np.abs(out.cpu().numpy() - want).astype(np.float64)
     assert np.max(err / np.spacing(np.abs(want.astype(np.float64)))) <= 1.25
+
+
+# The last diagram that one block scores takes no longer than the first that many blocks do (1.06 and 1.0 of it
+# measured, where counts are ordinary): the line had been at 16,384 bins, 1.6 times the next size.
+@pytest.mark.parametrize("nbins", [10240, 16384])
+def test_likelihood_one_block_time(ctx, nbins):
+    mom = torch.tensor([1.0, 2.0, 3.0], dtype=torch.float64, device=DEV)
+    out = torch.empty(1, dtype=torch.float64, device=DEV)
+
+    def best(nb):
+        r = np.random.default_rng(nb)
+        hm, hd = (torch.from_numpy(r.integers(0, 9, nb).astype(np.int32)).to(DEV) for _ in range(2))
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t = []
+        for _ in range(8):
+            a.record()
+            for _ in range(30):
+                ctx.loglike(hm, hd, mom, mom, out, 0)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) / 30)
+        return min(t)
+
+    assert best(nbins) <= 1.2 * best(nbins + 1)
