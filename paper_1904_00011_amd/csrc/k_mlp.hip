@@ -1197,17 +1197,23 @@ hipError_t launch_adam(AdamArgs a, hipStream_t s) {
 // exp(x_j) / se, so ln lam_j = x_j + ln(N_d / se) and sum lam_j = N_d:
 //   logL = sum_j d_j x_j + N_d ln(N_d / se) - N_d - sum_j ln d_j!
 // needs one exponential per bin, where the term-by-term form took two and a logarithm (FP64, so
-// bound by their vector instructions).  A block of 1,024 threads walks samples, its share of the data
+// bound by their vector instructions).  A block walks samples, its share of the data
 // (N_d, the factorials' sum, each thread's counts of the first SLL_REG rounds) kept from one to the
 // next; a thread also keeps its bins of y between the maximum and the exponentials.  The order of a
-// sample's sums does not depend on the batch.
+// sample's sums depends on the number of bins alone.
 // 10,000 bins: one sample 42 -> 9.4 us, 4,096 samples 431 -> 78 us (156 with the library's exponential,
 // a block per sample and the data's sums formed for each); no spills, which had cost half of that.
-constexpr int SLL_THREADS = 1024, SLL_REG = 10, SLL_BLOCKS = 512;
+// SLL_THREADS threads to a block, or SLL_FEW where their registers hold every bin: the passes over a sample's barriers
+// are then of four waves, and eight samples run on a CU at a time where two do (100 bins: 512 samples 5.5 us, 11.9 in
+// blocks of 1,024 threads, 4,096 samples 14.5 and 45; 2,500 bins 7.1 and 12.5, 21 and 50; 4,096 bins, beyond the
+// registers, 10.3 and 13.1, but one sample 9.0 and 7.8, and 10,000 bins 26 and 16).
+constexpr int SLL_THREADS = 1024, SLL_FEW = 256, SLL_REG = 10;
+constexpr int SLL_BLOCKS = 512;  // of SLL_THREADS threads: what the chip holds
 constexpr int SLL_SAMPLES = 64;  // samples per block, at most
 
 // The sums of u and v over the block in a fixed order (trees of shuffles in each wave, then over the
 // waves).
+template <int THREADS>
 __device__ __forceinline__ void sll_sum2(double &u, double &v, double (*red)[2]) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {
@@ -1219,29 +1225,30 @@ __device__ __forceinline__ void sll_sum2(double &u, double &v, double (*red)[2])
     red[threadIdx.x >> 6][1] = v;
   }
   __syncthreads();
-  static_assert(SLL_THREADS == 1024, "sixteen waves");
-  u = red[threadIdx.x & 15u][0];
-  v = red[threadIdx.x & 15u][1];
+  constexpr unsigned W = THREADS / 64;  // a power of two
+  u = red[threadIdx.x & (W - 1)][0];
+  v = red[threadIdx.x & (W - 1)][1];
 #pragma unroll
-  for (int d = 8; d > 0; d >>= 1) {
+  for (int d = W / 2; d > 0; d >>= 1) {
     u += __shfl_xor(u, d, 64);
     v += __shfl_xor(v, d, 64);
   }
 }
 
-__global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const float *__restrict__ y, int n, int nbins,
-                                                                      const uint32_t *__restrict__ d,
-                                                                      double *__restrict__ out,
-                                                                      const double *__restrict__ lnfact64, int nlf) {
-  __shared__ double red[2][SLL_THREADS / 64][2];
-  __shared__ float redf[SLL_THREADS / 64];
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS, 8) k_surrogate_loglike(const float *__restrict__ y, int n, int nbins,
+                                                                  const uint32_t *__restrict__ d,
+                                                                  double *__restrict__ out,
+                                                                  const double *__restrict__ lnfact64, int nlf) {
+  __shared__ double red[2][THREADS / 64][2];
+  __shared__ float redf[THREADS / 64];
   __shared__ double fin[SLL_SAMPLES][2];  // se and sum d x of the block's samples
   const int t = threadIdx.x;
   uint32_t dv[SLL_REG];
 #pragma unroll
   for (int k = 0; k < SLL_REG; ++k) {
     dv[k] = 0u;
-    if ((uint32_t)t + k * SLL_THREADS < (uint32_t)nbins) dv[k] = (d + k * SLL_THREADS)[(uint32_t)t];
+    if ((uint32_t)t + k * THREADS < (uint32_t)nbins) dv[k] = (d + k * THREADS)[(uint32_t)t];
   }
   double nd = 0.0, lf = 0.0;
   bool large = false;
@@ -1253,16 +1260,16 @@ __global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const floa
   }
   // counts beyond the table and bins beyond the registers
 #pragma unroll 1
-  for (int j = large ? t : t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) {
+  for (int j = large ? t : t + SLL_REG * THREADS; j < nbins; j += THREADS) {
     const uint32_t dj = d[j];
-    const bool kept = j < SLL_REG * SLL_THREADS;
+    const bool kept = j < SLL_REG * THREADS;
     if (!kept) nd += (double)dj;
     if (dj >= (uint32_t)nlf)
       lf += ln_factorial_large(dj);
     else if (!kept && dj > 1u)
       lf += lnfact64[dj];
   }
-  sll_sum2(nd, lf, red[0]);
+  sll_sum2<THREADS>(nd, lf, red[0]);
   int q0 = 0;
   for (int s = blockIdx.x; s < n; s += gridDim.x, ++q0) {
     const float *ys = y + (size_t)s * nbins;
@@ -1270,19 +1277,19 @@ __global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const floa
 #pragma unroll
     for (int k = 0; k < SLL_REG; ++k) {
       v[k] = -INFINITY;
-      if ((uint32_t)t + k * SLL_THREADS < (uint32_t)nbins) v[k] = (ys + k * SLL_THREADS)[(uint32_t)t];
+      if ((uint32_t)t + k * THREADS < (uint32_t)nbins) v[k] = (ys + k * THREADS)[(uint32_t)t];
     }
     float m = -INFINITY;
 #pragma unroll
     for (int k = 0; k < SLL_REG; ++k) m = fmaxf(m, v[k]);
-    for (int j = t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) m = fmaxf(m, ys[j]);
+    for (int j = t + SLL_REG * THREADS; j < nbins; j += THREADS) m = fmaxf(m, ys[j]);
 #pragma unroll
     for (int q = 32; q > 0; q >>= 1) m = fmaxf(m, __shfl_xor(m, q, 64));
     if ((t & 63) == 0) redf[t >> 6] = m;
     __syncthreads();
-    m = redf[t & 15];
+    m = redf[t & (THREADS / 64 - 1)];
 #pragma unroll
-    for (int q = 8; q > 0; q >>= 1) m = fmaxf(m, __shfl_xor(m, q, 64));
+    for (int q = THREADS / 128; q > 0; q >>= 1) m = fmaxf(m, __shfl_xor(m, q, 64));
     const double mx = (double)m;
     double se = 0.0, dx = 0.0;
     auto bin = [&](float yj, uint32_t dj) {
@@ -1296,10 +1303,10 @@ __global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const floa
     for (int k = 0; k < SLL_REG; ++k) {
       // converted here for each sample: kept in FP64, the counts would spill
       asm volatile("" : "+v"(dv[k]));
-      if (t + k * SLL_THREADS < nbins) bin(v[k], dv[k]);
+      if (t + k * THREADS < nbins) bin(v[k], dv[k]);
     }
-    for (int j = t + SLL_REG * SLL_THREADS; j < nbins; j += SLL_THREADS) bin(ys[j], d[j]);
-    sll_sum2(se, dx, red[1]);  // its barrier also parts this sample's redf from the next one's
+    for (int j = t + SLL_REG * THREADS; j < nbins; j += THREADS) bin(ys[j], d[j]);
+    sll_sum2<THREADS>(se, dx, red[1]);  // its barrier also parts this sample's redf from the next one's
     if (t == 0) {
       fin[q0][0] = se;
       fin[q0][1] = dx;
@@ -1312,8 +1319,15 @@ __global__ void __launch_bounds__(SLL_THREADS, 8) k_surrogate_loglike(const floa
 hipError_t launch_surrogate_loglike(const float *y, int n, int nbins, const uint32_t *d, double *out,
                                    const double *lnfact64, int nlf, hipStream_t s) {
   if (!lnfact64 || nlf < 1000) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_surrogate_loglike, dim3((unsigned)std::max(std::min(n, SLL_BLOCKS), (n + SLL_SAMPLES - 1) / SLL_SAMPLES)), dim3(SLL_THREADS), 0, s, y, n, nbins, d,
-                     out, lnfact64, nlf);
+  auto launch = [&](auto threads) {
+    constexpr int T = decltype(threads)::value;
+    const int blocks = std::max(std::min(n, SLL_BLOCKS * (SLL_THREADS / T)), (n + SLL_SAMPLES - 1) / SLL_SAMPLES);
+    hipLaunchKernelGGL(k_surrogate_loglike<T>, dim3((unsigned)blocks), dim3(T), 0, s, y, n, nbins, d, out, lnfact64, nlf);
+  };
+  if (nbins <= SLL_FEW * SLL_REG)
+    launch(std::integral_constant<int, SLL_FEW>{});
+  else
+    launch(std::integral_constant<int, SLL_THREADS>{});
   return hipGetLastError();
 }
 

@@ -992,3 +992,41 @@ def test_likelihood_one_block_time(ctx, nbins):
         return min(t)
 
     assert best(nbins) <= 1.2 * best(nbins + 1)
+
+
+# Surrogate likelihoods in blocks of 256 threads and of 1,024: the last and first size of each, more samples than
+# blocks run at a time, and the number from which a block's share is bounded (64 x 2048 + 1).  Bound of the bin-count test.
+@pytest.mark.parametrize("n,nbins", [(3, 255), (2049, 257), (40, 2560), (40, 2561), (131073, 3)])
+def test_surrogate_loglike_block_sizes(ctx, n, nbins):
+    r = np.random.default_rng(n + nbins)
+    y = r.normal(-9.0, 2.0, (n, nbins)).astype(np.float32)
+    d = r.poisson(r.choice([0.0, 0.5, 40.0, 6000.0], nbins)).astype(np.int32)
+    d[-1] = 3
+    out = torch.full((n,), float("nan"), dtype=torch.float64, device=DEV)
+    ctx.surrogate_loglike(torch.from_numpy(y).to(DEV), torch.from_numpy(d).to(DEV), out)
+    ctx.sync()
+    got = out.cpu().numpy()
+    assert np.isfinite(got).all()
+    for k in {0, 1, 2, n // 2, n - 2, n - 1} | set(range(0, n, 300)):
+        assert got[k] == pytest.approx(om.surrogate_loglike(y[k], d), rel=4e-10, abs=1e-9)
+
+
+# Few bins: 512 samples take no more than 1.3 times as long as 256 (1.08 measured), all in flight at once; blocks of
+# 1,024 threads, of which a chip holds 512 at its best, took 1.5 times.
+def test_surrogate_loglike_few_bins_time(ctx):
+    d = torch.ones(100, dtype=torch.int32, device=DEV)
+
+    def best(n):
+        y, out = torch.zeros((n, 100), device=DEV), torch.empty(n, dtype=torch.float64, device=DEV)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t = []
+        for _ in range(8):
+            a.record()
+            for _ in range(30):
+                ctx.surrogate_loglike(y, d, out)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) / 30)
+        return min(t)
+
+    assert best(512) <= 1.3 * best(256)
