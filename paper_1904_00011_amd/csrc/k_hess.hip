@@ -30,8 +30,11 @@ constexpr int HESS_LDS_MAX_BINS = 40000;  // 160,000 bytes of LDS (of 163,840 pe
 constexpr int HESS_UNROLL = 4;            // pixels per lane whose loads are issued together
 // Up to this many pixels one block bins the whole image, and then stores its histogram and sums
 // instead of merging them: no launch to clear the result, no atomics (64 x 64 pixels: 12.6 + 2.2 ->
-// 7.1 us).  At 201 x 201 the ten blocks and the clearing take 14 us, one block 5 times the work.
+// 7.1 us; from 8,193 pixels two blocks and the clearing 10.6).
+// A diagram beyond LDS has nothing to clear or to merge in a block, and its small images are spread over blocks of
+// a pixel per lane, up to HESS_SPREAD (256 x 256 bins, 8,192 pixels: 16.9 us in one block, 8.7 in eight).
 constexpr int64_t HESS_ONE_BLOCK = 8192;
+constexpr int HESS_SPREAD = HESS_ONE_BLOCK / HESS_THREADS;
 int hess_max_blocks() { return HESS_MAX_BLOCKS; }
 
 __device__ __forceinline__ int bin_of(double t, int n) {
@@ -71,17 +74,23 @@ __device__ __forceinline__ void block_sum3(double (&v)[3], double (*red)[3]) {
       for (int c = 0; c < 3; ++c) v[c] += red[w][c];
 }
 
-__host__ __device__ static inline int hess_blocks_of(int64_t npx) {
-  if (npx <= HESS_ONE_BLOCK) return 1;
+// Does not fall as npx grows: a launch over several jobs has the blocks of the largest.
+__host__ __device__ static inline int hess_blocks_of(int64_t npx, int nbins) {
+  const bool lds = nbins <= HESS_LDS_MAX_BINS;
+  if (lds && npx <= HESS_ONE_BLOCK) return 1;
   // enough pixels per block to amortise clearing and merging the private histogram
   int64_t blocks = (npx + 4095) / 4096;
+  if (!lds && blocks < HESS_SPREAD) {
+    blocks = (npx + HESS_THREADS - 1) / HESS_THREADS;
+    if (blocks > HESS_SPREAD) blocks = HESS_SPREAD;
+  }
   if (blocks > HESS_MAX_BLOCKS) blocks = HESS_MAX_BLOCKS;
   return (int)blocks;
 }
-int hess_blocks(int64_t npx) { return hess_blocks_of(npx); }
+int hess_blocks(int64_t npx, int nbins) { return hess_blocks_of(npx, nbins); }
 bool hess_use_lds(int nbins) { return nbins <= HESS_LDS_MAX_BINS; }
 // one block with a private histogram: the result needs no clearing
-static bool hess_stores(int64_t npx, int nbins) { return hess_use_lds(nbins) && hess_blocks(npx) == 1; }
+static bool hess_stores(int64_t npx, int nbins) { return hess_use_lds(nbins) && hess_blocks(npx, nbins) == 1; }
 
 // by nblk blocks
 __device__ __forceinline__ void hess_body(const HessArgs &a, unsigned nblk) {
@@ -147,8 +156,8 @@ __device__ __forceinline__ void hess_body(const HessArgs &a, unsigned nblk) {
   }
   if (threadIdx.x == 0) {
     // The partial goes out by device-scope stores, which reach memory that every XCD reads, and is
-    // complete before the block counts itself.  A __threadfence here would write back the whole L2
-    // of the XCD, once per block.
+    // complete before the block counts itself.  A __threadfence or a releasing count would write back the whole
+    // L2 of the XCD, once per block (4096 x 4096 pixels: 116 us, 101 so).
 #pragma unroll
     for (int c = 0; c < 3; ++c)
       __hip_atomic_store(a.mom_part + blockIdx.x * 3 + c, sum[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -179,7 +188,7 @@ __device__ __forceinline__ void hess_body(const HessArgs &a, unsigned nblk) {
 __global__ void __launch_bounds__(HESS_THREADS, 8) k_hess(HessArgs a) { hess_body(a, gridDim.x); }
 __global__ void __launch_bounds__(HESS_THREADS, 8) k_hess_jobs(const HessArgs *__restrict__ t) {
   const HessArgs a = t[blockIdx.y];
-  const unsigned nblk = (unsigned)hess_blocks_of(a.npx);  // those of the same single call
+  const unsigned nblk = (unsigned)hess_blocks_of(a.npx, a.nx * a.ny);  // those of the same single call
   if (blockIdx.x < nblk) hess_body(a, nblk);
 }
 
@@ -190,7 +199,7 @@ hipError_t launch_hess(const HessArgs &a, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   const size_t lds = a.use_lds ? (size_t)nb * sizeof(uint32_t) : 0;
-  hipLaunchKernelGGL(k_hess, dim3((unsigned)hess_blocks(a.npx)), dim3(HESS_THREADS), lds, s, a);
+  hipLaunchKernelGGL(k_hess, dim3((unsigned)hess_blocks(a.npx, nb)), dim3(HESS_THREADS), lds, s, a);
   return hipGetLastError();
 }
 
@@ -210,7 +219,7 @@ hipError_t launch_hess_clear_jobs(const HessArgs *table, int n, int nbins, hipSt
 // 26 together.)
 hipError_t launch_hess_jobs(const HessArgs *table, int n, int64_t npx_max, int nbins, hipStream_t s) {
   const size_t lds = hess_use_lds(nbins) ? (size_t)nbins * sizeof(uint32_t) : 0;
-  hipLaunchKernelGGL(k_hess_jobs, dim3((unsigned)hess_blocks(npx_max), n), dim3(HESS_THREADS), lds, s, table);
+  hipLaunchKernelGGL(k_hess_jobs, dim3((unsigned)hess_blocks(npx_max, nbins), n), dim3(HESS_THREADS), lds, s, table);
   return hipGetLastError();
 }
 

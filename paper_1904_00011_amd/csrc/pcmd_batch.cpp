@@ -504,7 +504,7 @@ static hipError_t enqueue(pcmd_ctx *c, pcmd_batch_plan *p, hipStream_t s) {
                  : launch_noise_mag_job(na, j, ji.npx, ji.B, s);
   }
   for (int k0 = 0, k1; k0 < p->n_jobs && e == hipSuccess; k0 = k1) {
-    k1 = run_end(k0, p->n_jobs, [&](int k) { return hess_blocks(npx(k)); });
+    k1 = run_end(k0, p->n_jobs, [&](int k) { return hess_blocks(npx(k), p->nbins); });
     e = launch_hess_clear_jobs(ha + k0, k1 - k0, p->nbins, s);
     if (e == hipSuccess) e = launch_hess_jobs(ha + k0, k1 - k0, npx(k0), p->nbins, s);
   }

@@ -269,7 +269,7 @@ hipError_t launch_conv_fft(const float *F, const float *psf, int B, int N, int K
 // k_hess.hip
 hipError_t launch_fill_u32(uint32_t *p, uint32_t v, int64_t n, hipStream_t s);
 int hess_max_blocks();
-int hess_blocks(int64_t npx);
+int hess_blocks(int64_t npx, int nbins);
 bool hess_use_lds(int nbins);
 hipError_t launch_hess(const HessArgs &a, hipStream_t s);
 hipError_t launch_hess_clear_jobs(const HessArgs *table, int n, int nbins, hipStream_t s);

@@ -1030,3 +1030,54 @@ def test_surrogate_loglike_few_bins_time(ctx):
         return min(t)
 
     assert best(512) <= 1.3 * best(256)
+
+
+# Diagrams beyond the private histogram: images at the edges of a pixel per lane, of eight blocks and of four pixels
+# per lane.
+@pytest.mark.parametrize("npx", [1024, 1025, 8191, 32768, 32769])
+def test_hess_spread_small_images(ctx, npx):
+    test_hess_pixel_counts(ctx, npx, 201, 203, (1, 2, 0))
+
+
+# ... jobs of several such sizes in one launch, each scored as alone.
+def test_batch_of_wide_diagrams(ctx):
+    r = np.random.default_rng(23)
+    hgrid = dict(x0=-2.0, dx=0.02, y0=-5.0, dy=0.05, nx=256, ny=256)
+    jobs = []
+    for k, nim in enumerate([90, 32, 91, 181, 64, 182]):
+        obs = si.Obs(nim=nim, seed=41 + k, dmod=0.0, dust_model=2, dust_frac=0.5, dust_R=(3.6, 1.9, 1.3, 1.0), psf=None, noise_model=0,
+                     noise_sigma_mag=(0.02,) * 4, exptime=(100.0,) * 4, zp=(25.0,) * 4, sky=(1.0,) * 4)
+        jobs.append(dict(lam=torch.from_numpy(10.0 ** r.uniform(-2.0, 0.0, 30)).to(DEV), obs=obs, conv_path=1, psf=None,
+                         flux=torch.from_numpy((10.0 ** r.uniform(-3.0, 0.0, (3, 30))).astype(np.float32)).to(DEV)))
+    data = torch.ones(65536, dtype=torch.int32, device=DEV)
+    mom_d = torch.tensor([1.0, 2.0, 3.0], dtype=torch.float64, device=DEV)
+
+    def run(js):
+        out = torch.empty(len(js), dtype=torch.float64, device=DEV)
+        ctx.batch_run(js, hgrid, data, mom_d, out, use_graph=False, bands=(0, 1, 1))
+        ctx.sync()
+        return out
+
+    assert torch.equal(run(jobs), torch.cat([run([j]) for j in jobs]))
+
+
+# A small image of such a diagram has more than one block: 8,192 pixels take no more than 1.5 times as long as 1,024
+# (1.14 measured; 2.2 in one block).
+def test_hess_spread_time(ctx):
+    grid = dict(x0=-2.0, dx=4.0 / 256, y0=23.0, dy=4.0 / 256, nx=256, ny=256)
+    h, mom = torch.empty(65536, dtype=torch.int32, device=DEV), torch.empty(3, dtype=torch.float64, device=DEV)
+
+    def best(npx):
+        m = torch.from_numpy(np.random.default_rng(npx).normal(25.0, 0.4, (3, npx)).astype(np.float32)).to(DEV)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t = []
+        for _ in range(8):
+            a.record()
+            for _ in range(30):
+                ctx.hess(m, 3, npx, grid, h, mom)
+            b.record()
+            b.synchronize()
+            t.append(a.elapsed_time(b) / 30)
+        return min(t)
+
+    assert best(8192) <= 1.5 * best(1024)
