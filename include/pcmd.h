@@ -298,7 +298,9 @@ typedef struct {
  * pcmd_hess + pcmd_loglike on the same inputs.  The per-point sampler runs as one persistent
  * launch whose (job, 64-pixel block, entry chunk) tiles are drawn from a shared counter, so jobs of
  * uneven image size and entry count load-balance; a job with the block-skip or hybrid sampler
- * draws its block-rule stars in a launch of its own after it; the other steps run per job.  All jobs share n_bands;
+ * draws its block-rule stars in a launch of its own after it, and the convolution runs per job.  The tables,
+ * the thinned entries, the sums, the Hess diagrams and the likelihoods take launches over several jobs (of like
+ * size, where a launch has a grid for the largest).  All jobs share n_bands;
  * a job's convolution must resolve to the direct path (PCMD_E_UNSUPPORTED otherwise).
  * use_graph != 0: the first call with a given shape signature (n_jobs, each job's nim, n_entries,
  * psf_k, sampler, PSF grid and how dust splits its stars: none, F = 1/2, F = 1 or another F, the

@@ -158,7 +158,8 @@ __device__ __forceinline__ void prep_body(const PrepArgs &a, int i) {
 }
 
 __global__ void __launch_bounds__(256) k_prep(PrepArgs a) { prep_body(a, blockIdx.x * blockDim.x + threadIdx.x); }
-// batched: the jobs j + blockIdx.z of a descriptor table, the grid sized for the largest of them (a launch
+// batched: the jobs j + blockIdx.z of a descriptor table, the grid sized for the first of them, the largest (the
+// table is sorted, and the host ends the run where most of such a grid would be empty; a launch
 // per job left most of the chip idle in each: 24 uneven jobs' tables 24 x 18 us, sums 24 x 25)
 __global__ void __launch_bounds__(256) k_prep_job(const PrepArgs *__restrict__ t, int j) {
   const PrepArgs a = t[j + blockIdx.z];

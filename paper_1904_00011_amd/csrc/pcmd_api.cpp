@@ -99,7 +99,7 @@ int pcmd_create(pcmd_ctx **out, int hip_device) {
     acc = acc + log((double)k);
     tab[k] = (float)acc;
   }
-  // ln k! in FP64 for the likelihoods' ln d_j! (k < LNFACT64_N; lgamma beyond)
+  // ln k! in FP64 for the likelihoods' ln d_j! (k < LNFACT64_N; Stirling's series beyond)
   std::vector<double> lf(LNFACT64_N);
   for (int k = 0; k < LNFACT64_N; ++k) lf[k] = std::lgamma((double)k + 1.0);
   if (hipMalloc(&c->lnfact, sizeof tab) != hipSuccess || hipMalloc(&c->status, 32) != hipSuccess ||

@@ -56,12 +56,13 @@ struct AdamArgs {
   float lr, beta1, beta2, eps, bc1, bc2;
 };
 
-// Workspace (bytes) launch_gemm needs for an M x N x K product: transposed copies of K-major
-// operands (at: A(m, k) = A[k][m]; bt: B(n, k) = B[k][n]) and split-K partials.
 // Partial sums that an EPI_BIAS_MSE product writes (0: this shape cannot take that epilogue).
 int64_t gemm_loss_parts(int M, int N, int K);
 // Whether a product of these sizes takes A in FP32 (A32): where that is faster than rounding it first.
 bool gemm_reads_f32(int M, int N, int K);
+// Workspace (bytes) launch_gemm needs for an M x N x K product: transposed copies of K-major
+// operands (at: A(m, k) = A[k][m]; bt: B(n, k) = B[k][n]) where its tiles do not read them in place, and split-K
+// partials.
 size_t gemm_workspace_bytes(int M, int N, int K, bool at, bool bt);
 hipError_t launch_gemm(const GemmArgs &g, bool at, bool bt, int epi, void *ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float *x, void *y, int64_t n, hipStream_t s);
