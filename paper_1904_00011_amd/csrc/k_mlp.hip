@@ -1122,8 +1122,8 @@ hipError_t launch_sum_partials(const double *part, int64_t nb, double scale, flo
 // first[l + 1] - 1; the tile's rows' biases go with the first tile of a row), a row of a wave at a time, and writes
 // W^T's rows from an LDS copy of the tile: a column-strided 2-byte store per weight had cost the
 // update half its time.  Bound by the 32 bytes per weight (moments, master, gradient, copies).
-// 5.4 million weights: 67 us in five launches -> 41 us (4.2 TB/s of a copy's 4.7).
-// Networks of few 64-row tiles are bound by the latency of a wave's rows one after another, and take 16 rows
+// 5.4 million weights: 67 us in five launches -> 37 us in one, 33 us (5.2 TB/s) with the short tiles below.
+// Networks of up to 1,535 64-row tiles are bound by the latency of a wave's rows one after another, and take 16 rows
 // (four to a wave): 512 x 512 11.0 -> 5.0 us, 3 -> 580 13.8 -> 5.9 us, 2048 x 1024 (512 tiles) 18.8 -> 11.4 us; at
 // 1,504 tiles 39 us with either, at 4,096 tiles 110 with 16 rows and 96 with 64 (W^T in pieces of 128 bytes, not 32).
 constexpr int AT = 64, ADAM_SHORT = 16;
